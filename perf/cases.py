@@ -147,8 +147,8 @@ def work(case):
 def tolerance(case):
     # About four times the largest difference from the same problem in 64 bits (see _reference_error):
     # outputs are rounded once to the 16-bit type, P and dS once as operands, O once before the backward.
-    # Measured: at most 2.5e-3 in bf16 and 3.2e-4 in fp16 over the listed cases.
-    return {"rel": 1e-2} if case["dtype"] == "bf16" else {"rel": 1.3e-3}
+    # Measured: at most 2.5e-3 in bf16 and 3.8e-4 in fp16 over the listed cases.
+    return {"rel": 1e-2} if case["dtype"] == "bf16" else {"rel": 1.5e-3}
 
 
 def _reference_error(case, seed=1):
