@@ -1,0 +1,262 @@
+// Attention forward for grids that leave most of the chip idle: few queries (down to one row per
+// head), few heads, short sequences.
+//
+// mha_fwd_kernel gives a workgroup 128 query rows and walks the keys in one serial chain; with 64
+// such workgroups three quarters of the CUs have nothing to do and the others run one wave per
+// SIMD, so the time is the chain of N_k / 64 iterations (0.7 us each at d = 64, 1.0 us at d = 128).
+// Here a workgroup owns 32 query rows and its 8 waves split the KEYS: wave w takes key tiles w,
+// w + 8, ..., keeps its own (m, l, O) and the eight partial results are merged once at the end
+// through LDS with Eq. 3 of Sec. 3.2.1.  That gives four times as many workgroups, two waves per
+// SIMD, and chains an eighth as long.
+//
+// Every wave has its own K and V buffer in LDS (8 KB each) and fills it itself by direct
+// global->LDS loads, so the loop has no barrier at all: the next K tile is requested as soon as
+// the scores have consumed the present one, the next V tile as soon as P V has, and each wait is a
+// vmcnt that leaves the other request in flight.  128 KB per CU are then in flight or in use, which
+// is what a single query row, a pure read of K and V, needs to approach the memory rate.
+// The price is operand traffic: K and V are read from L2 once per 32 query rows instead of once per
+// 128 (8 waves on 8 KB + 8 KB of their own per 32 x 32 ... 64 block, against 64 B per clock from L2:
+// about the rate of one wave per SIMD of the other kernel), hence only for grids that fit the chip in
+// one go.  Measured: 1 head, N = 8192: d = 64 fp16 91 -> 29 us, d = 128 134 -> 51 us; one query row
+// against 2048 keys, 128 heads, d = 128: 40.7 -> 29.3 us (4.6 TB/s, the rate of a large copy).
+#pragma once
+#include "dropout_gfx950.hpp"
+#include "mma_gfx950.hpp"
+#include "tiles_gfx950.hpp"
+
+namespace spark {
+
+template <int D> struct FwdSplitCfg {
+  static constexpr int NW = 8;                   // waves = key streams of a workgroup
+  static constexpr int BM = 32;                  // query rows per workgroup
+  static constexpr int BN = D == 64 ? 64 : 32;   // keys per tile: 8 KB of K, 8 KB of V
+  static constexpr int ROWB = D * 2;
+  static constexpr int TILE = BN * ROWB;
+  static constexpr int NLOAD = TILE / 1024;      // direct loads per tile of K or V
+  static constexpr int GROUPS = D / 8;           // accumulator quads (4 registers) per lane
+  static constexpr int GPW = GROUPS / NW;        // ... that each wave sums in the merge
+  static constexpr int XCH = NW * NW * GPW * 1024;  // partial O: [source wave][summing wave][quad][lane]
+  static constexpr int BUF = NW * 2 * TILE > XCH ? NW * 2 * TILE : XCH;
+  static constexpr int STAT0 = BUF;              // m and l: [wave][row]
+  static constexpr int OSTR = D * 2 + 16;
+  static constexpr int STG0 = STAT0 + 2 * NW * BM * 4;  // 16-bit rows on their way out
+  static constexpr int SMEM = STG0 + BM * OSTR;
+};
+
+template <typename T, int D, bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
+    float* __restrict__ LSE, TensorMap mq, TensorMap mk, TensorMap mv, TensorMap mo, int H, int Nq, int Nk,
+    int dh, int nqt, int paired, float scale_log2, Dropout dr) {
+  using F = Frag<T>;
+  using v8 = typename F::v8;
+  using v4 = typename F::v4;
+  using C = FwdSplitCfg<D>;
+  constexpr int KS = D / 16, DT = D / 32, HALVES = C::BN / 32;
+
+  SPARK_LDS char* const smem = lds_origin();
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 5, c32 = lane & 31;
+  SPARK_LDS char* const kb = smem + wave * 2 * C::TILE;
+  SPARK_LDS char* const vb = kb + C::TILE;
+
+  // causal: query tiles (nqt-1-p, p) are paired for equal work, unless there are so few tiles that
+  // each gets a CU of its own
+  const int items = paired ? causal_items<CAUSAL>(nqt) : nqt;
+  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int head = logical / items;
+  const int item = logical - head * items;
+
+  const BufView kview(K + head_base(mk, head, H), head_span_bytes(mk, Nk, dh));
+  const BufView vview(V + head_base(mv, head, H), head_span_bytes(mv, Nk, dh));
+  const uint32_t k_row_bytes = (uint32_t)mk.row * 2, v_row_bytes = (uint32_t)mv.row * 2;
+  const WaveDma<D> kdma(lane, k_row_bytes, dh), vdma(lane, v_row_bytes, dh);
+  const SwzLane<D> off(lane);
+
+  for (int rep = 0; rep < (CAUSAL && paired ? 2 : 1); ++rep) {
+    const int qt = CAUSAL && rep == 0 ? nqt - 1 - item : item;
+    if (CAUSAL && rep == 1) {
+      if (qt == nqt - 1 - item) break;  // odd tile count: the middle tile has no partner
+      __syncthreads();                  // the first tile's output has left the LDS
+    }
+    const int q0 = qt * C::BM, qrow = q0 + c32;
+    const T* qp = Q + head_base(mq, head, H) + (size_t)(qrow < Nq ? qrow : Nq - 1) * (size_t)mq.row;
+
+    int kv_end = Nk;
+    if (CAUSAL && q0 + C::BM < Nk) kv_end = q0 + C::BM;
+    const int nt = (kv_end + C::BN - 1) / C::BN;
+    // tiles [0, n_plain) need no mask: they end within the keys and, if causal, at or below row q0
+    int n_plain = Nk / C::BN;
+    if (CAUSAL && (q0 + 1) / C::BN < n_plain) n_plain = (q0 + 1) / C::BN;
+
+    v8 qf[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = load_row_chunk<v8>(qp, ks * 16 + g * 8, dh);
+
+    f32x16 o[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+    float m_run = -1e30f;  // finite, so that a masked score (-inf) minus the reference is not NaN
+    float l_run = 0.f;
+
+    auto fetch_k = [&](int j) { kdma.template tile<C::BN>(kview, j * C::BN, kb, k_row_bytes); };
+    auto fetch_v = [&](int j) { vdma.template tile<C::BN>(vview, j * C::BN, vb, v_row_bytes); };
+    if (wave < nt) {
+      fetch_k(wave);
+      fetch_v(wave);
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));  // Q is awaited here, not in the loop
+
+    // One tile; next: this wave has another one.  On entry at most NLOAD loads of K and, behind them,
+    // NLOAD of V are outstanding.
+    auto tile = [&](const int j, auto masked_tag, const bool next) {
+      constexpr bool MASKED = decltype(masked_tag)::value;
+      const int k0 = j * C::BN;
+      f32x16 s[HALVES];
+#pragma unroll
+      for (int h = 0; h < HALVES; ++h)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[h][r] = 0.f;
+      wait_vmem<C::NLOAD>();  // K is here; V may still be on its way
+      v8 kf[HALVES][KS];
+#pragma unroll
+      for (int h = 0; h < HALVES; ++h)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) kf[h][ks] = lds_read16<v8>(kb, off.row[ks] + h * 32 * C::ROWB);
+#pragma unroll
+      for (int h = 0; h < HALVES; ++h)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) s[h] = F::mfma(kf[h][ks], qf[ks], s[h]);
+      if (next) {
+        wait_lds_all();  // every read of this K tile has returned
+        fetch_k(j + C::NW);
+      }
+
+      float t[HALVES * 16];
+      auto load_scores = [&](int h) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          t[h * 16 + r] = s[h][r];
+          if (MASKED) {
+            const int key = k0 + h * 32 + 8 * (r / 4) + 4 * g + (r % 4);
+            if (!(key < Nk && (!CAUSAL || key <= qrow))) t[h * 16 + r] = -INFINITY;
+          }
+        }
+      };
+      auto exp_all = [&]() {
+        float rs = 0.f;
+#pragma unroll
+        for (int i = 0; i < HALVES * 16; ++i) {
+          t[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(t[i], scale_log2, -m_run));
+          rs += t[i];
+        }
+        return rs;
+      };
+#pragma unroll
+      for (int h = 0; h < HALVES; ++h) load_scores(h);
+      // lazy reference as in mha_fwd_kernel: exponentials against the present one first; only if
+      // the row sum shows that it was too low, the maximum, the rescale of Eq. 3 and P once more
+      float rs = exp_all();
+      if (__any(!(rs <= 256.0f))) {
+#pragma unroll
+        for (int h = 0; h < HALVES; ++h) load_scores(h);
+        float mx = t[0];
+#pragma unroll
+        for (int i = 1; i < HALVES * 16; ++i) mx = fmaxf(mx, t[i]);
+        const float m_new = fmaxf(m_run, half_pair_max(mx) * scale_log2);
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+        rs = exp_all();
+      }
+      l_run += rs;
+      if (DROP) {
+#pragma unroll
+        for (int h = 0; h < HALVES; ++h) {
+          uint32_t keep[4];
+          keep_bytes_query_lane(dr, head, qrow, k0 + 32 * h, lane, keep);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            if (!keep_reg(keep, r, dr.thr)) t[h * 16 + r] = 0.f;
+            asm volatile("" : "+v"(t[h * 16 + r]));  // the select stays in front of the packed conversion
+          }
+        }
+      }
+      if (next)
+        wait_vmem<C::NLOAD>();  // V is here; the next K may still be on its way
+      else
+        wait_vmem_all();
+#pragma unroll
+      for (int kk = 0; kk < 2 * HALVES; ++kk) {
+        const v8 pf = pack8<T>(&t[8 * kk]);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+          const int ro = kk * 16 * C::ROWB;
+          o[dt] = F::mfma(read_tr_pair<T>(vb, off.tr[0][dt] + ro, off.tr[1][dt] + ro), pf, o[dt]);
+        }
+      }
+      if (next) {
+        wait_lds_all();
+        fetch_v(j + C::NW);
+      }
+    };
+    int j = wave;
+    for (; j < n_plain; j += C::NW) tile(j, std::false_type{}, j + C::NW < nt);
+    for (; j < nt; j += C::NW) tile(j, std::true_type{}, j + C::NW < nt);
+
+    // ---- merge of the partial results (Eq. 3) ----
+    l_run = half_pair_sum(l_run);
+    SPARK_LDS float* const stat = reinterpret_cast<SPARK_LDS float*>(smem + C::STAT0);
+    if (g == 0) {
+      stat[wave * C::BM + c32] = m_run;
+      stat[(C::NW + wave) * C::BM + c32] = l_run;
+    }
+    __syncthreads();  // also: every wave has left its tiles
+    const int used = nt < C::NW ? nt : C::NW;  // the waves behind that had no tile
+    float m_all = stat[c32];
+    for (int w = 1; w < used; ++w) m_all = fmaxf(m_all, stat[w * C::BM + c32]);
+    float l_all = 0.f;
+    for (int w = 0; w < used; ++w)
+      l_all += stat[(C::NW + w) * C::BM + c32] * __builtin_amdgcn_exp2f(stat[w * C::BM + c32] - m_all);
+    const float mul = __builtin_amdgcn_exp2f(m_run - m_all) * (DROP ? dr.rescale : 1.0f) / l_all;
+    if (wave < used) {
+#pragma unroll
+      for (int q = 0; q < C::GROUPS; ++q) {
+        f32x4 x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = o[q / 4][(q % 4) * 4 + e] * mul;
+        // quad q goes to wave q / GPW, in the lane order of the accumulators (no bank conflicts)
+        lds_write(smem, (wave * C::GROUPS + q) * 1024 + lane * 16, x);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int gi = 0; gi < C::GPW; ++gi) {
+      const int q = wave * C::GPW + gi;
+      f32x4 sum = lds_read16<f32x4>(smem, q * 1024 + lane * 16);
+      for (int w = 1; w < used; ++w) sum += lds_read16<f32x4>(smem, (w * C::GROUPS + q) * 1024 + lane * 16);
+      v4 pk;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pk[e] = (T)sum[e];
+      lds_write(smem + C::STG0, c32 * C::OSTR + (8 * q + 4 * g) * 2, pk);
+    }
+    __syncthreads();
+    constexpr int CPR = D / 8;
+    const int row = tid / CPR, cc = tid % CPR;
+    if (row < C::BM && q0 + row < Nq && cc * 8 < dh)
+      *reinterpret_cast<u32x4*>(O + head_base(mo, head, H) + (size_t)(q0 + row) * (size_t)mo.row + cc * 8) =
+          lds_read16<u32x4>(smem + C::STG0, row * C::OSTR + cc * 16);
+    if (wave == 0 && g == 0 && qrow < Nq)
+      LSE[(size_t)head * Nq + qrow] = (m_all + __builtin_amdgcn_logf(l_all)) * 0.6931471805599453f;
+  }  // rep
+}
+
+}  // namespace spark

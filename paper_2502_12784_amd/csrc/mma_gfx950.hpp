@@ -187,4 +187,14 @@ static __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_ba
 // s_waitcnt vmcnt(0): every outstanding global/buffer load of this wave has returned.
 static __device__ __forceinline__ void wait_vmem_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// For a wave that reads what it loaded itself, with no barrier in between: wait until at most N of its
+// vector memory operations are outstanding / until its LDS reads have returned.  As assembly with a memory
+// clobber, because nothing else keeps the compiler from moving LDS reads across the wait.  Loads
+// complete in order; a store still on its way can only make wait_vmem longer, never too short.
+template <int N>
+static __device__ __forceinline__ void wait_vmem() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+static __device__ __forceinline__ void wait_lds_all() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
 }  // namespace spark

@@ -12,6 +12,7 @@
 #include "bwd_atomic_kernels.hpp"
 #include "bwd_kernels.hpp"
 #include "fwd_kernel.hpp"
+#include "fwd_split_kernel.hpp"
 #include "layout_probe.hpp"
 
 // Scratch memory of spark_mha_bwd_static: the backward's workspace (D and LSE * log2(e)) for callers
@@ -177,8 +178,50 @@ int launch_fwd_nw(const Problem& p, const void* Q, const void* K, const void* V,
   return launch_ok("forward kernel") ? SPARK_OK : SPARK_ERR_LAUNCH;
 }
 
+// Grid of mha_fwd_split_kernel (32 query rows per workgroup, one workgroup per CU).  Causal tiles are
+// paired for equal work only when they would not each get a CU of their own.
+template <bool CAUSAL>
+int64_t fwd_split_workgroups(const Problem& p, int* paired) {
+  const int nqt = (p.Nq + 31) / 32;
+  const int64_t bh = (int64_t)p.B * p.H;
+  *paired = CAUSAL && bh * nqt > 256;
+  return bh * (*paired ? causal_items<true>(nqt) : nqt);
+}
+
+// The split forward needs keys to split (up to 256 of them the merge costs what the shorter chain
+// gains: 5.1 -> 5.2 us at N = 192, d = 64) and every workgroup resident at once: measured, fp16
+// d = 64 / bf16 d = 128, us, mha_fwd_kernel -> split:
+//   1 head, N = 8192 (256 workgroups)       91 -> 29  / 134 -> 51
+//   8 heads, N = 1024 (256)                14.6 -> 8.0 / 20.6 -> 11.7
+//   1 query, 128 heads, 2048 keys (128)          -    / 40.7 -> 29.3
+//   1 query, 256 heads, 2048 keys (256)    30.8 -> 26.0 / 50.3 -> 50.5
+//   16 heads, N = 1024 (512)               14.7 -> 14.9 / 21.1 -> 23.6
+template <bool CAUSAL>
+bool split_forward(const Problem& p) {
+  int paired;
+  return p.Nk > 256 && fwd_split_workgroups<CAUSAL>(p, &paired) <= 256;
+}
+
+template <typename T, int D, bool CAUSAL, bool DROP>
+int launch_fwd_split(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* LSE) {
+  using C = FwdSplitCfg<D>;
+  auto kernel = mha_fwd_split_kernel<T, D, CAUSAL, DROP>;
+  static std::atomic<uint64_t> ready{0};
+  const int attr = ensure_smem(kernel, C::SMEM, ready);
+  if (attr != SPARK_OK) return attr;
+  const int nqt = (p.Nq + C::BM - 1) / C::BM;
+  int paired;
+  const int64_t grid = fwd_split_workgroups<CAUSAL>(p, &paired);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * C::NW), C::SMEM, p.st,
+                     static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
+                     static_cast<T*>(O), LSE, p.mq, p.mk, p.mv, p.mo, p.H, p.Nq, p.Nk, p.d, nqt, paired,
+                     p.scale * 1.4426950408889634f, make_dropout(p.thr, p.seed, p.offset));
+  return launch_ok("forward kernel (split keys)") ? SPARK_OK : SPARK_ERR_LAUNCH;
+}
+
 template <typename T, int D, bool CAUSAL, bool DROP>
 int launch_fwd(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* LSE) {
+  if (split_forward<CAUSAL>(p)) return launch_fwd_split<T, D, CAUSAL, DROP>(p, Q, K, V, O, LSE);
   if constexpr (D == 128) {
     // ... with the K/V tiles requested two at a time and one barrier every second iteration (the
     // workgroup has the CU's LDS to itself): another -1 ... -3 % on the forward.

@@ -130,6 +130,23 @@ static __device__ __forceinline__ void tile_dma(const BufView& view, int r0, SPA
     view.load16_to_lds(dst + (i * 4 + wave) * 1024, lane_src, (uint32_t)(r0 + i * RPG) * row_bytes);
 }
 
+// The same for ONE wave that fills a whole ROWS x D tile by itself.  A 1 KB block holds 16 / NV rows, so the
+// swizzle repeats every NV blocks and a lane needs NV source offsets.
+template <int D> struct WaveDma {
+  static constexpr int NV = D / 32;
+  uint32_t src[NV];
+  __device__ __forceinline__ WaveDma(int lane, uint32_t row_bytes, int dh) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) src[v] = dma_lane_src<D>(v, lane, row_bytes, dh);
+  }
+  template <int ROWS>
+  __device__ __forceinline__ void tile(const BufView& view, int r0, SPARK_LDS char* dst, uint32_t row_bytes) const {
+#pragma unroll
+    for (int b = 0; b < ROWS * 2 * D / 1024; ++b)
+      view.load16_to_lds(dst + b * 1024, src[b % NV], (uint32_t)(r0 + (b / NV) * 16) * row_bytes);
+  }
+};
+
 // Write a wave's transposed accumulator (D x 32, lane = column) times `mul` as 32 rows of D
 // 16-bit values: through the wave's LDS slice `ob`, then 16-byte row stores for rows < N
 // and columns < dh (`row_stride` elements apart).
