@@ -69,7 +69,8 @@ __global__ __launch_bounds__(256, (D == 64 && !DROP) ? 2 : 1) void mha_bwd_dkdv_
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const T* __restrict__ dO, const float* __restrict__ LSE2, const float* __restrict__ Dws,
     T* __restrict__ dK, T* __restrict__ dV, TensorMap mq, TensorMap mk, TensorMap mv, TensorMap mdo,
-    TensorMap mdk, TensorMap mdv, int H, int Nq, int Nk, int dh, int nkt, float scale, Dropout dr) {
+    TensorMap mdk, TensorMap mdv, int H, int Nq, int Nk, int dh, int nkt, int paired, float scale,
+    Dropout dr) {
   using F = Frag<T>;
   using v8 = typename F::v8;
   using C = BwdKvPipeCfg<D>;
@@ -80,7 +81,7 @@ __global__ __launch_bounds__(256, (D == 64 && !DROP) ? 2 : 1) void mha_bwd_dkdv_
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 5, c32 = lane & 31;
 
-  const int items = causal_items<CAUSAL>(nkt);  // causal: key tiles (p, nkt-1-p) are paired
+  const int items = paired ? causal_items<CAUSAL>(nkt) : nkt;  // causal: key tiles (p, nkt-1-p)
   const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
   const int head = logical / items;
   const int item = logical - head * items;
@@ -95,8 +96,8 @@ __global__ __launch_bounds__(256, (D == 64 && !DROP) ? 2 : 1) void mha_bwd_dkdv_
   const uint32_t do_lane_src = dma_lane_src<D>(wave, lane, do_row_bytes, dh);
   const float scale_log2 = scale * 1.4426950408889634f;
 
-  for (int rep = 0; rep < (CAUSAL ? 2 : 1); ++rep) {
-    const int kt = CAUSAL ? (rep == 0 ? item : nkt - 1 - item) : item;  // the long tile first
+  for (int rep = 0; rep < (CAUSAL && paired ? 2 : 1); ++rep) {
+    const int kt = rep == 0 ? item : nkt - 1 - item;  // the long tile first
     if (CAUSAL && rep == 1) {
       if (kt == item) break;  // odd tile count: the middle tile has no partner
       __syncthreads();        // the first tile's epilogue is done with the LDS
@@ -439,8 +440,8 @@ __global__ __launch_bounds__(256, 2) void mha_bwd_dq_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const T* __restrict__ O, const T* __restrict__ dO, const float* __restrict__ LSE,
     float* __restrict__ Dout, float* __restrict__ LSE2out, T* __restrict__ dQ, TensorMap mq, TensorMap mk,
-    TensorMap mv, TensorMap mo, TensorMap mdo, TensorMap mdq, int H, int Nq, int Nk, int dh, int nqt, float scale,
-    float scale_log2, Dropout dr) {
+    TensorMap mv, TensorMap mo, TensorMap mdo, TensorMap mdq, int H, int Nq, int Nk, int dh, int nqt, int paired,
+    float scale, float scale_log2, Dropout dr) {
   using F = Frag<T>;
   using v8 = typename F::v8;
   using C = BwdQCfg<D>;
@@ -451,7 +452,7 @@ __global__ __launch_bounds__(256, 2) void mha_bwd_dq_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 5, c32 = lane & 31;
 
-  const int items = causal_items<CAUSAL>(nqt);  // causal: query tiles (nqt-1-p, p) are paired
+  const int items = paired ? causal_items<CAUSAL>(nqt) : nqt;  // causal: query tiles (nqt-1-p, p)
   const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
   const int head = logical / items;
   const int item = logical - head * items;
@@ -471,8 +472,8 @@ __global__ __launch_bounds__(256, 2) void mha_bwd_dq_kernel(
     tile_dma<D, C::BN>(vview, j * C::BN, smem + buf * C::STAGE + C::TILE, wave, v_lane_src, v_row_bytes);
   };
 
-  for (int rep = 0; rep < (CAUSAL ? 2 : 1); ++rep) {
-    const int qt = CAUSAL ? (rep == 0 ? nqt - 1 - item : item) : item;  // the long tile first
+  for (int rep = 0; rep < (CAUSAL && paired ? 2 : 1); ++rep) {
+    const int qt = CAUSAL && rep == 0 ? nqt - 1 - item : item;  // the long tile first
     if (CAUSAL && rep == 1) {
       if (qt == nqt - 1 - item) break;  // odd tile count: the middle tile has no partner
       __syncthreads();                  // the first tile's epilogue is done with the LDS

@@ -57,7 +57,7 @@ template <typename T, int D, bool CAUSAL, bool DROP, int NW = 4, bool PAIR = fal
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void mha_fwd_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     T* __restrict__ O, float* __restrict__ LSE, TensorMap mq, TensorMap mk, TensorMap mv,
-    TensorMap mo, int H, int Nq, int Nk, int dh, int nqt, float scale_log2, Dropout dr) {
+    TensorMap mo, int H, int Nq, int Nk, int dh, int nqt, int paired, float scale_log2, Dropout dr) {
   using F = Frag<T>;
   using v8 = typename F::v8;
   using v4 = typename F::v4;
@@ -74,10 +74,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void mha_fwd_kernel(
   const uint32_t k_lane_src = dma_lane_src<D>(wave & 3, lane, k_row_bytes, dh);
   const uint32_t v_lane_src = dma_lane_src<D>(wave & 3, lane, v_row_bytes, dh);
 
-  // Work items.  Non-causal: one query tile per workgroup.  Causal: a workgroup takes the pair
-  // of tiles (nqt-1-p, p), whose loop lengths add up to the same total for every p, so that
-  // all workgroups carry equal work and the launch has no tail of long tiles.
-  const int items = causal_items<CAUSAL>(nqt);
+  // Work items.  Non-causal, or a causal grid too small for pairs: one query tile per workgroup.
+  // Otherwise a causal workgroup takes the pair of tiles (nqt-1-p, p), whose loop lengths add up to
+  // the same total for every p, so that all workgroups carry equal work and the launch has no
+  // tail of long tiles.
+  const int items = paired ? causal_items<CAUSAL>(nqt) : nqt;
   const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
   const int head = logical / items;
   const int item = logical - head * items;
@@ -87,8 +88,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void mha_fwd_kernel(
   const T* Kh = K + head_base(mk, head, H);
   const T* Vh = V + head_base(mv, head, H);
 
-  for (int rep = 0; rep < (CAUSAL ? 2 : 1); ++rep) {
-    const int qt = CAUSAL ? (rep == 0 ? nqt - 1 - item : item) : item;
+  for (int rep = 0; rep < (CAUSAL && paired ? 2 : 1); ++rep) {
+    const int qt = CAUSAL && rep == 0 ? nqt - 1 - item : item;
     if (CAUSAL && rep == 1) {
       if (qt == nqt - 1 - item) break;  // odd tile count: the middle tile has no partner
       __syncthreads();                  // the first tile's epilogue is done with the LDS

@@ -161,6 +161,22 @@ bool wide_workgroups(const Problem& p) {
   return p.d > 64 && p.Nk >= 2048 && (int64_t)p.B * p.H * causal_items<CAUSAL>((int)tiles) >= 512;
 }
 
+// Whether a causal grid runs as complementary pairs of tiles, (n-1-p, p) in one workgroup: equal work for
+// every workgroup, at the price of half as many of them, each with two prologues and epilogues in
+// series.  `n` tiles per head, `bh` heads, `per_cu` workgroups of the kernel on a CU.  Not paired:
+//  * up to one tile per CU: the longest tile alone is shorter than a pair (forward / dQ / dK/dV, paired ->
+//    unpaired us, 256 tiles: N = 256 d = 64 11.9/16.9/17.1 -> 8.0/12.1/12.4; N = 1024 d = 128
+//    30.3/42.0/44.2 -> 24.8/33.6/37.1; N = 4096 d = 64 53.6/61.9/75.8 -> 49.3/55.6/70.4; from 320 tiles on
+//    the pairs win: N = 4096 53.5/61.5/75.9 against 67.8/81.3/100.8);
+//  * two tiles per head while all are resident: lengths differ by a factor of two at most (512 tiles, d = 64
+//    12.2/19.5/18.6 -> 10.5/17.0/17.8);
+//  * three tiles per head: the middle one stays alone in a workgroup with half the others' work (2049 tiles,
+//    d = 128: 79/135/175 -> 65/108/139).
+int pair_tiles(bool causal, int64_t bh, int n, int per_cu) {
+  if (!causal || bh * n <= 256 || n == 3) return 0;
+  return !(n == 2 && bh * n <= 256 * per_cu);
+}
+
 template <typename T, int D, bool CAUSAL, bool DROP, int NW, bool PAIR = false>
 int launch_fwd_nw(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* LSE) {
   using C = FwdCfg<D, NW, PAIR>;
@@ -171,9 +187,10 @@ int launch_fwd_nw(const Problem& p, const void* Q, const void* K, const void* V,
   const int BH = p.B * p.H;
   const int nqt = (p.Nq + C::BM - 1) / C::BM;
   const float scale_log2 = p.scale * 1.4426950408889634f;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * causal_items<CAUSAL>(nqt))), dim3(64 * NW), C::SMEM, p.st,
-                     static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
-                     static_cast<T*>(O), LSE, p.mq, p.mk, p.mv, p.mo, p.H, p.Nq, p.Nk, p.d, nqt, scale_log2,
+  const int paired = pair_tiles(CAUSAL, BH, nqt, 2);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * (paired ? causal_items<true>(nqt) : nqt))), dim3(64 * NW), C::SMEM,
+                     p.st, static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
+                     static_cast<T*>(O), LSE, p.mq, p.mk, p.mv, p.mo, p.H, p.Nq, p.Nk, p.d, nqt, paired, scale_log2,
                      make_dropout(p.thr, p.seed, p.offset));
   return launch_ok("forward kernel") ? SPARK_OK : SPARK_ERR_LAUNCH;
 }
@@ -256,9 +273,10 @@ int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, co
     const int attr = ensure_smem(kernel, C::SMEM, ready);
     if (attr != SPARK_OK) return attr;
     const int nqt = (p.Nq + C::BM - 1) / C::BM;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * causal_items<CAUSAL>(nqt))), dim3(256), C::SMEM, p.st,
+    const int paired = pair_tiles(CAUSAL, BH, nqt, 2);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * (paired ? causal_items<true>(nqt) : nqt))), dim3(256), C::SMEM, p.st,
                        q, k, v, o, dout, LSE, Dws, LSE2ws, static_cast<T*>(dQ), p.mq, p.mk, p.mv, p.mo,
-                       p.mdo, p.mdq, p.H, p.Nq, p.Nk, p.d, nqt, p.scale, p.scale * 1.4426950408889634f, dr);
+                       p.mdo, p.mdq, p.H, p.Nq, p.Nk, p.d, nqt, paired, p.scale, p.scale * 1.4426950408889634f, dr);
     if (!launch_ok("dQ kernel") || !mark(1)) return SPARK_ERR_LAUNCH;
   }
   {  // dK, dV: one workgroup per tile of 128 keys, software-pipelined
@@ -268,9 +286,10 @@ int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, co
     const int attr = ensure_smem(kernel, C::SMEM, ready);
     if (attr != SPARK_OK) return attr;
     const int nkt = (p.Nk + C::BN - 1) / C::BN;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * causal_items<CAUSAL>(nkt))), dim3(256), C::SMEM, p.st,
+    const int paired = pair_tiles(CAUSAL, BH, nkt, D == 64 ? 2 : 1);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * (paired ? causal_items<true>(nkt) : nkt))), dim3(256), C::SMEM, p.st,
                        q, k, v, dout, LSE2ws, Dws, static_cast<T*>(dK), static_cast<T*>(dV), p.mq, p.mk,
-                       p.mv, p.mdo, p.mdk, p.mdv, p.H, p.Nq, p.Nk, p.d, nkt, p.scale, dr);
+                       p.mv, p.mdo, p.mdk, p.mdv, p.H, p.Nq, p.Nk, p.d, nkt, paired, p.scale, dr);
     if (!launch_ok("dK/dV kernel") || !mark(2)) return SPARK_ERR_LAUNCH;
   }
   return SPARK_OK;
