@@ -1,9 +1,12 @@
-"""Thin ctypes binding of the C ABI in ``include/spark_mha.h``.
+"""Thin binding of the C ABI in ``include/spark_mha.h``.
 
 Argument marshalling only: every step of the attention path runs in the HIP
 kernels of ``libspark_mha.so``.  torch is used for device memory and for the
 current stream.  There is no fallback: if the library is missing or a call
 fails, an exception is raised.
+
+Ordinary calls are marshalled by the extension ``_spark_host`` (csrc/host_binding.cpp);
+what it does not take (and every error) goes through the ctypes code below.
 """
 from __future__ import annotations
 
@@ -12,6 +15,7 @@ import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libspark_mha.so")
+HOST_PATH = os.path.join(HERE, "_spark_host.so")
 
 SPARK_F16 = 0
 SPARK_BF16 = 1
@@ -25,6 +29,10 @@ EXPORTS = ("spark_mha_fwd", "spark_mha_bwd", "spark_mha_bwd_marked",
            "spark_mha_bwd_atomic_workspace_bytes", "spark_mha_dropout_bwd_marked")
 
 _lib = None
+_host = None  # the extension module; loaded together with the library
+
+# what an entry point accepts, as csrc/host_binding.cpp numbers it
+_SELF, _CROSS, _STRIDED = 0, 1, 2
 
 
 class Strides(ctypes.Structure):
@@ -49,21 +57,36 @@ def library_is_stale() -> bool:
     return any(os.path.getmtime(f) > built for f in sources if os.path.exists(f))
 
 
+def host_binding_is_stale() -> bool:
+    """The same for the host extension."""
+    if not os.path.exists(HOST_PATH):
+        return True
+    sources = (os.path.join(HERE, "csrc", "host_binding.cpp"),
+               os.path.join(os.path.dirname(HERE), "include", "spark_mha.h"))
+    return any(os.path.getmtime(f) > os.path.getmtime(HOST_PATH) for f in sources if os.path.exists(f))
+
+
 def load_library() -> ctypes.CDLL:
     """Load the in-tree shared library; build it first if it is missing or older than its sources
     (an edit under csrc/ must never be tested or timed against the previous binary)."""
-    global _lib
+    global _lib, _host
     if _lib is not None:
         return _lib
     if library_is_stale():
         from .build import build_library
         build_library()
+    if host_binding_is_stale():
+        from .build import build_host_binding
+        build_host_binding()
     # torch first: its wheel brings its own copy of the HIP runtime, and the streams and pointers this
     # binding passes belong to that copy.  Loaded after torch, the library binds to the runtime that
     # is already in the process; loaded before it, it would pull in a second one and every launch
     # on a torch stream would be refused.
-    import torch  # noqa: F401
+    import torch
     lib = ctypes.CDLL(LIB_PATH)
+    from . import _spark_host
+    if hasattr(torch._C, "_cuda_getCurrentRawStream"):  # not in a torch without GPU support: takes no call then
+        _spark_host.bind(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
     vp, i, f = ctypes.c_void_p, ctypes.c_int, ctypes.c_float
     lib.spark_mha_fwd.restype = i
     lib.spark_mha_fwd.argtypes = [vp, vp, vp, vp, vp, i, i, i, i, f, i, i, vp]
@@ -109,6 +132,7 @@ def load_library() -> ctypes.CDLL:
     lib.spark_layout_probe.argtypes = [vp, i, vp]
     lib.spark_status_str.restype = ctypes.c_char_p
     lib.spark_status_str.argtypes = [i]
+    _host = _spark_host
     _lib = lib
     return lib
 
@@ -138,6 +162,13 @@ def _require(t, shape, dtype, name):
         raise ValueError("%s must be a contiguous %s tensor of shape %s" % (name, dtype, tuple(shape)))
 
 
+def _native(out):
+    """Result of a call that the host extension took: its status, if it is one, becomes an exception."""
+    if type(out) is int:
+        _check(out)
+    return out
+
+
 def _stream_ptr():
     import torch
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
@@ -147,6 +178,9 @@ def spark_mha_fwd(Q, K, V, scale: float, causal: bool, O=None, LSE=None):
     """O, LSE = fused attention forward of [B,H,N,d] device tensors on the current stream."""
     import torch
     lib = load_library()
+    out = _host.fwd(Q, K, V, O, LSE, scale, causal, 0.0, 0, 0, _SELF)
+    if out is not None:
+        return _native(out)
     B, H, N, d = Q.shape
     for t, n in ((Q, "Q"), (K, "K"), (V, "V")):
         _require(t, (B, H, N, d), Q.dtype, n)
@@ -189,6 +223,9 @@ def spark_mha_cross_fwd(Q, K, V, scale: float, causal: bool = False, O=None, LSE
     dropout: None, or (p_drop, seed, offset) -> spark_mha_dropout_fwd."""
     import torch
     lib = load_library()
+    out = _host.fwd(Q, K, V, O, LSE, scale, causal, *((0.0, 0, 0) if dropout is None else dropout), _CROSS)
+    if out is not None:
+        return _native(out)
     B, H, Nq, d = Q.shape
     Nk = K.shape[2]
     _require(Q, (B, H, Nq, d), Q.dtype, "Q")
@@ -233,6 +270,11 @@ def spark_mha_cross_bwd(Q, K, V, O, LSE, dO, scale: float, causal: bool = False,
     dropout: None, or (p_drop, seed, offset) -> spark_mha_dropout_bwd."""
     import torch
     lib = load_library()
+    if events is None and workspace is None:
+        out = _host.bwd(Q, K, V, O, LSE, dO, dQ, dK, dV, scale, causal,
+                        *((0.0, 0, 0) if dropout is None else dropout), _CROSS)
+        if out is not None:
+            return _native(out)
     B, H, Nq, d = Q.shape
     Nk = K.shape[2]
     for t, n in ((Q, "Q"), (O, "O"), (dO, "dO")):
@@ -283,6 +325,9 @@ def spark_mha_strided_fwd(Q, K, V, scale: float, causal: bool = False, p_drop: f
     [B,N,H,d] projection output, or slices of a packed QKV buffer)."""
     import torch
     lib = load_library()
+    out = _host.fwd(Q, K, V, O, LSE, scale, causal, p_drop, seed, offset, _STRIDED)
+    if out is not None:
+        return _native(out)
     B, H, Nq, d = Q.shape
     Nk = K.shape[2]
     if O is None:
@@ -305,6 +350,10 @@ def spark_mha_strided_bwd(Q, K, V, O, LSE, dO, scale: float, causal: bool = Fals
     """Backward on strided [B,H,N,d] views; gradients default to the layouts of Q, K, V."""
     import torch
     lib = load_library()
+    if workspace is None:
+        out = _host.bwd(Q, K, V, O, LSE, dO, dQ, dK, dV, scale, causal, p_drop, seed, offset, _STRIDED)
+        if out is not None:
+            return _native(out)
     B, H, Nq, d = Q.shape
     Nk = K.shape[2]
     dQ = torch.empty_like(Q) if dQ is None else dQ
@@ -381,6 +430,10 @@ def spark_mha_bwd(Q, K, V, O, LSE, dO, scale: float, causal: bool, dQ=None, dK=N
     records 3 events starting at that index around the two kernels (dQ, then dK/dV)."""
     import torch
     lib = load_library()
+    if events is None and workspace is None:
+        out = _host.bwd(Q, K, V, O, LSE, dO, dQ, dK, dV, scale, causal, 0.0, 0, 0, _SELF)
+        if out is not None:
+            return _native(out)
     B, H, N, d = Q.shape
     for t, n in ((Q, "Q"), (K, "K"), (V, "V"), (O, "O"), (dO, "dO")):
         _require(t, (B, H, N, d), Q.dtype, n)

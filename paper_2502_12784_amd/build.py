@@ -1,4 +1,5 @@
-"""Compile the HIP sources into ``libspark_mha.so`` next to this file (gfx950 only)."""
+"""Compile the HIP sources into ``libspark_mha.so`` and the host binding into ``_spark_host.so``, next to
+this file (gfx950 only)."""
 from __future__ import annotations
 
 import os
@@ -28,6 +29,30 @@ def build_library(verbose: bool = False) -> str:
         print(out)
     os.replace(tmp, LIB)
     return LIB
+
+
+HOST_EXT = os.path.join(HERE, "_spark_host.so")
+HOST_SOURCE = os.path.join(CSRC, "host_binding.cpp")
+
+
+def build_host_binding() -> str:
+    """Compile csrc/host_binding.cpp (host code only) into the CPython extension ``_spark_host``; it
+    links against the library next to it, which must have been built, and against torch."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    tmp = HOST_EXT + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    cmd += ["-isystem" + d for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]]
+    cmd += [HOST_SOURCE, "-o", tmp] + ["-L" + d for d in cpp_extension.library_paths()]
+    cmd += ["-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-L" + HERE, "-l:libspark_mha.so",
+            "-Wl,-rpath,$ORIGIN"]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("building the host binding failed:\n" + res.stdout)
+    os.replace(tmp, HOST_EXT)
+    return HOST_EXT
 
 
 MIX_BENCH = os.path.join(HERE, "mix_floor_bench")
@@ -134,3 +159,4 @@ if __name__ == "__main__":
         print(build_mix_floor_bench())
     else:
         print(build_library(verbose=True))
+        print(build_host_binding())

@@ -1,0 +1,84 @@
+"""The native marshalling of ordinary calls (csrc/host_binding.cpp) against the general ctypes path: the same
+kernels, so the same bits, layouts and errors; and calls that it must leave to the general path."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+class _NotTaken:
+    """Stands in for the extension: takes no call."""
+
+    @staticmethod
+    def fwd(*args):
+        return None
+
+    bwd = fwd
+
+
+def _calls(kind, dtype):
+    import torch
+    import paper_2502_12784_amd as pkg
+    g = torch.Generator(device="cuda").manual_seed(7)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda").to(dtype)
+    if kind == "packed":
+        qkv, dO = n(2, 77, 3, 3, 40), n(2, 77, 3, 40).permute(0, 2, 1, 3)
+        Q, K, V = (qkv[:, :, i].permute(0, 2, 1, 3) for i in range(3))
+        O, L = pkg.spark_mha_strided_fwd(Q, K, V, 0.2, True, 0.1, -5, 1 << 40)
+        return (O, L) + pkg.spark_mha_strided_bwd(Q, K, V, O, L, dO, 0.2, True, 0.1, -5, 1 << 40)
+    Nk = 130 if kind == "cross" else 70
+    Q, dO, K, V = n(2, 3, 70, 64), n(2, 3, 70, 64), n(2, 3, Nk, 64), n(2, 3, Nk, 64)
+    if kind == "self":
+        O, L = pkg.spark_mha_fwd(Q, K, V, 0.125, True)
+        return (O, L) + pkg.spark_mha_bwd(Q, K, V, O, L, dO, 0.125, True)
+    if kind == "given":  # outputs of the caller
+        O, L, dQ, dK, dV = (torch.full_like(Q, 9.0) for _ in range(5))
+        L = torch.full((2, 3, 70), 9.0, device="cuda")
+        out = pkg.spark_mha_fwd(Q, K, V, 0.125, False, O, L)
+        grads = pkg.spark_mha_bwd(Q, K, V, O, L, dO, 0.125, False, dQ, dK, dV)
+        assert out[0].data_ptr() == O.data_ptr() and grads[2].data_ptr() == dV.data_ptr()
+        return out + grads
+    if kind == "dropout":
+        O, L = pkg.spark_mha_dropout_fwd(Q, K, V, 0.125, False, 0.1, 12345678901234, 3)
+        return (O, L) + pkg.spark_mha_dropout_bwd(Q, K, V, O, L, dO, 0.125, False, 0.1, 12345678901234, 3)
+    O, L = pkg.spark_mha_cross_fwd(Q, K, V, 0.125)
+    return (O, L) + pkg.spark_mha_cross_bwd(Q, K, V, O, L, dO, 0.125)
+
+
+@pytest.mark.parametrize("dtype", ["float16", "bfloat16"])
+@pytest.mark.parametrize("kind", ["self", "given", "cross", "dropout", "packed"])
+def test_native_and_general_path_agree(kind, dtype, monkeypatch):
+    import torch
+    from paper_2502_12784_amd import binding
+    binding.load_library()
+    dt = getattr(torch, dtype)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):  # the current stream, not the default one
+        got = _calls(kind, dt)
+    side.synchronize()
+    monkeypatch.setattr(binding, "_host", _NotTaken)
+    want = _calls(kind, dt)
+    for a, b in zip(got, want):
+        assert a.shape == b.shape and a.stride() == b.stride() and a.dtype == b.dtype
+        assert torch.equal(a, b)
+
+
+def test_unusual_calls_take_the_general_path():
+    import torch
+    from paper_2502_12784_amd import SparkError, binding, spark_mha_fwd
+    binding.load_library()
+    q = torch.randn(1, 2, 33, 64, device="cuda").half()
+    host = binding._host
+    args = (None, None, 0.125, False, 0.0, 0, 0, 0)
+    assert host.fwd(q, q, q, *args) is not None
+    for bad in (q.cpu(), q[0], q.float(), q.transpose(2, 3), torch.nn.Parameter(q).to_sparse(), q[:, :, :32], "q"):
+        assert host.fwd(q, bad, q, *args) is None
+    assert host.fwd(q, q, q, None, None, 1, False, 0.0, 0, 0, 0) is None  # an int for the scale
+    O, _ = spark_mha_fwd(q, q, q, 1, 0)                                   # ... which the general path converts
+    assert torch.equal(O, spark_mha_fwd(q, q, q, 1.0, False)[0])
+    with pytest.raises(ValueError):
+        spark_mha_fwd(q, q[:, :, :32], q, 0.125, False)
+    with pytest.raises(SparkError):
+        spark_mha_fwd(q, q, q, float("nan"), False)
+    with pytest.raises(SparkError):
+        spark_mha_fwd(q.float(), q.float(), q.float(), 0.125, False)
