@@ -113,8 +113,8 @@ int spark_mha_bwd(const void* Q, const void* K, const void* V, const void* O, co
 /*
  * spark_mha_bwd with profiling marks: identical work, and additionally records the caller's
  * three HIP events (hipEvent_t handles, host array) on `stream`: events[0] before the dQ
- * kernel, events[1] after it, events[2] after the dK/dV kernel.  The caller creates, reads and
- * destroys the events.  SPARK_ERR_NULL if any is NULL.
+ * kernel, events[1] after it, events[2] after the dK/dV kernel; where one kernel does both (small
+ * problems) events[1] and events[2] follow it.  The caller creates, reads and destroys the events.  SPARK_ERR_NULL if any is NULL.
  */
 int spark_mha_bwd_marked(const void* Q, const void* K, const void* V, const void* O,
                          const float* LSE, const void* dO, void* dQ, void* dK, void* dV,

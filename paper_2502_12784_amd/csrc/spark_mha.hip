@@ -11,6 +11,7 @@
 
 #include "bwd_atomic_kernels.hpp"
 #include "bwd_kernels.hpp"
+#include "bwd_split_kernel.hpp"
 #include "fwd_kernel.hpp"
 #include "fwd_split_kernel.hpp"
 #include "layout_probe.hpp"
@@ -247,6 +248,40 @@ int launch_fwd(const Problem& p, const void* Q, const void* K, const void* V, vo
   return launch_fwd_nw<T, D, CAUSAL, DROP, 4>(p, Q, K, V, O, LSE);
 }
 
+// Grid of mha_bwd_split_kernel: 32 queries or 32 keys per workgroup, one workgroup per CU.
+int64_t bwd_split_workgroups(const Problem& p) {
+  return (int64_t)p.B * p.H * ((p.Nq + 31) / 32 + (p.Nk + 31) / 32);
+}
+// It is taken while every CU has at most two of them, or four of a long causal problem (whose workgroups
+// differ in length and fill each other's gaps): a further round costs it 16 iterations of chain at N = 4096,
+// while the two kernels below still find idle CUs.  Backward, us, fp16, two kernels -> split
+// (n workgroups), square problems of BH heads:
+//   d = 64:  2 x 128 (16)  11.6 -> 6.4    16 x 256 (256)  15.1 -> 8.6    4 x 1024 (256)   35.3 -> 13.2
+//            8 x 1024 (512) 35.5 -> 22.4  2 x 4096 (512) 115.5 -> 58.5   16 x 1024 (1024) 36.0 -> 43.3 (not taken)
+//            causal 4 x 4096 (1024) 119 -> 73, 16 x 1024 (1024) 38.0 -> 33.5, 32 x 512 (1024) 24.6 -> 28.5 (not)
+//   d = 128: 2 x 128 17.6 -> 9.5    4 x 1024 58.4 -> 23.5    8 x 1024 58.7 -> 39.2    2 x 4096 197 -> 129
+//            causal 4 x 4096 203 -> 145, 16 x 1024 61.9 -> 54.4
+bool split_backward(const Problem& p) {
+  return bwd_split_workgroups(p) <= (p.causal && p.Nk >= 1024 ? 1024 : 512);
+}
+
+template <typename T, int D, bool CAUSAL, bool DROP>
+int launch_bwd_split(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const float* LSE,
+                     const void* dO, void* dQ, void* dK, void* dV) {
+  using C = BwdSplitCfg<D>;
+  auto kernel = mha_bwd_split_kernel<T, D, CAUSAL, DROP>;
+  static std::atomic<uint64_t> ready{0};
+  const int attr = ensure_smem(kernel, C::SMEM, ready);
+  if (attr != SPARK_OK) return attr;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)bwd_split_workgroups(p)), dim3(64 * C::NW), C::SMEM, p.st,
+                     static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
+                     static_cast<const T*>(O), static_cast<const T*>(dO), LSE, static_cast<T*>(dQ),
+                     static_cast<T*>(dK), static_cast<T*>(dV), p.mq, p.mk, p.mv, p.mo, p.mdo, p.mdq, p.mdk, p.mdv,
+                     p.H, p.Nq, p.Nk, p.d, (p.Nq + C::BM - 1) / C::BM, (p.Nk + C::BM - 1) / C::BM, p.scale,
+                     make_dropout(p.thr, p.seed, p.offset));
+  return launch_ok("backward kernel (split)") ? SPARK_OK : SPARK_ERR_LAUNCH;
+}
+
 template <typename T, int D, bool CAUSAL, bool DROP>
 int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, const void* O,
                const float* LSE, const void* dO, void* dQ, void* dK, void* dV, float* Dws,
@@ -265,6 +300,11 @@ int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, co
   };
 
   if (!mark(0)) return SPARK_ERR_LAUNCH;
+  if (split_backward(p)) {  // one kernel: both later marks follow it
+    const int rc = launch_bwd_split<T, D, CAUSAL, DROP>(p, Q, K, V, O, LSE, dO, dQ, dK, dV);
+    if (rc != SPARK_OK) return rc;
+    return mark(1) && mark(2) ? SPARK_OK : SPARK_ERR_LAUNCH;
+  }
   {  // dQ: one workgroup per tile of 128 queries (8-wave workgroups measured 3 % slower here).
      // Also writes D = rowsum(dO o O) and LSE * log2(e) for the dK/dV kernel.
     using C = BwdQCfg<D>;
