@@ -64,13 +64,14 @@ template <int D> struct BwdKvPipeCfg {
   static_assert(4 * 32 * OSTR <= SLOTS * STAGE, "epilogue staging must fit");
 };
 
+// The workgroup's part: key tile `item` of `head`, and its partner if the causal tiles are paired.
 template <typename T, int D, bool CAUSAL, bool DROP>
-__global__ __launch_bounds__(256, (D == 64 && !DROP) ? 2 : 1) void mha_bwd_dkdv_pipe_kernel(
+static __device__ __forceinline__ void bwd_dkdv_pipe(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const T* __restrict__ dO, const float* __restrict__ LSE2, const float* __restrict__ Dws,
-    T* __restrict__ dK, T* __restrict__ dV, TensorMap mq, TensorMap mk, TensorMap mv, TensorMap mdo,
-    TensorMap mdk, TensorMap mdv, int H, int Nq, int Nk, int dh, int nkt, int paired, float scale,
-    Dropout dr) {
+    T* __restrict__ dK, T* __restrict__ dV, const TensorMap& mq, const TensorMap& mk, const TensorMap& mv,
+    const TensorMap& mdo, const TensorMap& mdk, const TensorMap& mdv, int H, int Nq, int Nk, int dh, int nkt,
+    int paired, float scale, const Dropout& dr, int head, int item) {
   using F = Frag<T>;
   using v8 = typename F::v8;
   using C = BwdKvPipeCfg<D>;
@@ -80,11 +81,6 @@ __global__ __launch_bounds__(256, (D == 64 && !DROP) ? 2 : 1) void mha_bwd_dkdv_
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 5, c32 = lane & 31;
-
-  const int items = paired ? causal_items<CAUSAL>(nkt) : nkt;  // causal: key tiles (p, nkt-1-p)
-  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int head = logical / items;
-  const int item = logical - head * items;
 
   const T* Kh = K + head_base(mk, head, H);
   const T* Vh = V + head_base(mv, head, H);
@@ -419,6 +415,20 @@ __global__ __launch_bounds__(256, (D == 64 && !DROP) ? 2 : 1) void mha_bwd_dkdv_
   }  // rep
 }
 
+template <typename T, int D, bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(256, (D == 64 && !DROP) ? 2 : 1) void mha_bwd_dkdv_pipe_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
+    const T* __restrict__ dO, const float* __restrict__ LSE2, const float* __restrict__ Dws,
+    T* __restrict__ dK, T* __restrict__ dV, TensorMap mq, TensorMap mk, TensorMap mv, TensorMap mdo,
+    TensorMap mdk, TensorMap mdv, int H, int Nq, int Nk, int dh, int nkt, int paired, float scale,
+    Dropout dr) {
+  const int items = paired ? causal_items<CAUSAL>(nkt) : nkt;  // causal: key tiles (p, nkt-1-p)
+  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int head = logical / items;
+  bwd_dkdv_pipe<T, D, CAUSAL, DROP>(Q, K, V, dO, LSE2, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq, Nk, dh, nkt,
+                                    paired, scale, dr, head, logical - head * items);
+}
+
 // ---------------------------------------------------------------------------------------
 // dQ
 // ---------------------------------------------------------------------------------------
@@ -435,13 +445,17 @@ template <int D> struct BwdQCfg {
   static_assert((STAGE & (STAGE - 1)) == 0, "XOR buffer switch");
 };
 
-template <typename T, int D, bool CAUSAL, bool DROP>
-__global__ __launch_bounds__(256, 2) void mha_bwd_dq_kernel(
+// The workgroup's part: query tile `item` of `head`, and its partner if the causal tiles are paired.
+// STATS: the workspace holds -D and LSE * log2(e) already (mha_bwd_stats_kernel); otherwise they are
+// formed here and left there for the dK/dV kernel.
+template <typename T, int D, bool CAUSAL, bool DROP, bool STATS>
+static __device__ __forceinline__ void bwd_dq(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const T* __restrict__ O, const T* __restrict__ dO, const float* __restrict__ LSE,
-    float* __restrict__ Dout, float* __restrict__ LSE2out, T* __restrict__ dQ, TensorMap mq, TensorMap mk,
-    TensorMap mv, TensorMap mo, TensorMap mdo, TensorMap mdq, int H, int Nq, int Nk, int dh, int nqt, int paired,
-    float scale, float scale_log2, Dropout dr) {
+    float* __restrict__ Dws, float* __restrict__ LSE2ws, T* __restrict__ dQ, const TensorMap& mq,
+    const TensorMap& mk, const TensorMap& mv, const TensorMap& mo, const TensorMap& mdo, const TensorMap& mdq, int H,
+    int Nq, int Nk, int dh, int nqt, int paired, float scale, float scale_log2, const Dropout& dr, int head,
+    int item) {
   using F = Frag<T>;
   using v8 = typename F::v8;
   using C = BwdQCfg<D>;
@@ -452,14 +466,9 @@ __global__ __launch_bounds__(256, 2) void mha_bwd_dq_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 5, c32 = lane & 31;
 
-  const int items = paired ? causal_items<CAUSAL>(nqt) : nqt;  // causal: query tiles (nqt-1-p, p)
-  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int head = logical / items;
-  const int item = logical - head * items;
-
   const T* Qh = Q + head_base(mq, head, H);
   const T* dOh = dO + head_base(mdo, head, H);
-  const T* Oh = O + head_base(mo, head, H);
+  const T* Oh = STATS ? nullptr : O + head_base(mo, head, H);
   const BufView kview(K + head_base(mk, head, H), head_span_bytes(mk, Nk, dh));
   const BufView vview(V + head_base(mv, head, H), head_span_bytes(mv, Nk, dh));
   const uint32_t k_row_bytes = (uint32_t)mk.row * 2, v_row_bytes = (uint32_t)mv.row * 2;
@@ -487,9 +496,10 @@ __global__ __launch_bounds__(256, 2) void mha_bwd_dq_kernel(
     for (int ks = 0; ks < KS; ++ks) {
       qf[ks] = load_row_chunk<v8>(Qh + (size_t)qrow_c * (size_t)mq.row, ks * 16 + g * 8, dh);
       dof[ks] = load_row_chunk<v8>(dOh + (size_t)qrow_c * (size_t)mdo.row, ks * 16 + g * 8, dh);
-      of[ks] = load_row_chunk<v8>(Oh + (size_t)qrow_c * (size_t)mo.row, ks * 16 + g * 8, dh);
+      if (!STATS) of[ks] = load_row_chunk<v8>(Oh + (size_t)qrow_c * (size_t)mo.row, ks * 16 + g * 8, dh);
     }
-    float lse2 = LSE[(size_t)head * Nq + qrow_c];
+    float lse2 = STATS ? LSE2ws[(size_t)head * Nq + qrow_c] : LSE[(size_t)head * Nq + qrow_c];
+    float Dq = STATS ? -Dws[(size_t)head * Nq + qrow_c] : 0.f;
 
     int kv_end = Nk;
     if (CAUSAL) {
@@ -512,16 +522,17 @@ __global__ __launch_bounds__(256, 2) void mha_bwd_dq_kernel(
     // 32 further on the other half.  Under dropout dS = r P o (M o dPraw - D (1-p)), so D is kept
     // multiplied by the keep probability.  The dK/dV kernel runs after this one and reads D and
     // LSE * log2(e) from the workspace.
-    float Dq = 0.f;
+    if (!STATS) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
+      for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) Dq = __builtin_fmaf((float)of[ks][i], (float)dof[ks][i], Dq);
-    Dq = half_pair_sum(Dq) * (DROP ? dr.keep_prob : 1.0f);
-    lse2 *= 1.4426950408889634f;
-    if (g == 0 && qrow < Nq) {
-      Dout[(size_t)head * Nq + qrow] = -Dq;  // negated: the dK/dV kernel starts its dP accumulators from it
-      LSE2out[(size_t)head * Nq + qrow] = lse2;
+        for (int i = 0; i < 8; ++i) Dq = __builtin_fmaf((float)of[ks][i], (float)dof[ks][i], Dq);
+      Dq = half_pair_sum(Dq) * (DROP ? dr.keep_prob : 1.0f);
+      lse2 *= 1.4426950408889634f;
+      if (g == 0 && qrow < Nq) {
+        Dws[(size_t)head * Nq + qrow] = -Dq;  // negated: the dK/dV kernel starts its dP accumulators from it
+        LSE2ws[(size_t)head * Nq + qrow] = lse2;
+      }
     }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]), "+v"(dof[ks]));
@@ -689,6 +700,75 @@ __global__ __launch_bounds__(256, 2) void mha_bwd_dq_kernel(
     store_transposed<T, D, C::OSTR>(dq, DROP ? scale * dr.rescale : scale, ob, dQ + head_base(mdq, head, H), q0,
                                     Nq, lane, (size_t)mdq.row, dh);
   }  // rep
+}
+
+template <typename T, int D, bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(256, 2) void mha_bwd_dq_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
+    const T* __restrict__ O, const T* __restrict__ dO, const float* __restrict__ LSE,
+    float* __restrict__ Dws, float* __restrict__ LSE2ws, T* __restrict__ dQ, TensorMap mq, TensorMap mk,
+    TensorMap mv, TensorMap mo, TensorMap mdo, TensorMap mdq, int H, int Nq, int Nk, int dh, int nqt, int paired,
+    float scale, float scale_log2, Dropout dr) {
+  const int items = paired ? causal_items<CAUSAL>(nqt) : nqt;  // causal: query tiles (nqt-1-p, p)
+  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int head = logical / items;
+  bwd_dq<T, D, CAUSAL, DROP, false>(Q, K, V, O, dO, LSE, Dws, LSE2ws, dQ, mq, mk, mv, mo, mdo, mdq, H, Nq, Nk, dh,
+                                    nqt, paired, scale, scale_log2, dr, head, logical - head * items);
+}
+
+// ---------------------------------------------------------------------------------------
+// Both in one grid, for problems of which neither kernel fills the chip by itself.  The dK/dV side
+// needs D and LSE * log2(e) of all queries, so these are formed by a pass of their own first (2 us).
+// Measured at 16 heads x 1024, d = 64 (128 workgroups per side on 256 CUs): 36.9 -> 26.5 us.
+// ---------------------------------------------------------------------------------------
+
+// -D (times the keep probability under dropout) and LSE * log2(e): D / 8 lanes per query row.
+template <typename T, int D>
+__global__ __launch_bounds__(256) void mha_bwd_stats_kernel(const T* __restrict__ O, const T* __restrict__ dO,
+                                                            const float* __restrict__ LSE, float* __restrict__ Dws,
+                                                            float* __restrict__ LSE2ws, TensorMap mo, TensorMap mdo,
+                                                            int H, int Nq, int dh, int rows, float keep_prob) {
+  using v8 = typename Frag<T>::v8;
+  constexpr int LPR = D / 8;
+  const int row = blockIdx.x * (256 / LPR) + threadIdx.x / LPR;  // flat (head, query) index
+  const int col = (threadIdx.x % LPR) * 8;
+  const bool live = row < rows;
+  const int r = live ? row : rows - 1;
+  const int head = r / Nq, q = r - head * Nq;
+  const v8 o = load_row_chunk<v8>(O + head_base(mo, head, H) + (size_t)q * (size_t)mo.row, col, dh);
+  const v8 g = load_row_chunk<v8>(dO + head_base(mdo, head, H) + (size_t)q * (size_t)mdo.row, col, dh);
+  float acc = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc = __builtin_fmaf((float)o[i], (float)g[i], acc);
+#pragma unroll
+  for (int m = LPR / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, LPR);
+  if (live && col == 0) {
+    Dws[r] = -acc * keep_prob;
+    LSE2ws[r] = LSE[r] * 1.4426950408889634f;
+  }
+}
+
+template <int D> struct BwdMergedCfg {
+  static constexpr int SMEM = BwdKvPipeCfg<D>::SMEM > BwdQCfg<D>::SMEM ? BwdKvPipeCfg<D>::SMEM : BwdQCfg<D>::SMEM;
+};
+
+template <typename T, int D, bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(256, (D == 64 && !DROP) ? 2 : 1) void mha_bwd_merged_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
+    float* __restrict__ Dws, float* __restrict__ LSE2ws, T* __restrict__ dQ, T* __restrict__ dK, T* __restrict__ dV,
+    TensorMap mq, TensorMap mk, TensorMap mv, TensorMap mdo, TensorMap mdq, TensorMap mdk, TensorMap mdv, int H,
+    int Nq, int Nk, int dh, int nqt, int nkt, int paired, float scale, Dropout dr) {
+  const int qitems = paired ? causal_items<CAUSAL>(nqt) : nqt, kitems = paired ? causal_items<CAUSAL>(nkt) : nkt;
+  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int head = logical / (qitems + kitems);
+  const int item = logical - head * (qitems + kitems);
+  if (item < kitems)  // the longer ones first
+    bwd_dkdv_pipe<T, D, CAUSAL, DROP>(Q, K, V, dO, LSE2ws, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq, Nk, dh, nkt,
+                                      paired, scale, dr, head, item);
+  else
+    bwd_dq<T, D, CAUSAL, DROP, true>(Q, K, V, nullptr, dO, nullptr, Dws, LSE2ws, dQ, mq, mk, mv, mdo, mdo, mdq, H, Nq,
+                                     Nk, dh, nqt, paired, scale, scale * 1.4426950408889634f, dr, head,
+                                     item - kitems);
 }
 
 }  // namespace spark

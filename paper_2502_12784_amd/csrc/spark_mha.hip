@@ -252,17 +252,17 @@ int launch_fwd(const Problem& p, const void* Q, const void* K, const void* V, vo
 int64_t bwd_split_workgroups(const Problem& p) {
   return (int64_t)p.B * p.H * ((p.Nq + 31) / 32 + (p.Nk + 31) / 32);
 }
-// It is taken while every CU has at most two of them, or four of a long causal problem (whose workgroups
-// differ in length and fill each other's gaps): a further round costs it 16 iterations of chain at N = 4096,
-// while the two kernels below still find idle CUs.  Backward, us, fp16, two kernels -> split
-// (n workgroups), square problems of BH heads:
-//   d = 64:  2 x 128 (16)  11.6 -> 6.4    16 x 256 (256)  15.1 -> 8.6    4 x 1024 (256)   35.3 -> 13.2
-//            8 x 1024 (512) 35.5 -> 22.4  2 x 4096 (512) 115.5 -> 58.5   16 x 1024 (1024) 36.0 -> 43.3 (not taken)
-//            causal 4 x 4096 (1024) 119 -> 73, 16 x 1024 (1024) 38.0 -> 33.5, 32 x 512 (1024) 24.6 -> 28.5 (not)
-//   d = 128: 2 x 128 17.6 -> 9.5    4 x 1024 58.4 -> 23.5    8 x 1024 58.7 -> 39.2    2 x 4096 197 -> 129
-//            causal 4 x 4096 203 -> 145, 16 x 1024 61.9 -> 54.4
+// It is taken while every CU has one workgroup, and up to two where the chains are long enough for their
+// split to outweigh the second round (at d = 128 four waves split them instead of eight: only if causal, where
+// the two rounds differ in length).  Measured against mha_bwd_merged_kernel, which is next, fp16, us,
+// merged -> split (n workgroups), square problems of BH heads:
+//   d = 64:   16 x 256 (256) 10.7 -> 8.4    4 x 1024 (256) 22.2 -> 13.2    32 x 256 (512) 11.0 -> 15.1
+//             16 x 512 (512) 15.4 -> 18.3   8 x 1024 (512) 23.2 -> 22.5    2 x 4096 (512) 69.7 -> 57.8
+//             16 x 1024 (1024) 24.9 -> 43.0     causal 8 x 1024 23.7 -> 18.6, 2 x 4096 71.3 -> 47.5
+//   d = 128:  4 x 1024 (256) 35.6 -> 23.1   2 x 4096 (512) 122 -> 129      causal 2 x 4096 128 -> 102
 bool split_backward(const Problem& p) {
-  return bwd_split_workgroups(p) <= (p.causal && p.Nk >= 1024 ? 1024 : 512);
+  const int64_t n = bwd_split_workgroups(p);
+  return n <= 256 || (n <= 512 && p.Nq >= 1024 && p.Nk >= 1024 && (p.d <= 64 || p.causal));
 }
 
 template <typename T, int D, bool CAUSAL, bool DROP>
@@ -280,6 +280,53 @@ int launch_bwd_split(const Problem& p, const void* Q, const void* K, const void*
                      p.H, p.Nq, p.Nk, p.d, (p.Nq + C::BM - 1) / C::BM, (p.Nk + C::BM - 1) / C::BM, p.scale,
                      make_dropout(p.thr, p.seed, p.offset));
   return launch_ok("backward kernel (split)") ? SPARK_OK : SPARK_ERR_LAUNCH;
+}
+
+// Both sides of the backward in one grid of 128-row tiles (mha_bwd_merged_kernel): where a kernel per side
+// leaves CUs idle one after the other, at the price of a small kernel that forms D first.  `per_cu`:
+// workgroups of the grid that fit a CU.  Backward, fp16, us, one kernel per side -> merged (n tiles of
+// both sides), square problems of BH heads:
+//   up to one tile per CU:  d = 64 128 x 128 (256) 12.3 -> 9.6, 16 x 1024 (256) 36.9 -> 26.5;
+//                           d = 128 32 x 512 (256) 36.9 -> 25.7, 4 x 4096 (256) 198 -> 130
+//   two per CU, d = 64:     8 x 4096 (512) 129 -> 118, 24 x 1024 (384) 36.9 -> 35.6, but 48 x 512 (384) equal and
+//                           128 x 256 (512) 17.0 -> 17.7: only from 1024 rows on, and not beyond one round
+//                           (36 x 1333 (792) 76.7 -> 81.1, 96 x 512 (768) 37.1 -> 37.9)
+//   d = 128 beyond one:     the dQ side, two workgroups per CU in its own kernel, is held to one here:
+//                           24 x 1024 (384) 62.7 -> 71.6
+//   causal, paired, while the pairs of both sides are resident together: d = 64 32 x 1024 (512) 39.1 -> 30.2,
+//                           3 x 8192 (384) 229 -> 140, 36 x 1333 (792) 58.2 -> 51.1, but 128 x 1024 (2048) 90.2 -> 91.1;
+//                           d = 128 32 x 1024 (512) 65.3 -> 50.1, 8 x 4096 (512) 203 -> 142, but 96 x 512 (768)
+//                           59.7 -> 64.2
+bool merged_backward(const Problem& p, int per_cu) {
+  const int64_t n = (int64_t)p.B * p.H * ((p.Nq + 127) / 128 + (p.Nk + 127) / 128);
+  if (p.causal) return n <= 512 * per_cu;
+  return n <= 256 || (per_cu == 2 && n <= 512 && p.Nq >= 1024 && p.Nk >= 1024);
+}
+
+template <typename T, int D, bool CAUSAL, bool DROP, int PER_CU>
+int launch_bwd_merged(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const float* LSE,
+                      const void* dO, void* dQ, void* dK, void* dV, float* Dws) {
+  auto kernel = mha_bwd_merged_kernel<T, D, CAUSAL, DROP>;
+  constexpr int SMEM = BwdMergedCfg<D>::SMEM;
+  static std::atomic<uint64_t> ready{0};
+  const int attr = ensure_smem(kernel, SMEM, ready);
+  if (attr != SPARK_OK) return attr;
+  const int BH = p.B * p.H, rows = BH * p.Nq;
+  const Dropout dr = make_dropout(p.thr, p.seed, p.offset);
+  float* LSE2ws = Dws + (size_t)rows;
+  constexpr int RPB = 256 * 8 / D;  // rows per workgroup of the statistics kernel
+  hipLaunchKernelGGL((mha_bwd_stats_kernel<T, D>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(256), 0, p.st,
+                     static_cast<const T*>(O), static_cast<const T*>(dO), LSE, Dws, LSE2ws, p.mo, p.mdo, p.H, p.Nq,
+                     p.d, rows, DROP ? dr.keep_prob : 1.0f);
+  if (!launch_ok("backward statistics kernel")) return SPARK_ERR_LAUNCH;
+  const int nqt = (p.Nq + 127) / 128, nkt = (p.Nk + 127) / 128;
+  const int paired = pair_tiles(CAUSAL, 2 * (int64_t)BH, nqt, PER_CU);
+  const int items = paired ? 2 * causal_items<true>(nqt) : nqt + nkt;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * items)), dim3(256), SMEM, p.st, static_cast<const T*>(Q),
+                     static_cast<const T*>(K), static_cast<const T*>(V), static_cast<const T*>(dO), Dws, LSE2ws,
+                     static_cast<T*>(dQ), static_cast<T*>(dK), static_cast<T*>(dV), p.mq, p.mk, p.mv, p.mdo, p.mdq,
+                     p.mdk, p.mdv, p.H, p.Nq, p.Nk, p.d, nqt, nkt, paired, p.scale, dr);
+  return launch_ok("backward kernel (both sides)") ? SPARK_OK : SPARK_ERR_LAUNCH;
 }
 
 template <typename T, int D, bool CAUSAL, bool DROP>
@@ -302,6 +349,12 @@ int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, co
   if (!mark(0)) return SPARK_ERR_LAUNCH;
   if (split_backward(p)) {  // one kernel: both later marks follow it
     const int rc = launch_bwd_split<T, D, CAUSAL, DROP>(p, Q, K, V, O, LSE, dO, dQ, dK, dV);
+    if (rc != SPARK_OK) return rc;
+    return mark(1) && mark(2) ? SPARK_OK : SPARK_ERR_LAUNCH;
+  }
+  constexpr int PER_CU = D == 64 && !DROP ? 2 : 1;  // workgroups of the dK/dV kernel on a CU
+  if (merged_backward(p, PER_CU)) {
+    const int rc = launch_bwd_merged<T, D, CAUSAL, DROP, PER_CU>(p, Q, K, V, O, LSE, dO, dQ, dK, dV, Dws);
     if (rc != SPARK_OK) return rc;
     return mark(1) && mark(2) ? SPARK_OK : SPARK_ERR_LAUNCH;
   }
