@@ -274,6 +274,21 @@ int spark_mha_strided_fwd(const void* Q, const void* K, const void* V, void* O, 
                           float p_drop, unsigned long long seed, unsigned offset,
                           spark_dtype_t dtype, void* stream);
 
+/*
+ * spark_mha_strided_fwd with an optional workspace.  A few query rows against long memories (not causal) give
+ * too few workgroups to fill the chip unless several of them share the keys of a row; they then need room for
+ * their partial results: spark_mha_fwd_workspace_bytes(...) bytes of device memory, 16-byte aligned, contents
+ * unspecified on return.  0 bytes: the problem needs none (or is invalid).  workspace may be NULL: same
+ * operation, each row by one workgroup.  SPARK_ERR_WORKSPACE if it is not NULL and too small.
+ */
+size_t spark_mha_fwd_workspace_bytes(int B, int H, int Nq, int Nk, int d, int causal, spark_dtype_t dtype);
+int spark_mha_workspace_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
+                            const spark_strides_t* sQ, const spark_strides_t* sK,
+                            const spark_strides_t* sV, const spark_strides_t* sO, void* workspace,
+                            size_t workspace_bytes, int B, int H, int Nq, int Nk, int d, float scale,
+                            int causal, float p_drop, unsigned long long seed, unsigned offset,
+                            spark_dtype_t dtype, void* stream);
+
 int spark_mha_strided_bwd(const void* Q, const void* K, const void* V, const void* O,
                           const float* LSE, const void* dO, void* dQ, void* dK, void* dV,
                           const spark_strides_t* sQ, const spark_strides_t* sK,

@@ -31,12 +31,17 @@ struct Dropout {
 struct Philox {
   uint32_t c0, c1, c2, c3;
 };
+// The two exclusive ors of three words are one v_bitop3_b32 each (truth table 0x96): 4 vector
+// instructions a round instead of 6.
+static __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
 static __device__ __forceinline__ void philox_round(Philox& s, uint32_t key0, uint32_t key1, int round) {
   const uint32_t k0 = key0 + (uint32_t)round * 0x9E3779B9u, k1 = key1 + (uint32_t)round * 0xBB67AE85u;
   const uint64_t p0 = (uint64_t)0xD2511F53u * s.c0;
   const uint64_t p1 = (uint64_t)0xCD9E8D57u * s.c2;
-  const uint32_t n0 = (uint32_t)(p1 >> 32) ^ s.c1 ^ k0;
-  const uint32_t n2 = (uint32_t)(p0 >> 32) ^ s.c3 ^ k1;
+  const uint32_t n0 = xor3((uint32_t)(p1 >> 32), s.c1, k0);
+  const uint32_t n2 = xor3((uint32_t)(p0 >> 32), s.c3, k1);
   s.c1 = (uint32_t)p1;
   s.c3 = (uint32_t)p0;
   s.c0 = n0;

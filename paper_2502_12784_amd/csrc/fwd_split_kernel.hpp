@@ -17,7 +17,9 @@
 // The price is operand traffic: K and V are read from L2 once per 32 query rows instead of once per
 // 128 (8 waves on 8 KB + 8 KB of their own per 32 x 32 ... 64 block, against 64 B per clock from L2:
 // about the rate of one wave per SIMD of the other kernel), hence only for grids that fit the chip in
-// one go.  Measured: 1 head, N = 8192: d = 64 fp16 91 -> 29 us, d = 128 134 -> 51 us; one query row
+// one go.  With a few rows against a long memory even these are few (8 heads: 8 workgroups on 256 CUs); then
+// several workgroups share the keys of a query tile and a small kernel merges them (2 queries, 8 heads, 8318
+// keys, d = 128: 64.0 -> 19.3 us).  Measured: 1 head, N = 8192: d = 64 fp16 91 -> 29 us, d = 128 134 -> 51 us; one query row
 // against 2048 keys, 128 heads, d = 128: 40.7 -> 29.3 us (4.6 TB/s, the rate of a large copy).
 #pragma once
 #include "dropout_gfx950.hpp"
@@ -43,11 +45,13 @@ template <int D> struct FwdSplitCfg {
   static constexpr int SMEM = STG0 + BM * OSTR;
 };
 
-template <typename T, int D, bool CAUSAL, bool DROP>
+// PART (not causal): `parts` workgroups share the keys of a query tile; each leaves its m, l and unnormalised
+// O of the rows below Nq in fp32, and mha_fwd_combine_kernel merges them.
+template <typename T, int D, bool CAUSAL, bool DROP, bool PART = false>
 __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ LSE, TensorMap mq, TensorMap mk, TensorMap mv, TensorMap mo, int H, int Nq, int Nk,
-    int dh, int nqt, int paired, float scale_log2, Dropout dr) {
+    int dh, int nqt, int paired, float scale_log2, Dropout dr, int parts, float* __restrict__ partial) {
   using F = Frag<T>;
   using v8 = typename F::v8;
   using v4 = typename F::v4;
@@ -64,7 +68,8 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
   // causal: query tiles (nqt-1-p, p) are paired for equal work, unless there are so few tiles that
   // each gets a CU of its own
   const int items = paired ? causal_items<CAUSAL>(nqt) : nqt;
-  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int flat = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int logical = PART ? flat / parts : flat, part = PART ? flat - logical * parts : 0;
   const int head = logical / items;
   const int item = logical - head * items;
 
@@ -85,7 +90,13 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
 
     int kv_end = Nk;
     if (CAUSAL && q0 + C::BM < Nk) kv_end = q0 + C::BM;
-    const int nt = (kv_end + C::BN - 1) / C::BN;
+    int nt = (kv_end + C::BN - 1) / C::BN;
+    int j0 = 0;  // this workgroup's tiles are [j0, nt)
+    if (PART) {
+      const int per = (nt + parts - 1) / parts;
+      j0 = part * per;
+      nt = j0 + per < nt ? j0 + per : nt;  // the host leaves no part without a tile
+    }
     // tiles [0, n_plain) need no mask: they end within the keys and, if causal, at or below row q0
     int n_plain = Nk / C::BN;
     if (CAUSAL && (q0 + 1) / C::BN < n_plain) n_plain = (q0 + 1) / C::BN;
@@ -104,9 +115,9 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
 
     auto fetch_k = [&](int j) { kdma.template tile<C::BN>(kview, j * C::BN, kb, k_row_bytes); };
     auto fetch_v = [&](int j) { vdma.template tile<C::BN>(vview, j * C::BN, vb, v_row_bytes); };
-    if (wave < nt) {
-      fetch_k(wave);
-      fetch_v(wave);
+    if (j0 + wave < nt) {
+      fetch_k(j0 + wave);
+      fetch_v(j0 + wave);
     }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));  // Q is awaited here, not in the loop
@@ -208,7 +219,8 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
         fetch_v(j + C::NW);
       }
     };
-    int j = wave;
+    int j = j0 + wave;
+    if (n_plain > nt) n_plain = nt;
     for (; j < n_plain; j += C::NW) tile(j, std::false_type{}, j + C::NW < nt);
     for (; j < nt; j += C::NW) tile(j, std::true_type{}, j + C::NW < nt);
 
@@ -220,13 +232,14 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
       stat[(C::NW + wave) * C::BM + c32] = l_run;
     }
     __syncthreads();  // also: every wave has left its tiles
-    const int used = nt < C::NW ? nt : C::NW;  // the waves behind that had no tile
+    const int used = nt - j0 < C::NW ? nt - j0 : C::NW;  // the waves behind that had no tile
     float m_all = stat[c32];
     for (int w = 1; w < used; ++w) m_all = fmaxf(m_all, stat[w * C::BM + c32]);
     float l_all = 0.f;
     for (int w = 0; w < used; ++w)
       l_all += stat[(C::NW + w) * C::BM + c32] * __builtin_amdgcn_exp2f(stat[w * C::BM + c32] - m_all);
-    const float mul = __builtin_amdgcn_exp2f(m_run - m_all) * (DROP ? dr.rescale : 1.0f) / l_all;
+    const float mul = __builtin_amdgcn_exp2f(m_run - m_all) * (PART ? 1.0f : (DROP ? dr.rescale : 1.0f) / l_all);
+    const size_t prow = ((size_t)head * Nq + qrow) * (size_t)(PART ? parts : 1) + part;  // row of the partial result
     if (wave < used) {
 #pragma unroll
       for (int q = 0; q < C::GROUPS; ++q) {
@@ -243,10 +256,20 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
       const int q = wave * C::GPW + gi;
       f32x4 sum = lds_read16<f32x4>(smem, q * 1024 + lane * 16);
       for (int w = 1; w < used; ++w) sum += lds_read16<f32x4>(smem, (w * C::GROUPS + q) * 1024 + lane * 16);
+      if (PART) {
+        if (qrow < Nq) *reinterpret_cast<f32x4*>(partial + prow * (D + 4) + 8 * q + 4 * g) = sum;
+        continue;
+      }
       v4 pk;
 #pragma unroll
       for (int e = 0; e < 4; ++e) pk[e] = (T)sum[e];
       lds_write(smem + C::STG0, c32 * C::OSTR + (8 * q + 4 * g) * 2, pk);
+    }
+    if (PART) {
+      if (wave == 0 && g == 0 && qrow < Nq) {
+        *reinterpret_cast<f32x4*>(partial + prow * (D + 4) + D) = f32x4{m_all, l_all, 0.f, 0.f};
+      }
+      return;
     }
     __syncthreads();
     constexpr int CPR = D / 8;
@@ -257,6 +280,57 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
     if (wave == 0 && g == 0 && qrow < Nq)
       LSE[(size_t)head * Nq + qrow] = (m_all + __builtin_amdgcn_logf(l_all)) * 0.6931471805599453f;
   }  // rep
+}
+
+// Merge of the partial results of a row (Eq. 3): D / 4 lanes per row.  A partial result is D + 4 floats: O, m,
+// l, two unused (16-byte alignment).
+template <typename T, int D, bool DROP>
+__global__ __launch_bounds__(256) void mha_fwd_combine_kernel(const float* __restrict__ partial, T* __restrict__ O,
+                                                              float* __restrict__ LSE, TensorMap mo, int H, int Nq,
+                                                              int dh, int rows, int parts, float rescale) {
+  using v4 = typename Frag<T>::v4;
+  constexpr int LPR = D / 4;
+  const int row = blockIdx.x * (256 / LPR) + threadIdx.x / LPR;  // flat (head, query) index
+  const int col = (threadIdx.x % LPR) * 4;
+  if (row >= rows) return;
+  const float* p = partial + (size_t)row * (size_t)parts * (D + 4);
+  // four parts at a time, so that their loads are in flight together; behind the last part its weight is 0
+  float m = p[D];
+  for (int s = 1; s < parts; s += 4) {
+    float x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = p[(size_t)(s + u < parts ? s + u : 0) * (D + 4) + D];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m = fmaxf(m, x[u]);
+  }
+  float l = 0.f;
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  for (int s = 0; s < parts; s += 4) {
+    f32x4 x[4], st[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float* ps = p + (size_t)(s + u < parts ? s + u : 0) * (D + 4);
+      st[u] = *reinterpret_cast<const f32x4*>(ps + D);
+      x[u] = *reinterpret_cast<const f32x4*>(ps + col);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (s + u >= parts) break;
+      const float w = __builtin_amdgcn_exp2f(st[u][0] - m);
+      l += st[u][1] * w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf(x[u][e], w, o[e]);
+    }
+  }
+  const int head = row / Nq, q = row - head * Nq;
+  const float inv = (DROP ? rescale : 1.0f) / l;
+  if (col < dh) {
+    v4 pk;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) pk[e] = (T)(o[e] * inv);
+    *reinterpret_cast<v4*>(O + head_base(mo, head, H) + (size_t)q * (size_t)mo.row + col) = pk;
+  }
+  if (col == 0) LSE[row] = (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
 }
 
 }  // namespace spark

@@ -48,8 +48,10 @@ bool stats_shaped(const at::Tensor& t, int64_t B, int64_t H, int64_t N) {
   return t.scalar_type() == at::kFloat && t.size(0) == B && t.size(1) == H && t.size(2) == N && t.is_contiguous();
 }
 
-spark_strides_t strides(const at::Tensor& t) {
-  return spark_strides_t{t.stride(0), t.stride(1), t.stride(2)};
+// A contiguous tensor may have any stride in a dimension of size one: those of its sizes are passed then.
+spark_strides_t strides(const at::Tensor& t, int kind) {
+  if (kind == STRIDED) return spark_strides_t{t.stride(0), t.stride(1), t.stride(2)};
+  return spark_strides_t{t.size(1) * t.size(2) * t.size(3), t.size(2) * t.size(3), t.size(3)};
 }
 
 // torch._C._cuda_getDevice and torch._C._cuda_getCurrentRawStream, handed over once by bind()
@@ -127,21 +129,20 @@ PyObject* host_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Py_RETURN_NONE;
   const at::Tensor O = Og ? *Og : at::empty_like(*Q);
   const at::Tensor L = Lg ? *Lg : at::empty({s.B, s.H, s.Nq}, Q->options().dtype(at::kFloat));
+  const size_t need = spark_mha_fwd_workspace_bytes(s.B, s.H, s.Nq, s.Nk, s.d, x.causal, s.code);
+  at::Tensor ws;
+  if (need) ws = at::empty({(int64_t)need}, Q->options().dtype(at::kByte));
   const void *q = Q->data_ptr(), *k = K->data_ptr(), *v = V->data_ptr();
-  void* o = O.data_ptr();
+  void *o = O.data_ptr(), *work = need ? ws.data_ptr() : nullptr;
   float* lse = static_cast<float*>(L.data_ptr());
   void* stream;
   if (!current_stream(&stream)) return nullptr;
   int rc;
   Py_BEGIN_ALLOW_THREADS;
-  if (x.kind == STRIDED) {
-    const spark_strides_t sq = strides(*Q), sk = strides(*K), sv = strides(*V), so = strides(O);
-    rc = spark_mha_strided_fwd(q, k, v, o, lse, &sq, &sk, &sv, &so, s.B, s.H, s.Nq, s.Nk, s.d, x.scale, x.causal,
-                               x.p_drop, x.seed, x.offset, s.code, stream);
-  } else {
-    rc = spark_mha_dropout_fwd(q, k, v, o, lse, s.B, s.H, s.Nq, s.Nk, s.d, x.scale, x.causal, x.p_drop, x.seed,
-                               x.offset, s.code, stream);
-  }
+  const spark_strides_t sq = strides(*Q, x.kind), sk = strides(*K, x.kind), sv = strides(*V, x.kind),
+                        so = strides(O, x.kind);
+  rc = spark_mha_workspace_fwd(q, k, v, o, lse, &sq, &sk, &sv, &so, work, need, s.B, s.H, s.Nq, s.Nk, s.d, x.scale,
+                               x.causal, x.p_drop, x.seed, x.offset, s.code, stream);
   Py_END_ALLOW_THREADS;
   if (rc != SPARK_OK) return PyLong_FromLong(rc);
   PyObject* out = PyTuple_New(2);
@@ -185,8 +186,10 @@ PyObject* host_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
   int rc;
   Py_BEGIN_ALLOW_THREADS;
   if (x.kind == STRIDED) {
-    const spark_strides_t sq = strides(*Q), sk = strides(*K), sv = strides(*V), so = strides(*O), sdo = strides(*dO),
-                          sdq = strides(dQ), sdk = strides(dK), sdv = strides(dV);
+    const int st4 = STRIDED;
+    const spark_strides_t sq = strides(*Q, st4), sk = strides(*K, st4), sv = strides(*V, st4), so = strides(*O, st4),
+                          sdo = strides(*dO, st4), sdq = strides(dQ, st4), sdk = strides(dK, st4),
+                          sdv = strides(dV, st4);
     rc = spark_mha_strided_bwd(q, k, v, o, lse, dout, dq, dk, dv, &sq, &sk, &sv, &so, &sdo, &sdq, &sdk, &sdv, work,
                                (size_t)wbytes, s.B, s.H, s.Nq, s.Nk, s.d, x.scale, x.causal, x.p_drop, x.seed, x.offset,
                                s.code, stream);

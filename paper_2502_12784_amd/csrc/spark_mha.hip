@@ -63,6 +63,7 @@ struct Problem {
   // element strides of the [B,H,N,d] tensors
   TensorMap mq, mk, mv, mo, mdo, mdq, mdk, mdv;
   hipStream_t st;
+  void* fwd_ws;  // the forward's optional workspace, large enough, or nullptr
 };
 
 TensorMap contiguous(int H, int N, int d) {
@@ -220,6 +221,55 @@ bool split_forward(const Problem& p) {
   return p.Nk > 256 && fwd_split_workgroups<CAUSAL>(p, &paired) <= 256;
 }
 
+// Workgroups that share the keys of one query tile, 1 = no sharing.  For grids of at most half the CUs: as
+// many as give every CU a workgroup, with two rounds of tiles left to each of its 8 waves (one round left
+// costs more in the merge than it saves), at most 16 (the merge walks them).  Worth the merge kernel, 3 us,
+// from four rounds saved on; near 128 workgroups the memory rate is reached without sharing, and only long
+// memories gain.  Forward, fp16, us, one workgroup -> shared, queries x heads over keys:
+//   d = 64:   1 x 2 over 4096 15.2 -> 10.1    2 x 8 over 8318 25.7 -> 13.3    40 x 48 over 12096 58.3 -> 38.9
+//             1 x 100 over 8192 50.0 -> 42.5  1 x 128 over 4096 29.3 -> 29.7 (not taken)
+//   d = 128:  1 x 2 over 2048 15.6 -> 11.0    2 x 8 over 8318 64.0 -> 19.3    16 x 24 over 4067 42.9 -> 19.3
+//             1 x 128 over 16384 204 -> 181   1 x 128 over 2048 29.9 -> 30.9 (not taken)
+int fwd_parts(const Problem& p) {
+  if (p.causal) return 1;
+  const int64_t w = (int64_t)p.B * p.H * ((p.Nq + 31) / 32);
+  if (w > 128) return 1;
+  const int nt = p.d <= 64 ? (p.Nk + 63) / 64 : (p.Nk + 31) / 32;
+  const int rounds = (nt + 7) / 8;
+  int parts = (int)(256 / w);
+  if (parts > rounds / 2) parts = rounds / 2;
+  if (parts > 16) parts = 16;
+  if (parts < 2 || rounds - rounds / parts < (w > 96 ? 8 : 4)) return 1;
+  const int per = (nt + parts - 1) / parts;
+  return (nt + per - 1) / per;  // no part without a tile
+}
+
+size_t fwd_workspace_bytes(const Problem& p) {
+  const int parts = fwd_parts(p);
+  return parts == 1 ? 0 : (size_t)p.B * p.H * p.Nq * parts * ((p.d <= 64 ? 64 : 128) + 4) * sizeof(float);
+}
+
+template <typename T, int D, bool DROP>
+int launch_fwd_parts(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* LSE, int parts) {
+  using C = FwdSplitCfg<D>;
+  auto kernel = mha_fwd_split_kernel<T, D, false, DROP, true>;
+  static std::atomic<uint64_t> ready{0};
+  const int attr = ensure_smem(kernel, C::SMEM, ready);
+  if (attr != SPARK_OK) return attr;
+  const int nqt = (p.Nq + C::BM - 1) / C::BM, rows = p.B * p.H * p.Nq;
+  const Dropout dr = make_dropout(p.thr, p.seed, p.offset);
+  float* partial = static_cast<float*>(p.fwd_ws);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H * nqt * parts)), dim3(64 * C::NW), C::SMEM, p.st,
+                     static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
+                     static_cast<T*>(O), LSE, p.mq, p.mk, p.mv, p.mo, p.H, p.Nq, p.Nk, p.d, nqt, 0,
+                     p.scale * 1.4426950408889634f, dr, parts, partial);
+  if (!launch_ok("forward kernel (shared keys)")) return SPARK_ERR_LAUNCH;
+  constexpr int RPB = 256 * 4 / D;
+  hipLaunchKernelGGL((mha_fwd_combine_kernel<T, D, DROP>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(256), 0,
+                     p.st, partial, static_cast<T*>(O), LSE, p.mo, p.H, p.Nq, p.d, rows, parts, dr.rescale);
+  return launch_ok("forward merge kernel") ? SPARK_OK : SPARK_ERR_LAUNCH;
+}
+
 template <typename T, int D, bool CAUSAL, bool DROP>
 int launch_fwd_split(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* LSE) {
   using C = FwdSplitCfg<D>;
@@ -233,12 +283,16 @@ int launch_fwd_split(const Problem& p, const void* Q, const void* K, const void*
   hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * C::NW), C::SMEM, p.st,
                      static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
                      static_cast<T*>(O), LSE, p.mq, p.mk, p.mv, p.mo, p.H, p.Nq, p.Nk, p.d, nqt, paired,
-                     p.scale * 1.4426950408889634f, make_dropout(p.thr, p.seed, p.offset));
+                     p.scale * 1.4426950408889634f, make_dropout(p.thr, p.seed, p.offset), 1, nullptr);
   return launch_ok("forward kernel (split keys)") ? SPARK_OK : SPARK_ERR_LAUNCH;
 }
 
 template <typename T, int D, bool CAUSAL, bool DROP>
 int launch_fwd(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* LSE) {
+  if constexpr (!CAUSAL) {
+    const int parts = p.fwd_ws ? fwd_parts(p) : 1;
+    if (parts > 1) return launch_fwd_parts<T, D, DROP>(p, Q, K, V, O, LSE, parts);
+  }
   if (split_forward<CAUSAL>(p)) return launch_fwd_split<T, D, CAUSAL, DROP>(p, Q, K, V, O, LSE);
   if constexpr (D == 128) {
     // ... with the K/V tiles requested two at a time and one barrier every second iteration (the
@@ -460,6 +514,7 @@ int make_problem(Problem* p, int B, int H, int Nq, int Nk, int d, float scale, i
   p->mq = p->mo = p->mdo = p->mdq = contiguous(H, Nq, d);
   p->mk = p->mv = p->mdk = p->mdv = contiguous(H, Nk, d);
   p->st = static_cast<hipStream_t>(stream);
+  p->fwd_ws = nullptr;
   return SPARK_OK;
 }
 
@@ -514,6 +569,22 @@ int spark_mha_strided_fwd(const void* Q, const void* K, const void* V, void* O, 
                           int Nk, int d, float scale, int causal, float p_drop,
                           unsigned long long seed, unsigned offset, spark_dtype_t dtype,
                           void* stream) {
+  return spark_mha_workspace_fwd(Q, K, V, O, LSE, sQ, sK, sV, sO, nullptr, 0, B, H, Nq, Nk, d, scale, causal, p_drop,
+                                 seed, offset, dtype, stream);
+}
+
+size_t spark_mha_fwd_workspace_bytes(int B, int H, int Nq, int Nk, int d, int causal, spark_dtype_t dtype) {
+  Problem p;
+  if (make_problem(&p, B, H, Nq, Nk, d, 1.0f, causal, 0, 0, 0, dtype, nullptr) != SPARK_OK) return 0;
+  return fwd_workspace_bytes(p);
+}
+
+int spark_mha_workspace_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
+                            const spark_strides_t* sQ, const spark_strides_t* sK,
+                            const spark_strides_t* sV, const spark_strides_t* sO, void* workspace,
+                            size_t workspace_bytes, int B, int H, int Nq, int Nk, int d, float scale,
+                            int causal, float p_drop, unsigned long long seed, unsigned offset,
+                            spark_dtype_t dtype, void* stream) {
   if (!Q || !K || !V || !O || !LSE) return SPARK_ERR_NULL;
   Problem p;
   int rc = make_problem(&p, B, H, Nq, Nk, d, scale, causal, drop_threshold(p_drop), seed, offset,
@@ -523,6 +594,12 @@ int spark_mha_strided_fwd(const void* Q, const void* K, const void* V, void* O, 
   if ((rc = check_strides(sK, Nk, d, &p.mk)) != SPARK_OK) return rc;
   if ((rc = check_strides(sV, Nk, d, &p.mv)) != SPARK_OK) return rc;
   if ((rc = check_strides(sO, Nq, d, &p.mo, true, B, H)) != SPARK_OK) return rc;
+  if (workspace) {
+    if (!aligned16(workspace)) return SPARK_ERR_ALIGN;
+    const size_t need = fwd_workspace_bytes(p);
+    if (workspace_bytes < need) return SPARK_ERR_WORKSPACE;
+    if (need) p.fwd_ws = workspace;
+  }
   return run_fwd(p, Q, K, V, O, LSE);
 }
 
@@ -705,8 +782,8 @@ const char* spark_status_str(int status) {
     case SPARK_ERR_DTYPE: return "unsupported dtype (need SPARK_F16 or SPARK_BF16)";
     case SPARK_ERR_ALIGN: return "a pointer or stride is not 16-byte aligned";
     case SPARK_ERR_WORKSPACE:
-      return "workspace smaller than spark_mha_bwd_workspace_bytes(), or B*H*N above "
-             "spark_mha_bwd_static_max_rows() for spark_mha_bwd_static";
+      return "workspace smaller than spark_mha_bwd_workspace_bytes() or spark_mha_fwd_workspace_bytes(), or "
+             "B*H*N above spark_mha_bwd_static_max_rows() for spark_mha_bwd_static";
     case SPARK_ERR_LAUNCH: return "the HIP runtime refused a kernel launch";
     default: return "unknown status";
   }
