@@ -208,17 +208,22 @@ int64_t fwd_split_workgroups(const Problem& p, int* paired) {
 }
 
 // The split forward needs keys to split (up to 256 of them the merge costs what the shorter chain
-// gains: 5.1 -> 5.2 us at N = 192, d = 64) and every workgroup resident at once: measured, fp16
+// gains: 5.1 -> 5.2 us at N = 192, d = 64) and every workgroup resident at once, or long chains in two rounds
+// (an eighth of the chain, twice): measured, fp16
 // d = 64 / bf16 d = 128, us, mha_fwd_kernel -> split:
 //   1 head, N = 8192 (256 workgroups)       91 -> 29  / 134 -> 51
 //   8 heads, N = 1024 (256)                14.6 -> 8.0 / 20.6 -> 11.7
 //   1 query, 128 heads, 2048 keys (128)          -    / 40.7 -> 29.3
 //   1 query, 256 heads, 2048 keys (256)    30.8 -> 26.0 / 50.3 -> 50.5
-//   16 heads, N = 1024 (512)               14.7 -> 14.9 / 21.1 -> 23.6
+//   16 heads, N = 1024 (512)               14.7 -> 14.9 / 21.1 -> 23.6 (not taken)
+//   8 heads, N = 2048 (512)                26.4 -> 20.1 / 37.6 -> 31.9   1 head, N = 16384  184 -> 103 / 266 -> 190
+//   causal, 6 heads, N = 4096 (384)        48.9 -> 39.5 / 85.0 -> 61.4   12 heads, N = 2048 (384) 27.1 -> 29.6 (not)
+//   12 heads, N = 2048 (768)               26.6 -> 29.0 / 37.9 -> 46.6 (not)
 template <bool CAUSAL>
 bool split_forward(const Problem& p) {
   int paired;
-  return p.Nk > 256 && fwd_split_workgroups<CAUSAL>(p, &paired) <= 256;
+  const int64_t n = fwd_split_workgroups<CAUSAL>(p, &paired);
+  return p.Nk > 256 && (n <= 256 || (n <= 512 && p.Nk >= (CAUSAL ? 4096 : 2048)));
 }
 
 // Workgroups that share the keys of one query tile, 1 = no sharing.  For grids of at most half the CUs: as

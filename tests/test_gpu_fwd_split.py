@@ -21,6 +21,8 @@ CASES = [
     (1, 2, 257, 257, 64, synth.F16, True, 0), (1, 1, 321, 321, 128, synth.BF16, True, 0),
     (1, 2, 1037, 1037, 64, synth.BF16, True, 26),
     (4, 8, 290, 290, 64, synth.F16, True, 0), (4, 8, 290, 290, 128, synth.BF16, True, 26),  # paired, odd
+    (1, 8, 2048, 2048, 64, synth.F16, False, 0), (2, 17, 300, 2050, 128, synth.BF16, False, 0),  # two rounds
+    (1, 5, 4100, 4100, 64, synth.BF16, True, 0),
     # shared keys
     (1, 1, 1, 6200, 64, synth.F16, False, 0), (1, 3, 1, 16384, 128, synth.BF16, False, 0),
     (1, 2, 33, 5000, 72, synth.F16, False, 0), (2, 2, 7, 4097, 128, synth.F16, False, 26),
