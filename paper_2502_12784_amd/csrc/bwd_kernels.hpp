@@ -210,10 +210,10 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2, -l[r8 >> 2][r8 & 3]));
       if (mask) pe = krow > q0s + 8 * (r / 4) + 4 * g + (r % 4) ? 0.f : pe;
       if (DROP) {
-        const bool keep = keep_reg(kb, r, dr.thr);
-        p[r8] = keep ? pe : 0.f;
+        p[r8] = keep_reg(kb, r, dr.thr) ? pe : 0.f;
         asm volatile("" : "+v"(p[r8]));  // keeps the select in front of the packed conversion
-        ds[r8] = pe * ((keep ? dp[r] : 0.f) + d[r8 >> 2][r8 & 3]);  // d holds -D (1-p)
+        // pe (M o dP + d) with the mask already in p: a select less; d holds -D (1-p)
+        ds[r8] = __builtin_fmaf(p[r8], dp[r], pe * d[r8 >> 2][r8 & 3]);
       } else {
         p[r8] = pe;
         ds[r8] = pe * dp[r];  // the accumulator started from -D
@@ -325,7 +325,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
           if (DROP) {
 #pragma unroll
             for (int round = i * 10 / (4 * NG); round < (i + 1) * 10 / (4 * NG); ++round)
-              philox_round(rng, dr.key0, dr.key1, round);
+              philox_round<true>(rng, dr.key0, dr.key1, round);
           }
           sched_fence();
         }
@@ -537,11 +537,11 @@ static __device__ __forceinline__ void bwd_dq(
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]), "+v"(dof[ks]));
     asm volatile("" : "+v"(lse2), "+v"(Dq));
-    // Without dropout dS = P o (dP - D) needs no subtraction: every dP accumulator starts from -D
+    // dS = P o (dP - D) needs no subtraction: every dP accumulator starts from -D
     // (one value per lane here: lane = query), handed to the first MFMA as its addend.  That costs 16
     // registers for the whole loop; at D = 128 the kernel has none to spare (the causal one would
     // spill, measured +4 %), so only D = 64 does it (dQ kernel -2 ... -3 %).
-    constexpr bool FOLD_D = !DROP && D == 64;
+    constexpr bool FOLD_D = D == 64;
     f32x16 dneg;
 #pragma unroll
     for (int r = 0; r < 16; ++r) dneg[r] = -Dq;
@@ -644,7 +644,8 @@ static __device__ __forceinline__ void bwd_dq(
         auto ds_elem = [&](int e) {
           const int mt = e / 16, r = e % 16;
           if (FOLD_D) {
-            ds[e] = pe[e] * dp[mt][r];  // the accumulator started from -D
+            // the accumulator started from -D, which is also what a dropped entry has instead of M o dP - D
+            ds[e] = pe[e] * (DROP && !keep_reg(keep[mt], r, dr.thr) ? -Dq : dp[mt][r]);
           } else {
             const float dpe = DROP && !keep_reg(keep[mt], r, dr.thr) ? 0.f : dp[mt][r];
             ds[e] = pe[e] * (dpe - Dq);

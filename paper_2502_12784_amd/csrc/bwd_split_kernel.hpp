@@ -295,9 +295,8 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
         float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2, -l[r >> 2][r & 3]));
         if (diag) pe = krow > t * C::BM + 8 * (r / 4) + 4 * g + (r % 4) ? 0.f : pe;
         if (DROP) {
-          const bool k = keep_reg(keep, r, dr.thr);
-          p[r] = k ? pe : 0.f;
-          ds[r] = pe * ((k ? dp[r] : 0.f) + d[r >> 2][r & 3]);
+          p[r] = keep_reg(keep, r, dr.thr) ? pe : 0.f;
+          ds[r] = __builtin_fmaf(p[r], dp[r], pe * d[r >> 2][r & 3]);  // as in the dK/dV kernel
         } else {
           p[r] = pe;
           ds[r] = pe * dp[r];

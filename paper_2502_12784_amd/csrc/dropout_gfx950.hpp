@@ -36,10 +36,16 @@ struct Philox {
 static __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
   return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
 }
+template <bool SPREAD = false>
 static __device__ __forceinline__ void philox_round(Philox& s, uint32_t key0, uint32_t key1, int round) {
   const uint32_t k0 = key0 + (uint32_t)round * 0x9E3779B9u, k1 = key1 + (uint32_t)round * 0xBB67AE85u;
-  const uint64_t p0 = (uint64_t)0xD2511F53u * s.c0;
-  const uint64_t p1 = (uint64_t)0xCD9E8D57u * s.c2;
+  uint64_t p0 = (uint64_t)0xD2511F53u * s.c0;
+  uint64_t p1 = (uint64_t)0xCD9E8D57u * s.c2;
+  // SPREAD (rounds spread over MFMA slots): kept whole, so that each product is one v_mad_u64_u32; the compiler
+  // otherwise splits every second one into v_mul_lo_u32 and v_mul_hi_u32, quarter-rate instructions like it (48
+  // per stage of the dK/dV loop instead of 32).  The first products are loop-invariant or uniform.
+  if (SPREAD && round >= 1) asm("" : "+v"(p0));
+  if (SPREAD && round >= 2) asm("" : "+v"(p1));
   const uint32_t n0 = xor3((uint32_t)(p1 >> 32), s.c1, k0);
   const uint32_t n2 = xor3((uint32_t)(p0 >> 32), s.c3, k1);
   s.c1 = (uint32_t)p1;
@@ -53,12 +59,6 @@ static __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, u
 #pragma unroll
   for (int round = 0; round < 10; ++round) philox_round(s, k0, k1, round);
   out[0] = s.c0; out[1] = s.c1; out[2] = s.c2; out[3] = s.c3;
-}
-
-// value of `v` in lane A of this lane's quad (all four lanes must be active)
-template <int A>
-static __device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, A * 0x55, 0xF, 0xF, true);
 }
 
 // 4 x 4 transpose inside every quad: on return x[a] holds what lane a of the quad had in x[w],
@@ -117,19 +117,17 @@ static __device__ __forceinline__ void keep_bytes_key_lane(const Dropout& dr, in
   keep_key_lane_finish(s, lane, kb);
 }
 static __device__ __forceinline__ void keep_key_lane_finish(const Philox& s, int lane, uint32_t (&kb)[4]) {
-  const int w = lane & 3;
-  const uint32_t x[4] = {s.c0, s.c1, s.c2, s.c3};
-  // byte (key mod 4) of each of the four words (queries) of a call, gathered into one word
-  const uint32_t sel_lo = 0x0c0c0400u + 0x0101u * (uint32_t)w;  // v_perm: bytes {w of S1, w of S0, 0, 0}
-  auto own_col = [&](uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3) {
-    const uint32_t lo = __builtin_amdgcn_perm(x1, x0, sel_lo);  // byte0 = x0[w], byte1 = x1[w]
-    const uint32_t hi = __builtin_amdgcn_perm(x3, x2, sel_lo);  // byte0 = x2[w], byte1 = x3[w]
-    return lo | (hi << 16);
-  };
-  kb[0] = own_col(quad_bcast<0>(x[0]), quad_bcast<0>(x[1]), quad_bcast<0>(x[2]), quad_bcast<0>(x[3]));
-  kb[1] = own_col(quad_bcast<1>(x[0]), quad_bcast<1>(x[1]), quad_bcast<1>(x[2]), quad_bcast<1>(x[3]));
-  kb[2] = own_col(quad_bcast<2>(x[0]), quad_bcast<2>(x[1]), quad_bcast<2>(x[2]), quad_bcast<2>(x[3]));
-  kb[3] = own_col(quad_bcast<3>(x[0]), quad_bcast<3>(x[1]), quad_bcast<3>(x[2]), quad_bcast<3>(x[3]));
+  // byte k of the call's four words (queries) belongs to the lane with key mod 4 = k: 4 x 4 byte transpose
+  // inside the lane (8 byte permutes), then word k of strip a's call to lane k
+  const uint32_t a01 = __builtin_amdgcn_perm(s.c1, s.c0, 0x05010400u);  // c0[0] c1[0] c0[1] c1[1]
+  const uint32_t b01 = __builtin_amdgcn_perm(s.c1, s.c0, 0x07030602u);  // c0[2] c1[2] c0[3] c1[3]
+  const uint32_t a23 = __builtin_amdgcn_perm(s.c3, s.c2, 0x05010400u);
+  const uint32_t b23 = __builtin_amdgcn_perm(s.c3, s.c2, 0x07030602u);
+  kb[0] = __builtin_amdgcn_perm(a23, a01, 0x05040100u);
+  kb[1] = __builtin_amdgcn_perm(a23, a01, 0x07060302u);
+  kb[2] = __builtin_amdgcn_perm(b23, b01, 0x05040100u);
+  kb[3] = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
+  quad_transpose(kb, lane & 3);
 }
 
 // decision for accumulator register r (0..15) from the bytes of its strip
