@@ -46,8 +46,12 @@ static __device__ __forceinline__ void philox_round(Philox& s, uint32_t key0, ui
   // per stage of the dK/dV loop instead of 32).  The first products are loop-invariant or uniform.
   if (SPREAD && round >= 1) asm("" : "+v"(p0));
   if (SPREAD && round >= 2) asm("" : "+v"(p1));
-  const uint32_t n0 = xor3((uint32_t)(p1 >> 32), s.c1, k0);
-  const uint32_t n2 = xor3((uint32_t)(p0 >> 32), s.c3, k1);
+  // Head, offset and keys are uniform: in rounds 0 and 1 most of these words are scalar and the scalar unit joins
+  // them.  v_bitop3_b32 takes one scalar operand only; the others would sit in vector registers for the
+  // whole loop, and the causal wide forward at D = 128 spilled inside its masked loop (scratch 140 -> 108 bytes).
+  const uint32_t h1 = (uint32_t)(p1 >> 32), h0 = (uint32_t)(p0 >> 32);
+  const uint32_t n0 = round < 2 ? h1 ^ s.c1 ^ k0 : xor3(h1, s.c1, k0);
+  const uint32_t n2 = round < 2 ? h0 ^ s.c3 ^ k1 : xor3(h0, s.c3, k1);
   s.c1 = (uint32_t)p1;
   s.c3 = (uint32_t)p0;
   s.c0 = n0;
