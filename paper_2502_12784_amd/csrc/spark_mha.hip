@@ -152,15 +152,22 @@ int ensure_smem(KernelT kernel, int bytes, std::atomic<uint64_t>& done) {
 }
 
 // Workgroups of 8 waves (256 query rows, one per CU) instead of 4 (128 rows, two per CU): each
-// K/V tile brought into LDS then serves twice as many MFMAs.  Pays at d = 128 when the wider
-// tiles still give every CU at least two workgroups and the loop over the keys is long enough
-// to outweigh running one workgroup per CU with nothing to overlap its prologue and epilogue
+// K/V tile brought into LDS then serves twice as many MFMAs.  Pays at d = 128 when the loop over the keys is
+// long enough to outweigh running one workgroup per CU with nothing to overlap its prologue and epilogue
 // (measured on the grid of Sec. 4.1, hidden size 2048: -5 ... -7 % from 2048 keys on, +7 ... +10 %
-// at 512, equal at 1024; at d = 64 it costs 2 %).
+// at 512, equal at 1024; at d = 64 it costs 2 %) and the last round of one per CU is not nearly empty:
+// two rounds or more, almost two, or one round where the narrow grid puts two workgroups on some CU (the time is
+// that CU's).  Forward, bf16, us, narrow -> wide (n wide workgroups):
+//   16 heads x 4096 (256) 125.6 -> 117.0   24 x 2048 (192) 59.1 -> 52.8   40 x 1024 over 4096 keys (160) 105.8 -> 93.8
+//   causal 8 x 16384 (256) 503.7 -> 456.9   24 x 4096 (192) 122.3 -> 111.7   64 x 2048 (256) 80.6 -> 81.4
+//   not taken: 40 x 2048 (320) 95.1 -> 107.5   12 x 8192 (384) 369 -> 394   causal 40 x 4096 (320) 211.7 -> 225.4
+//   almost two: 56 x 2048 (448) 121.2 -> 113.7   causal 112 x 2048 (448) 145.8 -> 140.0
 template <bool CAUSAL>
 bool wide_workgroups(const Problem& p) {
-  const int64_t tiles = (p.Nq + 255) / 256;
-  return p.d > 64 && p.Nk >= 2048 && (int64_t)p.B * p.H * causal_items<CAUSAL>((int)tiles) >= 512;
+  const int64_t bh = (int64_t)p.B * p.H;
+  const int64_t wide = bh * causal_items<CAUSAL>((p.Nq + 255) / 256);
+  const int64_t narrow = bh * causal_items<CAUSAL>((p.Nq + 127) / 128);
+  return p.d > 64 && p.Nk >= 2048 && (wide >= 512 || narrow >= 896 || (wide <= 256 && narrow > 256));
 }
 
 // Whether a causal grid runs as complementary pairs of tiles, (n-1-p, p) in one workgroup: equal work for
