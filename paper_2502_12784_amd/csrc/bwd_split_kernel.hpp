@@ -17,6 +17,7 @@
 // 1.7 us per round of eight tiles at D = 64 and of four at D = 128.  Measured against the two kernels, fp16:
 // 2 heads x 128, d = 64: 11.6 -> 6.4 us; 4 heads x 1024: 35.3 -> 13.2 us, d = 128 58.4 -> 23.5 us.
 #pragma once
+#include "bwd_kernels.hpp"
 #include "dropout_gfx950.hpp"
 #include "mma_gfx950.hpp"
 #include "tiles_gfx950.hpp"
@@ -295,8 +296,9 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
         float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2, -l[r >> 2][r & 3]));
         if (diag) pe = krow > t * C::BM + 8 * (r / 4) + 4 * g + (r % 4) ? 0.f : pe;
         if (DROP) {
-          p[r] = keep_reg(keep, r, dr.thr) ? pe : 0.f;
-          ds[r] = __builtin_fmaf(p[r], dp[r], pe * d[r >> 2][r & 3]);  // as in the dK/dV kernel
+          const bool kept = keep_reg(keep, r, dr.thr);
+          p[r] = kept ? pe : 0.f;
+          ds[r] = dropout_ds<T>(kept, pe, p[r], dp[r], d[r >> 2][r & 3]);
         } else {
           p[r] = pe;
           ds[r] = pe * dp[r];

@@ -41,6 +41,8 @@ template <typename T> struct Frag;
 template <> struct Frag<_Float16> {
   typedef f16x8 v8;
   typedef f16x4 v4;
+  // whether a contraction over d of finite operands is finite in fp32: 128 * 65504^2 = 5.5e11
+  static constexpr bool FINITE_DOT = true;
   static __device__ __forceinline__ f32x16 mfma(v8 a, v8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
   }
@@ -49,6 +51,7 @@ template <> struct Frag<_Float16> {
 template <> struct Frag<__bf16> {
   typedef bf16x8 v8;
   typedef bf16x4 v4;
+  static constexpr bool FINITE_DOT = false;  // bf16 has the range of fp32
   static __device__ __forceinline__ f32x16 mfma(v8 a, v8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
