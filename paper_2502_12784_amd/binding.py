@@ -180,6 +180,29 @@ def _stream_ptr():
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
+def _shared_keys_fwd(lib, Q, K, V, O, LSE, strides, scale, causal, p_drop, seed, offset) -> bool:
+    """The forward with the workspace it asks for, allocated here, as the native path calls it; False
+    if this problem needs none (spark_mha_fwd_workspace_bytes is 0) and the plain entry points do."""
+    import torch
+    B, H, Nq, d = Q.shape
+    sizes = (B, H, Nq, K.shape[2], d)
+    need = lib.spark_mha_fwd_workspace_bytes(*sizes, int(bool(causal)), _dtype_code(Q))
+    if not need:
+        return False
+    workspace = torch.empty(need, dtype=torch.uint8, device=Q.device)
+    _check(lib.spark_mha_workspace_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), LSE.data_ptr(),
+                                       *strides, workspace.data_ptr(), need, *sizes, float(scale),
+                                       int(bool(causal)), float(p_drop), int(seed), int(offset),
+                                       _dtype_code(Q), _stream_ptr()))
+    return True
+
+
+def _contiguous_strides(t):
+    # of the sizes: a contiguous tensor may have any stride in a dimension of size one
+    _, H, N, d = t.shape
+    return Strides(H * N * d, N * d, d)
+
+
 def spark_mha_fwd(Q, K, V, scale: float, causal: bool, O=None, LSE=None):
     """O, LSE = fused attention forward of [B,H,N,d] device tensors on the current stream."""
     import torch
@@ -196,6 +219,8 @@ def spark_mha_fwd(Q, K, V, scale: float, causal: bool, O=None, LSE=None):
         LSE = torch.empty((B, H, N), dtype=torch.float32, device=Q.device)
     _require(O, (B, H, N, d), Q.dtype, "O")
     _require(LSE, (B, H, N), torch.float32, "LSE")
+    if _shared_keys_fwd(lib, Q, K, V, O, LSE, [_contiguous_strides(t) for t in (Q, K, V, O)], scale, causal, 0.0, 0, 0):
+        return O, LSE
     _check(lib.spark_mha_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), LSE.data_ptr(),
                              B, H, N, d, float(scale), int(bool(causal)), _dtype_code(Q), _stream_ptr()))
     return O, LSE
@@ -243,6 +268,9 @@ def spark_mha_cross_fwd(Q, K, V, scale: float, causal: bool = False, O=None, LSE
         LSE = torch.empty((B, H, Nq), dtype=torch.float32, device=Q.device)
     _require(O, (B, H, Nq, d), Q.dtype, "O")
     _require(LSE, (B, H, Nq), torch.float32, "LSE")
+    if _shared_keys_fwd(lib, Q, K, V, O, LSE, [_contiguous_strides(t) for t in (Q, K, V, O)], scale, causal,
+                        *((0.0, 0, 0) if dropout is None else dropout)):
+        return O, LSE
     if dropout is None:
         _check(lib.spark_mha_cross_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
                                        LSE.data_ptr(), B, H, Nq, Nk, d, float(scale),
@@ -343,6 +371,8 @@ def spark_mha_strided_fwd(Q, K, V, scale: float, causal: bool = False, p_drop: f
     sq, so = _strided(Q, (B, H, Nq, d), Q.dtype, "Q"), _strided(O, (B, H, Nq, d), Q.dtype, "O")
     sk, sv = _strided(K, (B, H, Nk, d), Q.dtype, "K"), _strided(V, (B, H, Nk, d), Q.dtype, "V")
     _require(LSE, (B, H, Nq), torch.float32, "LSE")
+    if _shared_keys_fwd(lib, Q, K, V, O, LSE, (sq, sk, sv, so), scale, causal, p_drop, seed, offset):
+        return O, LSE
     _check(lib.spark_mha_strided_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
                                      LSE.data_ptr(), sq, sk, sv, so, B, H, Nq, Nk, d, float(scale),
                                      int(bool(causal)), float(p_drop), int(seed), int(offset),

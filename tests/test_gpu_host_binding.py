@@ -25,6 +25,15 @@ def _calls(kind, dtype):
         Q, K, V = (qkv[:, :, i].permute(0, 2, 1, 3) for i in range(3))
         O, L = pkg.spark_mha_strided_fwd(Q, K, V, 0.2, True, 0.1, -5, 1 << 40)
         return (O, L) + pkg.spark_mha_strided_bwd(Q, K, V, O, L, dO, 0.2, True, 0.1, -5, 1 << 40)
+    if kind.startswith("few"):  # few queries, long memories: workgroups share the keys, through a workspace
+        kv, q = n(2, 8000, 2, 2, 64), n(2, 3, 2, 64)
+        Q, K, V = q.permute(0, 2, 1, 3), kv[:, :, 0].permute(0, 2, 1, 3), kv[:, :, 1].permute(0, 2, 1, 3)
+        if kind == "few-strided":
+            return pkg.spark_mha_strided_fwd(Q, K, V, 0.125) + pkg.spark_mha_strided_fwd(Q, K, V, 0.125, False, 0.1, 7, 1)
+        Q, K, V = Q.contiguous(), K.contiguous(), V.contiguous()
+        return pkg.spark_mha_cross_fwd(Q, K, V, 0.125) + pkg.spark_mha_dropout_fwd(Q, K, V, 0.125, False, 0.1, 7, 1)
+    if kind == "long":
+        return pkg.spark_mha_fwd(*(n(1, 1, 3000, 128) for _ in range(3)), 0.088, False)
     Nk = 130 if kind == "cross" else 70
     Q, dO, K, V = n(2, 3, 70, 64), n(2, 3, 70, 64), n(2, 3, Nk, 64), n(2, 3, Nk, 64)
     if kind == "self":
@@ -45,7 +54,7 @@ def _calls(kind, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["float16", "bfloat16"])
-@pytest.mark.parametrize("kind", ["self", "given", "cross", "dropout", "packed"])
+@pytest.mark.parametrize("kind", ["self", "given", "cross", "dropout", "packed", "few", "few-strided", "long"])
 def test_native_and_general_path_agree(kind, dtype, monkeypatch):
     import torch
     from paper_2502_12784_amd import binding
