@@ -204,7 +204,7 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
       if (next)
         wait_vmem<C::NLOAD>();  // V is here; the next K may still be on its way
       else
-        wait_vmem_all();
+        wait_vmem<0>();
 #pragma unroll
       for (int kk = 0; kk < 2 * HALVES; ++kk) {
         const v8 pf = pack8<T>(&t[8 * kk]);

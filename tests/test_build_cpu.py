@@ -1,4 +1,5 @@
 """Checks on the compiled device code that need no GPU."""
+import os
 import re
 
 import pytest
@@ -30,3 +31,17 @@ def test_tile_loops_do_not_spill():
     rows = [l.split() for l in table.splitlines() if l.startswith("mha_")]
     assert len(rows) > 60
     assert all(r[-1] == "0" for r in rows), [r for r in rows if r[-1] != "0"]
+
+
+def test_waits_without_a_barrier_are_compiler_fences():
+    """In the split kernels a wave reads LDS that its own direct loads filled, with no barrier between.  Nothing but a
+    memory clobber keeps the compiler from moving such a read in front of the wait: the bare wait_vmem_all()
+    belongs in front of a barrier, these kernels wait with wait_vmem<N>() and wait_lds_all()."""
+    def code(name):
+        return re.sub(r"//.*", "", open(os.path.join(build.CSRC, name)).read())
+    for name in ("fwd_split_kernel.hpp", "bwd_split_kernel.hpp"):
+        assert "load16_to_lds" in code(name) or ".template tile<" in code(name)
+        assert "wait_vmem<" in code(name) and "wait_vmem_all" not in code(name), name
+    helpers = code("mma_gfx950.hpp")
+    for asm_text in (r's_waitcnt vmcnt\(%0\)" ::"n"\(N\)', r's_waitcnt lgkmcnt\(0\)" ::'):
+        assert re.search(asm_text + r'[^;]*: "memory"\)', helpers)
