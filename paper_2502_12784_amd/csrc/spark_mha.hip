@@ -363,8 +363,13 @@ int launch_bwd_split(const Problem& p, const void* Q, const void* K, const void*
 //                           3 x 8192 (384) 229 -> 140, 36 x 1333 (792) 58.2 -> 51.1, but 128 x 1024 (2048) 90.2 -> 91.1;
 //                           d = 128 32 x 1024 (512) 65.3 -> 50.1, 8 x 4096 (512) 203 -> 142, but 96 x 512 (768)
 //                           59.7 -> 64.2
+//   causal, one tile per head (nothing to pair): while all are resident, three per CU at d = 64 without dropout;
+//                           64 rows 114 heads (228) 10.4 -> 7.7, 359 (718) 14.3 -> 13.2, but 399 (798) 14.7 -> 15.0;
+//                           d = 128 109 (218) 14.9 -> 10.7, but 213 (426) 16.2 -> 18.4; dropout, d = 64 114 x 128 (228)
+//                           16.5 -> 11.6, but 133 x 128 (266) 16.9 -> 18.8
 bool merged_backward(const Problem& p, int per_cu) {
   const int64_t n = (int64_t)p.B * p.H * ((p.Nq + 127) / 128 + (p.Nk + 127) / 128);
+  if (p.causal && p.Nq <= 128) return n <= 256 * (per_cu == 2 ? 3 : 1);
   if (p.causal) return n <= 512 * per_cu;
   return n <= 256 || (per_cu == 2 && n <= 512 && p.Nq >= 1024 && p.Nk >= 1024);
 }

@@ -1,0 +1,76 @@
+"""Which kernels a call launches, at the edges of the rules that the timings beside them in csrc/spark_mha.hip draw: the
+call is captured into a graph (nothing runs) and the grids of its kernel nodes are compared.
+"""
+import ctypes
+import math
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+class _Dim3(ctypes.Structure):
+    _fields_ = [("x", ctypes.c_uint), ("y", ctypes.c_uint), ("z", ctypes.c_uint)]
+
+
+class _KernelNode(ctypes.Structure):  # hipKernelNodeParams
+    _fields_ = [("block", _Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", _Dim3),
+                ("params", ctypes.c_void_p), ("smem", ctypes.c_uint)]
+
+
+def _grids(call):
+    """Grid sizes (in x) of the kernels that `call` launches, in order."""
+    import torch
+    hip = ctypes.CDLL("libamdhip64.so")
+    call()  # sets the kernels up, which a capture does not allow
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    stream, graph, n = ctypes.c_void_p(side.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t()
+    with torch.cuda.stream(side):
+        assert hip.hipStreamBeginCapture(stream, 1) == 0
+        try:
+            call()
+        finally:
+            assert hip.hipStreamEndCapture(stream, ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        p = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        out.append(p.grid.x)
+    assert hip.hipGraphDestroy(graph) == 0
+    return out
+
+
+def _tensors(H, Nq, Nk, d):
+    import torch
+    def z(n):
+        return torch.zeros(1, H, n, d, dtype=torch.float16, device="cuda")
+    return z(Nq), z(Nk), z(Nk), z(Nq), torch.zeros(1, H, Nq, device="cuda"), z(Nq)
+
+
+def _backward(H, Nq, Nk, d, causal, p):
+    import torch
+    from paper_2502_12784_amd import spark_mha_dropout_bwd
+    Q, K, V, O, L, dO = _tensors(H, Nq, Nk, d)
+    out = [torch.empty_like(t) for t in (Q, K, V)]
+    ws = torch.empty(8 * H * Nq + 16, dtype=torch.uint8, device="cuda")
+    return _grids(lambda: spark_mha_dropout_bwd(Q, K, V, O, L, dO, 1 / math.sqrt(d), causal, p, 1, 0, *out, ws))
+
+
+def _stats(H, Nq, d):  # grid of the pass in front of the backward in one grid: 2048 elements per workgroup
+    per = 2048 // (64 if d <= 64 else 128)
+    return (H * Nq + per - 1) // per
+
+
+# heads, N, d, dropout rate, whether both sides run in one grid (causal, one tile of 128 rows per head and side)
+ONE_TILE = [(128, 64, 128, 0.0, True), (129, 64, 128, 0.0, False), (240, 128, 96, 0.0, False), (128, 128, 64, 0.1, True),
+            (200, 100, 64, 0.1, False), (384, 128, 64, 0.0, True), (385, 128, 64, 0.0, False)]
+
+
+@pytest.mark.parametrize("case", ONE_TILE)
+def test_causal_heads_of_one_tile(case):
+    H, N, d, p, one_grid = case
+    assert _backward(H, N, N, d, True, p) == ([_stats(H, N, d), 2 * H] if one_grid else [H, H])
