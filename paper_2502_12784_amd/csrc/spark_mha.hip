@@ -450,7 +450,7 @@ int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, co
     const int attr = ensure_smem(kernel, C::SMEM, ready);
     if (attr != SPARK_OK) return attr;
     const int nkt = (p.Nk + C::BN - 1) / C::BN;
-    const int paired = pair_tiles(CAUSAL, BH, nkt, D == 64 ? 2 : 1);
+    const int paired = pair_tiles(CAUSAL, BH, nkt, PER_CU);
     hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * (paired ? causal_items<true>(nkt) : nkt))), dim3(256), C::SMEM, p.st,
                        q, k, v, dout, LSE2ws, Dws, static_cast<T*>(dK), static_cast<T*>(dV), p.mq, p.mk,
                        p.mv, p.mdo, p.mdk, p.mdv, p.H, p.Nq, p.Nk, p.d, nkt, paired, p.scale, dr);

@@ -74,3 +74,13 @@ ONE_TILE = [(128, 64, 128, 0.0, True), (129, 64, 128, 0.0, False), (240, 128, 96
 def test_causal_heads_of_one_tile(case):
     H, N, d, p, one_grid = case
     assert _backward(H, N, N, d, True, p) == ([_stats(H, N, d), 2 * H] if one_grid else [H, H])
+
+
+# heads, N, d, dropout rate, whether the dK/dV kernel pairs the two causal tiles of a head (beyond the merged grids)
+TWO_TILES = [(140, 192, 64, 0.1, True), (256, 200, 64, 0.1, True), (130, 256, 128, 0.0, True), (257, 256, 64, 0.0, True)]
+
+
+@pytest.mark.parametrize("case", TWO_TILES)
+def test_causal_heads_of_two_tiles(case):
+    H, N, d, p, paired = case
+    assert _backward(H, N, N, d, True, p)[1] == (H if paired else 2 * H)
