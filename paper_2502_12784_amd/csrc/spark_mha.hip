@@ -180,9 +180,13 @@ bool wide_workgroups(const Problem& p) {
 //  * two tiles per head while all are resident: lengths differ by a factor of two at most (512 tiles, d = 64
 //    12.2/19.5/18.6 -> 10.5/17.0/17.8);
 //  * three tiles per head: the middle one stays alone in a workgroup with half the others' work (2049 tiles,
-//    d = 128: 79/135/175 -> 65/108/139).
+//    d = 128: 79/135/175 -> 65/108/139), unless a kernel with one workgroup per CU fits its pairs in one round and
+//    its tiles not (dK/dV, d = 128, paired / unpaired: 92 heads 28.4 / 30.8, 118 heads 24.8 / 30.0, 127 heads
+//    30.1 / 34.0; both sides in one grid, 47 heads 25.3 / 27.2, 59 heads 26.8 / 32.4; but 86 heads, two tiles
+//    too many, 24.2 / 19.2, and 132 heads, pairs in two rounds, unpaired is 0.7 of it).
 int pair_tiles(bool causal, int64_t bh, int n, int per_cu) {
-  if (!causal || bh * n <= 256 || n == 3) return 0;
+  if (!causal || bh * n <= 256) return 0;
+  if (n == 3) return per_cu == 1 && bh > 88 && bh <= 128;
   return !(n == 2 && bh * n <= 256 * per_cu);
 }
 

@@ -84,3 +84,14 @@ TWO_TILES = [(140, 192, 64, 0.1, True), (256, 200, 64, 0.1, True), (130, 256, 12
 def test_causal_heads_of_two_tiles(case):
     H, N, d, p, paired = case
     assert _backward(H, N, N, d, True, p)[1] == (H if paired else 2 * H)
+
+
+# the same for three tiles: paired (two workgroups per head) or not
+THREE_TILES = [(88, 300, 128, 0.0, False), (89, 300, 128, 0.0, True), (128, 384, 128, 0.0, True), (129, 384, 128, 0.0, False),
+               (200, 300, 64, 0.0, False), (90, 320, 64, 0.1, True), (130, 320, 64, 0.1, False)]
+
+
+@pytest.mark.parametrize("case", THREE_TILES)
+def test_causal_heads_of_three_tiles(case):
+    H, N, d, p, paired = case
+    assert _backward(H, N, N, d, True, p)[1] == (2 * H if paired else 3 * H)
