@@ -200,7 +200,7 @@ int launch_fwd_nw(const Problem& p, const void* Q, const void* K, const void* V,
   const int BH = p.B * p.H;
   const int nqt = (p.Nq + C::BM - 1) / C::BM;
   const float scale_log2 = p.scale * 1.4426950408889634f;
-  const int paired = pair_tiles(CAUSAL, BH, nqt, 2);
+  const int paired = pair_tiles(CAUSAL, BH, nqt, NW == 4 ? 2 : 1);
   hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * (paired ? causal_items<true>(nqt) : nqt))), dim3(64 * NW), C::SMEM,
                      p.st, static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
                      static_cast<T*>(O), LSE, p.mq, p.mk, p.mv, p.mo, p.H, p.Nq, p.Nk, p.d, nqt, paired, scale_log2,
