@@ -200,7 +200,12 @@ int launch_fwd_nw(const Problem& p, const void* Q, const void* K, const void* V,
   const int BH = p.B * p.H;
   const int nqt = (p.Nq + C::BM - 1) / C::BM;
   const float scale_log2 = p.scale * 1.4426950408889634f;
-  const int paired = pair_tiles(CAUSAL, BH, nqt, NW == 4 ? 2 : 1);
+  // Three tiles per head at two workgroups per CU: paired only where the pairs fit one round and the tiles are well
+  // past it, and only here (d = 128, paired / unpaired us: 188 x 384 27.1 / 25.6, 200 x 300 23.6 / 24.4, 233 x 270
+  // 24.1 / 26.0, 257 x 306 34.6 / 25.7; with dropout 228 x 384 35.3 / 34.8; at d = 64 three workgroups fit, and dQ
+  // gains unpaired: 244 heads 0.9 of it).
+  const bool one_round = D == 128 && !DROP && nqt == 3 && BH > 192 && BH <= 256;
+  const int paired = CAUSAL && one_round ? 1 : pair_tiles(CAUSAL, BH, nqt, NW == 4 ? 2 : 1);
   hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * (paired ? causal_items<true>(nqt) : nqt))), dim3(64 * NW), C::SMEM,
                      p.st, static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
                      static_cast<T*>(O), LSE, p.mq, p.mk, p.mv, p.mo, p.H, p.Nq, p.Nk, p.d, nqt, paired, scale_log2,

@@ -18,6 +18,7 @@ CASES = [
     (3, 43, 250, 64, synth.F16), (3, 43, 250, 128, synth.BF16),    # 258 tiles, 2 per head
     (5, 52, 130, 64, synth.BF16),                                  # 520 tiles, 2 per head
     (3, 30, 300, 128, synth.F16),                                  # 270 tiles, 3 per head
+    (2, 47, 300, 128, synth.BF16), (2, 100, 270, 96, synth.F16),   # 282 and 600 tiles, 3 per head: dK/dV, forward paired
 ]
 
 

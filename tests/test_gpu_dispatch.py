@@ -95,3 +95,20 @@ THREE_TILES = [(88, 300, 128, 0.0, False), (89, 300, 128, 0.0, True), (128, 384,
 def test_causal_heads_of_three_tiles(case):
     H, N, d, p, paired = case
     assert _backward(H, N, N, d, True, p)[1] == (2 * H if paired else 3 * H)
+
+
+def _forward(H, Nq, Nk, d, causal, p):
+    from paper_2502_12784_amd import spark_mha_dropout_fwd
+    Q, K, V, O, L, _ = _tensors(H, Nq, Nk, d)
+    return _grids(lambda: spark_mha_dropout_fwd(Q, K, V, 1 / math.sqrt(d), causal, p, 1, 0, O, L))
+
+
+# heads, d, dropout rate, whether the forward pairs the three causal tiles of a head
+THREE_TILES_FWD = [(192, 128, 0.0, False), (193, 128, 0.0, True), (256, 96, 0.0, True), (257, 128, 0.0, False),
+                   (220, 64, 0.0, False), (220, 128, 0.1, False)]
+
+
+@pytest.mark.parametrize("case", THREE_TILES_FWD)
+def test_forward_of_causal_heads_of_three_tiles(case):
+    H, d, p, paired = case
+    assert _forward(H, 300, 300, d, True, p) == [2 * H if paired else 3 * H]
