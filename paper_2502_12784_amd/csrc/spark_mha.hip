@@ -376,7 +376,14 @@ int launch_bwd_split(const Problem& p, const void* Q, const void* K, const void*
 //                           64 rows 114 heads (228) 10.4 -> 7.7, 359 (718) 14.3 -> 13.2, but 399 (798) 14.7 -> 15.0;
 //                           d = 128 109 (218) 14.9 -> 10.7, but 213 (426) 16.2 -> 18.4; dropout, d = 64 114 x 128 (228)
 //                           16.5 -> 11.6, but 133 x 128 (266) 16.9 -> 18.8
+//   d = 128 with few queries over many keys: the time is the dQ side's chain over the keys, whose iterations are
+//                           slower here (more than 256 registers, so matrix results come through accumulation registers:
+//                           1.3 of them without dropout, 1.15 with), against a launch and the other side's chain: 6 x 323 over 1457 50.5 -> 47.6,
+//                           9 x 669 over 2235 73.9 -> 69.8, but 1 x 2 over 10565 227 -> 294, 4 x 32 over 4379 105 -> 127,
+//                           6 x 254 over 1858 58.6 -> 59.8, 2 x 992 over 5424 146 -> 155; dropout 6 x 450 over 2837
+//                           106 -> 102, but 2 x 592 over 4902 169 -> 172 (the line is where both are equal within 2 %)
 bool merged_backward(const Problem& p, int per_cu) {
+  if (p.d > 64 && !p.causal && p.Nk > (p.thr ? 7 * (int64_t)p.Nq + 640 : 4 * (int64_t)p.Nq + 512)) return false;
   const int64_t n = (int64_t)p.B * p.H * ((p.Nq + 127) / 128 + (p.Nk + 127) / 128);
   if (p.causal && p.Nq <= 128) return n <= 256 * (per_cu == 2 ? 3 : 1);
   if (p.causal) return n <= 512 * per_cu;

@@ -21,6 +21,7 @@ MERGED = [
     (2, 60, 250, 250, 128, synth.F16, True, 0), (3, 20, 300, 300, 64, synth.F16, True, 26),     # 480; 360: three tiles
 ]
 SEPARATE = [
+    (1, 6, 1, 1600, 128, synth.F16, False, 0), (1, 3, 40, 2900, 104, synth.BF16, False, 26),     # long memories
     (2, 33, 250, 250, 64, synth.F16, False, 0), (2, 33, 250, 250, 128, synth.BF16, False, 26),  # n = 264
     (4, 27, 600, 600, 64, synth.BF16, True, 0), (4, 14, 600, 600, 128, synth.F16, True, 0),     # 1080, 560
     (4, 14, 600, 600, 64, synth.F16, True, 26), (3, 60, 300, 300, 128, synth.BF16, True, 0),    # 560, 1080

@@ -112,3 +112,16 @@ THREE_TILES_FWD = [(192, 128, 0.0, False), (193, 128, 0.0, True), (256, 96, 0.0,
 def test_forward_of_causal_heads_of_three_tiles(case):
     H, d, p, paired = case
     assert _forward(H, 300, 300, d, True, p) == [2 * H if paired else 3 * H]
+
+
+# heads, Nq, Nk, d, dropout rate, whether both sides run in one grid
+FEW_QUERIES = [(8, 256, 1536, 128, 0.0, True), (8, 256, 1537, 96, 0.0, False), (6, 1, 1600, 128, 0.0, False),
+               (4, 100, 5000, 64, 0.0, True), (8, 256, 2432, 128, 0.1, True), (8, 256, 2433, 128, 0.1, False),
+               (4, 5000, 100, 128, 0.0, True)]
+
+
+@pytest.mark.parametrize("case", FEW_QUERIES)
+def test_backward_of_few_queries_over_many_keys(case):
+    H, Nq, Nk, d, p, one_grid = case
+    nq, nk = H * ((Nq + 127) // 128), H * ((Nk + 127) // 128)
+    assert _backward(H, Nq, Nk, d, False, p) == ([_stats(H, Nq, d), nq + nk] if one_grid else [nq, nk])
