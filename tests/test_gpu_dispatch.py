@@ -20,6 +20,11 @@ class _KernelNode(ctypes.Structure):  # hipKernelNodeParams
 
 def _grids(call):
     """Grid sizes (in x) of the kernels that `call` launches, in order."""
+    return [grid for grid, _ in _launches(call)]
+
+
+def _launches(call):
+    """(grid size, threads per workgroup) of the same."""
     import torch
     hip = ctypes.CDLL("libamdhip64.so")
     call()  # sets the kernels up, which a capture does not allow
@@ -39,7 +44,7 @@ def _grids(call):
     for node in nodes:
         p = _KernelNode()
         assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
-        out.append(p.grid.x)
+        out.append((p.grid.x, p.block.x))
     assert hip.hipGraphDestroy(graph) == 0
     return out
 
@@ -97,10 +102,10 @@ def test_causal_heads_of_three_tiles(case):
     assert _backward(H, N, N, d, True, p)[1] == (2 * H if paired else 3 * H)
 
 
-def _forward(H, Nq, Nk, d, causal, p):
+def _forward(H, Nq, Nk, d, causal, p, launches=_grids):
     from paper_2502_12784_amd import spark_mha_dropout_fwd
     Q, K, V, O, L, _ = _tensors(H, Nq, Nk, d)
-    return _grids(lambda: spark_mha_dropout_fwd(Q, K, V, 1 / math.sqrt(d), causal, p, 1, 0, O, L))
+    return launches(lambda: spark_mha_dropout_fwd(Q, K, V, 1 / math.sqrt(d), causal, p, 1, 0, O, L))
 
 
 # heads, d, dropout rate, whether the forward pairs the three causal tiles of a head
@@ -125,3 +130,19 @@ def test_backward_of_few_queries_over_many_keys(case):
     H, Nq, Nk, d, p, one_grid = case
     nq, nk = H * ((Nq + 127) // 128), H * ((Nk + 127) // 128)
     assert _backward(H, Nq, Nk, d, False, p) == ([_stats(H, Nq, d), nq + nk] if one_grid else [nq, nk])
+
+
+# heads, Nq, Nk, d, dropout rate, whether the forward splits the keys over the 8 waves of 32-row workgroups, or has
+# 4 waves for 128 rows
+FEW_ROWS = [(256, 32, 2048, 128, 0.0, True), (257, 32, 2048, 128, 0.0, False), (300, 1, 3000, 104, 0.0, False),
+            (300, 1, 3000, 96, 0.0, True), (300, 1, 3000, 128, 0.1, True),
+            (150, 64, 2500, 128, 0.0, False), (100, 96, 8191, 128, 0.0, True), (100, 96, 8192, 128, 0.0, False),
+            (70, 129, 2500, 128, 0.0, True), (256, 32, 384, 128, 0.0, False), (256, 32, 705, 128, 0.0, True),
+            (224, 32, 384, 128, 0.0, True), (256, 32, 384, 96, 0.0, True)]
+
+
+@pytest.mark.parametrize("case", FEW_ROWS)
+def test_forward_of_few_rows(case):
+    H, Nq, Nk, d, p, split = case
+    want = (H * ((Nq + 31) // 32), 512) if split else (H * ((Nq + 127) // 128), 256)
+    assert _forward(H, Nq, Nk, d, False, p, _launches) == [want]
