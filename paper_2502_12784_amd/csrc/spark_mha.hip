@@ -235,23 +235,24 @@ int64_t fwd_split_workgroups(const Problem& p, int* paired) {
 //   8 heads, N = 2048 (512)                26.4 -> 20.1 / 37.6 -> 31.9   1 head, N = 16384  184 -> 103 / 266 -> 190
 //   causal, 6 heads, N = 4096 (384)        48.9 -> 39.5 / 85.0 -> 61.4   12 heads, N = 2048 (384) 27.1 -> 29.6 (not)
 //   12 heads, N = 2048 (768)               26.6 -> 29.0 / 37.9 -> 46.6 (not)
-// Not beyond one round where a few rows per head make the time a pure read of K and V and a row has more than 192 bytes:
-// a second, partly filled round then costs more than the split saves (mha_fwd_kernel's heads of one tile all fit at once).
-// Up to 64 rows per head always, up to 128 from 400 MB of K and V on, which the memory-side cache does not hold
-// (d = 128, rows x heads over keys: 15 x 257 over 3840 97 -> 117, 32 x 288 over 6541 173 -> 204, 40 x 150 over 5000
-// 77 -> 82, 85 x 150 over 11264 167 -> 181; but 104 x 67 over 8536 is 0.75 of it).  With 512 heads and more the other kernel would be the 8-wave one,
-// at twice the time (2 x 512 over 2048 132 -> 104).  Nor, in a nearly full round, up to 704 keys for heads of one tile: two or
-// three key tiles per wave (32 x 256, d = 128, over 384 12.0 -> 13.2, over 512 14.1 -> 15.1).  With dropout the split wins at all
-// of these.
+// Not beyond one round where a few rows per head of nearly 128 columns make the time a read of K and V: a second,
+// mostly empty round then costs more than the split saves (mha_fwd_kernel's heads of one tile fit at once).  So for up to 32
+// rows below 320 workgroups, up to 64 rows, and up to 128 rows from 400 MB of K and V on, which no cache holds (d = 128,
+// rows x heads over keys: 15 x 257 over 3840 101 -> 118, 32 x 288 over 6541 186 -> 207, 40 x 150 over 5000 101 -> 106,
+// 85 x 150 over 11264 216 -> 230; equal at 1 x 350 over 3071 and 96 x 100 over 8191).  With 512 heads and more the other kernel would be
+// the 8-wave one (2 x 512 over 2048 146 -> 104).  Nor, in a nearly full round, up to 704 keys for heads of one tile: two or
+// three key tiles per wave (32 x 256, d = 128, over 384 12.0 -> 13.2, over 512 14.3 -> 15.3).  With dropout the split wins
+// at all of these.
 template <bool CAUSAL>
 bool split_forward(const Problem& p) {
   int paired;
   const int64_t bh = (int64_t)p.B * p.H, n = fwd_split_workgroups<CAUSAL>(p, &paired);
   if (p.Nk <= 256 || n > (p.Nk >= (CAUSAL ? 4096 : 2048) ? 512 : 256)) return false;
   if (CAUSAL || p.thr || p.d <= 96) return true;
-  if (n > 256 && bh < 512)
-    return p.Nq > 64 && (p.Nq > 128 || bh * p.Nk * p.d * 4 < (int64_t)400 << 20);
-  return !(n > 224 && p.Nq <= 32 && p.Nk <= 704);
+  if (n <= 256) return !(p.d > 112 && n > 224 && p.Nq <= 32 && p.Nk <= 704);
+  if (bh >= 512 || p.Nq > 128) return true;
+  if (p.Nq > 64) return bh * p.Nk * p.d * 4 < (int64_t)400 << 20;
+  return p.d <= 112 || (p.Nq <= 32 && (p.d <= 120 || n >= 320));
 }
 
 // Workgroups that share the keys of one query tile, 1 = no sharing.  For grids of at most half the CUs: as

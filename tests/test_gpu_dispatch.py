@@ -134,9 +134,10 @@ def test_backward_of_few_queries_over_many_keys(case):
 
 # heads, Nq, Nk, d, dropout rate, whether the forward splits the keys over the 8 waves of 32-row workgroups, or has
 # 4 waves for 128 rows
-FEW_ROWS = [(256, 32, 2048, 128, 0.0, True), (257, 32, 2048, 128, 0.0, False), (300, 1, 3000, 104, 0.0, False),
-            (300, 1, 3000, 96, 0.0, True), (300, 1, 3000, 128, 0.1, True),
-            (150, 64, 2500, 128, 0.0, False), (100, 96, 8191, 128, 0.0, True), (100, 96, 8192, 128, 0.0, False),
+FEW_ROWS = [(256, 32, 2048, 128, 0.0, True), (257, 32, 2048, 128, 0.0, False), (319, 1, 3000, 128, 0.0, False),
+            (320, 1, 3000, 128, 0.0, True), (300, 1, 3000, 120, 0.0, True), (300, 1, 3000, 128, 0.1, True),
+            (150, 64, 2500, 128, 0.0, False), (150, 64, 2500, 112, 0.0, True), (240, 64, 2500, 120, 0.0, False),
+            (100, 96, 8191, 128, 0.0, True), (100, 96, 8192, 128, 0.0, False), (104, 96, 10400, 104, 0.0, False),
             (70, 129, 2500, 128, 0.0, True), (256, 32, 384, 128, 0.0, False), (256, 32, 705, 128, 0.0, True),
             (224, 32, 384, 128, 0.0, True), (256, 32, 384, 96, 0.0, True)]
 
