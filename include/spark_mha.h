@@ -99,10 +99,15 @@ size_t spark_mha_bwd_workspace_bytes(int B, int H, int N, int d, spark_dtype_t d
  *   dQ, dK, dV     : out, device, [B,H,N,d] dtype, fully overwritten (no need to zero)
  *   workspace      : device scratch of at least spark_mha_bwd_workspace_bytes(...)
  *                    bytes, 16-byte aligned; contents on return are unspecified.
- * Enqueues, in order on `stream`: the dQ kernel (one workgroup per query tile; a
- * separate deterministic pass in place of the paper's atomic adds into HBM; it
- * also forms D for its rows and leaves it in the workspace) and the dK/dV kernel
- * (one workgroup per key/value tile, accumulating dK and dV on chip as in Sec. 3.3).
+ * Enqueues on `stream`, depending on the sizes:
+ *  - in general, in order, the dQ kernel (one workgroup per query tile; a separate deterministic pass in
+ *    place of the paper's atomic adds into HBM; it also forms D for its rows and leaves it in the
+ *    workspace) and the dK/dV kernel (one workgroup per key/value tile, accumulating dK and dV on chip as
+ *    in Sec. 3.3);
+ *  - where a kernel per side leaves CUs idle, a kernel that forms D and one grid with the tiles of both sides;
+ *  - on grids that stay small with 32 rows per workgroup, one kernel for everything (D never leaves the chip
+ *    and the workspace is not used).
+ * All three are deterministic.
  */
 int spark_mha_bwd(const void* Q, const void* K, const void* V, const void* O, const float* LSE,
                   const void* dO, void* dQ, void* dK, void* dV,
@@ -112,15 +117,24 @@ int spark_mha_bwd(const void* Q, const void* K, const void* V, const void* O, co
 
 /*
  * spark_mha_bwd with profiling marks: identical work, and additionally records the caller's
- * three HIP events (hipEvent_t handles, host array) on `stream`: events[0] before the dQ
- * kernel, events[1] after it, events[2] after the dK/dV kernel; where one kernel does both (small
- * problems) events[1] and events[2] follow it.  The caller creates, reads and destroys the events.  SPARK_ERR_NULL if any is NULL.
+ * three HIP events (hipEvent_t handles, host array) on `stream`: events[0] before the first
+ * kernel, events[1] after the dQ kernel, events[2] after the dK/dV kernel; where one grid does both sides
+ * (the second and third case above) events[1] and events[2] both follow it, with nothing between, and the
+ * time from events[0] to events[1] is the whole backward.  The caller creates, reads and destroys the
+ * events.  SPARK_ERR_NULL if any is NULL.
  */
 int spark_mha_bwd_marked(const void* Q, const void* K, const void* V, const void* O,
                          const float* LSE, const void* dO, void* dQ, void* dK, void* dV,
                          void* workspace, size_t workspace_bytes,
                          int B, int H, int N, int d, float scale, int causal,
                          spark_dtype_t dtype, void* stream, void* const events[3]);
+
+/*
+ * How many grids hold the two sides of the backward of this problem: 2 (the dQ kernel, then the dK/dV kernel) or 1
+ * (one grid for both).  A negative spark_status_t for an invalid problem.  Decides nothing: it reports the choice that
+ * the backward entry points make by themselves, for readers of the marked calls' events.
+ */
+int spark_mha_bwd_grids(int B, int H, int Nq, int Nk, int d, int causal, float p_drop, spark_dtype_t dtype);
 
 /*
  * The backward exactly as the paper builds it (Sec. 3.3): ONE fused kernel whose workgroups each own a

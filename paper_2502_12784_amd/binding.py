@@ -27,7 +27,7 @@ EXPORTS = ("spark_mha_fwd", "spark_mha_bwd", "spark_mha_bwd_marked",
            "spark_mha_strided_bwd", "spark_status_str", "spark_mha_bwd_static",
            "spark_mha_bwd_static_max_rows", "spark_layout_probe", "spark_mha_bwd_atomic",
            "spark_mha_bwd_atomic_workspace_bytes", "spark_mha_dropout_bwd_marked",
-           "spark_mha_workspace_fwd", "spark_mha_fwd_workspace_bytes")
+           "spark_mha_workspace_fwd", "spark_mha_fwd_workspace_bytes", "spark_mha_bwd_grids")
 
 _lib = None
 _host = None  # the extension module; loaded together with the library
@@ -122,6 +122,8 @@ def load_library() -> ctypes.CDLL:
     lib.spark_mha_workspace_fwd.restype = i
     lib.spark_mha_workspace_fwd.argtypes = ([vp] * 5 + [sp] * 4 + [vp, ctypes.c_size_t, i, i, i, i, i, f, i, f, u64,
                                                                   u32, i, vp])
+    lib.spark_mha_bwd_grids.restype = i
+    lib.spark_mha_bwd_grids.argtypes = [i, i, i, i, i, i, f, i]
     lib.spark_mha_fwd_workspace_bytes.restype = ctypes.c_size_t
     lib.spark_mha_fwd_workspace_bytes.argtypes = [i, i, i, i, i, i, i]
     lib.spark_mha_bwd_marked.restype = i

@@ -452,7 +452,7 @@ int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, co
     if (rc != SPARK_OK) return rc;
     return mark(1) && mark(2) ? SPARK_OK : SPARK_ERR_LAUNCH;
   }
-  constexpr int PER_CU = D == 64 && !DROP ? 2 : 1;  // workgroups of the dK/dV kernel on a CU
+  constexpr int PER_CU = D == 64 && !DROP ? 2 : 1;  // workgroups of the dK/dV kernel on a CU (also spark_mha_bwd_grids)
   if (merged_backward(p, PER_CU)) {
     const int rc = launch_bwd_merged<T, D, CAUSAL, DROP, PER_CU>(p, Q, K, V, O, LSE, dO, dQ, dK, dV, Dws);
     if (rc != SPARK_OK) return rc;
@@ -653,6 +653,13 @@ size_t spark_mha_cross_bwd_workspace_bytes(int B, int H, int Nq, int Nk, int d,
                                            spark_dtype_t dtype) {
   if (check_common(B, H, Nq, Nk, d, 1.0f, 0, (int)dtype) != SPARK_OK) return 0;
   return workspace_bytes(B, H, Nq);  // D and LSE*log2(e), fp32 [B,H,Nq] each
+}
+
+int spark_mha_bwd_grids(int B, int H, int Nq, int Nk, int d, int causal, float p_drop, spark_dtype_t dtype) {
+  Problem p;
+  const int rc = make_problem(&p, B, H, Nq, Nk, d, 1.0f, causal, drop_threshold(p_drop), 0, 0, dtype, nullptr);
+  if (rc != SPARK_OK) return rc;
+  return split_backward(p) || merged_backward(p, p.d <= 64 && !p.thr ? 2 : 1) ? 1 : 2;
 }
 
 size_t spark_mha_bwd_workspace_bytes(int B, int H, int N, int d, spark_dtype_t dtype) {

@@ -34,6 +34,21 @@ def test_config_table_figures():
     assert float(cells[3][2]) == pytest.approx(100 * (w.fwd_flops + w.bwd_flops) / 2.5e-3 / 1e12 / 2500, abs=0.06)
 
 
+def test_backward_in_one_grid_is_one_kernel():
+    k = {"fwd": 0.005, "bwd_dq": 0.0089, "bwd_dkdv": 0.0, "step_min": 0.02}
+    w = synth.WORKLOADS["C1"]
+    assert bench.one_grid_backward(w)
+    ms, alg = bench.kernel_accounting(w, k)
+    assert ms == {"fwd": 0.005, "bwd": 0.0089}
+    assert alg["bwd"] == w.bwd_flops == 2.5 * alg["fwd"]
+    for name in ("C2", "C3", "C4", "C5"):
+        w = synth.WORKLOADS[name]
+        assert not bench.one_grid_backward(w) and not bench.one_grid_backward(w, 0.1)
+        ms, alg = bench.kernel_accounting(w, dict(k, bwd_dkdv=0.012))
+        assert ms == {"fwd": 0.005, "bwd_dq": 0.0089, "bwd_dkdv": 0.012}
+        assert alg["bwd_dq"] + alg["bwd_dkdv"] == w.bwd_flops and alg["bwd_dkdv"] == 4 * alg["bwd_dq"]
+
+
 def test_traffic_is_quoted_only_for_matching_sources(tmp_path, monkeypatch):
     root = tmp_path
     csrc = root / "paper_2502_12784_amd" / "csrc"

@@ -27,7 +27,7 @@ def _launches(call):
     """(grid size, threads per workgroup) of the same."""
     import torch
     hip = ctypes.CDLL("libamdhip64.so")
-    call()  # sets the kernels up, which a capture does not allow
+    call()  # sets the kernels up, outside of the capture
     torch.cuda.synchronize()
     side = torch.cuda.Stream()
     stream, graph, n = ctypes.c_void_p(side.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t()
@@ -147,3 +147,16 @@ def test_forward_of_few_rows(case):
     H, Nq, Nk, d, p, split = case
     want = (H * ((Nq + 31) // 32), 512) if split else (H * ((Nq + 127) // 128), 256)
     assert _forward(H, Nq, Nk, d, False, p, _launches) == [want]
+
+
+def test_bwd_grids_reports_the_route():
+    """spark_mha_bwd_grids against the launches: one kernel, or the statistics pass and one grid, or one kernel per side."""
+    from paper_2502_12784_amd import load_library
+    lib = load_library()
+    for H, Nq, Nk, d, causal, p in ((2, 128, 128, 64, 0, 0.0), (128, 64, 64, 128, 1, 0.0), (129, 64, 64, 128, 1, 0.0),
+                                    (20, 1100, 1100, 64, 0, 0.0), (20, 1100, 1100, 64, 0, 0.1), (8, 256, 1536, 128, 0, 0.0),
+                                    (8, 256, 1537, 96, 0, 0.0), (140, 192, 192, 64, 1, 0.1)):
+        got = _backward(H, Nq, Nk, d, bool(causal), p)
+        one_grid = len(got) == 1 or got[0] == _stats(H, Nq, d)
+        assert lib.spark_mha_bwd_grids(1, H, Nq, Nk, d, causal, p, 0) == (1 if one_grid else 2), (H, Nq, Nk, d, causal, p, got)
+    assert lib.spark_mha_bwd_grids(1, 2, 8, 16, 64, 1, 0.0, 0) < 0  # causal needs a square

@@ -123,12 +123,14 @@ def test_dropout_full_size_configs_sampled_heads(name):
         assert np.isfinite(pu.to_f64(gpu[n])).all(), n
 
 
-def test_marked_dropout_backward_is_the_same_work():
-    """spark_mha_dropout_bwd_marked: identical gradients, and its three events are ordered in time."""
+@pytest.mark.parametrize("heads,one_grid", [((2, 3), True), ((4, 12), False)])
+def test_marked_dropout_backward_is_the_same_work(heads, one_grid):
+    """spark_mha_dropout_bwd_marked: identical gradients, and its three events are ordered in time: around the dQ
+    and the dK/dV kernel, or all of it in front of the second where one grid does both."""
     import torch
     from paper_2502_12784_amd import HipEvents, spark_mha_dropout_bwd, spark_mha_dropout_fwd
-    B, H, N, d, dtype = 2, 3, 700, 128, synth.BF16
-    inp = synth.make_inputs(B, H, N, d, dtype, seed=6500)
+    N, d, dtype = 700, 128, synth.BF16  # 72 tiles of both sides, or 576: beyond the 512 that share a grid
+    inp = synth.make_inputs(*heads, N, d, dtype, seed=6500)
     Q, K, V, dO = (pu.to_device(inp[n], dtype) for n in ("Q", "K", "V", "dO"))
     drop = (0.1, SEED, 9)
     O, LSE = spark_mha_dropout_fwd(Q, K, V, 0.1, True, *drop)
@@ -138,5 +140,11 @@ def test_marked_dropout_backward_is_the_same_work():
     torch.cuda.synchronize()
     for a, b, n in zip(got, want, ("dQ", "dK", "dV")):
         assert torch.equal(a, b), n
-    assert ev.elapsed_ms(0, 1) > 0 and ev.elapsed_ms(1, 2) > 0
+    first, second = ev.elapsed_ms(0, 1), ev.elapsed_ms(1, 2)
+    print(f"\n[marks] {heads}: {first:.4f} {second:.4f} ms", flush=True)
+    assert first > 0
+    if one_grid:  # nothing lies between the later two
+        assert 0 <= second < first
+    else:  # four contractions against three
+        assert second > 0.25 * first
     ev.close()
