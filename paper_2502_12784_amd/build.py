@@ -3,6 +3,7 @@ this file (gfx950 only)."""
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -42,7 +43,9 @@ def build_host_binding() -> str:
     import torch
     from torch.utils import cpp_extension
     tmp = HOST_EXT + ".tmp.%d" % os.getpid()
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+    # any host compiler does: without g++ the one that comes with hipcc, which the library needs anyway
+    cxx = os.environ.get("CXX") or shutil.which("g++") or "/opt/rocm/llvm/bin/clang++"
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
     cmd += ["-isystem" + d for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]]
     cmd += [HOST_SOURCE, "-o", tmp] + ["-L" + d for d in cpp_extension.library_paths()]
