@@ -159,9 +159,13 @@ int ensure_smem(KernelT kernel, int bytes, std::atomic<uint64_t>& done) {
 // two rounds or more, almost two, or one round where the narrow grid puts two workgroups on some CU (the time is
 // that CU's).  Forward, bf16, us, narrow -> wide (n wide workgroups):
 //   16 heads x 4096 (256) 125.6 -> 117.0   24 x 2048 (192) 59.1 -> 52.8   40 x 1024 over 4096 keys (160) 105.8 -> 93.8
-//   causal 8 x 16384 (256) 503.7 -> 456.9   24 x 4096 (192) 122.3 -> 111.7   64 x 2048 (256) 80.6 -> 81.4
+//   causal 8 x 16384 (256) 503.7 -> 456.9   24 x 4096 (192) 122.3 -> 111.7   64 x 2048 (256) 80.6 -> 81.4 (one run each; below)
 //   not taken: 40 x 2048 (320) 95.1 -> 107.5   12 x 8192 (384) 369 -> 394   causal 40 x 4096 (320) 211.7 -> 225.4
 //   almost two: 56 x 2048 (448) 121.2 -> 113.7   causal 112 x 2048 (448) 145.8 -> 140.0
+// Checked over 68 problems around these two classes (medians in alternating order; with dropout and d = 72 ... 104 among them):
+// 0.85 ... 0.99 of the narrow kernel's time at all that are taken, among them causal 64 x 2048 83.9 -> 78.5 and with dropout
+// 101.7 -> 98.5, 43 x 700 over 2048 (129 against 258, the fewest) 56.1 -> 52.4, 450 x 250 over 2100 152.9 -> 150.9; not
+// taken 1.08 ... 1.76, except 20 x 5000 (400, d = 96) 273.6 -> 247.3.
 template <bool CAUSAL>
 bool wide_workgroups(const Problem& p) {
   const int64_t bh = (int64_t)p.B * p.H;
