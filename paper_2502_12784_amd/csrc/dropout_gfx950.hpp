@@ -12,7 +12,7 @@
 // lane holds, per 32 x 32 block, four strips of four consecutive rows of one column: four 1 x 4
 // (or 4 x 1) pieces of four different calls.  The four lanes of a quad hold the complementary
 // pieces of the same four calls, so each lane evaluates one call and the quad exchanges the
-// words with DPP quad broadcasts: one generator call per 16 entries, none wasted.
+// words (a 4 x 4 transpose by DPP moves): one generator call per 16 entries, none wasted.
 #pragma once
 #include <stdint.h>
 

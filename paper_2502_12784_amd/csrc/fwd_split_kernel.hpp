@@ -17,7 +17,7 @@
 // The price is operand traffic: K and V are read from L2 once per 32 query rows instead of once per
 // 128 (8 waves on 8 KB + 8 KB of their own per 32 x 32 ... 64 block, against 64 B per clock from L2:
 // about the rate of one wave per SIMD of the other kernel), hence only for grids that fit the chip in
-// one go.  With a few rows against a long memory even these are few (8 heads: 8 workgroups on 256 CUs); then
+// one go, or in two where the chains are long (the rule and its times: split_forward).  With a few rows against a long memory even these are few (8 heads: 8 workgroups on 256 CUs); then
 // several workgroups share the keys of a query tile and a small kernel merges them (2 queries, 8 heads, 8318
 // keys, d = 128: 64.0 -> 19.3 us).  Measured: 1 head, N = 8192: d = 64 fp16 91 -> 29 us, d = 128 134 -> 51 us; one query row
 // against 2048 keys, 128 heads, d = 128: 40.7 -> 29.3 us (4.6 TB/s, the rate of a large copy).
