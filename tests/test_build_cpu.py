@@ -45,3 +45,23 @@ def test_waits_without_a_barrier_are_compiler_fences():
     helpers = code("mma_gfx950.hpp")
     for asm_text in (r's_waitcnt vmcnt\(%0\)" ::"n"\(N\)', r's_waitcnt lgkmcnt\(0\)" ::'):
         assert re.search(asm_text + r'[^;]*: "memory"\)', helpers)
+
+
+def test_host_binding_needs_no_compiler_but_hipccs(monkeypatch, tmp_path):
+    """Without g++ the host extension is compiled with the clang++ of the ROCm toolchain."""
+    seen = []
+
+    def run(cmd, **_):
+        seen.append(cmd)
+        open(cmd[cmd.index("-o") + 1], "w").close()
+        return type("Done", (), {"returncode": 0, "stdout": ""})
+
+    monkeypatch.setattr(build, "HOST_EXT", str(tmp_path / "_spark_host.so"))
+    monkeypatch.setattr(build.subprocess, "run", run)
+    monkeypatch.setattr(build.shutil, "which", lambda name: None)
+    monkeypatch.delenv("CXX", raising=False)
+    build.build_host_binding()
+    assert os.path.exists(seen[0][0]) and seen[0][0].endswith("clang++")
+    monkeypatch.setenv("CXX", "some-c++")
+    build.build_host_binding()
+    assert seen[1][0] == "some-c++"
