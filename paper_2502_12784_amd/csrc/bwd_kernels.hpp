@@ -210,15 +210,16 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
     };
 
     // One element of P and dS from finished scores: the unit of VALU work that is placed between
-    // MFMAs.  r8 = register index within the half (0..7).
+    // MFMAs.  r8 = register index within the half (0..7).  ahead: how far the lane's key lies behind the
+    // step's first query of this lane, so that the causal mask is one compare with a constant per element.
     // Under dropout (kb: the step's decision bytes) the dV operand is the dropped P, and
     // dS = r P o (M o dPraw - D (1-p)): the workspace holds D (1-p), r goes into the final scales.
     auto softmax_elem = [&](const f32x16& s, const f32x16& dp, int half, int r8, const f32x4 (&l)[2],
-                            const f32x4 (&d)[2], int q0s, bool mask, const uint32_t (&kb)[4], float* p,
+                            const f32x4 (&d)[2], int ahead, bool mask, const uint32_t (&kb)[4], float* p,
                             float* ds, uint32_t (&pk_p)[4], uint32_t (&pk_ds)[4]) {
       const int r = 8 * half + r8;
       float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2, -l[r8 >> 2][r8 & 3]));
-      if (mask) pe = krow > q0s + 8 * (r / 4) + 4 * g + (r % 4) ? 0.f : pe;
+      if (mask) pe = ahead > 8 * (r / 4) + (r % 4) ? 0.f : pe;
       if (DROP) {
         const bool keep = keep_reg(kb, r, dr.thr);
         p[r8] = keep ? pe : 0.f;
@@ -237,6 +238,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
         pk_ds[r8 >> 1] = pack2<T>(ds[r8 - 1], ds[r8]);
       }
     };
+    auto ahead_of = [&](int q0s) { return krow - q0s - 4 * g; };
     uint32_t kbCur[4] = {0, 0, 0, 0}, kbNew[4] = {0, 0, 0, 0};  // decision bytes of the current / next step
 
     // ---- prologue: stages s_begin and s_begin+1 resident, scores of the first step formed ----
@@ -290,7 +292,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       if (DROP) keep_bytes_key_lane(dr, head, krow, s_begin * C::BM, lane, kbCur);
 #pragma unroll
       for (int r = 0; r < 8; ++r)
-        softmax_elem(sX, dpX, 0, r, lL, dL, s_begin * C::BM, CAUSAL, kbCur, p, ds, pk_p, pk_ds);
+        softmax_elem(sX, dpX, 0, r, lL, dL, ahead_of(s_begin * C::BM), CAUSAL, kbCur, p, ds, pk_p, pk_ds);
       pfL = join_pairs<T>(pk_p);
       dsfL = join_pairs<T>(pk_ds);
     }
@@ -309,6 +311,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       // (sub_new inside the stage rowA / statA point at).
       auto step = [&](f32x16& s_new, f32x16& dp_new, int sub_new, int q0_new, const f32x16& s_cur,
                       const f32x16& dp_cur, int sub_cur, int q0_cur, auto&& request_next) {
+        const int ahead_cur = ahead_of(q0_cur), ahead_new = ahead_of(q0_new);
         // ---- region 1: scores of the next step  ||  second half of P, dS of the current step ----
         float p[8], ds[8];
         uint32_t pk_p[4], pk_ds[4];
@@ -330,7 +333,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
           if (i == 2 * NG + 1) load_thalf(1, sub_cur, 1);
           if (i & 1) {
 #pragma unroll
-            for (int x = 0; x < E1; ++x) softmax_elem(s_cur, dp_cur, 1, (i / 2) * E1 + x, lH, dH, q0_cur, mask, kbCur, p, ds, pk_p, pk_ds);
+            for (int x = 0; x < E1; ++x) softmax_elem(s_cur, dp_cur, 1, (i / 2) * E1 + x, lH, dH, ahead_cur, mask, kbCur, p, ds, pk_p, pk_ds);
           }
           if (DROP) {
 #pragma unroll
@@ -352,9 +355,9 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
           for (int e = 0; e < 2; ++e) {
             dv[dt0 + e] = F::mfma(ft[tg & 1][2 * e], kk ? pfH : pfL, dv[dt0 + e]);
             dk[dt0 + e] = F::mfma(ft[tg & 1][2 * e + 1], kk ? dsfH : dsfL, dk[dt0 + e]);
-            softmax_elem(s_new, dp_new, 0, (8 / NTG) * tg + e, lL, dL, q0_new, mask, kbNew, p, ds, pk_p, pk_ds);
+            softmax_elem(s_new, dp_new, 0, (8 / NTG) * tg + e, lL, dL, ahead_new, mask, kbNew, p, ds, pk_p, pk_ds);
             if (8 / NTG > 2)
-              softmax_elem(s_new, dp_new, 0, (8 / NTG) * tg + 2 + e, lL, dL, q0_new, mask, kbNew, p, ds, pk_p, pk_ds);
+              softmax_elem(s_new, dp_new, 0, (8 / NTG) * tg + 2 + e, lL, dL, ahead_new, mask, kbNew, p, ds, pk_p, pk_ds);
             if (tg + 2 < NTG) load_thalf(tg + 2, sub_cur, e);  // into the operands just used
             sched_fence();
           }
@@ -558,6 +561,9 @@ static __device__ __forceinline__ void bwd_dq(
     if (FOLD_D) asm volatile("" : "+v"(dneg));
     __syncthreads();
 
+    // last key this lane's query attends to, less the 4 g that every register's key contains: the mask is one
+    // compare with a constant per element
+    const int last_key = (CAUSAL && qrow < Nk ? qrow : Nk - 1) - 4 * g;
     // One iteration, compiled twice: MASKED for tiles that the diagonal or the end of the keys
     // crosses, and without any mask arithmetic for all the others.
     auto iteration = [&](const int j, auto masked_tag) {
@@ -615,11 +621,7 @@ static __device__ __forceinline__ void bwd_dq(
         auto p_elem = [&](int e) {  // e = mt * 16 + r
           const int mt = e / 16, r = e % 16;
           float x = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mt][r], scale_log2, -lse2));
-          if (MASKED) {
-            const int key = k0 + mt * 32 + 8 * (r / 4) + 4 * g + (r % 4);
-            const bool ok = key < Nk && (!CAUSAL || key <= qrow);
-            if (!ok) x = 0.f;
-          }
+          if (MASKED) x = mt * 32 + 8 * (r / 4) + (r % 4) > last_key - k0 ? 0.f : x;
           pe[e] = x;
           asm volatile("" : "+v"(pe[e]));
         };

@@ -155,6 +155,7 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
 #pragma unroll
       for (int r = 0; r < 16; ++r) dq[dt][r] = 0.f;
 
+    const int last_key = (CAUSAL && qrow < Nk ? qrow : Nk - 1) - 4 * g;  // the mask: one compare with a constant
     auto tile = [&](const int j, const int b, auto masked_tag, const bool next) {
       constexpr bool MASKED = decltype(masked_tag)::value;
       SPARK_LDS char* const kb = wbuf + b * C::STAGE;
@@ -179,10 +180,7 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2, -lse2));
-        if (MASKED) {
-          const int key = j * C::BM + 8 * (r / 4) + 4 * g + (r % 4);
-          if (!(key < Nk && (!CAUSAL || key <= qrow))) p = 0.f;
-        }
+        if (MASKED && 8 * (r / 4) + (r % 4) > last_key - j * C::BM) p = 0.f;
         ds[r] = DROP ? p * ((keep_reg(keep, r, dr.thr) ? dp[r] : 0.f) - Dq) : p * dp[r];
       }
 #pragma unroll
@@ -294,7 +292,7 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2, -l[r >> 2][r & 3]));
-        if (diag) pe = krow > t * C::BM + 8 * (r / 4) + 4 * g + (r % 4) ? 0.f : pe;
+        if (diag) pe = c32 - 4 * g > 8 * (r / 4) + (r % 4) ? 0.f : pe;  // krow - t * BM = c32
         if (DROP) {
           const bool kept = keep_reg(keep, r, dr.thr);
           p[r] = kept ? pe : 0.f;

@@ -139,6 +139,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void mha_fwd_kernel(
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));
     __syncthreads();
 
+    // last key this lane's query attends to, less the 4 g that every register's key contains: the mask is one
+    // compare with a constant per score (with both limits compared, four instructions; us, causal, d = 64, 256
+    // heads x 512 22.8 -> 21.6, d = 80, 36 x 1333 35.9 -> 31.9)
+    const int last_key = (CAUSAL && qrow < Nk ? qrow : Nk - 1) - 4 * g;
     // One iteration, compiled twice: MASKED for tiles that the diagonal or the end of the keys
     // crosses, and without any mask arithmetic for all the others (left to a run-time flag, the
     // compiler evaluates the mask predicate for every score of every tile).
@@ -198,9 +202,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void mha_fwd_kernel(
           if (MASKED) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-              const int key = k0 + h * 32 + 8 * (r / 4) + 4 * g + (r % 4);
-              const bool ok = key < Nk && (!CAUSAL || key <= qrow);
-              if (!ok) t[h * 16 + r] = -INFINITY;
+              if (h * 32 + 8 * (r / 4) + (r % 4) > last_key - k0) t[h * 16 + r] = -INFINITY;
             }
           }
         };

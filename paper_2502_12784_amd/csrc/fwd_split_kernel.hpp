@@ -122,6 +122,7 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));  // Q is awaited here, not in the loop
 
+    const int last_key = (CAUSAL && qrow < Nk ? qrow : Nk - 1) - 4 * g;  // as in mha_fwd_kernel
     // One tile; next: this wave has another one.  On entry at most NLOAD loads of K and, behind them,
     // NLOAD of V are outstanding.
     auto tile = [&](const int j, auto masked_tag, const bool next) {
@@ -153,8 +154,7 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
         for (int r = 0; r < 16; ++r) {
           t[h * 16 + r] = s[h][r];
           if (MASKED) {
-            const int key = k0 + h * 32 + 8 * (r / 4) + 4 * g + (r % 4);
-            if (!(key < Nk && (!CAUSAL || key <= qrow))) t[h * 16 + r] = -INFINITY;
+            if (h * 32 + 8 * (r / 4) + (r % 4) > last_key - k0) t[h * 16 + r] = -INFINITY;
           }
         }
       };
