@@ -176,6 +176,15 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
         if (DROP) d[x] = lds_read16<f32x4>(smem, o + C::BM * 4);
       }
     };
+    // RING (dropout at D = 64): the statistics go through two slots of four query rows each, refilled as soon as their
+    // four elements are done, instead of being held for a half step (8 rows) and the next one.  With that the kernel
+    // fits 256 registers and two workgroups share a CU (us, 256 heads x 2048 852 -> 660, causal 509 -> 386).
+    constexpr bool RING = DROP && D == 64;
+    auto load_quad = [&](f32x4 (&l)[2], f32x4 (&d)[2], int sub, int x) {
+      const int o = statA + (sub * 32 + 8 * x) * 4;
+      l[x & 1] = lds_read16<f32x4>(smem, o);
+      d[x & 1] = lds_read16<f32x4>(smem, o + C::BM * 4);
+    };
     // The workspace holds -D.  Without dropout dS = P o (dP - D) needs no subtraction: the dP
     // accumulator of a step starts from -D of its 16 query rows instead of from zero (the four
     // 16-byte reads below deliver them in exactly the accumulator's row order), so the MFMAs
@@ -296,7 +305,12 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       pfL = join_pairs<T>(pk_p);
       dsfL = join_pairs<T>(pk_ds);
     }
-    load_stats(lH, dH, 0, 1);
+    if (RING) {
+      load_quad(lL, dL, 0, 2);
+      load_quad(lL, dL, 0, 3);
+    } else {
+      load_stats(lH, dH, 0, 1);
+    }
 
     // One stage: steps (m, 0) and (m, 1).  On entry sX / dpX hold the scores of (m, 0), pfL / dsfL
     // their first half and lH / dH the statistics of their second half; rowA and trC point at
@@ -318,7 +332,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
         // dropout decisions of the next step: the ten generator rounds ride in the MFMA slots below
         Philox rng;
         if (DROP) rng = keep_key_lane_begin(dr, head, krow, q0_new, lane);
-        load_stats(lL, dL, sub_new, 0);
+        if (!RING) load_stats(lL, dL, sub_new, 0);
         load_thalf(0, sub_cur, 0);
 #pragma unroll
         for (int i = 0; i < 4 * NG; ++i) {
@@ -333,7 +347,10 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
           if (i == 2 * NG + 1) load_thalf(1, sub_cur, 1);
           if (i & 1) {
 #pragma unroll
-            for (int x = 0; x < E1; ++x) softmax_elem(s_cur, dp_cur, 1, (i / 2) * E1 + x, lH, dH, ahead_cur, mask, kbCur, p, ds, pk_p, pk_ds);
+            for (int x = 0; x < E1; ++x)
+              softmax_elem(s_cur, dp_cur, 1, (i / 2) * E1 + x, RING ? lL : lH, RING ? dL : dH, ahead_cur, mask, kbCur, p, ds,
+                           pk_p, pk_ds);
+            if (RING && (i & 3) == 3) load_quad(lL, dL, sub_new, i / 4);  // first half of the next step
           }
           if (DROP) {
 #pragma unroll
@@ -344,8 +361,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
         }
         if (DROP) keep_key_lane_finish(rng, lane, kbNew);
         const v8 pfH = join_pairs<T>(pk_p), dsfH = join_pairs<T>(pk_ds);
-        load_stats(lH, dH, sub_new, 1);
-        sched_fence();
+        if (!RING) load_stats(lH, dH, sub_new, 1);
         sched_fence();
         // ---- region 2: dV, dK of the current step  ||  first half of P, dS of the next step ----
 #pragma unroll
@@ -361,6 +377,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
             if (tg + 2 < NTG) load_thalf(tg + 2, sub_cur, e);  // into the operands just used
             sched_fence();
           }
+          if (RING) load_quad(lL, dL, sub_new, 2 + tg);  // second half of the next step
           // the fragment buffers are free since region 1 ended; one group per slot keeps the number
           // of LDS reads in flight under the 15 the wave's counter can track
           if (EARLY && tg == NTG / 2 - 1) request_next(0);
@@ -429,7 +446,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
 }
 
 template <typename T, int D, bool CAUSAL, bool DROP>
-__global__ __launch_bounds__(256, (D == 64 && !DROP) ? 2 : 1) void mha_bwd_dkdv_pipe_kernel(
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void mha_bwd_dkdv_pipe_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const T* __restrict__ dO, const float* __restrict__ LSE2, const float* __restrict__ Dws,
     T* __restrict__ dK, T* __restrict__ dV, TensorMap mq, TensorMap mk, TensorMap mv, TensorMap mdo,
@@ -766,7 +783,7 @@ template <int D> struct BwdMergedCfg {
 };
 
 template <typename T, int D, bool CAUSAL, bool DROP>
-__global__ __launch_bounds__(256, (D == 64 && !DROP) ? 2 : 1) void mha_bwd_merged_kernel(
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void mha_bwd_merged_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
     float* __restrict__ Dws, float* __restrict__ LSE2ws, T* __restrict__ dQ, T* __restrict__ dK, T* __restrict__ dV,
     TensorMap mq, TensorMap mk, TensorMap mv, TensorMap mdo, TensorMap mdq, TensorMap mdk, TensorMap mdv, int H,

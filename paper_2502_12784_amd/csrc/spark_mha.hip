@@ -375,8 +375,8 @@ int launch_bwd_split(const Problem& p, const void* Q, const void* K, const void*
 }
 
 // Both sides of the backward in one grid of 128-row tiles (mha_bwd_merged_kernel): where a kernel per side
-// leaves CUs idle one after the other, at the price of a small kernel that forms D first.  `per_cu`:
-// workgroups of the grid that fit a CU.  Backward, fp16, us, one kernel per side -> merged (n tiles of
+// leaves CUs idle one after the other, at the price of a small kernel that forms D first.  Two workgroups of the
+// grid fit a CU at d = 64, one at d = 128.  Backward, fp16, us, one kernel per side -> merged (n tiles of
 // both sides), square problems of BH heads:
 //   up to one tile per CU:  d = 64 128 x 128 (256) 12.3 -> 9.6, 16 x 1024 (256) 36.9 -> 26.5;
 //                           d = 128 32 x 512 (256) 36.9 -> 25.7, 4 x 4096 (256) 198 -> 130
@@ -392,14 +392,19 @@ int launch_bwd_split(const Problem& p, const void* Q, const void* K, const void*
 //   causal, one tile per head (nothing to pair): while all are resident, three per CU at d = 64 without dropout;
 //                           64 rows 114 heads (228) 10.4 -> 7.7, 359 (718) 14.3 -> 13.2, but 399 (798) 14.7 -> 15.0;
 //                           d = 128 109 (218) 14.9 -> 10.7, but 213 (426) 16.2 -> 18.4; dropout, d = 64 114 x 128 (228)
-//                           16.5 -> 11.6, but 133 x 128 (266) 16.9 -> 18.8
+//                           16.5 -> 11.6, but 133 x 128 (266) 21.9 -> 23.1, 256 x 128 (512) 22.9 -> 24.1
+//   dropout, d = 64, causal: two and three tiles per head keep the line of one workgroup per CU (150 x 300 (900) 37.6 ->
+//                           39.7), longer ones that of two (96 x 512 (768) 54.4 -> 50.0, 36 x 1333 (792) 85.4 -> 74.5,
+//                           16 x 4096 (1024) 202 -> 182); not causal as without it (24 x 1024 (384) 53.9 -> 52.0, but
+//                           128 x 256 (512) 25.6 -> 27.6)
 //   d = 128 with few queries over many keys: the time is the dQ side's chain over the keys, whose iterations are
 //                           slower here (more than 256 registers, so matrix results come through accumulation registers:
 //                           1.3 of them without dropout, 1.15 with), against a launch and the other side's chain: 6 x 323 over 1457 50.5 -> 47.6,
 //                           9 x 669 over 2235 73.9 -> 69.8, but 1 x 2 over 10565 227 -> 294, 4 x 32 over 4379 105 -> 127,
 //                           6 x 254 over 1858 58.6 -> 59.8, 2 x 992 over 5424 146 -> 155; dropout 6 x 450 over 2837
 //                           106 -> 102, but 2 x 592 over 4902 169 -> 172 (the line is where both are equal within 2 %)
-bool merged_backward(const Problem& p, int per_cu) {
+bool merged_backward(const Problem& p) {
+  const int per_cu = p.d <= 64 && !(p.thr && p.causal && p.Nq <= 384) ? 2 : 1;  // which line, as measured above
   if (p.d > 64 && !p.causal && p.Nk > (p.thr ? 7 * (int64_t)p.Nq + 640 : 4 * (int64_t)p.Nq + 512)) return false;
   const int64_t n = (int64_t)p.B * p.H * ((p.Nq + 127) / 128 + (p.Nk + 127) / 128);
   if (p.causal && p.Nq <= 128) return n <= 256 * (per_cu == 2 ? 3 : 1);
@@ -456,8 +461,8 @@ int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, co
     if (rc != SPARK_OK) return rc;
     return mark(1) && mark(2) ? SPARK_OK : SPARK_ERR_LAUNCH;
   }
-  constexpr int PER_CU = D == 64 && !DROP ? 2 : 1;  // workgroups of the dK/dV kernel on a CU (also spark_mha_bwd_grids)
-  if (merged_backward(p, PER_CU)) {
+  constexpr int PER_CU = D == 64 && !DROP ? 2 : 1;  // in pair_tiles; with dropout two fit at d = 64, too, and the line is kept
+  if (merged_backward(p)) {
     const int rc = launch_bwd_merged<T, D, CAUSAL, DROP, PER_CU>(p, Q, K, V, O, LSE, dO, dQ, dK, dV, Dws);
     if (rc != SPARK_OK) return rc;
     return mark(1) && mark(2) ? SPARK_OK : SPARK_ERR_LAUNCH;
@@ -663,7 +668,7 @@ int spark_mha_bwd_grids(int B, int H, int Nq, int Nk, int d, int causal, float p
   Problem p;
   const int rc = make_problem(&p, B, H, Nq, Nk, d, 1.0f, causal, drop_threshold(p_drop), 0, 0, dtype, nullptr);
   if (rc != SPARK_OK) return rc;
-  return split_backward(p) || merged_backward(p, p.d <= 64 && !p.thr ? 2 : 1) ? 1 : 2;
+  return split_backward(p) || merged_backward(p) ? 1 : 2;
 }
 
 size_t spark_mha_bwd_workspace_bytes(int B, int H, int N, int d, spark_dtype_t dtype) {
