@@ -87,6 +87,9 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
   using C = BwdKvPipeCfg<D>;
   constexpr int KS = D / 16, DT = D / 32;
 
+  // D = 64: few offset registers (250 instead of 256 registers with dropout, causal 16 instead of 52 bytes of spills:
+  // dK/dV, us, 256 causal heads x 512 44.1 -> 41.4; without dropout 0 ... 1 % less)
+  using LaneOffsets = std::conditional_t<D == 64, SwzLaneLean<D, true>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -128,7 +131,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
     const int ns = (Nq + C::BM - 1) / C::BM;
     const int s_begin = CAUSAL ? (kt * C::BN) / C::BM : 0;
 
-    const SwzLane<D> lane_off(lane);  // offsets inside slot 0
+    const LaneOffsets lane_off(lane);  // offsets inside slot 0
     const int lane_stat = C::STAT0 + 16 * g;
 
     // global -> LDS slot, asynchronously (completion is awaited with wait_vmem_all + barrier)
@@ -143,27 +146,22 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
     };
 
     // LDS read offsets of the step whose scores are being formed (row reads, statistics) ...
-    int rowA[KS], statA;
+    LaneOffsets offA(lane_off);
+    int statA;
     // ... and of the step whose dV / dK are being accumulated (transposing reads)
-    int trC[2][DT];
+    LaneOffsets offC(lane_off);
     auto point_A = [&](int slot) {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) rowA[ks] = lane_off.row[ks] + slot * C::STAGE;
+      offA.point_rows(lane_off, slot * C::STAGE);
       statA = lane_stat + slot * C::STAT;
     };
-    auto point_C = [&](int slot) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) trC[h][dt] = lane_off.tr[h][dt] + slot * C::STAGE;
-    };
+    auto point_C = [&](int slot) { offC.point_tr(lane_off, slot * C::STAGE); };
 
     v8 fa[2][4];
     auto load_agroup = [&](int gi, int sub) {
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
-        fa[gi & 1][2 * e] = lds_read16<v8>(smem, rowA[2 * gi + e] + sub * 32 * C::ROWB);
-        fa[gi & 1][2 * e + 1] = lds_read16<v8>(smem + C::TILE, rowA[2 * gi + e] + sub * 32 * C::ROWB);
+        fa[gi & 1][2 * e] = lds_read16<v8>(smem, offA.row_at(2 * gi + e) + sub * 32 * C::ROWB);
+        fa[gi & 1][2 * e + 1] = lds_read16<v8>(smem + C::TILE, offA.row_at(2 * gi + e) + sub * 32 * C::ROWB);
       }
     };
     // statistics of 8 of the 16 query rows a lane holds (half = 0: registers 0..7, 1: 8..15) of the
@@ -214,8 +212,8 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
     auto load_thalf = [&](int tg, int sub, int e) {
       const int kk = tg / (DT / 2), dt0 = 2 * (tg % (DT / 2));
       const int o = sub * 32 * C::ROWB + kk * 16 * C::ROWB;
-      ft[tg & 1][2 * e] = read_tr_pair<T>(smem + C::TILE, trC[0][dt0 + e] + o, trC[1][dt0 + e] + o);
-      ft[tg & 1][2 * e + 1] = read_tr_pair<T>(smem, trC[0][dt0 + e] + o, trC[1][dt0 + e] + o);
+      ft[tg & 1][2 * e] = read_tr_pair<T>(smem + C::TILE, offC.tr_at(0, dt0 + e) + o, offC.tr_at(1, dt0 + e) + o);
+      ft[tg & 1][2 * e + 1] = read_tr_pair<T>(smem, offC.tr_at(0, dt0 + e) + o, offC.tr_at(1, dt0 + e) + o);
     };
 
     // One element of P and dS from finished scores: the unit of VALU work that is placed between
@@ -491,6 +489,10 @@ static __device__ __forceinline__ void bwd_dq(
   using C = BwdQCfg<D>;
   constexpr int KS = D / 16, DT = D / 32;
 
+  // few offset registers in the causal kernels, for the reason given in mha_fwd_kernel (dQ, us: fp16 with dropout,
+  // D = 128, 512 heads x 512 135 -> 121; bf16, D = 128, 256 x 512 55.7 -> 54.5; fp16, D = 64, 256 x 512 31.8 -> 31.4)
+  constexpr int LEAN = !CAUSAL ? 0 : (D == 128) == DROP ? 2 : 1;
+  using LaneOffsets = std::conditional_t<LEAN != 0, SwzLaneLean<D, LEAN == 2>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -538,7 +540,7 @@ static __device__ __forceinline__ void bwd_dq(
     }
     const int nt = (kv_end + C::BN - 1) / C::BN;
 
-    SwzLane<D> off(lane);  // read offsets of the current buffer; switched by one XOR each
+    LaneOffsets off(lane);  // read offsets of the current buffer
 
     f32x16 dq[DT];
 #pragma unroll
@@ -614,7 +616,7 @@ static __device__ __forceinline__ void bwd_dq(
           const int ks = i < KS ? i : i - KS;
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt)
-            fa[i % AHEAD][mt] = lds_read16<v8>(i < KS ? kb : vb, off.row[ks] + mt * 32 * C::ROWB);
+            fa[i % AHEAD][mt] = lds_read16<v8>(i < KS ? kb : vb, off.row_at(ks) + mt * 32 * C::ROWB);
         };
         // Dropout: dS = r P o (M o dPraw - D (1-p)); the workspace holds D (1-p) and the factor r
         // goes into the final scale of dQ.
@@ -651,7 +653,7 @@ static __device__ __forceinline__ void bwd_dq(
           const int o = kk * 16 * C::ROWB;
 #pragma unroll
           for (int dt = 0; dt < DT; ++dt)
-            ft[kk & 1][dt] = read_tr_pair<T>(kb, off.tr[0][dt] + o, off.tr[1][dt] + o);
+            ft[kk & 1][dt] = read_tr_pair<T>(kb, off.tr_at(0, dt) + o, off.tr_at(1, dt) + o);
         };
         constexpr int EPM = 16 / KS;  // P elements per MFMA of dP
 #pragma unroll
@@ -707,12 +709,7 @@ static __device__ __forceinline__ void bwd_dq(
           sched_fence();
         }
       }
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) off.row[ks] ^= C::STAGE;
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) off.tr[h][dt] ^= C::STAGE;
+      off.flip(C::STAGE);
       wait_vmem_all();  // the next tile has landed (requested at the top of the iteration)
       __syncthreads();
     };

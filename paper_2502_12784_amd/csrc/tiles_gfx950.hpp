@@ -93,6 +93,68 @@ template <int D> struct SwzLane {
         tr[h][dt] = bias + swz_off<D>(8 * h + 4 * g + (i16 >> 2), dt * 4 + ((c32 >> 4) << 1) + ((i16 & 3) >> 1)) +
                     (i16 & 1) * 8;
   }
+  __device__ __forceinline__ int row_at(int ks) const { return row[ks]; }
+  __device__ __forceinline__ int tr_at(int h, int dt) const { return tr[h][dt]; }
+  // offsets of `s` moved on by `bytes` (a multiple of a tile)
+  __device__ __forceinline__ void point_rows(const SwzLane& s, int bytes) {
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) row[ks] = s.row[ks] + bytes;
+  }
+  __device__ __forceinline__ void point_tr(const SwzLane& s, int bytes) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt) tr[h][dt] = s.tr[h][dt] + bytes;
+  }
+  __device__ __forceinline__ void flip(int bits) {  // to the other buffer: one exclusive or each
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) row[ks] ^= bits;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt) tr[h][dt] ^= bits;
+  }
+};
+
+// The same offsets from fewer registers, for kernels that have none to spare.  Swizzle and chunk index only meet in
+// exclusive ors (row: chunk 2 ks + g; tr: d-tile dt, and rows 8 h further on, whose swizzle differs in bit 1), so an
+// offset is a base with constant bits flipped: one VALU instruction at its use instead of one to switch the buffer.
+// The row offsets always come from one register; LEAN_TR: the transposing ones, too (they are used more often).
+template <int D, bool LEAN_TR> struct SwzLaneLean {
+  int row0, tr0[LEAN_TR ? 1 : 2][LEAN_TR ? 1 : D / 32];
+  __device__ __forceinline__ explicit SwzLaneLean(int lane) {
+    const SwzLane<D> s(lane);
+    row0 = s.row[0];
+#pragma unroll
+    for (int h = 0; h < (LEAN_TR ? 1 : 2); ++h)
+#pragma unroll
+      for (int dt = 0; dt < (LEAN_TR ? 1 : D / 32); ++dt) tr0[h][dt] = s.tr[h][dt];
+  }
+  __device__ __forceinline__ int row_at(int ks) const { return row0 ^ (ks << 5); }
+  __device__ __forceinline__ int tr_at(int h, int dt) const {
+    if constexpr (LEAN_TR) return (tr0[0][0] ^ (dt << 6) ^ (h << 5)) + h * 16 * D;
+    return tr0[LEAN_TR ? 0 : h][LEAN_TR ? 0 : dt];
+  }
+  __device__ __forceinline__ void point_rows(const SwzLaneLean& s, int bytes) {
+    row0 = s.row0 + bytes;
+    asm volatile("" : "+v"(row0));
+  }
+  __device__ __forceinline__ void point_tr(const SwzLaneLean& s, int bytes) {
+#pragma unroll
+    for (int h = 0; h < (LEAN_TR ? 1 : 2); ++h)
+#pragma unroll
+      for (int dt = 0; dt < (LEAN_TR ? 1 : D / 32); ++dt) tr0[h][dt] = s.tr0[h][dt] + bytes;
+    if (LEAN_TR) asm volatile("" : "+v"(tr0[0][0]));
+  }
+  __device__ __forceinline__ void flip(int bits) {
+    row0 ^= bits;
+    asm volatile("" : "+v"(row0));  // opaque: otherwise the offsets of both buffers are formed ahead of the loop
+#pragma unroll
+    for (int h = 0; h < (LEAN_TR ? 1 : 2); ++h)
+#pragma unroll
+      for (int dt = 0; dt < (LEAN_TR ? 1 : D / 32); ++dt) tr0[h][dt] ^= bits;
+    if (LEAN_TR) asm volatile("" : "+v"(tr0[0][0]));
+  }
 };
 
 template <typename T>
