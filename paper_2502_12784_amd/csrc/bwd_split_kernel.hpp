@@ -223,8 +223,7 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
       const int row = t * C::BM + c32;
       const bool valid = row < Nq;
       const T* op = Oh + (size_t)(valid ? row : 0) * (size_t)mo.row;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) of[ks] = load_row_chunk<v8>(op, ks * 16 + g * 8, valid ? dh : 0);
+      load_row_frags(of, op, g, dh, valid);
       lse = valid ? LSE[(size_t)head * Nq + row] : 0.f;
     };
 

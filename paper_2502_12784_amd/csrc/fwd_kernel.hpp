@@ -109,9 +109,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
     const int qrow_c = qrow < Nq ? qrow : Nq - 1;
 
     v8 qf[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      qf[ks] = load_row_chunk<v8>(Qh + (size_t)qrow_c * (size_t)mq.row, ks * 16 + g * 8, dh);
+    load_row_frags(qf, Qh + (size_t)qrow_c * (size_t)mq.row, g, dh);
 
     int kv_end = Nk;
     if (CAUSAL) {

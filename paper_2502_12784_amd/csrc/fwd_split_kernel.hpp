@@ -102,8 +102,7 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
     if (CAUSAL && (q0 + 1) / C::BN < n_plain) n_plain = (q0 + 1) / C::BN;
 
     v8 qf[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = load_row_chunk<v8>(qp, ks * 16 + g * 8, dh);
+    load_row_frags(qf, qp, g, dh);
 
     f32x16 o[DT];
 #pragma unroll

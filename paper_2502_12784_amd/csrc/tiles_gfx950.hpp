@@ -43,6 +43,20 @@ static __device__ __forceinline__ V8 load_row_chunk(const T* row, int col, int d
   return col < dh ? *reinterpret_cast<const V8*>(row + col) : z;
 }
 
+// The row a lane holds as N fragments over d (half g of every 16 columns); zeros if not `valid`.  A head dimension that
+// fills the tile takes the loads without the test of every chunk, a mask and a branch each (us, causal, d = 128, 256
+// heads x 512: forward 32.7 -> 30.2, dQ 48.8 -> 46.8).
+template <typename V8, typename T, int N>
+static __device__ __forceinline__ void load_row_frags(V8 (&f)[N], const T* row, int g, int dh, bool valid = true) {
+  if (dh == 16 * N && __all(valid)) {
+#pragma unroll
+    for (int ks = 0; ks < N; ++ks) f[ks] = *reinterpret_cast<const V8*>(row + ks * 16 + g * 8);
+  } else {
+#pragma unroll
+    for (int ks = 0; ks < N; ++ks) f[ks] = load_row_chunk<V8>(row, ks * 16 + g * 8, valid ? dh : 0);
+  }
+}
+
 // Work items per head for a kernel that walks `tiles` tiles: causal kernels pair tile p with
 // tile tiles-1-p.
 template <bool CAUSAL>
