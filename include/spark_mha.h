@@ -25,9 +25,9 @@
  *     fp32.  Pointers must be 16-byte aligned.  Inputs and outputs must not
  *     alias each other.
  *   - Supported: d a multiple of 8 with 8 <= d <= 128 (the paper's own sizes are 64 and 128,
- *     Sec. 4.1; the kernels are built for rows of 64 and of 128 elements, and a smaller d runs in
- *     the next wider one with the missing columns read as zeros, so d = 96 costs what d = 128
- *     costs); any N >= 1; B, H >= 1; scale finite and > 0; causal is a flag (0 = all keys,
+ *     Sec. 4.1; the kernels are built for rows of 64, 96 and 128 elements, those for small grids
+ *     for 64 and 128, and a smaller d runs in the next wider one with the missing columns read
+ *     as zeros, so d = 72 costs what d = 96 costs); any N >= 1; B, H >= 1; scale finite and > 0; causal is a flag (0 = all keys,
  *     nonzero = masked).  Size limits: B*H*ceil(N/64) < 2^31 and (N + 256)*d*2 < 2^31.  Anything
  *     else returns SPARK_ERR_SHAPE; nothing is silently mis-computed.
  *   - causal != 0: query i attends to keys j <= i (Sec. 2.1, masked MHA).

@@ -54,11 +54,11 @@ namespace spark {
 // ---------------------------------------------------------------------------------------
 template <int D> struct BwdKvPipeCfg {
   static constexpr int BN = 128, BM = 64, SLOTS = 3;
-  static constexpr int ROWB = D * 2;
+  static constexpr int ROWB = lds_row<D> * 2;
   static constexpr int TILE = BM * ROWB;
   static constexpr int STAGE = 2 * TILE;
   static constexpr int STAT = 2 * BM * 4;  // LSE*log2(e) and D of the stage's rows
-  static constexpr int OSTR = D * 2 + 16;
+  static constexpr int OSTR = lds_row<D> * 2 + 16;
   static constexpr int STAT0 = SLOTS * STAGE;  // LDS = [slot 0..2 | stat 0..2]
   static constexpr int SMEM = SLOTS * STAGE + SLOTS * STAT;
   static_assert(4 * 32 * OSTR <= SLOTS * STAGE, "epilogue staging must fit");
@@ -201,16 +201,15 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       return c;
     };
     constexpr int NG = KS / 2;
-    constexpr int NTG = 2 * (DT / 2);
-    constexpr int E1 = 8 / (2 * NG);  // softmax elements per pair of score MFMAs in region 1
+    constexpr int NTG = DT;  // the 2 DT pairs of operands (one dO^T, one Q^T) of dV and dK, two to a group
     v8 ft[2][4];
-    // half e of transposed-fragment group tg (one dO^T and one Q^T operand: four reads); issued in
-    // halves so that no MFMA slot carries more than a few LDS reads
+    // half e of transposed-fragment group tg (one pair of operands: four reads); issued in halves so that no
+    // MFMA slot carries more than a few LDS reads
     auto load_thalf = [&](int tg, int sub, int e) {
-      const int kk = tg / (DT / 2), dt0 = 2 * (tg % (DT / 2));
+      const int kk = (2 * tg + e) / DT, dt = (2 * tg + e) % DT;
       const int o = sub * 32 * C::ROWB + kk * 16 * C::ROWB;
-      ft[tg & 1][2 * e] = read_tr_pair<T>(smem + C::TILE, offC.tr_at(0, dt0 + e) + o, offC.tr_at(1, dt0 + e) + o);
-      ft[tg & 1][2 * e + 1] = read_tr_pair<T>(smem, offC.tr_at(0, dt0 + e) + o, offC.tr_at(1, dt0 + e) + o);
+      ft[tg & 1][2 * e] = read_tr_pair<T>(smem + C::TILE, offC.tr_at(0, dt) + o, offC.tr_at(1, dt) + o);
+      ft[tg & 1][2 * e + 1] = read_tr_pair<T>(smem, offC.tr_at(0, dt) + o, offC.tr_at(1, dt) + o);
     };
 
     // One element of P and dS from finished scores: the unit of VALU work that is placed between
@@ -273,11 +272,11 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       if (gi + 2 < NG) load_agroup(gi + 2, 0);
       sched_fence();
     }
-    // At D = 128 every step requests the first two fragment groups of its successor half-way through
+    // At D > 64 every step requests the first two fragment groups of its successor half-way through
     // its own dV / dK region, so that no step starts by waiting for LDS (C4 backward -3 %); here
     // those of step (s_begin, 1).  At D = 64 the longer live ranges cost spills (+1 ... +3 %) and the
     // request stays at the start of the step that uses it.
-    constexpr bool EARLY = D == 128;
+    constexpr bool EARLY = D > 64;
     if (EARLY) {
       load_agroup(0, 1);
       load_agroup(1, 1);
@@ -342,8 +341,8 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
           if (i == 2 * NG + 1) load_thalf(1, sub_cur, 1);
           if (i & 1) {
 #pragma unroll
-            for (int x = 0; x < E1; ++x)
-              softmax_elem(s_cur, dp_cur, 1, (i / 2) * E1 + x, RING ? lL : lH, RING ? dL : dH, ahead_cur, mask, kbCur, p, ds,
+            for (int x = (i / 2) * 4 / NG; x < (i / 2 + 1) * 4 / NG; ++x)  // 8 elements in 2 NG slots
+              softmax_elem(s_cur, dp_cur, 1, x, RING ? lL : lH, RING ? dL : dH, ahead_cur, mask, kbCur, p, ds,
                            pk_p, pk_ds);
             if (RING && (i & 3) == 3) load_quad(lL, dL, sub_new, i / 4);  // first half of the next step
           }
@@ -361,22 +360,27 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
         // ---- region 2: dV, dK of the current step  ||  first half of P, dS of the next step ----
 #pragma unroll
         for (int tg = 0; tg < NTG; ++tg) {
-          const int kk = tg / (DT / 2), dt0 = 2 * (tg % (DT / 2));
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
-            dv[dt0 + e] = F::mfma(ft[tg & 1][2 * e], kk ? pfH : pfL, dv[dt0 + e]);
-            dk[dt0 + e] = F::mfma(ft[tg & 1][2 * e + 1], kk ? dsfH : dsfL, dk[dt0 + e]);
-            softmax_elem(s_new, dp_new, 0, (8 / NTG) * tg + e, lL, dL, ahead_new, mask, kbNew, p, ds, pk_p, pk_ds);
-            if (8 / NTG > 2)
-              softmax_elem(s_new, dp_new, 0, (8 / NTG) * tg + 2 + e, lL, dL, ahead_new, mask, kbNew, p, ds, pk_p, pk_ds);
+            const int slot = 2 * tg + e, kk = slot / DT, dt = slot % DT;
+            dv[dt] = F::mfma(ft[tg & 1][2 * e], kk ? pfH : pfL, dv[dt]);
+            dk[dt] = F::mfma(ft[tg & 1][2 * e + 1], kk ? dsfH : dsfL, dk[dt]);
+            if (NTG == 2) {  // two elements a slot, of different pairs
+              softmax_elem(s_new, dp_new, 0, 4 * tg + e, lL, dL, ahead_new, mask, kbNew, p, ds, pk_p, pk_ds);
+              softmax_elem(s_new, dp_new, 0, 4 * tg + 2 + e, lL, dL, ahead_new, mask, kbNew, p, ds, pk_p, pk_ds);
+            } else {
+#pragma unroll
+              for (int x = slot * 4 / NTG; x < (slot + 1) * 4 / NTG; ++x)
+                softmax_elem(s_new, dp_new, 0, x, lL, dL, ahead_new, mask, kbNew, p, ds, pk_p, pk_ds);
+            }
             if (tg + 2 < NTG) load_thalf(tg + 2, sub_cur, e);  // into the operands just used
             sched_fence();
           }
           if (RING) load_quad(lL, dL, sub_new, 2 + tg);  // second half of the next step
           // the fragment buffers are free since region 1 ended; one group per slot keeps the number
           // of LDS reads in flight under the 15 the wave's counter can track
-          if (EARLY && tg == NTG / 2 - 1) request_next(0);
-          if (EARLY && tg == NTG / 2) request_next(1);
+          if (EARLY && tg == (NTG - 1) / 2) request_next(0);
+          if (EARLY && tg == (NTG + 1) / 2) request_next(1);
           sched_fence();
         }
         pfL = join_pairs<T>(pk_p);
@@ -457,15 +461,16 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void mha_bwd_dkdv_pipe_kernel
 // ---------------------------------------------------------------------------------------
 // dQ
 // ---------------------------------------------------------------------------------------
-template <int D> struct BwdQCfg {
+template <int D, bool CAUSAL, bool DROP> struct BwdQCfg {
   static constexpr int BM = 128;  // query rows per workgroup (32 per wave)
   // keys per iteration: 32 at D = 128 keeps the kernel within 256 registers, so that two
-  // workgroups share a CU and one hides the other's softmax arithmetic and LDS latency
-  static constexpr int BN = D == 128 ? 32 : 64;
-  static constexpr int ROWB = D * 2;
+  // workgroups share a CU and one hides the other's softmax arithmetic and LDS latency.  At D = 96 (dQ, us, 32 -> 64
+  // keys, causal 36 heads x 1333 40.9 -> 36.8, 64 x 4096 309 -> 297) only the causal kernel with dropout spills.
+  static constexpr int BN = D == 128 || (D == 96 && CAUSAL && DROP) ? 32 : 64;
+  static constexpr int ROWB = lds_row<D> * 2;
   static constexpr int TILE = BN * ROWB;  // one of K, V (swizzled, unpadded)
   static constexpr int STAGE = 2 * TILE;  // power of two: the buffer is switched by one XOR
-  static constexpr int OSTR = D * 2 + 16;
+  static constexpr int OSTR = lds_row<D> * 2 + 16;
   static constexpr int SMEM = 2 * STAGE > 4 * 32 * OSTR ? 2 * STAGE : 4 * 32 * OSTR;  // tiles / epilogue
   static_assert((STAGE & (STAGE - 1)) == 0, "XOR buffer switch");
 };
@@ -483,12 +488,12 @@ static __device__ __forceinline__ void bwd_dq(
     int item) {
   using F = Frag<T>;
   using v8 = typename F::v8;
-  using C = BwdQCfg<D>;
+  using C = BwdQCfg<D, CAUSAL, DROP>;
   constexpr int KS = D / 16, DT = D / 32;
 
   // few offset registers in the causal kernels, for the reason given in mha_fwd_kernel (dQ, us: fp16 with dropout,
   // D = 128, 512 heads x 512 135 -> 121; bf16, D = 128, 256 x 512 55.7 -> 54.5; fp16, D = 64, 256 x 512 31.8 -> 31.4)
-  constexpr int LEAN = !CAUSAL ? 0 : (D == 128) == DROP ? 2 : 1;
+  constexpr int LEAN = !CAUSAL ? 0 : (D > 64) == DROP ? 2 : 1;
   using LaneOffsets = std::conditional_t<LEAN != 0, SwzLaneLean<D, LEAN == 2>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
 
@@ -652,14 +657,13 @@ static __device__ __forceinline__ void bwd_dq(
           for (int dt = 0; dt < DT; ++dt)
             ft[kk & 1][dt] = read_tr_pair<T>(kb, off.tr_at(0, dt) + o, off.tr_at(1, dt) + o);
         };
-        constexpr int EPM = 16 / KS;  // P elements per MFMA of dP
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt) {
             dp[mt] = F::mfma(fa[(KS + ks) % AHEAD][mt], dof[ks], dp[mt]);
 #pragma unroll
-            for (int x = 0; x < EPM; ++x) p_elem(mt * 16 + ks * EPM + x);
+            for (int x = ks * 16 / KS; x < (ks + 1) * 16 / KS; ++x) p_elem(mt * 16 + x);  // 16 in KS MFMAs
             sched_fence();
           }
           if (KS + ks + AHEAD < 2 * KS) load_step(KS + ks + AHEAD);
@@ -694,7 +698,7 @@ static __device__ __forceinline__ void bwd_dq(
             dq[dt] = F::mfma(ft[kk & 1][dt], dsf[kk], dq[dt]);
             if (kk + 1 < NKK) {
 #pragma unroll
-              for (int x = 0; x < 8 / DT; ++x) ds_elem(8 * (kk + 1) + dt * (8 / DT) + x);
+              for (int x = dt * 8 / DT; x < (dt + 1) * 8 / DT; ++x) ds_elem(8 * (kk + 1) + x);
             }
             sched_fence();
           }
@@ -753,7 +757,7 @@ __global__ __launch_bounds__(256) void mha_bwd_stats_kernel(const T* __restrict_
                                                             float* __restrict__ LSE2ws, TensorMap mo, TensorMap mdo,
                                                             int H, int Nq, int dh, int rows, float keep_prob) {
   using v8 = typename Frag<T>::v8;
-  constexpr int LPR = D / 8;
+  constexpr int LPR = lds_row<D> / 8;
   const int row = blockIdx.x * (256 / LPR) + threadIdx.x / LPR;  // flat (head, query) index
   const int col = (threadIdx.x % LPR) * 8;
   const bool live = row < rows;
@@ -773,7 +777,8 @@ __global__ __launch_bounds__(256) void mha_bwd_stats_kernel(const T* __restrict_
 }
 
 template <int D> struct BwdMergedCfg {
-  static constexpr int SMEM = BwdKvPipeCfg<D>::SMEM > BwdQCfg<D>::SMEM ? BwdKvPipeCfg<D>::SMEM : BwdQCfg<D>::SMEM;
+  static constexpr int SMEM = BwdKvPipeCfg<D>::SMEM;
+  static_assert(SMEM >= BwdQCfg<D, false, false>::SMEM, "the dK/dV side needs more, whatever the other's tile");
 };
 
 template <typename T, int D, bool CAUSAL, bool DROP>

@@ -44,10 +44,10 @@ namespace spark {
 template <int D, int NW = 4, bool PAIR = false> struct FwdCfg {
   static constexpr int BM = 32 * NW;  // query rows per workgroup (32 per wave)
   static constexpr int BN = 64;   // keys per iteration
-  static constexpr int ROWB = D * 2;      // bytes per (swizzled, unpadded) row
+  static constexpr int ROWB = lds_row<D> * 2;  // bytes per (swizzled, unpadded) row
   static constexpr int TILE = BN * ROWB;  // one of K, V
   static constexpr int STAGE = 2 * TILE;  // power of two: the buffer is switched by one XOR
-  static constexpr int OSTR = D * 2 + 16;  // epilogue staging row stride
+  static constexpr int OSTR = lds_row<D> * 2 + 16;  // epilogue staging row stride
   static constexpr int SLOTS = PAIR ? 4 : 2;  // tiles resident or in flight
   static constexpr int SMEM = SLOTS * STAGE > NW * 32 * OSTR ? SLOTS * STAGE : NW * 32 * OSTR;  // tiles / epilogue
   static_assert((STAGE & (STAGE - 1)) == 0, "XOR buffer switch");
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
   using C = FwdCfg<D, NW, PAIR>;
   constexpr int KS = D / 16;   // k-steps of the score contraction
   constexpr int DT = D / 32;   // 32-row tiles of O^T
-  constexpr int CPR = D / 8;   // 16-byte chunks per row
+  constexpr int CPR = lds_row<D> / 8;  // 16-byte chunks per row of a tile
 
   // Causal kernels hold their read offsets in few registers.  At D = 128 they otherwise spill some of them, and the
   // reload in front of the loop makes the compiler wait, inside it, for every outstanding vector memory
@@ -185,12 +185,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
           for (int r = 0; r < 16; ++r) s[mt][r] = 0.f;
-        constexpr int GPH = KS / 4;  // groups of 4 k-steps per half
-        v8 kf[2][4];
+        constexpr int GK = KS % 4 == 0 ? 4 : 3, GPH = KS / GK;  // groups of GK k-steps per half
+        v8 kf[2][GK];
         auto load_kgroup = [&](int gi) {  // gi = half * GPH + group
-          const int half = gi / GPH, ks0 = 4 * (gi % GPH);
+          const int half = gi / GPH, ks0 = GK * (gi % GPH);
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
+          for (int e = 0; e < GK; ++e)
             kf[gi & 1][e] = lds_read16<v8>(kb, off.row_at(ks0 + e) + half * 32 * C::ROWB);
         };
         v8 vf[2][DT];
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
 #pragma unroll
         for (int gi = 0; gi < GPH; ++gi) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) s[0] = F::mfma(kf[gi & 1][e], qf[4 * gi + e], s[0]);
+          for (int e = 0; e < GK; ++e) s[0] = F::mfma(kf[gi & 1][e], qf[GK * gi + e], s[0]);
           if (gi + 2 < 2 * GPH) load_kgroup(gi + 2);
           sched_fence();
         }
@@ -276,14 +276,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
 
         load_half(0);
         // ---- S_1  ||  exponentials of half 0 ----
-        constexpr int EPU = 16 / KS;  // elements per MFMA
 #pragma unroll
         for (int gi = GPH; gi < 2 * GPH; ++gi) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            s[1] = F::mfma(kf[gi & 1][e], qf[4 * (gi - GPH) + e], s[1]);
+          for (int e = 0; e < GK; ++e) {
+            const int i = (gi - GPH) * GK + e;  // KS MFMAs share the 16 elements
+            s[1] = F::mfma(kf[gi & 1][e], qf[i], s[1]);
 #pragma unroll
-            for (int x = 0; x < EPU; ++x) exp_elem(((gi - GPH) * 4 + e) * EPU + x, rs0);
+            for (int x = i * 16 / KS; x < (i + 1) * 16 / KS; ++x) exp_elem(x, rs0);
             sched_fence();
           }
           if (gi + 2 < 2 * GPH) load_kgroup(gi + 2);
@@ -303,14 +303,13 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
         pf[1] = pack8<T>(&t[8]);
         sched_fence();
         // ---- O^T += V_0^T P_0^T  ||  exponentials of half 1 ----
-        constexpr int EPV = 16 / (2 * DT);  // elements per MFMA
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
           for (int dt = 0; dt < DT; ++dt) {
             o[dt] = F::mfma(vf[kk & 1][dt], pf[kk], o[dt]);
 #pragma unroll
-            for (int x = 0; x < EPV; ++x) exp_elem(16 + (kk * DT + dt) * EPV + x, rs1);
+            for (int x = (kk * DT + dt) * 8 / DT; x < (kk * DT + dt + 1) * 8 / DT; ++x) exp_elem(16 + x, rs1);
             sched_fence();
           }
           load_vgroup(kk + 2);

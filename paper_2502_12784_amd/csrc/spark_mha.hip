@@ -208,7 +208,7 @@ int launch_fwd_nw(const Problem& p, const void* Q, const void* K, const void* V,
   // past it, and only here (d = 128, paired / unpaired us: 188 x 384 27.1 / 25.6, 200 x 300 23.6 / 24.4, 233 x 270
   // 24.1 / 26.0, 257 x 306 34.6 / 25.7; with dropout 228 x 384 35.3 / 34.8; at d = 64 three workgroups fit, and dQ
   // gains unpaired: 244 heads 0.9 of it).
-  const bool one_round = D == 128 && !DROP && nqt == 3 && BH > 192 && BH <= 256;
+  const bool one_round = D > 64 && !DROP && nqt == 3 && BH > 192 && BH <= 256;
   const int paired = CAUSAL && one_round ? 1 : pair_tiles(CAUSAL, BH, nqt, NW == 4 ? 2 : 1);
   hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * (paired ? causal_items<true>(nqt) : nqt))), dim3(64 * NW), C::SMEM,
                      p.st, static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
@@ -329,10 +329,10 @@ template <typename T, int D, bool CAUSAL, bool DROP>
 int launch_fwd(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* LSE) {
   if constexpr (!CAUSAL) {
     const int parts = p.fwd_ws ? fwd_parts(p) : 1;
-    if (parts > 1) return launch_fwd_parts<T, D, DROP>(p, Q, K, V, O, LSE, parts);
+    if (parts > 1) return launch_fwd_parts<T, lds_row<D>, DROP>(p, Q, K, V, O, LSE, parts);
   }
-  if (split_forward<CAUSAL>(p)) return launch_fwd_split<T, D, CAUSAL, DROP>(p, Q, K, V, O, LSE);
-  if constexpr (D == 128) {
+  if (split_forward<CAUSAL>(p)) return launch_fwd_split<T, lds_row<D>, CAUSAL, DROP>(p, Q, K, V, O, LSE);
+  if constexpr (D > 64) {
     // ... with the K/V tiles requested two at a time and one barrier every second iteration (the
     // workgroup has the CU's LDS to itself): another -1 ... -3 % on the forward.
     if (wide_workgroups<CAUSAL>(p)) return launch_fwd_nw<T, D, CAUSAL, DROP, 8, true>(p, Q, K, V, O, LSE);
@@ -423,7 +423,7 @@ int launch_bwd_merged(const Problem& p, const void* Q, const void* K, const void
   const int BH = p.B * p.H, rows = BH * p.Nq;
   const Dropout dr = make_dropout(p.thr, p.seed, p.offset);
   float* LSE2ws = Dws + (size_t)rows;
-  constexpr int RPB = 256 * 8 / D;  // rows per workgroup of the statistics kernel
+  constexpr int RPB = 256 * 8 / lds_row<D>;  // rows per workgroup of the statistics kernel
   hipLaunchKernelGGL((mha_bwd_stats_kernel<T, D>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(256), 0, p.st,
                      static_cast<const T*>(O), static_cast<const T*>(dO), LSE, Dws, LSE2ws, p.mo, p.mdo, p.H, p.Nq,
                      p.d, rows, DROP ? dr.keep_prob : 1.0f);
@@ -457,7 +457,7 @@ int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, co
 
   if (!mark(0)) return SPARK_ERR_LAUNCH;
   if (split_backward(p)) {  // one kernel: both later marks follow it
-    const int rc = launch_bwd_split<T, D, CAUSAL, DROP>(p, Q, K, V, O, LSE, dO, dQ, dK, dV);
+    const int rc = launch_bwd_split<T, lds_row<D>, CAUSAL, DROP>(p, Q, K, V, O, LSE, dO, dQ, dK, dV);
     if (rc != SPARK_OK) return rc;
     return mark(1) && mark(2) ? SPARK_OK : SPARK_ERR_LAUNCH;
   }
@@ -469,7 +469,7 @@ int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, co
   }
   {  // dQ: one workgroup per tile of 128 queries (8-wave workgroups measured 3 % slower here).
      // Also writes D = rowsum(dO o O) and LSE * log2(e) for the dK/dV kernel.
-    using C = BwdQCfg<D>;
+    using C = BwdQCfg<D, CAUSAL, DROP>;
     auto kernel = mha_bwd_dq_kernel<T, D, CAUSAL, DROP>;
     static std::atomic<uint64_t> ready{0};
     const int attr = ensure_smem(kernel, C::SMEM, ready);
@@ -542,13 +542,20 @@ int launch_bwd_atomic(const Problem& p, const void* Q, const void* K, const void
                                : FN<T, D, true, false>(__VA_ARGS__);                        \
     return p.thr ? FN<T, D, false, true>(__VA_ARGS__) : FN<T, D, false, false>(__VA_ARGS__); \
   } while (0)
+// The row width a kernel is built for: 64, 96 or 128.  From d = 72 to 96 the kernels of 96 columns leave out a quarter of
+// the products and of the accumulators of the 128-column ones; rows in LDS keep 256 bytes in both, a power of two for the
+// swizzle, and the kernels for small grids exist for 64 and 128 only.  Forward / dQ / dK/dV, us, 128 -> 96 columns:
+//   d = 96 causal 64 x 4096 238/352/514 -> 209/296/454      88, 64 x 1024 over 4096 keys 113/167/258 -> 98/145/229
+//   d = 80, 36 x 1333 32.5/44.9/48.2 -> 29.3/36.8/43.3      72, causal with dropout, 256 x 512 32.4/43.2/67.7 -> 30.3/40.4/62.6
 #define SPARK_DISPATCH(FN, ...)                                              \
   do {                                                                       \
     if (p.dtype == SPARK_F16) {                                              \
       if (p.d <= 64) SPARK_DISPATCH_CD(FN, _Float16, 64, __VA_ARGS__);       \
+      if (p.d <= 96) SPARK_DISPATCH_CD(FN, _Float16, 96, __VA_ARGS__);       \
       SPARK_DISPATCH_CD(FN, _Float16, 128, __VA_ARGS__);                     \
     }                                                                        \
     if (p.d <= 64) SPARK_DISPATCH_CD(FN, __bf16, 64, __VA_ARGS__);           \
+    if (p.d <= 96) SPARK_DISPATCH_CD(FN, __bf16, 96, __VA_ARGS__);           \
     SPARK_DISPATCH_CD(FN, __bf16, 128, __VA_ARGS__);                         \
   } while (0)
 

@@ -32,8 +32,8 @@ static __device__ __forceinline__ uint32_t head_span_bytes(const TensorMap& m, i
 }
 
 // Head dimensions below the tile width.  The kernels are compiled for rows of D = 64 or 128
-// elements; a head dimension dh < D (a multiple of 8) runs in the next wider one with the columns
-// dh..D-1 of every operand read as zeros (they add nothing to any contraction) and never stored.
+// elements, the larger ones also for 96; a head dimension dh < D (a multiple of 8) runs in the next wider one with
+// the columns dh..D-1 of every operand read as zeros (they add nothing to any contraction) and never stored.
 // A fragment load of 8 elements starting at column `col`:
 template <typename V8, typename T>
 static __device__ __forceinline__ V8 load_row_chunk(const T* row, int col, int dh) {
@@ -76,15 +76,18 @@ static __host__ __device__ __forceinline__ int causal_items(int tiles) {
 // on r mod 16 only, so per-lane offsets are computed once and every tile / sub-tile / k-step
 // displacement is an immediate.
 // ---------------------------------------------------------------------------------------
+// Tiles of D = 96 have the rows of D = 128 (twelve chunks do not fit the scheme); columns 96 to 127 are never read.
+template <int D> constexpr int lds_row = D == 96 ? 128 : D;  // elements
+
 template <int D>
 static __device__ __forceinline__ int swz(int row) {
-  if (D == 128) return ((row & 3) << 2) | ((row >> 2) & 3);
+  if (lds_row<D> == 128) return ((row & 3) << 2) | ((row >> 2) & 3);
   const int x = (row >> 1) & 7;
   return ((x & 1) << 2) | ((x >> 1) & 3);
 }
 template <int D>
 static __device__ __forceinline__ int swz_off(int row, int chunk) {
-  return row * (2 * D) + ((chunk ^ swz<D>(row)) << 4);
+  return row * (2 * lds_row<D>) + ((chunk ^ swz<D>(row)) << 4);
 }
 
 // Per-lane byte offsets into a swizzled tile.
@@ -146,7 +149,7 @@ template <int D, bool LEAN_TR> struct SwzLaneLean {
   }
   __device__ __forceinline__ int row_at(int ks) const { return row0 ^ (ks << 5); }
   __device__ __forceinline__ int tr_at(int h, int dt) const {
-    if constexpr (LEAN_TR) return (tr0[0][0] ^ (dt << 6) ^ (h << 5)) + h * 16 * D;
+    if constexpr (LEAN_TR) return (tr0[0][0] ^ (dt << 6) ^ (h << 5)) + h * 16 * lds_row<D>;
     return tr0[LEAN_TR ? 0 : h][LEAN_TR ? 0 : dt];
   }
   __device__ __forceinline__ void point_rows(const SwzLaneLean& s, int bytes) {
@@ -192,17 +195,17 @@ static __device__ __forceinline__ typename Frag<T>::v8 read_tr_pair(SPARK_LDS co
 template <int D>
 static __device__ __forceinline__ uint32_t dma_lane_src(int wave, int lane, uint32_t row_bytes, int dh) {
   const int byte = wave * 1024 + lane * 16;
-  const int row = byte / (2 * D), pc = (byte % (2 * D)) >> 4;
+  const int row = byte / (2 * lds_row<D>), pc = (byte % (2 * lds_row<D>)) >> 4;
   const int chunk = pc ^ swz<D>(row);
   return chunk * 8 < dh ? (uint32_t)row * row_bytes + (uint32_t)(chunk << 4) : 0x80000000u;
 }
 template <int D, int ROWS>
 static __device__ __forceinline__ void tile_dma(const BufView& view, int r0, SPARK_LDS char* dst,
                                                 int wave, uint32_t lane_src, uint32_t row_bytes) {
-  constexpr int RPG = 4 * 1024 / (2 * D);  // rows covered by one 1 KB block of each of the 4 waves
+  constexpr int RPG = 4 * 1024 / (2 * lds_row<D>);  // rows covered by one 1 KB block of each of the 4 waves
   static_assert(RPG % 16 == 0, "blocks of one wave must be 16 rows apart");
 #pragma unroll
-  for (int i = 0; i < ROWS * 2 * D / 4096; ++i)
+  for (int i = 0; i < ROWS * 2 * lds_row<D> / 4096; ++i)
     view.load16_to_lds(dst + (i * 4 + wave) * 1024, lane_src, (uint32_t)(r0 + i * RPG) * row_bytes);
 }
 
@@ -231,7 +234,7 @@ static __device__ __forceinline__ void store_transposed(const f32x16 (&acc)[D / 
                                                         SPARK_LDS char* ob, T* __restrict__ out,
                                                         int row0, int N, int lane, size_t row_stride, int dh) {
   using v4 = typename Frag<T>::v4;
-  constexpr int CPR = D / 8;
+  constexpr int CPR = lds_row<D> / 8;
   constexpr int RPP = 64 / CPR;
   const int g = lane >> 5, c32 = lane & 31;
 #pragma unroll
