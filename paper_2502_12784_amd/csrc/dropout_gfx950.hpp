@@ -90,16 +90,23 @@ static __device__ __forceinline__ void quad_transpose(uint32_t (&x)[4], int w) {
 // `qrow` (qrow mod 4 == lane mod 4) and it holds keys kblk + 8a + 4g + b of the 32-key block
 // starting at kblk (a multiple of 32), g = lane / 32.  kb[a] receives the four decision bytes of
 // strip a: byte b belongs to accumulator register 4a + b.
+// In three parts (counter, ten rounds of philox_round, exchange), see keep_key_lane_begin.
+static __device__ __forceinline__ Philox keep_query_lane_begin(const Dropout& dr, int head, int qrow, int kblk,
+                                                               int lane) {
+  const int w = lane & 3, g = lane >> 5;  // this lane evaluates the call of strip a = w
+  return Philox{(uint32_t)((kblk >> 2) + 2 * w + g), (uint32_t)(qrow >> 2), (uint32_t)head, dr.offset};
+}
+static __device__ __forceinline__ void keep_query_lane_finish(const Philox& s, int lane, uint32_t (&kb)[4]) {
+  // strip a needs word (query mod 4) = w of the call that lane a of the quad evaluated
+  kb[0] = s.c0; kb[1] = s.c1; kb[2] = s.c2; kb[3] = s.c3;
+  quad_transpose(kb, lane & 3);
+}
 static __device__ __forceinline__ void keep_bytes_query_lane(const Dropout& dr, int head, int qrow,
                                                              int kblk, int lane, uint32_t (&kb)[4]) {
-  const int w = lane & 3, g = lane >> 5;
-  uint32_t x[4];
-  philox4x32_10((uint32_t)((kblk >> 2) + 2 * w + g), (uint32_t)(qrow >> 2), (uint32_t)head, dr.offset,
-                dr.key0, dr.key1, x);  // this lane evaluates the call of strip a = w
-  // strip a needs word (query mod 4) = w of the call that lane a of the quad evaluated
-  quad_transpose(x, w);
+  Philox s = keep_query_lane_begin(dr, head, qrow, kblk, lane);
 #pragma unroll
-  for (int a = 0; a < 4; ++a) kb[a] = x[a];
+  for (int round = 0; round < 10; ++round) philox_round(s, dr.key0, dr.key1, round);
+  keep_query_lane_finish(s, lane, kb);
 }
 
 // Lane = key column (S layouts of the dK/dV kernel).  The lane's key is `krow`

@@ -17,18 +17,23 @@
 //     operand comes from the row-major V tile in LDS through transposing LDS reads.  P never
 //     touches LDS or HBM (the paper's Sec. 3.2.2 layout transform becomes register renaming).
 //   * K/V tiles are double-buffered in LDS and arrive there by direct global->LDS loads (no
-//     staging registers, no LDS store instructions); tile j+1 is requested before the
-//     arithmetic of tile j and awaited before the one barrier that ends the iteration.
+//     staging registers, no LDS store instructions), requested at the top of the round before the one
+//     that reads them and awaited before the one barrier that ends a round.
 //   * The tiles are unpadded and XOR-swizzled (tiles_gfx950.hpp) so that the 16-byte row reads
 //     of K and the 4-row transposing reads of V both spread over all banks.
-//   * Each 64-key tile runs as two 32-key online-softmax steps whose VALU work is interleaved,
-//     in program order, with the MFMAs of the other half (a wave issues in order); LDS operand
-//     reads are issued several MFMAs ahead and pinned there with scheduler fences.
+//   * Each 64-key tile runs as two 32-key online-softmax steps.  V runs one tile behind K, so that the VALU work of
+//     every step is interleaved, in program order (a wave issues in order), with the score MFMAs of
+//     the step after it and the PV MFMAs of the step before it; LDS operand reads are issued
+//     several MFMAs ahead and pinned there with scheduler fences.  (Within one tile the first scores and the last
+//     products had no VALU work beside them.  Forward, us, that -> this: bf16, d = 128, 64 heads x 1024 over
+//     4096 keys 133.8 -> 128.1, causal 64 x 4096 256.6 -> 251.2; fp16, causal 16 x 16384 1006 -> 984, d = 64 32 x
+//     8192 597 -> 590.  The loops run at 50 ... 60 % of the matrix cores' rate, at a clock that the power limit
+//     holds at 1.75 ... 2.0 of 2.4 GHz.)
 //   * Workgroups of 4 waves (128 queries, two per CU) or of 8 waves (256 queries, one per CU):
 //     with 8 waves each K/V tile that is brought into LDS serves twice as many MFMAs (measured
 //     -4 % at d = 128 on long sequences, +2 % at d = 64); the host picks per problem.  The 8-wave
 //     form has the CU's LDS to itself: it holds two stages of two tiles each, requests tiles two
-//     at a time and meets at a barrier every second iteration only (PAIR).
+//     at a time and meets at a barrier every second round only (PAIR; at d = 64 that is equal to 4 % slower).
 //   * Causal: the loop ends at the diagonal, only diagonal tiles are masked, waves skip tiles
 //     wholly above their rows, and a workgroup takes the complementary pair of query tiles
 //     (nqt-1-p, p) so every workgroup carries the same amount of work.
@@ -40,7 +45,7 @@
 namespace spark {
 
 // PAIR: the K/V buffers hold two stages of TWO 64-key tiles each instead of two single tiles: tiles
-// are requested two at a time and the workgroup meets at a barrier every second iteration only.
+// are requested two at a time and the workgroup meets at a barrier every second round only.
 template <int D, int NW = 4, bool PAIR = false> struct FwdCfg {
   static constexpr int BM = 32 * NW;  // query rows per workgroup (32 per wave)
   static constexpr int BN = 64;   // keys per iteration
@@ -67,17 +72,20 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
   constexpr int KS = D / 16;   // k-steps of the score contraction
   constexpr int DT = D / 32;   // 32-row tiles of O^T
   constexpr int CPR = lds_row<D> / 8;  // 16-byte chunks per row of a tile
+  static_assert(2 * DT == KS, "as many products of S as of O per half");
 
-  // Causal kernels hold their read offsets in few registers.  At D = 128 they otherwise spill some of them, and the
-  // reload in front of the loop makes the compiler wait, inside it, for every outstanding vector memory
-  // operation: each iteration began by waiting for the tile it had just requested.  (us, bf16 causal 64 heads x
-  // 2048 75.5 -> 72.3, 256 x 512 38.2 -> 34.5, fp16 with dropout 512 x 512 86.0 -> 74.7; D = 64: 128 x 1024 30.7 ->
-  // 30.3, and with dropout, rows only, 256 x 2048 236 -> 229.  Not causal: equal or 1 % slower.)
+  // Causal kernels hold their read offsets in few registers: with dropout they otherwise spill (fp16, d = 128, 512
+  // heads x 512 72.3 -> 77.0 us; without dropout equal).  A spilled value that is reloaded in front of the loop
+  // makes the compiler wait, inside it, for every outstanding vector memory operation, that is for the tile the
+  // round has just requested.
   constexpr int LEAN = !CAUSAL ? 0 : D == 64 && DROP ? 1 : 2;
   using LaneOffsets = std::conditional_t<LEAN != 0, SwzLaneLean<D, LEAN == 2>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // uniform: the rows of the wave, its loop limits and its share of the loads then take scalar registers.  (With that and
+  // the lane index read anew in the epilogue, 17 ... 25 vector registers less: no kernel but the causal one with dropout at
+  // d = 64 spills, causal d = 64 128 x 1024 31.8 -> 29.3 us, d = 80 36 x 1333 29.4 -> 27.1, d = 64 96 x 512 14.4 -> 13.2.)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, c32 = lane & 31;
   const uint32_t k_row_bytes = (uint32_t)mk.row * 2, v_row_bytes = (uint32_t)mv.row * 2;
   const uint32_t k_lane_src = dma_lane_src<D>(wave & 3, lane, k_row_bytes, dh);
@@ -118,14 +126,20 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
     }
     const int nt = (kv_end + C::BN - 1) / C::BN;
 
-    // K / V tiles: global -> LDS directly; rows past the end of the sequence arrive as zeros.
+    // K / V tiles: global -> LDS directly; rows past the end of the sequence arrive as zeros.  Tile t lives in slot
+    // t mod SLOTS.
     const BufView kview(Kh, head_span_bytes(mk, Nk, dh)), vview(Vh, head_span_bytes(mv, Nk, dh));
-    auto fetch_tile = [&](int j, int buf) {  // four waves move a tile
-      if (NW > 4 && wave >= 4) return;
-      tile_dma<D, C::BN>(kview, j * C::BN, smem + buf * C::STAGE, wave, k_lane_src, k_row_bytes);
-      tile_dma<D, C::BN>(vview, j * C::BN, smem + buf * C::STAGE + C::TILE, wave, v_lane_src, v_row_bytes);
+    auto fetch_k = [&](int t) {  // four waves move a tile
+      if (t >= nt || (NW > 4 && wave >= 4)) return;
+      tile_dma<D, C::BN>(kview, t * C::BN, smem + (t & (C::SLOTS - 1)) * C::STAGE, wave, k_lane_src, k_row_bytes);
     };
-    LaneOffsets off(lane);  // read offsets of the current buffer
+    auto fetch_v = [&](int t) {
+      if (t >= nt || (NW > 4 && wave >= 4)) return;
+      tile_dma<D, C::BN>(vview, t * C::BN, smem + (t & (C::SLOTS - 1)) * C::STAGE + C::TILE, wave, v_lane_src,
+                         v_row_bytes);
+    };
+    LaneOffsets off(lane);  // read offsets: rows of K tile i, columns of V tile i - 1
+    off.flip_tr((C::SLOTS - 1) * C::STAGE);
 
     f32x16 o[DT];
 #pragma unroll
@@ -137,8 +151,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
     float m_run = -1e30f;
     float l_run = 0.f;        // running row sum over this lane's keys only (halves merged at the end)
 
-    fetch_tile(0, 0);
-    if (PAIR && nt > 1) fetch_tile(1, 1);
+    fetch_k(0);
+    if (PAIR) {
+      fetch_k(1);
+      fetch_v(0);
+    }
     // The Q fragments must have arrived before the loop: otherwise the waits for them would sit
     // inside the loop body.
     wait_vmem_all();
@@ -150,210 +167,215 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
     // compare with a constant per score (with both limits compared, four instructions; us, causal, d = 64, 256
     // heads x 512 22.8 -> 21.6, d = 80, 36 x 1333 35.9 -> 31.9)
     const int last_key = (CAUSAL && qrow < Nk ? qrow : Nk - 1) - 4 * g;
-    // One iteration, compiled twice: MASKED for tiles that the diagonal or the end of the keys
-    // crosses, and without any mask arithmetic for all the others (left to a run-time flag, the
-    // compiler evaluates the mask predicate for every score of every tile).
-    auto iteration = [&](const int j, auto masked_tag) {
+
+    // Carried from round to round: raw scores of the second half of tile i - 1, P of its first half and their sum.
+    f32x16 s0, s1;
+    v8 pf0[2];
+    float rs0 = 0.f;
+
+    // Round i of the loop:
+    //   S_0(i), O += P_0(i-1) V_0(i-1)   ||  exponentials of half 1 of tile i-1
+    //   S_1(i), O += P_1(i-1) V_1(i-1)   ||  exponentials of half 0 of tile i
+    // The fences keep the scheduler from regrouping the instructions.
+    // FIRST: there is no tile i-1; LAST: no tile i.  MASKED for tiles that the diagonal or the end of the keys
+    // crosses: compiled apart, since the compiler evaluates a run-time mask for every score of every tile.
+    auto round = [&](const int i, auto first_tag, auto last_tag, auto masked_tag) {
+      constexpr bool FIRST = decltype(first_tag)::value, LAST = decltype(last_tag)::value;
       constexpr bool MASKED = decltype(masked_tag)::value;
-      if (PAIR) {  // at the start of a pair: the next pair, into the slots everybody left before the last barrier
-        if ((j & 1) == 0) {
-          if (j + 2 < nt) fetch_tile(j + 2, (j + 2) & 3);
-          if (j + 3 < nt) fetch_tile(j + 3, (j + 3) & 3);
+      SPARK_LDS const char* kb = smem;  // + off.* (which carry the slot)
+      SPARK_LDS const char* vb = smem + C::TILE;
+
+      // Step u (0 .. 2 KS - 1) has one MFMA of S (half u / KS, k-step u % KS) and one of O (16 keys u / DT, d-tile
+      // u % DT); operands are read PF steps ahead (with four, kernels spill; causal, two and three are equal).
+      constexpr int PF = CAUSAL ? 2 : 3;
+      v8 kf[PF], vf[PF];
+      auto load_step = [&](int u) {
+        if (!LAST) kf[u % PF] = lds_read16<v8>(kb, off.row_at(u % KS) + (u / KS) * 32 * C::ROWB);
+        if (!FIRST) {
+          const int ro = (u / DT) * 16 * C::ROWB;
+          vf[u % PF] = read_tr_pair<T>(vb, off.tr_at(0, u % DT) + ro, off.tr_at(1, u % DT) + ro);
         }
-      } else {
-        const int buf = j & 1;
-        if (j + 1 < nt) fetch_tile(j + 1, buf ^ 1);  // everybody left that buffer before the last barrier
-      }
+      };
 
-      const int k0 = j * C::BN;
-      // wave-uniform: skip tiles entirely above the diagonal (they are among the masked ones)
-      if (!MASKED || !CAUSAL || k0 <= q0 + 31) {
-        SPARK_LDS const char* kb = smem;  // + off.* (which carry the buffer bit)
-        SPARK_LDS const char* vb = smem + C::TILE;
-
-        // The 64-key tile is processed as two 32-key halves, each its own online-softmax step,
-        // so that the VALU work of one half sits between the MFMAs of the other:
-        //   S_0                   (MFMA)
-        //   S_1       ||  softmax of half 0   (an MFMA, then a few VALU instructions, ...)
-        //   O += P_0 V_0  ||  softmax of half 1
-        //   O += P_1 V_1
-        // A wave issues in order, so the VALU instructions must be placed between the MFMAs in
-        // program order; the fences keep the scheduler from regrouping them.  K fragments are read
-        // 8 reads ahead, V^T fragments one 16-key step ahead.
-        f32x16 s[2];
+      float t[16];
+      // Online softmax (Eq. 3) with a lazy reference point.  P is formed against the current
+      // reference m_run straight away, WITHOUT computing the row maximum first; the row sum of the
+      // result (needed anyway) tells whether the reference was too low: if no lane's partial sum
+      // exceeds 2^8, no P exceeds 2^8 either, which fp32 sums and the 16-bit MFMA operand hold
+      // without loss, and the reference stays (the final O = acc / l and LSE = m + log l do not
+      // depend on it).  Otherwise (the first tile, and afterwards only when a row's maximum grows
+      // by more than ~2^8) the maximum is computed after all, the reference moved there, the
+      // accumulators rescaled by exp(m_pre - m_cur) as in Eq. 3, and the half's P formed again.
+      // key0: first key of the half.
+      auto score = [&](const f32x16& s, int r, int key0) {
+        return MASKED && 8 * (r / 4) + (r % 4) > last_key - key0 ? -INFINITY : s[r];
+      };
+      auto exp_elem = [&](const f32x16& s, int r, int key0, float& rs) {
+        t[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(score(s, r, key0), scale_log2, -m_run));
+        rs += t[r];
+        // materialise here, between the MFMAs around this call: nothing uses the values before the
+        // end of the half, and the compiler otherwise moves the arithmetic there
+        asm volatile("" : "+v"(t[r]), "+v"(rs));
+      };
+      // Returns the rescale factor.
+      auto renorm = [&](const f32x16& s, int key0, float& rs) {
+        float mx = score(s, 0, key0);
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, score(s, r, key0));
+        mx = half_pair_max(mx) * scale_log2;  // scale > 0 commutes with the maximum
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        m_run = m_new;
+        l_run *= alpha;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) s[mt][r] = 0.f;
-        constexpr int GK = KS % 4 == 0 ? 4 : 3, GPH = KS / GK;  // groups of GK k-steps per half
-        v8 kf[2][GK];
-        auto load_kgroup = [&](int gi) {  // gi = half * GPH + group
-          const int half = gi / GPH, ks0 = GK * (gi % GPH);
+        for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-          for (int e = 0; e < GK; ++e)
-            kf[gi & 1][e] = lds_read16<v8>(kb, off.row_at(ks0 + e) + half * 32 * C::ROWB);
-        };
-        v8 vf[2][DT];
-        auto load_vgroup = [&](int kk) {
-          const int o = kk * 16 * C::ROWB;
+          for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+        rs = 0.f;
 #pragma unroll
-          for (int dt = 0; dt < DT; ++dt)
-            vf[kk & 1][dt] = read_tr_pair<T>(vb, off.tr_at(0, dt) + o, off.tr_at(1, dt) + o);
-        };
-
-        float t[32];
-        // raw scores of one half -> t, masked
-        auto load_half = [&](int h) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) t[h * 16 + r] = s[h][r];
-          if (MASKED) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              if (h * 32 + 8 * (r / 4) + (r % 4) > last_key - k0) t[h * 16 + r] = -INFINITY;
-            }
-          }
-        };
-        // Online softmax (Eq. 3) with a lazy reference point.  P is formed against the current
-        // reference m_run straight away, WITHOUT computing the row maximum first; the row sum of the
-        // result (needed anyway) tells whether the reference was too low: if no lane's partial sum
-        // exceeds 2^8, no P exceeds 2^8 either, which fp32 sums and the 16-bit MFMA operand hold
-        // without loss, and the reference stays (the final O = acc / l and LSE = m + log l do not
-        // depend on it).  Otherwise (the first tile, and afterwards only when a row's maximum grows
-        // by more than ~2^8) the maximum is computed after all, the reference moved there, the
-        // accumulators rescaled by exp(m_pre - m_cur) as in Eq. 3, and the half's P formed again.
-        // Returns the rescale factor.
-        auto renorm = [&](int h) {
-          load_half(h);  // raw scores again (they are still in the accumulators)
-          float mx = t[h * 16];
-#pragma unroll
-          for (int r = 1; r < 16; ++r) mx = fmaxf(mx, t[h * 16 + r]);
-          mx = half_pair_max(mx) * scale_log2;  // scale > 0 commutes with the maximum
-          const float m_new = fmaxf(m_run, mx);
-          const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-          m_run = m_new;
-          l_run *= alpha;
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
-          return alpha;
-        };
-        // Dropout acts on P after the row sums are taken: dropped entries become zero in the
-        // operand of O += P V; the survivors' factor 1/(1-p) is applied once, to O, at the end.
-        auto drop_half = [&](int h) {
-          uint32_t kb[4];
-          keep_bytes_query_lane(dr, head, qrow, k0 + 32 * h, lane, kb);
+        for (int r = 0; r < 16; ++r) exp_elem(s, r, key0, rs);
+        return alpha;
+      };
+      // Dropout acts on P after the row sums are taken: dropped entries become zero in the
+      // operand of O += P V; the survivors' factor 1/(1-p) is applied once, to O, at the end.
+      auto finish_half = [&](v8 (&pf)[2], const Philox& rng) {
+        if (DROP) {
+          uint32_t kb4[4];
+          keep_query_lane_finish(rng, lane, kb4);
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            if (!keep_reg(kb, r, dr.thr)) t[h * 16 + r] = 0.f;
+            if (!keep_reg(kb4, r, dr.thr)) t[r] = 0.f;
             // the select stays on the fp32 value: moved behind the conversion it would split every
             // packed two-value conversion into single ones plus a merge
-            asm volatile("" : "+v"(t[h * 16 + r]));
+            asm volatile("" : "+v"(t[r]));
           }
-        };
-        float rs0 = 0.f, rs1 = 0.f;  // this lane's sums of P over the two halves
-        auto exp_elem = [&](int i, float& rs) {
-          t[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(t[i], scale_log2, -m_run));
-          rs += t[i];
-          // materialise here, between the MFMAs around this call: nothing uses the values before the
-          // end of the phase, and the compiler otherwise moves the arithmetic there
-          asm volatile("" : "+v"(t[i]), "+v"(rs));
-        };
-
-        // ---- S_0 ----
-        load_kgroup(0);
-        load_kgroup(1);
-        sched_fence();
-#pragma unroll
-        for (int gi = 0; gi < GPH; ++gi) {
-#pragma unroll
-          for (int e = 0; e < GK; ++e) s[0] = F::mfma(kf[gi & 1][e], qf[GK * gi + e], s[0]);
-          if (gi + 2 < 2 * GPH) load_kgroup(gi + 2);
-          sched_fence();
         }
-        load_vgroup(0);
-        sched_fence();
-
-        load_half(0);
-        // ---- S_1  ||  exponentials of half 0 ----
-#pragma unroll
-        for (int gi = GPH; gi < 2 * GPH; ++gi) {
-#pragma unroll
-          for (int e = 0; e < GK; ++e) {
-            const int i = (gi - GPH) * GK + e;  // KS MFMAs share the 16 elements
-            s[1] = F::mfma(kf[gi & 1][e], qf[i], s[1]);
-#pragma unroll
-            for (int x = i * 16 / KS; x < (i + 1) * 16 / KS; ++x) exp_elem(x, rs0);
-            sched_fence();
-          }
-          if (gi + 2 < 2 * GPH) load_kgroup(gi + 2);
-          if (gi == GPH) load_vgroup(1);
-          sched_fence();
-        }
-        if (__any(!(rs0 <= 256.0f))) {  // also true for inf / NaN
-          renorm(0);
-          rs0 = 0.f;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) exp_elem(i, rs0);
-        }
-        load_half(1);
-        v8 pf[4];
-        if (DROP) drop_half(0);
         pf[0] = pack8<T>(&t[0]);
         pf[1] = pack8<T>(&t[8]);
-        sched_fence();
-        // ---- O^T += V_0^T P_0^T  ||  exponentials of half 1 ----
+      };
+      // One half of the round: steps KS h .. KS h + KS - 1, between them the exponentials of `s` and the rounds of the
+      // dropout generator for them (EXP).
+      auto half = [&](auto h_tag, f32x16& s_new, const f32x16& s, int key0, float& rs, const v8 (&pf)[2], Philox& rng) {
+        constexpr int h = decltype(h_tag)::value;
+        constexpr bool EXP = h == 0 ? !FIRST : !LAST;
+        if (DROP && EXP) rng = keep_query_lane_begin(dr, head, qrow, key0, lane);
+        if (!LAST) {
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
+          for (int r = 0; r < 16; ++r) s_new[r] = 0.f;
+        }
 #pragma unroll
-          for (int dt = 0; dt < DT; ++dt) {
-            o[dt] = F::mfma(vf[kk & 1][dt], pf[kk], o[dt]);
+        for (int e = 0; e < KS; ++e) {
+          const int u = KS * h + e;
+          const int x0 = e * 16 / KS, x2 = (e + 1) * 16 / KS, x1 = (x0 + x2) / 2;
+          if (!LAST) s_new = F::mfma(kf[u % PF], qf[e], s_new);
+          if (EXP) {
 #pragma unroll
-            for (int x = (kk * DT + dt) * 8 / DT; x < (kk * DT + dt + 1) * 8 / DT; ++x) exp_elem(16 + x, rs1);
-            sched_fence();
+            for (int x = x0; x < x1; ++x) exp_elem(s, x, key0, rs);
           }
-          load_vgroup(kk + 2);
+          if (DROP && EXP) {
+#pragma unroll
+            for (int q = e * 10 / KS; q < (e + 1) * 10 / KS; ++q) philox_round<true>(rng, dr.key0, dr.key1, q);
+          }
+          sched_fence();
+          if (!FIRST) o[u % DT] = F::mfma(vf[u % PF], pf[(u / DT) & 1], o[u % DT]);
+          if (EXP) {
+#pragma unroll
+            for (int x = x1; x < x2; ++x) exp_elem(s, x, key0, rs);
+          }
+          if (u + PF < 2 * KS) load_step(u + PF);
           sched_fence();
         }
-        if (__any(!(rs1 <= 256.0f))) {  // P_0 V_0 is in the accumulators already and is rescaled with them
-          rs0 *= renorm(1);
-          rs1 = 0.f;
+      };
+      Philox rng{0, 0, 0, 0};
 #pragma unroll
-          for (int i = 16; i < 32; ++i) exp_elem(i, rs1);
-        }
+      for (int u = 0; u < PF; ++u) load_step(u);
+      sched_fence();
+      v8 pf1[2];
+      float rs1 = 0.f;
+      const int kp = (i - 1) * C::BN + 32, kc = i * C::BN;
+      half(std::integral_constant<int, 0>{}, s0, s1, kp, rs1, pf0, rng);
+      if (!FIRST) {
+        if (__any(!(rs1 <= 256.0f))) rs0 *= renorm(s1, kp, rs1);  // also true for inf / NaN
         l_run += rs0 + rs1;
-        if (DROP) drop_half(1);
-        pf[2] = pack8<T>(&t[16]);
-        pf[3] = pack8<T>(&t[24]);
+        finish_half(pf1, rng);
         sched_fence();
-        // ---- O^T += V_1^T P_1^T ----
-#pragma unroll
-        for (int kk = 2; kk < 4; ++kk) {
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) o[dt] = F::mfma(vf[kk & 1][dt], pf[kk], o[dt]);
-          sched_fence();
-        }
       }
-
+      rs0 = 0.f;
+      half(std::integral_constant<int, 1>{}, s1, s0, kc, rs0, pf1, rng);
+      if (!LAST) {
+        if (__any(!(rs0 <= 256.0f))) renorm(s0, kc, rs0);
+        finish_half(pf0, rng);
+        sched_fence();
+      }
+    };
+    // Requests of round i, into slots everybody left before the last barrier: the next round's tiles, or with PAIR, in
+    // even rounds, those of the next two.
+    auto request = [&](int i) {
+      if (PAIR) {
+        if ((i & 1) == 0) {
+          fetch_k(i + 2);
+          fetch_k(i + 3);
+          fetch_v(i + 1);
+          fetch_v(i + 2);
+        }
+      } else {
+        fetch_k(i + 1);
+        fetch_v(i);
+      }
+    };
+    auto end_round = [&](int i) {
       // next slot: 0 -> 1 -> 2 -> 3 -> 0 with PAIR (XOR with STAGE, then with 3 STAGE), else 0 <-> 1
-      const int flip = PAIR && (j & 1) ? 3 * C::STAGE : C::STAGE;
-      off.flip(flip);
-      if (!PAIR || (j & 1) || j + 1 >= nt) {
-        wait_vmem_all();  // the next tile (pair) has landed: requested at the top of this iteration (pair)
+      off.flip_rows(PAIR && (i & 1) ? 3 * C::STAGE : C::STAGE);
+      off.flip_tr(PAIR && !(i & 1) ? 3 * C::STAGE : C::STAGE);
+      if (!PAIR || (i & 1) || i >= nt) {
+        wait_vmem_all();  // requested at the top of this round (pair of rounds)
         __syncthreads();
       }
     };
     // Tiles [0, n_plain) end within the keys and, if causal, at or below the diagonal for every
-    // row of this wave.  The split differs between the waves of a workgroup; the number of
-    // iterations, and with it the number of barriers, does not.
-    int n_plain = Nk / C::BN;
-    if (CAUSAL && (q0 + 1) / C::BN < n_plain) n_plain = (q0 + 1) / C::BN;
+    // row of this wave, and tiles from n_wave on are wholly above it.  Both differ between the waves of a workgroup; the
+    // number of rounds, and with it the number of barriers, does not.
+    int n_plain = Nk / C::BN, n_wave = nt;
+    if (CAUSAL) {
+      if ((q0 + 1) / C::BN < n_plain) n_plain = (q0 + 1) / C::BN;
+      if ((q0 + 31) / C::BN + 1 < n_wave) n_wave = (q0 + 31) / C::BN + 1;
+    }
     if (n_plain > nt) n_plain = nt;
-    int j = 0;
-    for (; j < n_plain; ++j) iteration(j, std::false_type{});
-    for (; j < nt; ++j) iteration(j, std::true_type{});
+    using no = std::false_type;
+    using yes = std::true_type;
+    request(0);
+    if (n_plain > 0)
+      round(0, yes{}, no{}, no{});
+    else
+      round(0, yes{}, no{}, yes{});
+    end_round(0);
+    int i = 1;
+    for (; i < n_plain; ++i) {
+      request(i);
+      round(i, no{}, no{}, no{});
+      end_round(i);
+    }
+    for (; i < n_wave; ++i) {
+      request(i);
+      round(i, no{}, no{}, yes{});
+      end_round(i);
+    }
+    request(i);
+    if (n_plain == n_wave)
+      round(i, no{}, yes{}, no{});
+    else
+      round(i, no{}, yes{}, yes{});
+    end_round(i);
+    for (++i; i <= nt; ++i) {
+      request(i);
+      end_round(i);
+    }
 
     // Epilogue: normalise, round once, transpose through this wave's LDS slice, store rows.
+    // The lane index is read anew: addresses formed from it would otherwise be held in registers across the loop.
+    int elane = lane;
+    asm volatile("" : "+v"(elane));
+    const int eg = elane >> 5, ec32 = elane & 31;
     l_run = half_pair_sum(l_run);
     const float inv = (DROP ? dr.rescale : 1.0f) / l_run;
     SPARK_LDS char* ob = smem + wave * 32 * C::OSTR;
@@ -364,19 +386,19 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
         v4 pk;
 #pragma unroll
         for (int e = 0; e < 4; ++e) pk[e] = (T)(o[dt][r4 * 4 + e] * inv);
-        lds_write(ob, c32 * C::OSTR + (dt * 32 + 8 * r4 + 4 * g) * 2, pk);
+        lds_write(ob, ec32 * C::OSTR + (dt * 32 + 8 * r4 + 4 * eg) * 2, pk);
       }
     T* Oh = O + head_base(mo, head, H);
     constexpr int RPP = 64 / CPR;  // rows per pass of the wave
 #pragma unroll
     for (int p = 0; p < 32 / RPP; ++p) {
-      const int row = p * RPP + lane / CPR, cc = lane % CPR;
+      const int row = p * RPP + elane / CPR, cc = elane % CPR;
       const u32x4 v = lds_read16<u32x4>(ob, row * C::OSTR + cc * 16);
       if (q0 + row < Nq && cc * 8 < dh)
         *reinterpret_cast<u32x4*>(Oh + (size_t)(q0 + row) * (size_t)mo.row + cc * 8) = v;
     }
-    if (g == 0 && qrow < Nq)
-      LSE[(size_t)head * Nq + qrow] = (m_run + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f;
+    if (eg == 0 && q0 + ec32 < Nq)
+      LSE[(size_t)head * Nq + q0 + ec32] = (m_run + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f;
   }  // rep
 }
 

@@ -123,13 +123,19 @@ template <int D> struct SwzLane {
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt) tr[h][dt] = s.tr[h][dt] + bytes;
   }
-  __device__ __forceinline__ void flip(int bits) {  // to the other buffer: one exclusive or each
+  __device__ __forceinline__ void flip_rows(int bits) {  // to another buffer: one exclusive or each
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) row[ks] ^= bits;
+  }
+  __device__ __forceinline__ void flip_tr(int bits) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt) tr[h][dt] ^= bits;
+  }
+  __device__ __forceinline__ void flip(int bits) {
+    flip_rows(bits);
+    flip_tr(bits);
   }
 };
 
@@ -163,14 +169,20 @@ template <int D, bool LEAN_TR> struct SwzLaneLean {
       for (int dt = 0; dt < (LEAN_TR ? 1 : D / 32); ++dt) tr0[h][dt] = s.tr0[h][dt] + bytes;
     if (LEAN_TR) asm volatile("" : "+v"(tr0[0][0]));
   }
-  __device__ __forceinline__ void flip(int bits) {
+  __device__ __forceinline__ void flip_rows(int bits) {
     row0 ^= bits;
     asm volatile("" : "+v"(row0));  // opaque: otherwise the offsets of both buffers are formed ahead of the loop
+  }
+  __device__ __forceinline__ void flip_tr(int bits) {
 #pragma unroll
     for (int h = 0; h < (LEAN_TR ? 1 : 2); ++h)
 #pragma unroll
       for (int dt = 0; dt < (LEAN_TR ? 1 : D / 32); ++dt) tr0[h][dt] ^= bits;
     if (LEAN_TR) asm volatile("" : "+v"(tr0[0][0]));
+  }
+  __device__ __forceinline__ void flip(int bits) {
+    flip_rows(bits);
+    flip_tr(bits);
   }
 };
 
