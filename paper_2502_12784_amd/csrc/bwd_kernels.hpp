@@ -92,7 +92,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
   using LaneOffsets = std::conditional_t<D == 64, SwzLaneLean<D, true>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, c32 = lane & 31;
 
   const T* Kh = K + head_base(mk, head, H);
@@ -497,7 +497,7 @@ static __device__ __forceinline__ void bwd_dq(
   using LaneOffsets = std::conditional_t<LEAN != 0, SwzLaneLean<D, LEAN == 2>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, c32 = lane & 31;
 
   const T* Qh = Q + head_base(mq, head, H);

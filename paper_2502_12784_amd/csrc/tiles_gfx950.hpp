@@ -248,6 +248,8 @@ static __device__ __forceinline__ void store_transposed(const f32x16 (&acc)[D / 
   using v4 = typename Frag<T>::v4;
   constexpr int CPR = lds_row<D> / 8;
   constexpr int RPP = 64 / CPR;
+  // read anew: addresses formed from the caller's index would be held in registers across its loop over tiles
+  asm volatile("" : "+v"(lane));
   const int g = lane >> 5, c32 = lane & 31;
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt)
