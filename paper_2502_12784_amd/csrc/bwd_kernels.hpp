@@ -491,8 +491,9 @@ static __device__ __forceinline__ void bwd_dq(
   using C = BwdQCfg<D, CAUSAL, DROP>;
   constexpr int KS = D / 16, DT = D / 32;
 
-  // few offset registers in the causal kernels, for the reason given in mha_fwd_kernel (dQ, us: fp16 with dropout,
-  // D = 128, 512 heads x 512 135 -> 121; bf16, D = 128, 256 x 512 55.7 -> 54.5; fp16, D = 64, 256 x 512 31.8 -> 31.4)
+  // few offset registers in the causal kernels (dQ, us: fp16 with dropout, D = 128, 512 heads x 512 135 -> 121; bf16,
+  // D = 128, 256 x 512 55.7 -> 54.5; fp16, D = 64, 256 x 512 31.8 -> 31.4, when wave indices took vector registers;
+  // since then equal, and 10 ... 25 registers less)
   constexpr int LEAN = !CAUSAL ? 0 : (D > 64) == DROP ? 2 : 1;
   using LaneOffsets = std::conditional_t<LEAN != 0, SwzLaneLean<D, LEAN == 2>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
@@ -573,13 +574,12 @@ static __device__ __forceinline__ void bwd_dq(
     asm volatile("" : "+v"(lse2), "+v"(Dq));
     // dS = P o (dP - D) needs no subtraction: every dP accumulator starts from -D
     // (one value per lane here: lane = query), handed to the first MFMA as its addend.  That costs 16
-    // registers for the whole loop; at D = 128 the kernel has none to spare (the causal one would
-    // spill, measured +4 %), so only D = 64 does it (dQ kernel -2 ... -3 %).
-    constexpr bool FOLD_D = D == 64;
+    // registers for the whole loop (dQ kernel at D = 64 -2 ... -3 %; backward, us, D = 128, causal 64 x 4096 923.7 ->
+    // 913.3, 16 x 16384 3536 -> 3513, D = 96 90 x 1500 344 -> 340, with dropout equal).
     f32x16 dneg;
 #pragma unroll
     for (int r = 0; r < 16; ++r) dneg[r] = -Dq;
-    if (FOLD_D) asm volatile("" : "+v"(dneg));
+    asm volatile("" : "+v"(dneg));
     __syncthreads();
 
     // last key this lane's query attends to, less the 4 g that every register's key contains: the mask is one
@@ -609,8 +609,8 @@ static __device__ __forceinline__ void bwd_dq(
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) { s[mt][r] = 0.f; dp[mt][r] = 0.f; }
-          if (FOLD_D) dp[mt] = dneg;
+          for (int r = 0; r < 16; ++r) s[mt][r] = 0.f;
+          dp[mt] = dneg;
         }
         constexpr int AHEAD = 4;
         v8 fa[AHEAD][MT];
@@ -675,13 +675,8 @@ static __device__ __forceinline__ void bwd_dq(
         float ds[16 * MT];
         auto ds_elem = [&](int e) {
           const int mt = e / 16, r = e % 16;
-          if (FOLD_D) {
-            // the accumulator started from -D, which is also what a dropped entry has instead of M o dP - D
-            ds[e] = pe[e] * (DROP && !keep_reg(keep[mt], r, dr.thr) ? -Dq : dp[mt][r]);
-          } else {
-            const float dpe = DROP && !keep_reg(keep[mt], r, dr.thr) ? 0.f : dp[mt][r];
-            ds[e] = pe[e] * (dpe - Dq);
-          }
+          // the accumulator started from -D, which is also what a dropped entry has instead of M o dP - D
+          ds[e] = pe[e] * (DROP && !keep_reg(keep[mt], r, dr.thr) ? -Dq : dp[mt][r]);
           asm volatile("" : "+v"(ds[e]));
         };
         // dQ^T += K^T dS^T, 16 keys per step; step kk uses elements 8 kk .. 8 kk + 7.  Those of
