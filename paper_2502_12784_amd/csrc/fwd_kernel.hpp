@@ -78,8 +78,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
   // heads x 512 72.3 -> 77.0 us; without dropout equal).  A spilled value that is reloaded in front of the loop
   // makes the compiler wait, inside it, for every outstanding vector memory operation, that is for the tile the
   // round has just requested.
-  constexpr int LEAN = !CAUSAL ? 0 : D == 64 && DROP ? 1 : 2;
-  using LaneOffsets = std::conditional_t<LEAN != 0, SwzLaneLean<D, LEAN == 2>, SwzLane<D>>;
+  using LaneOffsets = std::conditional_t<CAUSAL, SwzLaneLean<D, true>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
 
   // uniform: the rows of the wave, its loop limits and its share of the loads then take scalar registers.  (With that and
@@ -236,11 +235,18 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
         for (int r = 0; r < 16; ++r) exp_elem(s, r, key0, rs);
         return alpha;
       };
+      // The generator's rounds sit between the MFMAs, too, but in the causal kernel at d = 64, which has no registers for
+      // their state there (us, 256 heads x 512 30.6 -> 28.6, 256 x 2048 244.8 -> 238.7, 128 x 1024 44.2 -> 41.1).
+      constexpr bool SPREAD = DROP && !(D == 64 && CAUSAL);
       // Dropout acts on P after the row sums are taken: dropped entries become zero in the
       // operand of O += P V; the survivors' factor 1/(1-p) is applied once, to O, at the end.
-      auto finish_half = [&](v8 (&pf)[2], const Philox& rng) {
+      auto finish_half = [&](v8 (&pf)[2], Philox& rng) {
         if (DROP) {
           uint32_t kb4[4];
+          if (!SPREAD) {
+#pragma unroll
+            for (int q = 0; q < 10; ++q) philox_round<true>(rng, dr.key0, dr.key1, q);
+          }
           keep_query_lane_finish(rng, lane, kb4);
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
@@ -272,7 +278,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
 #pragma unroll
             for (int x = x0; x < x1; ++x) exp_elem(s, x, key0, rs);
           }
-          if (DROP && EXP) {
+          if (SPREAD && EXP) {
 #pragma unroll
             for (int q = e * 10 / KS; q < (e + 1) * 10 / KS; ++q) philox_round<true>(rng, dr.key0, dr.key1, q);
           }
