@@ -621,11 +621,14 @@ static __device__ __forceinline__ void bwd_dq(
             fa[i % AHEAD][mt] = lds_read16<v8>(i < KS ? kb : vb, off.row_at(ks) + mt * 32 * C::ROWB);
         };
         // Dropout: dS = r P o (M o dPraw - D (1-p)); the workspace holds D (1-p) and the factor r
-        // goes into the final scale of dQ.
+        // goes into the final scale of dQ.  The generator's rounds ride between the MFMAs of S, its exchange between
+        // the first ones of dP (backward, us, causal fp16 d = 64 256 heads x 2048 685 -> 662, 512 x 512 170.8 -> 169.4;
+        // bf16 d = 128 64 x 4096 1067 -> 1039; d = 80 36 x 1333 95.7 -> 92.2).
         uint32_t keep[MT][4];
+        Philox rng[MT];
         if (DROP) {
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) keep_bytes_query_lane(dr, head, qrow, k0 + 32 * mt, lane, keep[mt]);
+          for (int mt = 0; mt < MT; ++mt) rng[mt] = keep_query_lane_begin(dr, head, qrow, k0 + 32 * mt, lane);
         }
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) load_step(i);
@@ -633,7 +636,15 @@ static __device__ __forceinline__ void bwd_dq(
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) s[mt] = F::mfma(fa[ks % AHEAD][mt], qf[ks], s[mt]);
+          for (int mt = 0; mt < MT; ++mt) {
+            s[mt] = F::mfma(fa[ks % AHEAD][mt], qf[ks], s[mt]);
+            if (DROP) {
+#pragma unroll
+              for (int round = ks * 10 / KS; round < (ks + 1) * 10 / KS; ++round)
+                philox_round<true>(rng[mt], dr.key0, dr.key1, round);
+              sched_fence();
+            }
+          }
           load_step(ks + AHEAD);  // KS >= AHEAD: always a valid step
           sched_fence();
         }
@@ -662,6 +673,7 @@ static __device__ __forceinline__ void bwd_dq(
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt) {
             dp[mt] = F::mfma(fa[(KS + ks) % AHEAD][mt], dof[ks], dp[mt]);
+            if (DROP && ks == 0) keep_query_lane_finish(rng[mt], lane, keep[mt]);
 #pragma unroll
             for (int x = ks * 16 / KS; x < (ks + 1) * 16 / KS; ++x) p_elem(mt * 16 + x);  // 16 in KS MFMAs
             sched_fence();
