@@ -175,8 +175,8 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
     // four elements are done, instead of being held for a half step (8 rows) and the next one.  With that the kernel
     // fits 256 registers and two workgroups share a CU (us, 256 heads x 2048 852 -> 660, causal 509 -> 386).
     constexpr bool RING = DROP && D == 64;
-    auto load_quad = [&](f32x4 (&l)[2], f32x4 (&d)[2], int sub, int x) {
-      const int o = statA + (sub * 32 + 8 * x) * 4;
+    auto load_quad = [&](f32x4 (&l)[2], f32x4 (&d)[2], int stat, int sub, int x) {
+      const int o = stat + (sub * 32 + 8 * x) * 4;
       l[x & 1] = lds_read16<f32x4>(smem, o);
       d[x & 1] = lds_read16<f32x4>(smem, o + C::BM * 4);
     };
@@ -272,15 +272,12 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       if (gi + 2 < NG) load_agroup(gi + 2, 0);
       sched_fence();
     }
-    // At D > 64 every step requests the first two fragment groups of its successor half-way through
-    // its own dV / dK region, so that no step starts by waiting for LDS (C4 backward -3 %); here
-    // those of step (s_begin, 1).  At D = 64 the longer live ranges cost spills (+1 ... +3 %) and the
-    // request stays at the start of the step that uses it.
-    constexpr bool EARLY = D > 64;
-    if (EARLY) {
-      load_agroup(0, 1);
-      load_agroup(1, 1);
-    }
+    // Every step requests the first two fragment groups of its successor half-way through its own dV / dK region, so
+    // that no step starts by waiting for LDS (D = 128, causal 64 heads x 4096: backward -3 %; D = 64, us, 32 x 8192
+    // 1776 -> 1748, causal 128 x 1024 85.0 -> 83.9, both sides in one grid 24 x 1024 36.0 -> 34.6); here those
+    // of step (s_begin, 1).
+    load_agroup(0, 1);
+    load_agroup(1, 1);
     // With more than 256 registers per lane the MFMAs deliver the scores in accumulation registers,
     // which the VALU reaches through one v_accvgpr_read per element.  Such a read co-issues with
     // executing MFMAs as long as none of them writes the register read (measured), so each element
@@ -300,8 +297,8 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       dsfL = join_pairs<T>(pk_ds);
     }
     if (RING) {
-      load_quad(lL, dL, 0, 2);
-      load_quad(lL, dL, 0, 3);
+      load_quad(lL, dL, statA, 0, 2);
+      load_quad(lL, dL, statA, 0, 3);
     } else {
       load_stats(lH, dH, 0, 1);
     }
@@ -320,6 +317,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       auto step = [&](f32x16& s_new, f32x16& dp_new, int sub_new, int q0_new, const f32x16& s_cur,
                       const f32x16& dp_cur, int sub_cur, int q0_cur, auto&& request_next) {
         const int ahead_cur = ahead_of(q0_cur), ahead_new = ahead_of(q0_new);
+        const int stat_new = statA;  // request_next may move statA on before the last of its quads is read
         // ---- region 1: scores of the next step  ||  second half of P, dS of the current step ----
         float p[8], ds[8];
         uint32_t pk_p[4], pk_ds[4];
@@ -344,7 +342,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
             for (int x = (i / 2) * 4 / NG; x < (i / 2 + 1) * 4 / NG; ++x)  // 8 elements in 2 NG slots
               softmax_elem(s_cur, dp_cur, 1, x, RING ? lL : lH, RING ? dL : dH, ahead_cur, mask, kbCur, p, ds,
                            pk_p, pk_ds);
-            if (RING && (i & 3) == 3) load_quad(lL, dL, sub_new, i / 4);  // first half of the next step
+            if (RING && (i & 3) == 3) load_quad(lL, dL, stat_new, sub_new, i / 4);  // first half of the next step
           }
           if (DROP) {
 #pragma unroll
@@ -376,11 +374,11 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
             if (tg + 2 < NTG) load_thalf(tg + 2, sub_cur, e);  // into the operands just used
             sched_fence();
           }
-          if (RING) load_quad(lL, dL, sub_new, 2 + tg);  // second half of the next step
+          if (RING) load_quad(lL, dL, stat_new, sub_new, 2 + tg);  // second half of the next step
           // the fragment buffers are free since region 1 ended; one group per slot keeps the number
           // of LDS reads in flight under the 15 the wave's counter can track
-          if (EARLY && tg == (NTG - 1) / 2) request_next(0);
-          if (EARLY && tg == (NTG + 1) / 2) request_next(1);
+          if (tg == (NTG - 1) / 2) request_next(0);
+          if (tg == (NTG + 1) / 2) request_next(1);
           sched_fence();
         }
         pfL = join_pairs<T>(pk_p);
@@ -399,21 +397,15 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       for (int r = 0; r < 16; ++r) sY[r] = 0.f;
       dpY = dp_start(1);  // statA points at stage m here
       auto request_B = [&](int part) {
-        if (part != 1) point_A(slot1);  // stage m+1 has been resident since the end of stage m-1
-        if (part != 1) load_agroup(0, 0);
-        if (part != 0) load_agroup(1, 0);
+        if (part == 0) point_A(slot1);  // stage m+1 has been resident since the end of stage m-1
+        load_agroup(part, 0);
       };
-      auto request_A = [&](int part) {
-        if (part != 1) load_agroup(0, 1);
-        if (part != 0) load_agroup(1, 1);
-      };
-      if (!EARLY) request_A(2);
+      auto request_A = [&](int part) { load_agroup(part, 1); };
       sched_fence();
       step(sY, dpY, 1, m * C::BM + 32, sX, dpX, 0, m * C::BM, request_B);
       // (m+1, 0) scores  ||  (m, 1) softmax; then (m, 1) dV / dK
 #pragma unroll
       for (int r = 0; r < 16; ++r) sX[r] = 0.f;
-      if (!EARLY) request_B(2);
       dpX = dp_start(0);  // statA points at stage m + 1 by now (request_B moved it)
       sched_fence();
       step(sX, dpX, 0, (m + 1) * C::BM, sY, dpY, 1, m * C::BM + 32, request_A);
