@@ -216,14 +216,14 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
       qdma.template tile<C::BM>(qview, t * C::BM, wbuf + b * C::STAGE, q_row_bytes);
       dodma.template tile<C::BM>(doview, t * C::BM, wbuf + b * C::STAGE + C::TILE, do_row_bytes);
     };
+    const BufView oview(Oh, head_span_bytes(mo, Nq, dh));
     // row of O and LSE of this lane's query in tile t; zeros past the end (there dO reads as zeros, too)
     v8 of[KS];
     float lse = 0.f;
     auto load_o = [&](int t) {
       const int row = t * C::BM + c32;
       const bool valid = row < Nq;
-      const T* op = Oh + (size_t)(valid ? row : 0) * (size_t)mo.row;
-      load_row_frags(of, op, g, dh, valid);
+      load_row_frags(of, oview, (uint32_t)row * ((uint32_t)mo.row * 2), g, dh, valid);
       lse = valid ? LSE[(size_t)head * Nq + row] : 0.f;
     };
 

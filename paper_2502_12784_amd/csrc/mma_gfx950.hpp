@@ -145,6 +145,15 @@ struct BufView {
     desc[2] = bytes;
     desc[3] = 0x00020000u;
   }
+  // A lane offset that reads as zeros in every view: no head spans 2^31 bytes (the host checks it).
+  static constexpr uint32_t OUTSIDE = 0x80000000u;
+  // 16 bytes per lane to registers.  The compiler knows this load and waits for it where its result is used.
+  template <typename V8>
+  __device__ __forceinline__ V8 load16(uint32_t lane_off) const {
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<void*>((uint64_t)desc[1] << 32 | desc[0]), 0, (int)desc[2], (int)desc[3]);
+    return __builtin_bit_cast(V8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_off, 0, 0));
+  }
   // Direct global->LDS load (no registers): lane l of the wave writes its 16 (or 4) bytes at
   // LDS byte address dst + 16 l (4 l); dst must be wave-uniform.  Out-of-range lanes write
   // zeros.  Completion is counted by vmcnt.

@@ -47,6 +47,73 @@ def test_waits_without_a_barrier_are_compiler_fences():
         assert re.search(asm_text + r'[^;]*: "memory"\)', helpers)
 
 
+class Flow:
+    """Order of memory events in one compiled kernel: 'row' (a load to registers), 'tile' (a direct global->LDS load),
+    ('wait', N) (at most N vector memory operations outstanding), 'barrier' and 'mfma', with the branches between them."""
+
+    def __init__(self, body):
+        self.at, self.events, self.next = {}, [], []
+        jumps = []
+        for line in (l.split("//")[0].split(";")[0].strip() for l in body.split("\n")):
+            op = line.split()[0] if line else ""
+            if re.match(r"\.LBB\w+:", line):
+                self.at[op[:-1]] = len(self.events)
+                continue
+            event = None
+            if re.match(r"(buffer|global|flat)_load", op):
+                event = "tile" if line.endswith(" lds") else "row"
+            elif op == "s_waitcnt" and "vmcnt" in line:
+                event = ("wait", int(re.search(r"vmcnt\((\d+)\)", line).group(1)))
+            elif "mfma" in op or op in ("s_barrier", "s_endpgm"):
+                event = "mfma" if "mfma" in op else op[2:]
+            elif re.match(r"s_c?branch", op):
+                event = "jump"
+                jumps.append((len(self.events), line.split()[1], op == "s_branch"))
+            if event:
+                self.events.append(event)
+                self.next.append([len(self.events)] if event != "endpgm" else [])
+        for i, label, always in jumps:
+            self.next[i] = [self.at[label]] + ([] if always else [i + 1])
+
+    def in_loop(self, event):
+        """Whether event number `event` can follow itself."""
+        seen, todo = set(), list(self.next[event])
+        while todo:
+            i = todo.pop()
+            if i not in seen and i < len(self.events):
+                seen.add(i)
+                todo += self.next[i]
+        return event in seen
+
+
+def kernel_flows(asm, name):
+    for m in re.finditer(r"\n(_ZN5spark\d+%sI\w+):" % name, asm):
+        body = asm[m.end():]
+        yield m.group(1), Flow(body[:body.index("\n.Lfunc_end")])
+
+
+def test_split_backward_does_not_wait_for_the_tile_it_has_requested(asm):
+    """In the loops of the split backward a wave requests the next tile (and, for dK/dV, its row of O) and then works on
+    the present one: up to the first matrix instruction nothing may wait for what has been requested."""
+    kernels = list(kernel_flows(asm, "mha_bwd_split_kernel"))
+    assert len(kernels) == 16
+    for name, flow in kernels:
+        runs = [i for i, e in enumerate(flow.events) if e == "tile" and (i == 0 or flow.events[i - 1] != "tile")]
+        loops = [i for i in runs if flow.in_loop(i)]
+        assert len(loops) >= 2, name  # dQ and dK/dV
+        for i in loops:
+            best = {}  # event -> most operations requested on a way to it
+            todo = [(i, 0)]
+            while todo:
+                k, n = todo.pop()
+                if best.get(k, -1) >= n or flow.events[k] == "mfma":
+                    continue
+                best[k] = n
+                if isinstance(flow.events[k], tuple):
+                    assert flow.events[k][1] >= n, (name, flow.events[k], n)
+                todo += [(j, n + (flow.events[k] in ("tile", "row"))) for j in flow.next[k]]
+
+
 def test_host_binding_needs_no_compiler_but_hipccs(monkeypatch, tmp_path):
     """Without g++ the host extension is compiled with the clang++ of the ROCm toolchain."""
     seen = []
