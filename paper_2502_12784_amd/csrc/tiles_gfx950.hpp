@@ -43,31 +43,41 @@ static __device__ __forceinline__ V8 load_row_chunk(const T* row, int col, int d
   return col < dh ? *reinterpret_cast<const V8*>(row + col) : z;
 }
 
-// The row a lane holds as N fragments over d (half g of every 16 columns); zeros if not `valid`.  A head dimension that
-// fills the tile takes the loads without the test of every chunk, a mask and a branch each (us, causal, d = 128, 256
-// heads x 512: forward 32.7 -> 30.2, dQ 48.8 -> 46.8).
+// The row a lane holds as N fragments over d (half g of every 16 columns).  Three forms; what separates them is how the
+// compiler waits: where two paths of loads meet, it waits for every load outstanding.
+//
+// A test for every chunk:
 template <typename V8, typename T, int N>
-static __device__ __forceinline__ void load_row_frags(V8 (&f)[N], const T* row, int g, int dh, bool valid = true) {
-  if (dh == 16 * N && __all(valid)) {
+static __device__ __forceinline__ void load_row_chunks(V8 (&f)[N], const T* row, int g, int dh) {
+#pragma unroll
+  for (int ks = 0; ks < N; ++ks) f[ks] = load_row_chunk<V8>(row, ks * 16 + g * 8, dh);
+}
+// No tests where the head dimension fills the tile, at the price of the meeting of the two paths, once per tensor.  Faster
+// in the causal kernels, whose workgroups come two or three to a CU at different lengths and cover for each other (us, 512
+// heads x 512, d = 128, with dropout: dQ 103, with chunk tests 109, through a view 107), and in the forward (96 x 512, d = 128
+// 20.7, 21.0, 21.2).
+template <typename V8, typename T, int N>
+static __device__ __forceinline__ void load_row_frags(V8 (&f)[N], const T* row, int g, int dh) {
+  if (dh == 16 * N) {
 #pragma unroll
     for (int ks = 0; ks < N; ++ks) f[ks] = *reinterpret_cast<const V8*>(row + ks * 16 + g * 8);
   } else {
-#pragma unroll
-    for (int ks = 0; ks < N; ++ks) f[ks] = load_row_chunk<V8>(row, ks * 16 + g * 8, valid ? dh : 0);
+    load_row_chunks(f, row, g, dh);
   }
 }
-
-// The same through a buffer view, the row starting at byte `row_off`: chunks at columns >= dh, or all of them if not
-// `valid`, get an offset outside the view.  No branch: where two paths of loads meet, the compiler waits for every
-// outstanding load, and with them for the tile that has just been requested (split backward, d = 128, us: 4 heads x
-// 1024 25.2 -> 23.9, causal 2 x 4096 100.9 -> 97.4, with dropout 4 x 900 25.9 -> 23.7).
+// Through a buffer view, the row starting at byte `row_off`: chunks at columns >= dh, or all of them if not `valid`, get an
+// offset outside the view.  One straight line of loads, which nothing waits for before their use: for the split backward's
+// loop, where a wait would be one for the tile that has just been requested (d = 128, us: 4 heads x 1024 25.2 -> 23.9,
+// causal 2 x 4096 100.9 -> 97.4, with dropout 4 x 900 25.9 -> 23.7), and for dQ without a mask, which loads three
+// tensors' rows (us: 150 heads x 300, d = 56 14.6 -> 14.0; 300 x 256, d = 128 31.1 -> 30.3; equal from 96 x 512 on).
 template <typename V8, int N>
 static __device__ __forceinline__ void load_row_frags(V8 (&f)[N], const BufView& view, uint32_t row_off, int g, int dh,
                                                       bool valid = true) {
-  const int limit = valid ? dh - g * 8 : 0;
+  const int last = (valid ? dh : 0) - 8 * g - 1;  // negative once the chunk's column is taken off: outside
+  row_off += 16 * g;
 #pragma unroll
   for (int ks = 0; ks < N; ++ks)
-    f[ks] = view.load16<V8>((ks * 16 < limit ? row_off + 16 * g : BufView::OUTSIDE) + 32 * ks);
+    f[ks] = view.load16<V8>((row_off | ((uint32_t)(last - ks * 16) & BufView::OUTSIDE)) + 32 * ks);
 }
 
 // Work items per head for a kernel that walks `tiles` tiles: causal kernels pair tile p with

@@ -75,15 +75,16 @@ class Flow:
         for i, label, always in jumps:
             self.next[i] = [self.at[label]] + ([] if always else [i + 1])
 
-    def in_loop(self, event):
-        """Whether event number `event` can follow itself."""
+    def behind(self, event, *ends):
+        """Numbers of the events that can follow event number `event` with none of the kind `ends` before them."""
         seen, todo = set(), list(self.next[event])
         while todo:
             i = todo.pop()
             if i not in seen and i < len(self.events):
                 seen.add(i)
-                todo += self.next[i]
-        return event in seen
+                if self.events[i] not in ends:
+                    todo += self.next[i]
+        return seen
 
 
 def kernel_flows(asm, name):
@@ -99,7 +100,7 @@ def test_split_backward_does_not_wait_for_the_tile_it_has_requested(asm):
     assert len(kernels) == 16
     for name, flow in kernels:
         runs = [i for i, e in enumerate(flow.events) if e == "tile" and (i == 0 or flow.events[i - 1] != "tile")]
-        loops = [i for i in runs if flow.in_loop(i)]
+        loops = [i for i in runs if i in flow.behind(i)]
         assert len(loops) >= 2, name  # dQ and dK/dV
         for i in loops:
             best = {}  # event -> most operations requested on a way to it
@@ -112,6 +113,19 @@ def test_split_backward_does_not_wait_for_the_tile_it_has_requested(asm):
                 if isinstance(flow.events[k], tuple):
                     assert flow.events[k][1] >= n, (name, flow.events[k], n)
                 todo += [(j, n + (flow.events[k] in ("tile", "row"))) for j in flow.next[k]]
+
+
+@pytest.mark.parametrize("name, kernels", [("mha_bwd_dq_kernel", r"Li\d+ELb0E"), ("mha_bwd_dkdv_pipe_kernel", r"Li(64|96)ELb0E"),
+                                           ("mha_bwd_merged_kernel", r"Li(64|96)ELb0E")])
+def test_rows_and_first_tile_are_requested_together(asm, name, kernels):
+    """Without a mask a backward workgroup requests its rows of Q, K, V, O and dO and its first tile, and only then waits:
+    with a wait in between, the latencies of memory add up at its head."""
+    flows = [(k, f) for k, f in kernel_flows(asm, name) if re.search(kernels, k)]
+    assert len(flows) in (8, 12) and all("row" in f.events for _, f in flows)
+    for kernel, flow in flows:
+        for i in (i for i, e in enumerate(flow.events) if e == "row"):
+            for w in (w for w in flow.behind(i, "tile", "mfma", "barrier") if isinstance(flow.events[w], tuple)):
+                assert "tile" not in {flow.events[k] for k in flow.behind(w, "mfma", "barrier")}, kernel
 
 
 def test_host_binding_needs_no_compiler_but_hipccs(monkeypatch, tmp_path):
