@@ -248,7 +248,15 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
         pk_ds[r8 >> 1] = pack2<T>(ds[r8 - 1], ds[r8]);
       }
     };
-    auto ahead_of = [&](int q0s) { return krow - q0s - 4 * g; };
+    // bf16 with dropout at D = 64 has one register too few for krow - 4 g across the loop (its dS takes a select more): formed
+    // anew where a mask needs it.  Spilled, it was awaited inside the loop, together with the stage just requested
+    // (us, causal 256 heads x 512 39.4 -> 38.5, equal at 256 x 2048; fp16, which does not spill, 38.4 -> 38.8).
+    constexpr bool ANEW = DROP && D == 64 && !F::FINITE_DOT;
+    auto ahead_of = [&](int q0s) {
+      int l = lane;
+      if (ANEW) asm volatile("" : "+v"(l));
+      return ANEW ? k0w - q0s + (l & 31) - 4 * (l >> 5) : krow - q0s - 4 * g;
+    };
     uint32_t kbCur[4] = {0, 0, 0, 0}, kbNew[4] = {0, 0, 0, 0};  // decision bytes of the current / next step
 
     // ---- prologue: stages s_begin and s_begin+1 resident, scores of the first step formed ----
@@ -296,10 +304,11 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
     {
       float p[8], ds[8];
       uint32_t pk_p[4], pk_ds[4];
+      const int ahead_first = CAUSAL ? ahead_of(s_begin * C::BM) : 0;
       if (DROP) keep_bytes_key_lane(dr, head, krow, s_begin * C::BM, lane, kbCur);
 #pragma unroll
       for (int r = 0; r < 8; ++r)
-        softmax_elem(sX, dpX, 0, r, lL, dL, ahead_of(s_begin * C::BM), CAUSAL, kbCur, p, ds, pk_p, pk_ds);
+        softmax_elem(sX, dpX, 0, r, lL, dL, ahead_first, CAUSAL, kbCur, p, ds, pk_p, pk_ds);
       pfL = join_pairs<T>(pk_p);
       dsfL = join_pairs<T>(pk_ds);
     }
@@ -323,7 +332,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       // (sub_new inside the stage rowA / statA point at).
       auto step = [&](f32x16& s_new, f32x16& dp_new, int sub_new, int q0_new, const f32x16& s_cur,
                       const f32x16& dp_cur, int sub_cur, int q0_cur, auto&& request_next) {
-        const int ahead_cur = ahead_of(q0_cur), ahead_new = ahead_of(q0_new);
+        const int ahead_cur = mask ? ahead_of(q0_cur) : 0, ahead_new = mask ? ahead_of(q0_new) : 0;
         const int stat_new = statA;  // request_next may move statA on before the last of its quads is read
         // ---- region 1: scores of the next step  ||  second half of P, dS of the current step ----
         float p[8], ds[8];

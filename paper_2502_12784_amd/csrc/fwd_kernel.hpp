@@ -264,7 +264,13 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
       auto half = [&](auto h_tag, f32x16& s_new, const f32x16& s, int key0, float& rs, const v8 (&pf)[2], Philox& rng) {
         constexpr int h = decltype(h_tag)::value;
         constexpr bool EXP = h == 0 ? !FIRST : !LAST;
-        if (DROP && EXP) rng = keep_query_lane_begin(dr, head, qrow, key0, lane);
+        if (DROP && EXP) {
+          rng = keep_query_lane_begin(dr, head, qrow, key0, lane);
+          // Opaque there: otherwise products of the first rounds are held across the loop, spilled, and their reload
+          // awaited inside it together with the tile just requested (us, 256 heads x 512 25.2 -> 24.7, 512 x 300
+          // 27.9 -> 27.0, equal at 256 x 2048).
+          if (!SPREAD) asm volatile("" : "+v"(rng.c0), "+v"(rng.c1));
+        }
         if (!LAST) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) s_new[r] = 0.f;

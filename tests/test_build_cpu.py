@@ -128,6 +128,21 @@ def test_rows_and_first_tile_are_requested_together(asm, name, kernels):
                 assert "tile" not in {flow.events[k] for k in flow.behind(w, "mfma", "barrier")}, kernel
 
 
+@pytest.mark.parametrize("name", ["mha_fwd_kernel", "mha_bwd_dq_kernel", "mha_bwd_dkdv_pipe_kernel", "mha_bwd_merged_kernel"])
+def test_loops_wait_at_their_barrier_only(asm, name):
+    """A loop over tiles requests the next tile at its top and awaits it at the barrier that ends the round: no wait for
+    vector memory (a spilled value's reload, for one) with products still to come before that barrier."""
+    flows = list(kernel_flows(asm, name))
+    assert len(flows) >= 24
+    for kernel, flow in flows:
+        for i, e in enumerate(flow.events):
+            if e != "tile" or i not in flow.behind(i):
+                continue
+            for w in flow.behind(i, "barrier"):
+                if isinstance(flow.events[w], tuple):
+                    assert "mfma" not in {flow.events[k] for k in flow.behind(w, "barrier")}, kernel
+
+
 def test_host_binding_needs_no_compiler_but_hipccs(monkeypatch, tmp_path):
     """Without g++ the host extension is compiled with the clang++ of the ROCm toolchain."""
     seen = []
