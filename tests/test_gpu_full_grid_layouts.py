@@ -1,11 +1,12 @@
-"""The kernels of full grids (128-row forward, dQ, dK/dV; beyond the sizes that the split and the joint grids take) on
-tensors of other layouts, with head dimensions below the tile width.  First and last head against the oracle.
+"""The kernels of full grids (128-row forward, dQ, dK/dV; beyond the sizes that the split and, but for one case, the
+joint grids take) on tensors of other layouts, with head dimensions below the tile width.  First and last head against
+the oracle, the backward's route against the one stated.
 """
 import math
 
 import pytest
 
-from paper_2502_12784_amd import synth
+from paper_2502_12784_amd import load_library, synth
 from tests import parity_util as pu
 
 pytestmark = pytest.mark.gpu
@@ -17,11 +18,12 @@ CASES = [
     (2, 33, 300, 300, 40, synth.F16, False, 0, "packed"),       # 198 / 396
     (2, 33, 300, 300, 104, synth.BF16, False, 26, "padded"),
     (4, 27, 600, 600, 40, synth.BF16, True, 0, "padded"),       # 540 / 1080
-    (2, 27, 600, 600, 56, synth.F16, True, 26, "packed"),       # 270 / 540
+    (4, 27, 600, 600, 56, synth.F16, True, 26, "packed"),       # 540 / 1080
     (4, 14, 600, 600, 104, synth.F16, True, 0, "bnhd"),         # 280 / 560
     (2, 30, 200, 700, 104, synth.BF16, False, 0, "bnhd"),       # 120 / 480
     (3, 40, 130, 400, 24, synth.F16, False, 26, "padded"),      # 240 / 720
 ]
+ONE_GRID = (2, 27, 600, 600, 56, synth.F16, True, 26, "packed")  # 270 / 540
 
 
 def _store(t, layout):
@@ -35,11 +37,13 @@ def _store(t, layout):
     return s.copy_(t)
 
 
-@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("case", CASES + [ONE_GRID])
 def test_full_grids_on_other_layouts(case):
     import torch
     from paper_2502_12784_amd import spark_mha_strided_bwd, spark_mha_strided_fwd
     B, H, Nq, Nk, d, dtype, causal, thr, layout = case
+    grids = load_library().spark_mha_bwd_grids(B, H, Nq, Nk, d, causal, thr / 256.0, int(dtype == synth.BF16))
+    assert grids == (1 if case == ONE_GRID else 2)
     scale = 1.0 / math.sqrt(d)
     inp = synth.make_inputs(B, H, Nq, d, dtype, seed=9100 + Nq + d, Nk=Nk)
     dev = {n: pu.to_device(inp[n], dtype) for n in ("Q", "K", "V", "dO")}
