@@ -119,6 +119,18 @@ def test_forward_of_causal_heads_of_three_tiles(case):
     assert _forward(H, 300, 300, d, True, p) == [2 * H if paired else 3 * H]
 
 
+# heads, N, d, dropout rate, whether the causal forward has workgroups of 8 waves for 256 rows
+WIDE = [(30, 2303, 80, 0.0, True), (30, 2240, 96, 0.1, True), (30, 2303, 128, 0.0, True), (30, 2047, 96, 0.0, False),
+        (30, 2303, 64, 0.0, False)]
+
+
+@pytest.mark.parametrize("case", WIDE)
+def test_causal_forward_of_wide_workgroups(case):
+    H, N, d, p, wide = case
+    tiles = (N + 255) // 256 if wide else (N + 127) // 128
+    assert _forward(H, N, N, d, True, p, _launches) == [(H * ((tiles + 1) // 2), 512 if wide else 256)]
+
+
 # heads, Nq, Nk, d, dropout rate, whether both sides run in one grid
 FEW_QUERIES = [(8, 256, 1536, 128, 0.0, True), (8, 256, 1537, 96, 0.0, False), (6, 1, 1600, 128, 0.0, False),
                (4, 100, 5000, 64, 0.0, True), (8, 256, 2432, 128, 0.1, True), (8, 256, 2433, 128, 0.1, False),

@@ -21,6 +21,11 @@ CASES = [
     (64, 513, 770, 96, torch.bfloat16, False, 0.2, 2),
     (10, 1100, 1000, 80, torch.bfloat16, False, 0.0, 1),
     (12, 1030, 1030, 72, torch.float16, True, 0.1, 1),
+    # causal 256-row workgroups, in pairs: nine tiles of them a head, the middle one alone; 36 and 35 tiles of 64 keys
+    (30, 2303, 2303, 80, torch.float16, True, 0.0, 2),
+    (30, 2303, 2303, 96, torch.bfloat16, True, 0.1, 2),
+    (30, 2240, 2240, 96, torch.float16, True, 0.1, 2),
+    (30, 2240, 2240, 72, torch.bfloat16, True, 0.0, 2),
 ]
 
 
