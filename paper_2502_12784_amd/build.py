@@ -123,7 +123,7 @@ def kernel_resources() -> str:
         get = lambda key: int(re.search(key + r": (\d+)", block).group(1))
         # scratch traffic inside the kernel body: count the spill instructions the assembly holds
         body = asm[asm.index(mangled + ":"):]
-        body = body[:body.index("s_endpgm")]
+        body = body[:body.index("\n.Lfunc_end")]  # not the first s_endpgm: a kernel may end in several places
         # ... and how many of them sit in an innermost loop that holds matrix instructions, i.e. in one
         # of the loops over tiles (the rest is prologue / epilogue code, run once per tile).  A loop is
         # a branch back to an earlier label; innermost = no other such range inside it.
