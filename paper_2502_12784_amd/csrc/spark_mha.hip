@@ -182,12 +182,14 @@ bool wide_workgroups(const Problem& p) {
 //    30.3/42.0/44.2 -> 24.8/33.6/37.1; N = 4096 d = 64 53.6/61.9/75.8 -> 49.3/55.6/70.4; from 320 tiles on
 //    the pairs win: N = 4096 53.5/61.5/75.9 against 67.8/81.3/100.8);
 //  * two tiles per head while all are resident: lengths differ by a factor of two at most (512 tiles, d = 64
-//    12.2/19.5/18.6 -> 10.5/17.0/17.8);
+//    12.2/19.5/18.6 -> 10.5/17.0/17.8; dK/dV with dropout 130 x 256 19.5 -> 18.4, 256 x 256 21.4 -> 20.5, 256 x 192
+//    equal; both sides in one grid 66 x 256 19.5 -> 18.2, 128 x 200 19.9 -> 19.4);
 //  * three tiles per head: the middle one stays alone in a workgroup with half the others' work (2049 tiles,
 //    d = 128: 79/135/175 -> 65/108/139), unless a kernel with one workgroup per CU fits its pairs in one round and
 //    its tiles not (dK/dV, d = 128, paired / unpaired: 92 heads 28.4 / 30.8, 118 heads 24.8 / 30.0, 127 heads
 //    30.1 / 34.0; both sides in one grid, 47 heads 25.3 / 27.2, 59 heads 26.8 / 32.4; but 86 heads, two tiles
-//    too many, 24.2 / 19.2, and 132 heads, pairs in two rounds, unpaired is 0.7 of it).
+//    too many, 24.2 / 19.2, and 132 heads, pairs in two rounds, unpaired is 0.7 of it; d = 64, two per CU, with dropout
+//    100 x 384 22.5 / 21.5, both sides 64 x 384 22.8 / 20.2, 45 x 300 18.7 / 17.7).
 int pair_tiles(bool causal, int64_t bh, int n, int per_cu) {
   if (!causal || bh * n <= 256) return 0;
   if (n == 3) return per_cu == 1 && bh > 88 && bh <= 128;
@@ -412,7 +414,9 @@ bool merged_backward(const Problem& p) {
   return n <= 256 || (per_cu == 2 && n <= 512 && p.Nq >= 1024 && p.Nk >= 1024);
 }
 
-template <typename T, int D, bool CAUSAL, bool DROP, int PER_CU>
+template <int D> constexpr int dkdv_per_cu = D == 64 ? 2 : 1;  // workgroups of the dK/dV and of the merged kernel on a CU
+
+template <typename T, int D, bool CAUSAL, bool DROP>
 int launch_bwd_merged(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const float* LSE,
                       const void* dO, void* dQ, void* dK, void* dV, float* Dws) {
   auto kernel = mha_bwd_merged_kernel<T, D, CAUSAL, DROP>;
@@ -429,7 +433,7 @@ int launch_bwd_merged(const Problem& p, const void* Q, const void* K, const void
                      p.d, rows, DROP ? dr.keep_prob : 1.0f);
   if (!launch_ok("backward statistics kernel")) return SPARK_ERR_LAUNCH;
   const int nqt = (p.Nq + 127) / 128, nkt = (p.Nk + 127) / 128;
-  const int paired = pair_tiles(CAUSAL, 2 * (int64_t)BH, nqt, PER_CU);
+  const int paired = pair_tiles(CAUSAL, 2 * (int64_t)BH, nqt, dkdv_per_cu<D>);
   const int items = paired ? 2 * causal_items<true>(nqt) : nqt + nkt;
   hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * items)), dim3(256), SMEM, p.st, static_cast<const T*>(Q),
                      static_cast<const T*>(K), static_cast<const T*>(V), static_cast<const T*>(dO), Dws, LSE2ws,
@@ -461,9 +465,8 @@ int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, co
     if (rc != SPARK_OK) return rc;
     return mark(1) && mark(2) ? SPARK_OK : SPARK_ERR_LAUNCH;
   }
-  constexpr int PER_CU = D == 64 && !DROP ? 2 : 1;  // in pair_tiles; with dropout two fit at d = 64, too, and the line is kept
   if (merged_backward(p)) {
-    const int rc = launch_bwd_merged<T, D, CAUSAL, DROP, PER_CU>(p, Q, K, V, O, LSE, dO, dQ, dK, dV, Dws);
+    const int rc = launch_bwd_merged<T, D, CAUSAL, DROP>(p, Q, K, V, O, LSE, dO, dQ, dK, dV, Dws);
     if (rc != SPARK_OK) return rc;
     return mark(1) && mark(2) ? SPARK_OK : SPARK_ERR_LAUNCH;
   }
@@ -488,7 +491,7 @@ int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, co
     const int attr = ensure_smem(kernel, C::SMEM, ready);
     if (attr != SPARK_OK) return attr;
     const int nkt = (p.Nk + C::BN - 1) / C::BN;
-    const int paired = pair_tiles(CAUSAL, BH, nkt, PER_CU);
+    const int paired = pair_tiles(CAUSAL, BH, nkt, dkdv_per_cu<D>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * (paired ? causal_items<true>(nkt) : nkt))), dim3(256), C::SMEM, p.st,
                        q, k, v, dout, LSE2ws, Dws, static_cast<T*>(dK), static_cast<T*>(dV), p.mq, p.mk,
                        p.mv, p.mdo, p.mdk, p.mdv, p.H, p.Nq, p.Nk, p.d, nkt, paired, p.scale, dr);
