@@ -89,7 +89,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
 
   // D = 64: few offset registers (250 instead of 256 registers with dropout, causal 16 instead of 52 bytes of spills:
   // dK/dV, us, 256 causal heads x 512 44.1 -> 41.4; without dropout 0 ... 1 % less)
-  using LaneOffsets = std::conditional_t<D == 64, SwzLaneLean<D, true>, SwzLane<D>>;
+  using LaneOffsets = std::conditional_t<D == 64, SwzLaneLean<D>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -499,11 +499,9 @@ static __device__ __forceinline__ void bwd_dq(
   using C = BwdQCfg<D, CAUSAL, DROP>;
   constexpr int KS = D / 16, DT = D / 32;
 
-  // few offset registers in the causal kernels (dQ, us: fp16 with dropout, D = 128, 512 heads x 512 135 -> 121; bf16,
-  // D = 128, 256 x 512 55.7 -> 54.5; fp16, D = 64, 256 x 512 31.8 -> 31.4, when wave indices took vector registers;
-  // since then equal, and 10 ... 25 registers less)
-  constexpr int LEAN = !CAUSAL ? 0 : (D > 64) == DROP ? 2 : 1;
-  using LaneOffsets = std::conditional_t<LEAN != 0, SwzLaneLean<D, LEAN == 2>, SwzLane<D>>;
+  // few offset registers in the causal kernels: with dropout at D = 128 all of them spill (dQ, us, 512 heads x 512 115.7 ->
+  // 108.4, bf16 64 x 2048 122.3 -> 118.3; the others are equal)
+  using LaneOffsets = std::conditional_t<CAUSAL, SwzLaneLean<D>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -78,7 +78,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
   // heads x 512 72.3 -> 77.0 us; without dropout equal).  A spilled value that is reloaded in front of the loop
   // makes the compiler wait, inside it, for every outstanding vector memory operation, that is for the tile the
   // round has just requested.
-  using LaneOffsets = std::conditional_t<CAUSAL, SwzLaneLean<D, true>, SwzLane<D>>;
+  using LaneOffsets = std::conditional_t<CAUSAL, SwzLaneLean<D>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
 
   // uniform: the rows of the wave, its loop limits and its share of the loads then take scalar registers.  (With that and

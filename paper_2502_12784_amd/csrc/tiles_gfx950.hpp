@@ -165,43 +165,33 @@ template <int D> struct SwzLane {
 // The same offsets from fewer registers, for kernels that have none to spare.  Swizzle and chunk index only meet in
 // exclusive ors (row: chunk 2 ks + g; tr: d-tile dt, and rows 8 h further on, whose swizzle differs in bit 1), so an
 // offset is a base with constant bits flipped: one VALU instruction at its use instead of one to switch the buffer.
-// The row offsets always come from one register; LEAN_TR: the transposing ones, too (they are used more often).
-template <int D, bool LEAN_TR> struct SwzLaneLean {
-  int row0, tr0[LEAN_TR ? 1 : 2][LEAN_TR ? 1 : D / 32];
+template <int D> struct SwzLaneLean {
+  int row0, tr0;
   __device__ __forceinline__ explicit SwzLaneLean(int lane) {
     const SwzLane<D> s(lane);
     row0 = s.row[0];
-#pragma unroll
-    for (int h = 0; h < (LEAN_TR ? 1 : 2); ++h)
-#pragma unroll
-      for (int dt = 0; dt < (LEAN_TR ? 1 : D / 32); ++dt) tr0[h][dt] = s.tr[h][dt];
+    tr0 = s.tr[0][0];
   }
   __device__ __forceinline__ int row_at(int ks) const { return row0 ^ (ks << 5); }
   __device__ __forceinline__ int tr_at(int h, int dt) const {
-    if constexpr (LEAN_TR) return (tr0[0][0] ^ (dt << 6) ^ (h << 5)) + h * 16 * lds_row<D>;
-    return tr0[LEAN_TR ? 0 : h][LEAN_TR ? 0 : dt];
+    return (tr0 ^ (dt << 6) ^ (h << 5)) + h * 16 * lds_row<D>;
   }
+  // opaque: otherwise the offsets of all buffers are formed ahead of the loop
   __device__ __forceinline__ void point_rows(const SwzLaneLean& s, int bytes) {
     row0 = s.row0 + bytes;
     asm volatile("" : "+v"(row0));
   }
   __device__ __forceinline__ void point_tr(const SwzLaneLean& s, int bytes) {
-#pragma unroll
-    for (int h = 0; h < (LEAN_TR ? 1 : 2); ++h)
-#pragma unroll
-      for (int dt = 0; dt < (LEAN_TR ? 1 : D / 32); ++dt) tr0[h][dt] = s.tr0[h][dt] + bytes;
-    if (LEAN_TR) asm volatile("" : "+v"(tr0[0][0]));
+    tr0 = s.tr0 + bytes;
+    asm volatile("" : "+v"(tr0));
   }
   __device__ __forceinline__ void flip_rows(int bits) {
     row0 ^= bits;
-    asm volatile("" : "+v"(row0));  // opaque: otherwise the offsets of both buffers are formed ahead of the loop
+    asm volatile("" : "+v"(row0));
   }
   __device__ __forceinline__ void flip_tr(int bits) {
-#pragma unroll
-    for (int h = 0; h < (LEAN_TR ? 1 : 2); ++h)
-#pragma unroll
-      for (int dt = 0; dt < (LEAN_TR ? 1 : D / 32); ++dt) tr0[h][dt] ^= bits;
-    if (LEAN_TR) asm volatile("" : "+v"(tr0[0][0]));
+    tr0 ^= bits;
+    asm volatile("" : "+v"(tr0));
   }
   __device__ __forceinline__ void flip(int bits) {
     flip_rows(bits);
