@@ -279,8 +279,7 @@ def sweep_table(sweep, cmd, steps, warmup):
           "at 14-23 % of the MFMA peak.  A CU then holds one to three workgroups whose 4-10 iterations each cost a full "
           "dependent chain (tile load, score MFMAs, softmax, PV MFMAs): latency and the per-tile prologue / epilogue "
           "bound these points, not bandwidth or the matrix cores.",
-          "At d = 64 the dK/dV kernel with dropout needs more than 256 registers and runs one wave per SIMD, hence the "
-          "larger gap there."]
+          "At d = 64 the generator's integer multiplies bound the kernels with dropout (VALU), hence the larger gap there."]
     return "\n".join(L) + "\n"
 
 

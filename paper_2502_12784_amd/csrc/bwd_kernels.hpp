@@ -67,7 +67,7 @@ template <int D> struct BwdKvPipeCfg {
 // dS of one entry under dropout in the dK/dV kernels, P o (M o dP + d): pe = P, pm = M o P, d = -D (1-p).  With
 // the mask already in pm one select is saved, but only where dP cannot overflow: 0 * inf would turn a dropped
 // entry whose dP is past fp32's range into NaN.  (bf16 without that saving: dK/dV 885 -> 914 us at 256 heads x
-// 2048, d = 64, and 639 -> 648 at 64 x 4096 causal, d = 128.)
+// 2048, d = 64, with one workgroup per CU as it then was, and 639 -> 648 at 64 x 4096 causal, d = 128.)
 template <typename T>
 static __device__ __forceinline__ float dropout_ds(bool keep, float pe, float pm, float dp, float d) {
   if (Frag<T>::FINITE_DOT) return __builtin_fmaf(pm, dp, pe * d);
@@ -87,8 +87,8 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
   using C = BwdKvPipeCfg<D>;
   constexpr int KS = D / 16, DT = D / 32;
 
-  // D = 64: few offset registers (250 instead of 256 registers with dropout, causal 16 instead of 52 bytes of spills:
-  // dK/dV, us, 256 causal heads x 512 44.1 -> 41.4; without dropout 0 ... 1 % less)
+  // D = 64: few offset registers; with dropout the kernel needs 248 to 255 of its 256 and spilled with all of them
+  // (dK/dV, us, 256 causal heads x 512 44.1 -> 41.4; without dropout 0 ... 1 % less)
   using LaneOffsets = std::conditional_t<D == 64, SwzLaneLean<D>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
 
@@ -169,7 +169,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       }
     };
     // statistics of 8 of the 16 query rows a lane holds (half = 0: registers 0..7, 1: 8..15) of the
-    // step rowA / statA point at
+    // step offA / statA point at
     auto load_stats = [&](f32x4 (&l)[2], f32x4 (&d)[2], int sub, int half) {
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
@@ -320,8 +320,8 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
     }
 
     // One stage: steps (m, 0) and (m, 1).  On entry sX / dpX hold the scores of (m, 0), pfL / dsfL
-    // their first half and lH / dH the statistics of their second half; rowA and trC point at
-    // stage m.  On exit the same holds for (m+1, 0).
+    // their first half and lH / dH (RING: lL / dL, quads 2 and 3) the statistics of their second half;
+    // offA, statA and offC point at stage m.  On exit the same holds for (m+1, 0).
     auto stage = [&](int m, int slot, bool mask) {
       const int slot1 = slot == 2 ? 0 : slot + 1;
       const int slot2 = slot1 == 2 ? 0 : slot1 + 1;
@@ -329,7 +329,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       if (m + 2 < ns) fetch_stage(m + 2, slot2);
 
       // One step.  cur: scores complete, first half of P / dS packed.  new: the step after it
-      // (sub_new inside the stage rowA / statA point at).
+      // (sub_new inside the stage offA / statA point at).
       auto step = [&](f32x16& s_new, f32x16& dp_new, int sub_new, int q0_new, const f32x16& s_cur,
                       const f32x16& dp_cur, int sub_cur, int q0_cur, auto&& request_next) {
         const int ahead_cur = mask ? ahead_of(q0_cur) : 0, ahead_new = mask ? ahead_of(q0_new) : 0;

@@ -27,8 +27,9 @@
 //     several MFMAs ahead and pinned there with scheduler fences.  (Within one tile the first scores and the last
 //     products had no VALU work beside them.  Forward, us, that -> this: bf16, d = 128, 64 heads x 1024 over
 //     4096 keys 133.8 -> 128.1, causal 64 x 4096 256.6 -> 251.2; fp16, causal 16 x 16384 1006 -> 984, d = 64 32 x
-//     8192 597 -> 590.  The loops run at 50 ... 60 % of the matrix cores' rate, at a clock that the power limit
-//     holds at 1.75 ... 2.0 of 2.4 GHz.)
+//     8192 597 -> 590.  The loop takes 27 ns per MFMA and SIMD at d = 128 in bf16 (64 heads x 1024, 4096
+//     keys against 8192) and 36.5 at d = 64 in fp16; its instructions in a straight line take 24 and 32
+//     (mix_floor_bench), the MFMAs alone 18.5 and 20.)
 //   * Workgroups of 4 waves (128 queries, two per CU) or of 8 waves (256 queries, one per CU):
 //     with 8 waves each K/V tile that is brought into LDS serves twice as many MFMAs (measured
 //     -4 % at d = 128 on long sequences, +2 % at d = 64); the host picks per problem.  The 8-wave
@@ -82,8 +83,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
   SPARK_LDS char* const smem = lds_origin();
 
   // uniform: the rows of the wave, its loop limits and its share of the loads then take scalar registers.  (With that and
-  // the lane index read anew in the epilogue, 17 ... 25 vector registers less: no kernel but the causal one with dropout at
-  // d = 64 spills, causal d = 64 128 x 1024 31.8 -> 29.3 us, d = 80 36 x 1333 29.4 -> 27.1, d = 64 96 x 512 14.4 -> 13.2.)
+  // the lane index read anew in the epilogue, 17 ... 25 vector registers less and no spills: causal d = 64 128 x 1024
+  // 31.8 -> 29.3 us, d = 80 36 x 1333 29.4 -> 27.1, d = 64 96 x 512 14.4 -> 13.2.)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, c32 = lane & 31;
   const uint32_t k_row_bytes = (uint32_t)mk.row * 2, v_row_bytes = (uint32_t)mv.row * 2;

@@ -165,7 +165,9 @@ int ensure_smem(KernelT kernel, int bytes, std::atomic<uint64_t>& done) {
 // Checked over 68 problems around these two classes (medians in alternating order; with dropout and d = 72 ... 104 among them):
 // 0.85 ... 0.99 of the narrow kernel's time at all that are taken, among them causal 64 x 2048 83.9 -> 78.5 and with dropout
 // 101.7 -> 98.5, 43 x 700 over 2048 (129 against 258, the fewest) 56.1 -> 52.4, 450 x 250 over 2100 152.9 -> 150.9; not
-// taken 1.08 ... 1.76, except 20 x 5000 (400, d = 96) 273.6 -> 247.3.
+// taken 1.08 ... 1.76, except 20 x 5000 (400, d = 96) 273.6 -> 247.3.  The kernels of 96 columns, over 19 problems on both
+// sides: taken 0.91 ... 0.98 (43 x 700 over 2048 42.6 -> 39.2, causal 24 x 4096 93.4 -> 84.8, 128 x 2048 118.5 -> 115.9), not
+// taken 1.07 ... 1.14, except 20 x 5000 232.0 -> 210.3 and, with fewer keys, 64 x 1024 30.9 -> 29.2.
 template <bool CAUSAL>
 bool wide_workgroups(const Problem& p) {
   const int64_t bh = (int64_t)p.B * p.H;
@@ -189,7 +191,8 @@ bool wide_workgroups(const Problem& p) {
 //    its tiles not (dK/dV, d = 128, paired / unpaired: 92 heads 28.4 / 30.8, 118 heads 24.8 / 30.0, 127 heads
 //    30.1 / 34.0; both sides in one grid, 47 heads 25.3 / 27.2, 59 heads 26.8 / 32.4; but 86 heads, two tiles
 //    too many, 24.2 / 19.2, and 132 heads, pairs in two rounds, unpaired is 0.7 of it; d = 64, two per CU, with dropout
-//    100 x 384 22.5 / 21.5, both sides 64 x 384 22.8 / 20.2, 45 x 300 18.7 / 17.7).
+//    100 x 384 22.5 / 21.5, both sides 64 x 384 22.8 / 20.2, 45 x 300 18.7 / 17.7; 96 columns as 128: 92 heads x 384
+//    23.8 / 25.3, 127 24.8 / 28.6, but 86 23.7 / 19.6, 129 42.6 / 28.7; two tiles 140 x 256 21.2 / 25.6, 250 25.3 / 29.8).
 int pair_tiles(bool causal, int64_t bh, int n, int per_cu) {
   if (!causal || bh * n <= 256) return 0;
   if (n == 3) return per_cu == 1 && bh > 88 && bh <= 128;
@@ -209,7 +212,7 @@ int launch_fwd_nw(const Problem& p, const void* Q, const void* K, const void* V,
   // Three tiles per head at two workgroups per CU: paired only where the pairs fit one round and the tiles are well
   // past it, and only here (d = 128, paired / unpaired us: 188 x 384 27.1 / 25.6, 200 x 300 23.6 / 24.4, 233 x 270
   // 24.1 / 26.0, 257 x 306 34.6 / 25.7; with dropout 228 x 384 35.3 / 34.8; at d = 64 three workgroups fit, and dQ
-  // gains unpaired: 244 heads 0.9 of it).
+  // gains unpaired: 244 heads 0.9 of it; at 96 columns 200 x 300 16.4 / 16.2, 233 x 270 16.6 / 17.0, 256 x 384 20.2 / 19.6).
   const bool one_round = D > 64 && !DROP && nqt == 3 && BH > 192 && BH <= 256;
   const int paired = CAUSAL && one_round ? 1 : pair_tiles(CAUSAL, BH, nqt, NW == 4 ? 2 : 1);
   hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * (paired ? causal_items<true>(nqt) : nqt))), dim3(64 * NW), C::SMEM,
@@ -404,7 +407,10 @@ int launch_bwd_split(const Problem& p, const void* Q, const void* K, const void*
 //                           1.3 of them without dropout, 1.15 with), against a launch and the other side's chain: 6 x 323 over 1457 50.5 -> 47.6,
 //                           9 x 669 over 2235 73.9 -> 69.8, but 1 x 2 over 10565 227 -> 294, 4 x 32 over 4379 105 -> 127,
 //                           6 x 254 over 1858 58.6 -> 59.8, 2 x 992 over 5424 146 -> 155; dropout 6 x 450 over 2837
-//                           106 -> 102, but 2 x 592 over 4902 169 -> 172 (the line is where both are equal within 2 %)
+//                           106 -> 102, but 2 x 592 over 4902 169 -> 172 (the line is where both are equal within 2 %; at 96 columns
+//                           one grid wins up to 5 % further: 8 x 256 over 1536 37.3 -> 35.2, 1900 43.2 -> 42.3, 2400 50.4 -> 51.5,
+//                           4 x 512 over 2400 55.6 -> 51.3, 3000 63.9 -> 61.8, 3500 equal; dropout 6 x 450 over 2837 79.1 -> 74.6,
+//                           4500 111.4 -> 113.4)
 bool merged_backward(const Problem& p) {
   const int per_cu = p.d <= 64 && !(p.thr && p.causal && p.Nq <= 384) ? 2 : 1;  // which line, as measured above
   if (p.d > 64 && !p.causal && p.Nk > (p.thr ? 7 * (int64_t)p.Nq + 640 : 4 * (int64_t)p.Nq + 512)) return false;
