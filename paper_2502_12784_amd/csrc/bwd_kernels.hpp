@@ -18,8 +18,8 @@
 // gives bitwise reproducible gradients.  Both variants exist and were timed on the same inputs
 // (the atomic one is in bwd_atomic_kernels.hpp): with 128 keys per workgroup it adds N/128 fp32
 // values per dQ element, 2.2 GB for N = 4096, d = 128, 64 heads, causal; MI355X performs
-// device-scope atomics at the memory side, at 1.3 TB/s, so that variant takes 1.76 ms where these
-// two kernels take 0.95 ms.
+// device-scope atomics at the memory side, at 1.3 TB/s, so that variant takes 1.75 ms where these
+// two kernels take 0.91 ms.
 //
 // Register layouts follow mma_gfx950.hpp.  In the dK/dV kernels the score tile is computed as
 // S = Q K^T (lane = key column, registers = query rows) so that P and dS, packed to 16 bits,

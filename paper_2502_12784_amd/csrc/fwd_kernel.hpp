@@ -27,9 +27,9 @@
 //     several MFMAs ahead and pinned there with scheduler fences.  (Within one tile the first scores and the last
 //     products had no VALU work beside them.  Forward, us, that -> this: bf16, d = 128, 64 heads x 1024 over
 //     4096 keys 133.8 -> 128.1, causal 64 x 4096 256.6 -> 251.2; fp16, causal 16 x 16384 1006 -> 984, d = 64 32 x
-//     8192 597 -> 590.  The loop takes 27 ns per MFMA and SIMD at d = 128 in bf16 (64 heads x 1024, 4096
-//     keys against 8192) and 36.5 at d = 64 in fp16; its instructions in a straight line take 24 and 32
-//     (mix_floor_bench), the MFMAs alone 18.5 and 20.)
+//     8192 597 -> 590.  The loop takes 26.5 ns per MFMA and SIMD at d = 128 in bf16 (64 heads x 1024, 2048
+//     keys against 4096) and 36.5 at d = 64 in fp16; its instructions in a straight line take 24 and 32
+//     (mix_floor_bench), the MFMAs alone 18 and 20.)
 //   * Workgroups of 4 waves (128 queries, two per CU) or of 8 waves (256 queries, one per CU):
 //     with 8 waves each K/V tile that is brought into LDS serves twice as many MFMAs (measured
 //     -4 % at d = 128 on long sequences, +2 % at d = 64); the host picks per problem.  The 8-wave
