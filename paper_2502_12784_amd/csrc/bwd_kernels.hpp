@@ -93,7 +93,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
   SPARK_LDS char* const smem = lds_origin();
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, c32 = lane & 31;
+  const int g = lane >> 5, c32 = column_row<DROP>(lane);
 
   const T* Kh = K + head_base(mk, head, H);
   const T* Vh = V + head_base(mv, head, H);
@@ -255,7 +255,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
     auto ahead_of = [&](int q0s) {
       int l = lane;
       if (ANEW) asm volatile("" : "+v"(l));
-      return ANEW ? k0w - q0s + (l & 31) - 4 * (l >> 5) : krow - q0s - 4 * g;
+      return ANEW ? k0w - q0s + column_row<DROP>(l) - 4 * (l >> 5) : krow - q0s - 4 * g;
     };
     uint32_t kbCur[4] = {0, 0, 0, 0}, kbNew[4] = {0, 0, 0, 0};  // decision bytes of the current / next step
 
@@ -367,7 +367,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
           }
           sched_fence();
         }
-        if (DROP) keep_key_lane_finish(rng, lane, kbNew);
+        if (DROP) keep_key_lane_finish(rng, kbNew);
         const v8 pfH = join_pairs<T>(pk_p), dsfH = join_pairs<T>(pk_ds);
         if (!RING) load_stats(lH, dH, sub_new, 1);
         sched_fence();
@@ -445,9 +445,9 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
     }
 
     SPARK_LDS char* ob = smem + wave * 32 * C::OSTR;
-    store_transposed<T, D, C::OSTR>(dk, DROP ? scale * dr.rescale : scale, ob, dK + head_base(mdk, head, H), k0w,
+    store_transposed<T, D, C::OSTR, DROP>(dk, DROP ? scale * dr.rescale : scale, ob, dK + head_base(mdk, head, H), k0w,
                                     Nk, lane, (size_t)mdk.row, dh);
-    store_transposed<T, D, C::OSTR>(dv, DROP ? dr.rescale : 1.0f, ob, dV + head_base(mdv, head, H), k0w, Nk,
+    store_transposed<T, D, C::OSTR, DROP>(dv, DROP ? dr.rescale : 1.0f, ob, dV + head_base(mdv, head, H), k0w, Nk,
                                     lane, (size_t)mdv.row, dh);
   }  // rep
 }
@@ -505,7 +505,7 @@ static __device__ __forceinline__ void bwd_dq(
   SPARK_LDS char* const smem = lds_origin();
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, c32 = lane & 31;
+  const int g = lane >> 5, c32 = column_row<DROP>(lane);
 
   const T* Qh = Q + head_base(mq, head, H);
   const T* dOh = dO + head_base(mdo, head, H);
@@ -686,7 +686,7 @@ static __device__ __forceinline__ void bwd_dq(
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt) {
             dp[mt] = F::mfma(fa[(KS + ks) % AHEAD][mt], dof[ks], dp[mt]);
-            if (DROP && ks == 0) keep_query_lane_finish(rng[mt], lane, keep[mt]);
+            if (DROP && ks == 0) keep_query_lane_finish(rng[mt], keep[mt]);
 #pragma unroll
             for (int x = ks * 16 / KS; x < (ks + 1) * 16 / KS; ++x) p_elem(mt * 16 + x);  // 16 in KS MFMAs
             sched_fence();
@@ -745,7 +745,7 @@ static __device__ __forceinline__ void bwd_dq(
     for (; j < nt; ++j) iteration(j, std::true_type{});
 
     SPARK_LDS char* ob = smem + wave * 32 * C::OSTR;
-    store_transposed<T, D, C::OSTR>(dq, DROP ? scale * dr.rescale : scale, ob, dQ + head_base(mdq, head, H), q0,
+    store_transposed<T, D, C::OSTR, DROP>(dq, DROP ? scale * dr.rescale : scale, ob, dQ + head_base(mdq, head, H), q0,
                                     Nq, lane, (size_t)mdq.row, dh);
   }  // rep
 }

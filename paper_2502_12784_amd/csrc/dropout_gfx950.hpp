@@ -10,9 +10,9 @@
 //   u = byte (j mod 4) of x[i mod 4];   keep iff u >= thr;   survivors scaled by 256 / (256 - thr)
 // One call therefore covers a block of 4 queries x 4 keys.  In the MFMA accumulator layout a
 // lane holds, per 32 x 32 block, four strips of four consecutive rows of one column: four 1 x 4
-// (or 4 x 1) pieces of four different calls.  The four lanes of a quad hold the complementary
-// pieces of the same four calls, so each lane evaluates one call and the quad exchanges the
-// words (a 4 x 4 transpose by DPP moves): one generator call per 16 entries, none wasted.
+// (or 4 x 1) pieces of four different calls.  Four lanes hold the complementary pieces of the same
+// four calls, so each of them evaluates one call and they exchange the words (a 4 x 4
+// transpose): one generator call per 16 entries, none wasted.
 #pragma once
 #include <stdint.h>
 
@@ -65,69 +65,76 @@ static __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, u
   out[0] = s.c0; out[1] = s.c1; out[2] = s.c2; out[3] = s.c3;
 }
 
-// 4 x 4 transpose inside every quad: on return x[a] holds what lane a of the quad had in x[w],
-// w = this lane's position in the quad.  Two butterfly steps (partner lane w^1, then w^2), each
-// exchanging the two words that differ in that bit: 4 DPP moves and 12 selects.
-static __device__ __forceinline__ void quad_transpose(uint32_t (&x)[4], int w) {
-  const bool odd = w & 1, upper = w & 2;
+// Row of a block of 32 that a lane's column of the products stands for.  With dropout rows r and lanes are permuted, so that
+// the four rows of a call sit in lanes that differ in bits 3 (r bit 0) and 4 (r bit 1): across those a register
+// moves for half the instructions it takes inside a quad (exchange_words).
+template <bool DROP> static __device__ __forceinline__ int column_row(int lane) {
+  return DROP ? (lane & 7) << 2 | ((lane >> 3) & 3) : lane & 31;
+}
+static __device__ __forceinline__ int call_strip(int lane) { return (lane >> 3) & 3; }  // = column_row<true>(lane) % 4
+
+// 4 x 4 transpose over the four lanes of a call: on return x[a] holds what the lane of strip a had in x[w], w = this lane's
+// strip.  Two butterfly steps, each exchanging the two words that differ in that bit of w: across lane bit 3 a DPP move
+// into half of the lanes for each word (row_ror:8, banks of four lanes), across bit 4 one swap for two words.  8
+// instructions with the copies; inside a quad, where a move cannot be held to some of the lanes, it was 4 moves and 12 selects
+// (forward and backward, us, fp16, d = 64, 256 heads x 2048 1623 -> 1599; causal, d = 128, 512 x 512 351.5 -> 350.3).
+static __device__ __forceinline__ void exchange_words(uint32_t (&x)[4]) {
 #pragma unroll
-  for (int k = 0; k < 4; k += 2) {  // words k, k+1 <-> lane bit 0
-    const uint32_t send = odd ? x[k] : x[k + 1];
-    const uint32_t recv = (uint32_t)__builtin_amdgcn_mov_dpp((int)send, 0xB1, 0xF, 0xF, true);  // quad_perm [1,0,3,2]
-    x[k] = odd ? recv : x[k];
-    x[k + 1] = odd ? x[k + 1] : recv;
+  for (int k = 0; k < 4; k += 2) {
+    const int lo = (int)x[k], hi = (int)x[k + 1];
+    x[k] = (uint32_t)__builtin_amdgcn_update_dpp(lo, hi, 0x128, 0xF, 0xC, false);
+    x[k + 1] = (uint32_t)__builtin_amdgcn_update_dpp(hi, lo, 0x128, 0xF, 0x3, false);
   }
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {  // words k, k+2 <-> lane bit 1
-    const uint32_t send = upper ? x[k] : x[k + 2];
-    const uint32_t recv = (uint32_t)__builtin_amdgcn_mov_dpp((int)send, 0x4E, 0xF, 0xF, true);  // quad_perm [2,3,0,1]
-    x[k] = upper ? recv : x[k];
-    x[k + 2] = upper ? x[k + 2] : recv;
+  for (int k = 0; k < 2; ++k) {
+    const auto s = __builtin_amdgcn_permlane16_swap(x[k], x[k + 2], false, false);
+    x[k] = s[0];
+    x[k + 2] = s[1];
   }
 }
 
 // Lane = query column (S^T layouts of the forward and dQ kernels).  The lane's query is
-// `qrow` (qrow mod 4 == lane mod 4) and it holds keys kblk + 8a + 4g + b of the 32-key block
+// `qrow` (row column_row<true>(lane) of its block) and it holds keys kblk + 8a + 4g + b of the 32-key block
 // starting at kblk (a multiple of 32), g = lane / 32.  kb[a] receives the four decision bytes of
 // strip a: byte b belongs to accumulator register 4a + b.
 // In three parts (counter, ten rounds of philox_round, exchange), see keep_key_lane_begin.
 static __device__ __forceinline__ Philox keep_query_lane_begin(const Dropout& dr, int head, int qrow, int kblk,
                                                                int lane) {
-  const int w = lane & 3, g = lane >> 5;  // this lane evaluates the call of strip a = w
+  const int w = call_strip(lane), g = lane >> 5;  // this lane evaluates the call of strip a = w
   return Philox{(uint32_t)((kblk >> 2) + 2 * w + g), (uint32_t)(qrow >> 2), (uint32_t)head, dr.offset};
 }
-static __device__ __forceinline__ void keep_query_lane_finish(const Philox& s, int lane, uint32_t (&kb)[4]) {
-  // strip a needs word (query mod 4) = w of the call that lane a of the quad evaluated
+static __device__ __forceinline__ void keep_query_lane_finish(const Philox& s, uint32_t (&kb)[4]) {
+  // strip a needs word (query mod 4) = w of the call that the lane of strip a evaluated
   kb[0] = s.c0; kb[1] = s.c1; kb[2] = s.c2; kb[3] = s.c3;
-  quad_transpose(kb, lane & 3);
+  exchange_words(kb);
 }
 static __device__ __forceinline__ void keep_bytes_query_lane(const Dropout& dr, int head, int qrow,
                                                              int kblk, int lane, uint32_t (&kb)[4]) {
   Philox s = keep_query_lane_begin(dr, head, qrow, kblk, lane);
 #pragma unroll
   for (int round = 0; round < 10; ++round) philox_round(s, dr.key0, dr.key1, round);
-  keep_query_lane_finish(s, lane, kb);
+  keep_query_lane_finish(s, kb);
 }
 
 // Lane = key column (S layouts of the dK/dV kernel).  The lane's key is `krow`
-// (krow mod 4 == lane mod 4) and it holds queries qblk + 8a + 4g + b of the 32-query block
+// (row column_row<true>(lane) of its block) and it holds queries qblk + 8a + 4g + b of the 32-query block
 // starting at qblk (a multiple of 32).  kb[a] as above: byte b belongs to register 4a + b.
 // In three parts (counter, ten rounds of philox_round, exchange) so that the kernel can spread
 // the rounds over its MFMA slots; keep_bytes_key_lane runs them back to back.
 static __device__ __forceinline__ Philox keep_key_lane_begin(const Dropout& dr, int head, int krow, int qblk,
                                                              int lane) {
-  const int w = lane & 3, g = lane >> 5;  // this lane evaluates the call of strip a = w
+  const int w = call_strip(lane), g = lane >> 5;  // this lane evaluates the call of strip a = w
   return Philox{(uint32_t)(krow >> 2), (uint32_t)((qblk >> 2) + 2 * w + g), (uint32_t)head, dr.offset};
 }
-static __device__ __forceinline__ void keep_key_lane_finish(const Philox& s, int lane, uint32_t (&kb)[4]);
+static __device__ __forceinline__ void keep_key_lane_finish(const Philox& s, uint32_t (&kb)[4]);
 static __device__ __forceinline__ void keep_bytes_key_lane(const Dropout& dr, int head, int krow,
                                                            int qblk, int lane, uint32_t (&kb)[4]) {
   Philox s = keep_key_lane_begin(dr, head, krow, qblk, lane);
 #pragma unroll
   for (int round = 0; round < 10; ++round) philox_round(s, dr.key0, dr.key1, round);
-  keep_key_lane_finish(s, lane, kb);
+  keep_key_lane_finish(s, kb);
 }
-static __device__ __forceinline__ void keep_key_lane_finish(const Philox& s, int lane, uint32_t (&kb)[4]) {
+static __device__ __forceinline__ void keep_key_lane_finish(const Philox& s, uint32_t (&kb)[4]) {
   // byte k of the call's four words (queries) belongs to the lane with key mod 4 = k: 4 x 4 byte transpose
   // inside the lane (8 byte permutes), then word k of strip a's call to lane k
   const uint32_t a01 = __builtin_amdgcn_perm(s.c1, s.c0, 0x05010400u);  // c0[0] c1[0] c0[1] c1[1]
@@ -138,7 +145,7 @@ static __device__ __forceinline__ void keep_key_lane_finish(const Philox& s, int
   kb[1] = __builtin_amdgcn_perm(a23, a01, 0x07060302u);
   kb[2] = __builtin_amdgcn_perm(b23, b01, 0x05040100u);
   kb[3] = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
-  quad_transpose(kb, lane & 3);
+  exchange_words(kb);
 }
 
 // decision for accumulator register r (0..15) from the bytes of its strip

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
   // the lane index read anew in the epilogue, 17 ... 25 vector registers less and no spills: causal d = 64 128 x 1024
   // 31.8 -> 29.3 us, d = 80 36 x 1333 29.4 -> 27.1, d = 64 96 x 512 14.4 -> 13.2.)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, c32 = lane & 31;
+  const int g = lane >> 5, c32 = column_row<DROP>(lane);
   const uint32_t k_row_bytes = (uint32_t)mk.row * 2, v_row_bytes = (uint32_t)mv.row * 2;
   const uint32_t k_lane_src = dma_lane_src<D>(wave & 3, lane, k_row_bytes, dh);
   const uint32_t v_lane_src = dma_lane_src<D>(wave & 3, lane, v_row_bytes, dh);
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
 #pragma unroll
             for (int q = 0; q < 10; ++q) philox_round<true>(rng, dr.key0, dr.key1, q);
           }
-          keep_query_lane_finish(rng, lane, kb4);
+          keep_query_lane_finish(rng, kb4);
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             if (!keep_reg(kb4, r, dr.thr)) t[r] = 0.f;
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
     // The lane index is read anew: addresses formed from it would otherwise be held in registers across the loop.
     int elane = lane;
     asm volatile("" : "+v"(elane));
-    const int eg = elane >> 5, ec32 = elane & 31;
+    const int eg = elane >> 5, ec32 = column_row<DROP>(elane);
     l_run = half_pair_sum(l_run);
     const float inv = (DROP ? dr.rescale : 1.0f) / l_run;
     SPARK_LDS char* ob = smem + wave * 32 * C::OSTR;
