@@ -65,13 +65,13 @@ template <int D> struct BwdKvPipeCfg {
 };
 
 // dS of one entry under dropout in the dK/dV kernels, P o (M o dP + d): pe = P, pm = M o P, d = -D (1-p).  With
-// the mask already in pm one select is saved, but only where dP cannot overflow: 0 * inf would turn a dropped
-// entry whose dP is past fp32's range into NaN.  (bf16 without that saving: dK/dV 885 -> 914 us at 256 heads x
-// 2048, d = 64, with one workgroup per CU as it then was, and 639 -> 648 at 64 x 4096 causal, d = 128.)
+// the mask already in pm one instruction is saved, but only where dP cannot overflow: 0 * inf would turn a dropped
+// entry whose dP is past fp32's range into NaN.  (bf16 without that saving, a select then: dK/dV 639 -> 648 us at 64
+// heads x 4096 causal, d = 128.)  keep: ones or zeros.
 template <typename T>
-static __device__ __forceinline__ float dropout_ds(bool keep, float pe, float pm, float dp, float d) {
+static __device__ __forceinline__ float dropout_ds(uint32_t keep, float pe, float pm, float dp, float d) {
   if (Frag<T>::FINITE_DOT) return __builtin_fmaf(pm, dp, pe * d);
-  return pe * ((keep ? dp : 0.f) + d);
+  return pe * (keep_float(keep, dp) + d);
 }
 
 // The workgroup's part: key tile `item` of `head`, and its partner if the causal tiles are paired.
@@ -219,6 +219,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       ft[tg & 1][2 * e + 1] = read_tr_pair<T>(smem, offC.tr_at(0, dt) + o, offC.tr_at(1, dt) + o);
     };
 
+    uint32_t strip = 0;
     // One element of P and dS from finished scores: the unit of VALU work that is placed between
     // MFMAs.  r8 = register index within the half (0..7).  ahead: how far the lane's key lies behind the
     // step's first query of this lane, so that the causal mask is one compare with a constant per element.
@@ -231,8 +232,9 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2, -l[r8 >> 2][r8 & 3]));
       if (mask) pe = ahead > 8 * (r / 4) + (r % 4) ? 0.f : pe;
       if (DROP) {
-        const bool keep = keep_reg(kb, r, dr.thr);
-        p[r8] = keep ? pe : 0.f;
+        if ((r & 3) == 0) strip = keep_strip(kb[r >> 2], dr);  // in the slot of the first of four entries
+        const uint32_t keep = keep_mask(strip, r & 3);
+        p[r8] = keep_float(keep, pe);
         asm volatile("" : "+v"(p[r8]));  // keeps the select in front of the packed conversion
         ds[r8] = dropout_ds<T>(keep, pe, p[r8], dp[r], d[r8 >> 2][r8 & 3]);
       } else {
@@ -248,10 +250,10 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
         pk_ds[r8 >> 1] = pack2<T>(ds[r8 - 1], ds[r8]);
       }
     };
-    // bf16 with dropout at D = 64 has one register too few for krow - 4 g across the loop (its dS takes a select more): formed
-    // anew where a mask needs it.  Spilled, it was awaited inside the loop, together with the stage just requested
-    // (us, causal 256 heads x 512 39.4 -> 38.5, equal at 256 x 2048; fp16, which does not spill, 38.4 -> 38.8).
-    constexpr bool ANEW = DROP && D == 64 && !F::FINITE_DOT;
+    // With dropout at D = 64 there is one register too few for krow - 4 g across the loop: formed anew where a mask needs
+    // it.  Spilled, it was awaited inside the loop, together with the stage just requested (us, bf16, causal 256 heads x 512
+    // 39.4 -> 38.5, equal at 256 x 2048).
+    constexpr bool ANEW = DROP && D == 64;
     auto ahead_of = [&](int q0s) {
       int l = lane;
       if (ANEW) asm volatile("" : "+v"(l));
@@ -686,7 +688,15 @@ static __device__ __forceinline__ void bwd_dq(
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt) {
             dp[mt] = F::mfma(fa[(KS + ks) % AHEAD][mt], dof[ks], dp[mt]);
-            if (DROP && ks == 0) keep_query_lane_finish(rng[mt], keep[mt]);
+            if (DROP && ks == 0) {  // in two parts: in one slot, causal kernels at D > 64 lost 1 %
+              keep[mt][0] = rng[mt].c0; keep[mt][1] = rng[mt].c1; keep[mt][2] = rng[mt].c2; keep[mt][3] = rng[mt].c3;
+              exchange_bit3(keep[mt]);
+              asm volatile("" : "+v"(keep[mt][0]), "+v"(keep[mt][1]), "+v"(keep[mt][2]), "+v"(keep[mt][3]));
+            }
+            if (DROP && ks == 2) {
+              exchange_bit4(keep[mt]);
+              asm volatile("" : "+v"(keep[mt][0]), "+v"(keep[mt][1]), "+v"(keep[mt][2]), "+v"(keep[mt][3]));
+            }
 #pragma unroll
             for (int x = ks * 16 / KS; x < (ks + 1) * 16 / KS; ++x) p_elem(mt * 16 + x);  // 16 in KS MFMAs
             sched_fence();

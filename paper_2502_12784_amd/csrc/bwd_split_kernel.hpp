@@ -293,8 +293,9 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
         float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2, -l[r >> 2][r & 3]));
         if (diag) pe = col - 4 * g > 8 * (r / 4) + (r % 4) ? 0.f : pe;  // krow - t * BM = col
         if (DROP) {
-          const bool kept = keep_reg(keep, r, dr.thr);
-          p[r] = kept ? pe : 0.f;
+          if ((r & 3) == 0) keep[r >> 2] = keep_strip(keep[r >> 2], dr);
+          const uint32_t kept = keep_mask(keep[r >> 2], r & 3);
+          p[r] = keep_float(kept, pe);
           ds[r] = dropout_ds<T>(kept, pe, p[r], dp[r], d[r >> 2][r & 3]);
         } else {
           p[r] = pe;

@@ -22,6 +22,7 @@ struct Dropout {
   uint32_t key0, key1;  // seed, low and high word
   uint32_t offset;      // counter word 3: distinguishes calls that share a seed
   uint32_t thr;         // drop iff byte < thr (0..255)
+  uint32_t keep_add;    // 256 - thr in every byte: byte + (256 - thr) carries iff byte >= thr
   float keep_prob;      // (256 - thr) / 256
   float rescale;        // 256 / (256 - thr)
 };
@@ -78,19 +79,51 @@ static __device__ __forceinline__ int call_strip(int lane) { return (lane >> 3) 
 // into half of the lanes for each word (row_ror:8, banks of four lanes), across bit 4 one swap for two words.  8
 // instructions with the copies; inside a quad, where a move cannot be held to some of the lanes, it was 4 moves and 12 selects
 // (forward and backward, us, fp16, d = 64, 256 heads x 2048 1623 -> 1599; causal, d = 128, 512 x 512 351.5 -> 350.3).
-static __device__ __forceinline__ void exchange_words(uint32_t (&x)[4]) {
+static __device__ __forceinline__ void exchange_bit3(uint32_t (&x)[4]) {
 #pragma unroll
   for (int k = 0; k < 4; k += 2) {
     const int lo = (int)x[k], hi = (int)x[k + 1];
     x[k] = (uint32_t)__builtin_amdgcn_update_dpp(lo, hi, 0x128, 0xF, 0xC, false);
     x[k + 1] = (uint32_t)__builtin_amdgcn_update_dpp(hi, lo, 0x128, 0xF, 0x3, false);
   }
+}
+static __device__ __forceinline__ void exchange_bit4(uint32_t (&x)[4]) {
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const auto s = __builtin_amdgcn_permlane16_swap(x[k], x[k + 2], false, false);
     x[k] = s[0];
     x[k + 2] = s[1];
   }
+}
+static __device__ __forceinline__ void exchange_words(uint32_t (&x)[4]) {
+  exchange_bit3(x);
+  exchange_bit4(x);
+}
+
+// Decisions of four entries at once: v_lerp_u8 halves the nine-bit sums byte + (256 - thr), so bit 7 of byte b is the
+// carry, set iff entry b is kept.  v_perm_b32 copies bits 15 and 31 of its sources into whole bytes; the word shifted up by one
+// byte brings the others there.  A compare and a select for each entry are eight instructions for four; in pairs it is six, by
+// strips seven, whose last four (v_and_b32 of a sign-extended byte) sit where the entries are used (us, forward, d = 64 256
+// heads x 2048 403 -> 386, causal d = 128 64 x 4096 352 -> 339; dK/dV, d = 64, the same 640 -> 629).  In the dQ kernel, whose
+// entries choose between two values, a compare and a select stay the shorter form.
+static __device__ __forceinline__ uint32_t keep_flags(uint32_t bytes, const Dropout& dr) {
+  return __builtin_amdgcn_lerp(bytes, dr.keep_add, 0);
+}
+// ones or zeros for 16-bit values in pairs: entries 0, 1 of the strip, and 2, 3
+static __device__ __forceinline__ void keep_pairs(uint32_t flags, uint32_t (&mask)[2]) {
+  mask[0] = __builtin_amdgcn_perm(flags, flags << 8, 0x0A0A0808u);
+  mask[1] = __builtin_amdgcn_perm(flags, flags << 8, 0x0B0B0909u);
+}
+// ones or zeros in byte b for entry b of the strip; entry b's extended to 32 bits (in the instruction that uses it)
+static __device__ __forceinline__ uint32_t keep_strip(uint32_t bytes, const Dropout& dr) {
+  const uint32_t flags = keep_flags(bytes, dr);
+  return __builtin_amdgcn_perm(flags, flags << 8, 0x0B090A08u);
+}
+static __device__ __forceinline__ uint32_t keep_mask(uint32_t strip, int b) {
+  return (uint32_t)(int32_t)(int8_t)(strip >> (8 * b));
+}
+static __device__ __forceinline__ float keep_float(uint32_t mask, float x) {
+  return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & mask);
 }
 
 // Lane = query column (S^T layouts of the forward and dQ kernels).  The lane's query is

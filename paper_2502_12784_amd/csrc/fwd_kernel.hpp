@@ -249,16 +249,23 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
             for (int q = 0; q < 10; ++q) philox_round<true>(rng, dr.key0, dr.key1, q);
           }
           keep_query_lane_finish(rng, kb4);
+          // converted first, then dropped in pairs: six instructions for four entries, where a compare and a
+          // select of each fp32 value are eight
+          uint32_t pk[2][4];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            if (!keep_reg(kb4, r, dr.thr)) t[r] = 0.f;
-            // the select stays on the fp32 value: moved behind the conversion it would split every
-            // packed two-value conversion into single ones plus a merge
-            asm volatile("" : "+v"(t[r]));
+          for (int a = 0; a < 4; ++a) {
+            uint32_t mask[2];
+            keep_pairs(keep_flags(kb4[a], dr), mask);
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+              pk[a / 2][2 * (a % 2) + x] = pack2<T>(t[4 * a + 2 * x], t[4 * a + 2 * x + 1]) & mask[x];
           }
+          pf[0] = join_pairs<T>(pk[0]);
+          pf[1] = join_pairs<T>(pk[1]);
+        } else {
+          pf[0] = pack8<T>(&t[0]);
+          pf[1] = pack8<T>(&t[8]);
         }
-        pf[0] = pack8<T>(&t[0]);
-        pf[1] = pack8<T>(&t[8]);
       };
       // One half of the round: steps KS h .. KS h + KS - 1, between them the exponentials of `s` and the rounds of the
       // dropout generator for them (EXP).

@@ -118,6 +118,7 @@ Dropout make_dropout(int thr, unsigned long long seed, unsigned offset) {
   dr.key1 = (uint32_t)(seed >> 32);
   dr.offset = offset;
   dr.thr = (uint32_t)thr;
+  dr.keep_add = (uint32_t)(256 - thr) * 0x01010101u;
   dr.keep_prob = (float)(256 - thr) / 256.0f;
   dr.rescale = 256.0f / (float)(256 - thr);
   return dr;
