@@ -91,3 +91,22 @@ def test_unusual_calls_take_the_general_path():
         spark_mha_fwd(q, q, q, float("nan"), False)
     with pytest.raises(SparkError):
         spark_mha_fwd(q.float(), q.float(), q.float(), 0.125, False)
+
+
+@pytest.mark.parametrize("profiled", [False, True])
+def test_allocated_outputs_have_the_layout_of_empty_like(profiled):
+    """Outputs that the call allocates by itself, with and without a profiler that watches allocations."""
+    import contextlib
+    import torch
+    from paper_2502_12784_amd import spark_mha_strided_bwd, spark_mha_strided_fwd
+    dense = torch.randn(2, 3, 40, 64, device="cuda").half()
+    views = [dense, dense.transpose(0, 1).contiguous().transpose(0, 1), dense.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3),
+             dense[:, :1], dense[:1, :, :, :32], dense.as_strided((1, 3, 40, 64), (8, 2560, 64, 1)), dense[:, :, :1]]
+    watch = torch.profiler.profile if profiled else contextlib.nullcontext
+    with watch():
+        for q in views:
+            O, L = spark_mha_strided_fwd(q, q, q, 0.125)
+            out = (O,) + spark_mha_strided_bwd(q, q, q, O, L, torch.empty_like(q).copy_(q), 0.125)
+            for t in out:
+                assert t.stride() == torch.empty_like(q).stride() and t.device == q.device and not t.requires_grad
+            assert L.stride() == torch.empty(L.shape).stride() and L.dtype == torch.float32
