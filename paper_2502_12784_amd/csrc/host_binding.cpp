@@ -112,8 +112,9 @@ class Allocator {
                                                      c10::fromIntArrayRefSlow(sizes), st, c10::Layout::Strided,
                                                      like_.device(), std::nullopt, std::nullopt);
   }
-  // sizes, type and layout of `t`, as torch.empty_like
+  // sizes, type, layout and names of `t`, as torch.empty_like
   at::Tensor same(const at::Tensor& t) const {
+    if (t.has_names()) return at::empty_like(t);
     int64_t stride = 1;
     for (int i = 3; i >= 0; stride *= t.size(i--))
       if (t.stride(i) != stride || t.size(i) < 1) return at::empty_like(t);

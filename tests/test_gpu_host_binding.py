@@ -110,3 +110,24 @@ def test_allocated_outputs_have_the_layout_of_empty_like(profiled):
             for t in out:
                 assert t.stride() == torch.empty_like(q).stride() and t.device == q.device and not t.requires_grad
             assert L.stride() == torch.empty(L.shape).stride() and L.dtype == torch.float32
+
+
+@pytest.mark.filterwarnings("ignore:Named tensors")
+@pytest.mark.parametrize("layout", ["contiguous", "permuted"])
+def test_allocated_outputs_keep_the_names_of_named_inputs(layout):
+    """As torch.empty_like: O is named as Q, dQ, dK, dV as Q, K, V."""
+    import torch
+    from paper_2502_12784_amd import spark_mha_bwd, spark_mha_fwd, spark_mha_strided_bwd, spark_mha_strided_fwd
+    names, memory = ("B", "H", "N", "d"), ("B", "H", "M", "d")
+    x = torch.randn(2, 3, 40, 64, device="cuda").half()
+    if layout == "permuted":
+        x = x.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)
+    q, k = x.refine_names(*names), x.refine_names(*memory)
+    entries = [(spark_mha_strided_fwd, spark_mha_strided_bwd)]
+    if layout == "contiguous":
+        entries.append((spark_mha_fwd, spark_mha_bwd))
+    for fwd, bwd in entries:
+        O, L = fwd(q, k, k, 0.125, False)
+        outs = (O,) + tuple(bwd(q, k, k, O, L, q, 0.125, False))
+        assert [t.names for t in outs] == [names, names, memory, memory] and L.names == (None,) * 3
+        assert torch.equal(O.rename(None), fwd(x, x, x, 0.125, False)[0])
