@@ -75,7 +75,7 @@ static __device__ __forceinline__ float dropout_ds(uint32_t keep, float pe, floa
 }
 
 // The workgroup's part: key tile `item` of `head`, and its partner if the causal tiles are paired.
-template <typename T, int D, bool CAUSAL, bool DROP>
+template <typename T, int D, bool CAUSAL, bool DROP, Lanes M>
 static __device__ __forceinline__ void bwd_dkdv_pipe(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const T* __restrict__ dO, const float* __restrict__ LSE2, const float* __restrict__ Dws,
@@ -93,7 +93,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
   SPARK_LDS char* const smem = lds_origin();
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, c32 = column_row<DROP>(lane);
+  const int g = lane >> 5, c32 = column_row<M>(lane);
 
   const T* Kh = K + head_base(mk, head, H);
   const T* Vh = V + head_base(mv, head, H);
@@ -257,7 +257,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
     auto ahead_of = [&](int q0s) {
       int l = lane;
       if (ANEW) asm volatile("" : "+v"(l));
-      return ANEW ? k0w - q0s + column_row<DROP>(l) - 4 * (l >> 5) : krow - q0s - 4 * g;
+      return ANEW ? k0w - q0s + column_row<M>(l) - 4 * (l >> 5) : krow - q0s - 4 * g;
     };
     uint32_t kbCur[4] = {0, 0, 0, 0}, kbNew[4] = {0, 0, 0, 0};  // decision bytes of the current / next step
 
@@ -307,7 +307,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       float p[8], ds[8];
       uint32_t pk_p[4], pk_ds[4];
       const int ahead_first = CAUSAL ? ahead_of(s_begin * C::BM) : 0;
-      if (DROP) keep_bytes_key_lane(dr, head, krow, s_begin * C::BM, lane, kbCur);
+      if (DROP) keep_bytes_key_lane<M>(dr, head, krow, s_begin * C::BM, lane, kbCur);
 #pragma unroll
       for (int r = 0; r < 8; ++r)
         softmax_elem(sX, dpX, 0, r, lL, dL, ahead_first, CAUSAL, kbCur, p, ds, pk_p, pk_ds);
@@ -341,7 +341,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
         uint32_t pk_p[4], pk_ds[4];
         // dropout decisions of the next step: the ten generator rounds ride in the MFMA slots below
         Philox rng;
-        if (DROP) rng = keep_key_lane_begin(dr, head, krow, q0_new, lane);
+        if (DROP) rng = keep_key_lane_begin<M>(dr, head, krow, q0_new, lane);
         if (!RING) load_stats(lL, dL, sub_new, 0);
         load_thalf(0, sub_cur, 0);
 #pragma unroll
@@ -369,7 +369,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
           }
           sched_fence();
         }
-        if (DROP) keep_key_lane_finish(rng, kbNew);
+        if (DROP) keep_key_lane_finish<M>(rng, lane, kbNew);
         const v8 pfH = join_pairs<T>(pk_p), dsfH = join_pairs<T>(pk_ds);
         if (!RING) load_stats(lH, dH, sub_new, 1);
         sched_fence();
@@ -447,9 +447,9 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
     }
 
     SPARK_LDS char* ob = smem + wave * 32 * C::OSTR;
-    store_transposed<T, D, C::OSTR, DROP>(dk, DROP ? scale * dr.rescale : scale, ob, dK + head_base(mdk, head, H), k0w,
+    store_transposed<T, D, C::OSTR, M>(dk, DROP ? scale * dr.rescale : scale, ob, dK + head_base(mdk, head, H), k0w,
                                     Nk, lane, (size_t)mdk.row, dh);
-    store_transposed<T, D, C::OSTR, DROP>(dv, DROP ? dr.rescale : 1.0f, ob, dV + head_base(mdv, head, H), k0w, Nk,
+    store_transposed<T, D, C::OSTR, M>(dv, DROP ? dr.rescale : 1.0f, ob, dV + head_base(mdv, head, H), k0w, Nk,
                                     lane, (size_t)mdv.row, dh);
   }  // rep
 }
@@ -464,8 +464,23 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void mha_bwd_dkdv_pipe_kernel
   const int items = paired ? causal_items<CAUSAL>(nkt) : nkt;  // causal: key tiles (p, nkt-1-p)
   const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
   const int head = logical / items;
-  bwd_dkdv_pipe<T, D, CAUSAL, DROP>(Q, K, V, dO, LSE2, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq, Nk, dh, nkt,
-                                    paired, scale, dr, head, logical - head * items);
+  bwd_dkdv_pipe<T, D, CAUSAL, DROP, IN_ORDER>(Q, K, V, dO, LSE2, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq, Nk, dh,
+                                              nkt, paired, scale, dr, head, logical - head * items);
+}
+
+// With dropout, the rows far apart in the lanes (column_row); the rule is far_rows.
+template <typename T, int D, bool CAUSAL>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void mha_bwd_dkdv_pipe_far_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
+    const T* __restrict__ dO, const float* __restrict__ LSE2, const float* __restrict__ Dws,
+    T* __restrict__ dK, T* __restrict__ dV, TensorMap mq, TensorMap mk, TensorMap mv, TensorMap mdo,
+    TensorMap mdk, TensorMap mdv, int H, int Nq, int Nk, int dh, int nkt, int paired, float scale,
+    Dropout dr) {
+  const int items = paired ? causal_items<CAUSAL>(nkt) : nkt;  // causal: key tiles (p, nkt-1-p)
+  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int head = logical / items;
+  bwd_dkdv_pipe<T, D, CAUSAL, true, FAR>(Q, K, V, dO, LSE2, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq, Nk, dh,
+                                         nkt, paired, scale, dr, head, logical - head * items);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -488,7 +503,7 @@ template <int D, bool CAUSAL, bool DROP> struct BwdQCfg {
 // The workgroup's part: query tile `item` of `head`, and its partner if the causal tiles are paired.
 // STATS: the workspace holds -D and LSE * log2(e) already (mha_bwd_stats_kernel); otherwise they are
 // formed here and left there for the dK/dV kernel.
-template <typename T, int D, bool CAUSAL, bool DROP, bool STATS>
+template <typename T, int D, bool CAUSAL, bool DROP, bool STATS, Lanes M>
 static __device__ __forceinline__ void bwd_dq(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const T* __restrict__ O, const T* __restrict__ dO, const float* __restrict__ LSE,
@@ -507,7 +522,7 @@ static __device__ __forceinline__ void bwd_dq(
   SPARK_LDS char* const smem = lds_origin();
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, c32 = column_row<DROP>(lane);
+  const int g = lane >> 5, c32 = column_row<M>(lane);
 
   const T* Qh = Q + head_base(mq, head, H);
   const T* dOh = dO + head_base(mdo, head, H);
@@ -643,7 +658,7 @@ static __device__ __forceinline__ void bwd_dq(
         Philox rng[MT];
         if (DROP) {
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) rng[mt] = keep_query_lane_begin(dr, head, qrow, k0 + 32 * mt, lane);
+          for (int mt = 0; mt < MT; ++mt) rng[mt] = keep_query_lane_begin<M>(dr, head, qrow, k0 + 32 * mt, lane);
         }
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) load_step(i);
@@ -690,11 +705,11 @@ static __device__ __forceinline__ void bwd_dq(
             dp[mt] = F::mfma(fa[(KS + ks) % AHEAD][mt], dof[ks], dp[mt]);
             if (DROP && ks == 0) {  // in two parts: in one slot, causal kernels at D > 64 lost 1 %
               keep[mt][0] = rng[mt].c0; keep[mt][1] = rng[mt].c1; keep[mt][2] = rng[mt].c2; keep[mt][3] = rng[mt].c3;
-              exchange_bit3(keep[mt]);
+              exchange_bit0<M>(keep[mt], lane);
               asm volatile("" : "+v"(keep[mt][0]), "+v"(keep[mt][1]), "+v"(keep[mt][2]), "+v"(keep[mt][3]));
             }
             if (DROP && ks == 2) {
-              exchange_bit4(keep[mt]);
+              exchange_bit1<M>(keep[mt], lane);
               asm volatile("" : "+v"(keep[mt][0]), "+v"(keep[mt][1]), "+v"(keep[mt][2]), "+v"(keep[mt][3]));
             }
 #pragma unroll
@@ -755,7 +770,7 @@ static __device__ __forceinline__ void bwd_dq(
     for (; j < nt; ++j) iteration(j, std::true_type{});
 
     SPARK_LDS char* ob = smem + wave * 32 * C::OSTR;
-    store_transposed<T, D, C::OSTR, DROP>(dq, DROP ? scale * dr.rescale : scale, ob, dQ + head_base(mdq, head, H), q0,
+    store_transposed<T, D, C::OSTR, M>(dq, DROP ? scale * dr.rescale : scale, ob, dQ + head_base(mdq, head, H), q0,
                                     Nq, lane, (size_t)mdq.row, dh);
   }  // rep
 }
@@ -770,8 +785,23 @@ __global__ __launch_bounds__(256, 2) void mha_bwd_dq_kernel(
   const int items = paired ? causal_items<CAUSAL>(nqt) : nqt;  // causal: query tiles (nqt-1-p, p)
   const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
   const int head = logical / items;
-  bwd_dq<T, D, CAUSAL, DROP, false>(Q, K, V, O, dO, LSE, Dws, LSE2ws, dQ, mq, mk, mv, mo, mdo, mdq, H, Nq, Nk, dh,
-                                    nqt, paired, scale, scale_log2, dr, head, logical - head * items);
+  bwd_dq<T, D, CAUSAL, DROP, false, IN_ORDER>(Q, K, V, O, dO, LSE, Dws, LSE2ws, dQ, mq, mk, mv, mo, mdo, mdq, H, Nq,
+                                              Nk, dh, nqt, paired, scale, scale_log2, dr, head, logical - head * items);
+}
+
+// With dropout, the rows far apart in the lanes (column_row); the rule is far_rows.
+template <typename T, int D, bool CAUSAL>
+__global__ __launch_bounds__(256, 2) void mha_bwd_dq_far_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
+    const T* __restrict__ O, const T* __restrict__ dO, const float* __restrict__ LSE,
+    float* __restrict__ Dws, float* __restrict__ LSE2ws, T* __restrict__ dQ, TensorMap mq, TensorMap mk,
+    TensorMap mv, TensorMap mo, TensorMap mdo, TensorMap mdq, int H, int Nq, int Nk, int dh, int nqt, int paired,
+    float scale, float scale_log2, Dropout dr) {
+  const int items = paired ? causal_items<CAUSAL>(nqt) : nqt;  // causal: query tiles (nqt-1-p, p)
+  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int head = logical / items;
+  bwd_dq<T, D, CAUSAL, true, false, FAR>(Q, K, V, O, dO, LSE, Dws, LSE2ws, dQ, mq, mk, mv, mo, mdo, mdq, H, Nq,
+                                         Nk, dh, nqt, paired, scale, scale_log2, dr, head, logical - head * items);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -822,10 +852,10 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void mha_bwd_merged_kernel(
   const int head = logical / (qitems + kitems);
   const int item = logical - head * (qitems + kitems);
   if (item < kitems)  // the longer ones first
-    bwd_dkdv_pipe<T, D, CAUSAL, DROP>(Q, K, V, dO, LSE2ws, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq, Nk, dh, nkt,
+    bwd_dkdv_pipe<T, D, CAUSAL, DROP, IN_ORDER>(Q, K, V, dO, LSE2ws, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq, Nk, dh, nkt,
                                       paired, scale, dr, head, item);
   else
-    bwd_dq<T, D, CAUSAL, DROP, true>(Q, K, V, nullptr, dO, nullptr, Dws, LSE2ws, dQ, mq, mk, mv, mdo, mdo, mdq, H, Nq,
+    bwd_dq<T, D, CAUSAL, DROP, true, IN_ORDER>(Q, K, V, nullptr, dO, nullptr, Dws, LSE2ws, dQ, mq, mk, mv, mdo, mdo, mdq, H, Nq,
                                      Nk, dh, nqt, paired, scale, scale * 1.4426950408889634f, dr, head,
                                      item - kitems);
 }

@@ -42,14 +42,14 @@ template <int D> struct BwdSplitCfg {
 
 // Sum of the accumulators (D x 32, lane = column) of waves 0 .. used-1, times `mul`, stored as 32 rows of D
 // 16-bit values: rows < N, columns < dh.  All waves call it; the LDS tiles are overwritten.
-template <typename T, int D, bool DROP>
+template <typename T, int D>
 static __device__ __forceinline__ void merge_store(const f32x16 (&acc)[D / 32], float mul, int used,
                                                    SPARK_LDS char* smem, int tid, T* __restrict__ out, int row0, int N,
                                                    size_t row_stride, int dh) {
   using C = BwdSplitCfg<D>;
   using v4 = typename Frag<T>::v4;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, c32 = column_row<DROP>(lane);
+  const int g = lane >> 5, c32 = lane & 31;
   __syncthreads();  // every wave has left its tiles, and an earlier merge its staging rows
   if (wave < used) {
 #pragma unroll
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
   SPARK_LDS char* const smem = lds_origin();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, c32 = lane & 31, col = column_row<DROP>(lane);
+  const int g = lane >> 5, c32 = lane & 31;
   SPARK_LDS char* const wbuf = smem + wave * 2 * C::STAGE;
   const float scale_log2 = scale * 1.4426950408889634f;
 
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
     // ------------------------------------------------------------------ dQ of 32 queries
     // As in mha_bwd_dq_kernel: S^T = K Q^T, dP^T = V dO^T (lane = query), dQ^T += K^T dS^T.
     const int qt = CAUSAL ? nqt - 1 - (item - nkt) : item - nkt;
-    const int q0 = qt * C::BM, qrow = q0 + col;
+    const int q0 = qt * C::BM, qrow = q0 + c32;
     const int qrow_c = qrow < Nq ? qrow : Nq - 1;
     const int kv_end = CAUSAL && q0 + C::BM < Nk ? q0 + C::BM : Nk;
     const int nt = (kv_end + C::BM - 1) / C::BM;
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) s = F::mfma(lds_read16<v8>(kb, off.row[ks]), qf[ks], s);
       uint32_t keep[4];
-      if (DROP) keep_bytes_query_lane(dr, head, qrow, j * C::BM, lane, keep);
+      if (DROP) keep_bytes_query_lane<IN_ORDER>(dr, head, qrow, j * C::BM, lane, keep);
       float ds[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -201,13 +201,13 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
         tile(j, b, std::true_type{}, j + C::NW < nt);
       b ^= 1;
     }
-    merge_store<T, D, DROP>(dq, DROP ? scale * dr.rescale : scale, nt < C::NW ? nt : C::NW, smem, tid,
+    merge_store<T, D>(dq, DROP ? scale * dr.rescale : scale, nt < C::NW ? nt : C::NW, smem, tid,
                       dQ + head_base(mdq, head, H), q0, Nq, (size_t)mdq.row, dh);
   } else {
     // ------------------------------------------------------------------ dK, dV of 32 keys
     // As in mha_bwd_dkdv_pipe_kernel: S = Q K^T, dP = dO V^T (lane = key), dV^T += dO^T P, dK^T += Q^T dS.
     const int kt = item;
-    const int k0 = kt * C::BM, krow = k0 + col;
+    const int k0 = kt * C::BM, krow = k0 + c32;
     const int t0 = CAUSAL ? kt : 0;  // first query tile
     const BufView qview(Qh, head_span_bytes(mq, Nq, dh)), doview(dOh, head_span_bytes(mdo, Nq, dh));
     const uint32_t q_row_bytes = (uint32_t)mq.row * 2, do_row_bytes = (uint32_t)mdo.row * 2;
@@ -285,13 +285,13 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) s = F::mfma(lds_read16<v8>(qb, off.row[ks]), kf[ks], s);
       uint32_t keep[4];
-      if (DROP) keep_bytes_key_lane(dr, head, krow, t * C::BM, lane, keep);
+      if (DROP) keep_bytes_key_lane<IN_ORDER>(dr, head, krow, t * C::BM, lane, keep);
       const bool diag = CAUSAL && t == kt;
       float p[16], ds[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2, -l[r >> 2][r & 3]));
-        if (diag) pe = col - 4 * g > 8 * (r / 4) + (r % 4) ? 0.f : pe;  // krow - t * BM = col
+        if (diag) pe = c32 - 4 * g > 8 * (r / 4) + (r % 4) ? 0.f : pe;  // krow - t * BM = c32
         if (DROP) {
           if ((r & 3) == 0) keep[r >> 2] = keep_strip(keep[r >> 2], dr);
           const uint32_t kept = keep_mask(keep[r >> 2], r & 3);
@@ -319,9 +319,9 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
       b ^= 1;
     }
     const int used = nqt - t0 < C::NW ? nqt - t0 : C::NW;
-    merge_store<T, D, DROP>(dk, DROP ? scale * dr.rescale : scale, used, smem, tid, dK + head_base(mdk, head, H), k0, Nk,
+    merge_store<T, D>(dk, DROP ? scale * dr.rescale : scale, used, smem, tid, dK + head_base(mdk, head, H), k0, Nk,
                       (size_t)mdk.row, dh);
-    merge_store<T, D, DROP>(dv, DROP ? dr.rescale : 1.0f, used, smem, tid, dV + head_base(mdv, head, H), k0, Nk,
+    merge_store<T, D>(dv, DROP ? dr.rescale : 1.0f, used, smem, tid, dV + head_base(mdv, head, H), k0, Nk,
                       (size_t)mdv.row, dh);
   }
 }

@@ -66,38 +66,57 @@ static __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, u
   out[0] = s.c0; out[1] = s.c1; out[2] = s.c2; out[3] = s.c3;
 }
 
-// Row of a block of 32 that a lane's column of the products stands for.  With dropout rows r and lanes are permuted, so that
-// the four rows of a call sit in lanes that differ in bits 3 (r bit 0) and 4 (r bit 1): across those a register
-// moves for half the instructions it takes inside a quad (exchange_words).
-template <bool DROP> static __device__ __forceinline__ int column_row(int lane) {
-  return DROP ? (lane & 7) << 2 | ((lane >> 3) & 3) : lane & 31;
+// How the 32 rows of a block, the products' columns, are spread over the lanes.  With dropout the four rows of a call swap words
+// (exchange_words), which is cheap across lane bits 3 and 4 and dear inside a quad; but a kernel also loads its rows by 16 bytes
+// a lane, and such a load takes up to three times as long where neighbouring lanes' addresses agree in bit 6 (ns for a load by
+// a wave, eight waves on a CU, rows of 64 / 96 / 128 / 160 / 192 / 224 / 256 bytes in L2):
+//             bits 0, 1 of a row are lane bits   exchange, instructions   row load
+//   IN_ORDER  0, 1                               16                       15.4 /  9.2 / 27 / 13.0 / 14.1 / 14.0 / 27
+//   NEAR      0, 4                               10                       15.5 / 14.5 / 27 / 14.3 / 14.1 / 15.1 / 27
+//   FAR       3, 4                                8                       28.8 / 27.9 / 27 / 27.5 / 27.3 / 27.2 / 27
+// FAR in the forward at 64 columns, which loads one operand's rows for a long loop, and in a backward of two grids as far_rows
+// decides there; NEAR in mha_fwd_split_kernel, whose eight waves load the same rows; IN_ORDER elsewhere.  (FAR in all of them,
+// us, fp16: forward 4 heads x 512, d = 96 9.0 -> 9.6, now 8.8; 100 x 384, d = 112 17.9 -> 18.2, now 17.2; backward
+// causal 140 x 512, d = 48 55.0 -> 57.2; d = 96 87.9 -> 92.3; 4 x 512, d = 48 8.2 -> 8.9.)
+enum Lanes { IN_ORDER, NEAR, FAR };
+template <Lanes M> static __device__ __forceinline__ int column_row(int lane) {
+  return M == NEAR  ? (lane & 14) << 1 | ((lane >> 3) & 2) | (lane & 1)
+         : M == FAR ? (lane & 7) << 2 | ((lane >> 3) & 3)
+                    : lane & 31;
 }
-static __device__ __forceinline__ int call_strip(int lane) { return (lane >> 3) & 3; }  // = column_row<true>(lane) % 4
+template <Lanes M> static __device__ __forceinline__ int call_strip(int lane) { return column_row<M>(lane) & 3; }
 
 // 4 x 4 transpose over the four lanes of a call: on return x[a] holds what the lane of strip a had in x[w], w = this lane's
 // strip.  Two butterfly steps, each exchanging the two words that differ in that bit of w: across lane bit 3 a DPP move
-// into half of the lanes for each word (row_ror:8, banks of four lanes), across bit 4 one swap for two words.  8
-// instructions with the copies; inside a quad, where a move cannot be held to some of the lanes, it was 4 moves and 12 selects
-// (forward and backward, us, fp16, d = 64, 256 heads x 2048 1623 -> 1599; causal, d = 128, 512 x 512 351.5 -> 350.3).
-static __device__ __forceinline__ void exchange_bit3(uint32_t (&x)[4]) {
-#pragma unroll
-  for (int k = 0; k < 4; k += 2) {
-    const int lo = (int)x[k], hi = (int)x[k + 1];
-    x[k] = (uint32_t)__builtin_amdgcn_update_dpp(lo, hi, 0x128, 0xF, 0xC, false);
-    x[k + 1] = (uint32_t)__builtin_amdgcn_update_dpp(hi, lo, 0x128, 0xF, 0x3, false);
+// into half of the lanes for each word (row_ror:8, banks of four lanes), across bit 4 one swap for two words; inside a quad,
+// where a move cannot be held to some of the lanes, a move and three selects for two words.
+template <Lanes M, int B> static __device__ __forceinline__ void exchange_pair(uint32_t& lo, uint32_t& hi, int lane) {
+  const uint32_t a = lo, b = hi;
+  if (M == IN_ORDER || (M == NEAR && B == 0)) {
+    const bool upper = lane & (B == 0 ? 1 : 2);
+    const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)(upper ? a : b), B == 0 ? 0xB1 : 0x4E, 0xF, 0xF, true);
+    lo = upper ? got : a;
+    hi = upper ? b : got;
+  } else if (B == 0) {
+    lo = (uint32_t)__builtin_amdgcn_update_dpp((int)a, (int)b, 0x128, 0xF, 0xC, false);
+    hi = (uint32_t)__builtin_amdgcn_update_dpp((int)b, (int)a, 0x128, 0xF, 0x3, false);
+  } else {
+    const auto s = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    lo = s[0];
+    hi = s[1];
   }
 }
-static __device__ __forceinline__ void exchange_bit4(uint32_t (&x)[4]) {
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const auto s = __builtin_amdgcn_permlane16_swap(x[k], x[k + 2], false, false);
-    x[k] = s[0];
-    x[k + 2] = s[1];
-  }
+template <Lanes M> static __device__ __forceinline__ void exchange_bit0(uint32_t (&x)[4], int lane) {
+  exchange_pair<M, 0>(x[0], x[1], lane);
+  exchange_pair<M, 0>(x[2], x[3], lane);
 }
-static __device__ __forceinline__ void exchange_words(uint32_t (&x)[4]) {
-  exchange_bit3(x);
-  exchange_bit4(x);
+template <Lanes M> static __device__ __forceinline__ void exchange_bit1(uint32_t (&x)[4], int lane) {
+  exchange_pair<M, 1>(x[0], x[2], lane);
+  exchange_pair<M, 1>(x[1], x[3], lane);
+}
+template <Lanes M> static __device__ __forceinline__ void exchange_words(uint32_t (&x)[4], int lane) {
+  exchange_bit0<M>(x, lane);
+  exchange_bit1<M>(x, lane);
 }
 
 // Decisions of four entries at once: v_lerp_u8 halves the nine-bit sums byte + (256 - thr), so bit 7 of byte b is the
@@ -127,47 +146,54 @@ static __device__ __forceinline__ float keep_float(uint32_t mask, float x) {
 }
 
 // Lane = query column (S^T layouts of the forward and dQ kernels).  The lane's query is
-// `qrow` (row column_row<true>(lane) of its block) and it holds keys kblk + 8a + 4g + b of the 32-key block
+// `qrow` (row column_row<M>(lane) of its block) and it holds keys kblk + 8a + 4g + b of the 32-key block
 // starting at kblk (a multiple of 32), g = lane / 32.  kb[a] receives the four decision bytes of
 // strip a: byte b belongs to accumulator register 4a + b.
 // In three parts (counter, ten rounds of philox_round, exchange), see keep_key_lane_begin.
+template <Lanes M>
 static __device__ __forceinline__ Philox keep_query_lane_begin(const Dropout& dr, int head, int qrow, int kblk,
                                                                int lane) {
-  const int w = call_strip(lane), g = lane >> 5;  // this lane evaluates the call of strip a = w
+  const int w = call_strip<M>(lane), g = lane >> 5;  // this lane evaluates the call of strip a = w
   return Philox{(uint32_t)((kblk >> 2) + 2 * w + g), (uint32_t)(qrow >> 2), (uint32_t)head, dr.offset};
 }
-static __device__ __forceinline__ void keep_query_lane_finish(const Philox& s, uint32_t (&kb)[4]) {
+template <Lanes M>
+static __device__ __forceinline__ void keep_query_lane_finish(const Philox& s, int lane, uint32_t (&kb)[4]) {
   // strip a needs word (query mod 4) = w of the call that the lane of strip a evaluated
   kb[0] = s.c0; kb[1] = s.c1; kb[2] = s.c2; kb[3] = s.c3;
-  exchange_words(kb);
+  exchange_words<M>(kb, lane);
 }
+template <Lanes M>
 static __device__ __forceinline__ void keep_bytes_query_lane(const Dropout& dr, int head, int qrow,
                                                              int kblk, int lane, uint32_t (&kb)[4]) {
-  Philox s = keep_query_lane_begin(dr, head, qrow, kblk, lane);
+  Philox s = keep_query_lane_begin<M>(dr, head, qrow, kblk, lane);
 #pragma unroll
   for (int round = 0; round < 10; ++round) philox_round(s, dr.key0, dr.key1, round);
-  keep_query_lane_finish(s, kb);
+  keep_query_lane_finish<M>(s, lane, kb);
 }
 
 // Lane = key column (S layouts of the dK/dV kernel).  The lane's key is `krow`
-// (row column_row<true>(lane) of its block) and it holds queries qblk + 8a + 4g + b of the 32-query block
+// (row column_row<M>(lane) of its block) and it holds queries qblk + 8a + 4g + b of the 32-query block
 // starting at qblk (a multiple of 32).  kb[a] as above: byte b belongs to register 4a + b.
 // In three parts (counter, ten rounds of philox_round, exchange) so that the kernel can spread
 // the rounds over its MFMA slots; keep_bytes_key_lane runs them back to back.
+template <Lanes M>
 static __device__ __forceinline__ Philox keep_key_lane_begin(const Dropout& dr, int head, int krow, int qblk,
                                                              int lane) {
-  const int w = call_strip(lane), g = lane >> 5;  // this lane evaluates the call of strip a = w
+  const int w = call_strip<M>(lane), g = lane >> 5;  // this lane evaluates the call of strip a = w
   return Philox{(uint32_t)(krow >> 2), (uint32_t)((qblk >> 2) + 2 * w + g), (uint32_t)head, dr.offset};
 }
-static __device__ __forceinline__ void keep_key_lane_finish(const Philox& s, uint32_t (&kb)[4]);
+template <Lanes M>
+static __device__ __forceinline__ void keep_key_lane_finish(const Philox& s, int lane, uint32_t (&kb)[4]);
+template <Lanes M>
 static __device__ __forceinline__ void keep_bytes_key_lane(const Dropout& dr, int head, int krow,
                                                            int qblk, int lane, uint32_t (&kb)[4]) {
-  Philox s = keep_key_lane_begin(dr, head, krow, qblk, lane);
+  Philox s = keep_key_lane_begin<M>(dr, head, krow, qblk, lane);
 #pragma unroll
   for (int round = 0; round < 10; ++round) philox_round(s, dr.key0, dr.key1, round);
-  keep_key_lane_finish(s, kb);
+  keep_key_lane_finish<M>(s, lane, kb);
 }
-static __device__ __forceinline__ void keep_key_lane_finish(const Philox& s, uint32_t (&kb)[4]) {
+template <Lanes M>
+static __device__ __forceinline__ void keep_key_lane_finish(const Philox& s, int lane, uint32_t (&kb)[4]) {
   // byte k of the call's four words (queries) belongs to the lane with key mod 4 = k: 4 x 4 byte transpose
   // inside the lane (8 byte permutes), then word k of strip a's call to lane k
   const uint32_t a01 = __builtin_amdgcn_perm(s.c1, s.c0, 0x05010400u);  // c0[0] c1[0] c0[1] c1[1]
@@ -178,7 +204,7 @@ static __device__ __forceinline__ void keep_key_lane_finish(const Philox& s, uin
   kb[1] = __builtin_amdgcn_perm(a23, a01, 0x07060302u);
   kb[2] = __builtin_amdgcn_perm(b23, b01, 0x05040100u);
   kb[3] = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
-  exchange_words(kb);
+  exchange_words<M>(kb, lane);
 }
 
 // decision for accumulator register r (0..15) from the bytes of its strip

@@ -86,7 +86,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
   // the lane index read anew in the epilogue, 17 ... 25 vector registers less and no spills: causal d = 64 128 x 1024
   // 31.8 -> 29.3 us, d = 80 36 x 1333 29.4 -> 27.1, d = 64 96 x 512 14.4 -> 13.2.)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, c32 = column_row<DROP>(lane);
+  constexpr Lanes LANES = DROP && D == 64 ? FAR : IN_ORDER;
+  const int g = lane >> 5, c32 = column_row<LANES>(lane);
   const uint32_t k_row_bytes = (uint32_t)mk.row * 2, v_row_bytes = (uint32_t)mv.row * 2;
   const uint32_t k_lane_src = dma_lane_src<D>(wave & 3, lane, k_row_bytes, dh);
   const uint32_t v_lane_src = dma_lane_src<D>(wave & 3, lane, v_row_bytes, dh);
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
 #pragma unroll
             for (int q = 0; q < 10; ++q) philox_round<true>(rng, dr.key0, dr.key1, q);
           }
-          keep_query_lane_finish(rng, kb4);
+          keep_query_lane_finish<LANES>(rng, lane, kb4);
           // converted first, then dropped in pairs: six instructions for four entries, where a compare and a
           // select of each fp32 value are eight
           uint32_t pk[2][4];
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
         constexpr int h = decltype(h_tag)::value;
         constexpr bool EXP = h == 0 ? !FIRST : !LAST;
         if (DROP && EXP) {
-          rng = keep_query_lane_begin(dr, head, qrow, key0, lane);
+          rng = keep_query_lane_begin<LANES>(dr, head, qrow, key0, lane);
           // Opaque there: otherwise products of the first rounds are held across the loop, spilled, and their reload
           // awaited inside it together with the tile just requested (us, 256 heads x 512 25.2 -> 24.7, 512 x 300
           // 27.9 -> 27.0, equal at 256 x 2048).
@@ -395,7 +396,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
     // The lane index is read anew: addresses formed from it would otherwise be held in registers across the loop.
     int elane = lane;
     asm volatile("" : "+v"(elane));
-    const int eg = elane >> 5, ec32 = column_row<DROP>(elane);
+    const int eg = elane >> 5, ec32 = column_row<LANES>(elane);
     l_run = half_pair_sum(l_run);
     const float inv = (DROP ? dr.rescale : 1.0f) / l_run;
     SPARK_LDS char* ob = smem + wave * 32 * C::OSTR;

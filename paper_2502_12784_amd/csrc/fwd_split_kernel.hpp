@@ -61,7 +61,8 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
   SPARK_LDS char* const smem = lds_origin();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, c32 = column_row<DROP>(lane);
+  constexpr Lanes LANES = DROP ? NEAR : IN_ORDER;
+  const int g = lane >> 5, c32 = column_row<LANES>(lane);
   SPARK_LDS char* const kb = smem + wave * 2 * C::TILE;
   SPARK_LDS char* const vb = kb + C::TILE;
 
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
 #pragma unroll
         for (int h = 0; h < HALVES; ++h) {
           uint32_t keep[4];
-          keep_bytes_query_lane(dr, head, qrow, k0 + 32 * h, lane, keep);
+          keep_bytes_query_lane<LANES>(dr, head, qrow, k0 + 32 * h, lane, keep);
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             if (!keep_reg(keep, r, dr.thr)) t[h * 16 + r] = 0.f;

@@ -449,62 +449,86 @@ int launch_bwd_merged(const Problem& p, const void* Q, const void* K, const void
   return launch_ok("backward kernel (both sides)") ? SPARK_OK : SPARK_ERR_LAUNCH;
 }
 
-template <typename T, int D, bool CAUSAL, bool DROP>
-int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, const void* O,
-               const float* LSE, const void* dO, void* dQ, void* dK, void* dV, float* Dws,
-               void* const* ev) {
-  const T* q = static_cast<const T*>(Q);
-  const T* k = static_cast<const T*>(K);
-  const T* v = static_cast<const T*>(V);
-  const T* o = static_cast<const T*>(O);
-  const T* dout = static_cast<const T*>(dO);
+// Optional profiling marks between the kernels of a backward (spark_mha_bwd_marked).
+bool mark(const Problem& p, void* const* ev, int i) {
+  return !ev || hipEventRecord(static_cast<hipEvent_t>(ev[i]), p.st) == hipSuccess;
+}
+
+// How a kernel per side spreads its rows over the lanes under dropout (column_row): far apart the exchange of the generator's
+// words is cheaper, which is kept where no operand's rows load faster in order.  Neighbouring lanes' addresses agree in bit 6, in
+// order if rows are a multiple of 128 bytes apart, far apart already at a multiple of 32.  Backward, us, fp16 / bf16, in order -> far:
+//   d = 64:   64 heads x 2048 299 / 291 -> 292 / 283      512 x 192 48.0 / 47.5 -> 48.4 / 47.7
+//   d = 128:  64 x 2048 524 / 505 -> 513 / 493, causal 301 / 291 -> 297 / 287      140 x 512 120.2 / 117.9 -> 119.8 / 117.6
+//             but 512 x 192 94.1 / 93.0 -> 95.1 / 94.5, causal 140 x 512 109.1 / 107.9 -> 110.2 / 109.0: from 512 rows of the loop on
+//   rows of 96 and 224 bytes, causal 140 x 512: d = 48 55.0 / 56.3 -> 57.2 / 58.4, d = 112 100.0 / 100.5 -> 106.2 / 106.4
+// Not at 96 columns (d = 80, 64 x 2048 equal; 140 x 512 causal 85.6 -> 90.1).
+bool far_rows(const Problem& p) {
+  if (p.d > 64 && (p.Nq < p.Nk ? p.Nq : p.Nk) < (p.causal ? 1024 : 512)) return false;
+  for (const TensorMap* m : {&p.mq, &p.mk, &p.mv, &p.mo, &p.mdo})
+    if ((m->row * 2) % 32 == 0 && (m->row * 2) % 128 != 0) return false;
+  return true;
+}
+
+// One kernel per side.
+template <typename T, int D, bool CAUSAL, bool DROP, bool FAR_ROWS>
+int launch_bwd_sides(const Problem& p, const T* q, const T* k, const T* v, const T* o, const float* LSE, const T* dout,
+                     T* dq, T* dk, T* dv, float* Dws, void* const* ev) {
   const int BH = p.B * p.H;
   const Dropout dr = make_dropout(p.thr, p.seed, p.offset);
   float* LSE2ws = Dws + (size_t)BH * p.Nq;  // second half of the workspace: LSE * log2(e)
-  // optional profiling marks between the kernels (spark_mha_bwd_marked)
-  auto mark = [&](int i) {
-    return !ev || hipEventRecord(static_cast<hipEvent_t>(ev[i]), p.st) == hipSuccess;
-  };
-
-  if (!mark(0)) return SPARK_ERR_LAUNCH;
-  if (split_backward(p)) {  // one kernel: both later marks follow it
-    const int rc = launch_bwd_split<T, lds_row<D>, CAUSAL, DROP>(p, Q, K, V, O, LSE, dO, dQ, dK, dV);
-    if (rc != SPARK_OK) return rc;
-    return mark(1) && mark(2) ? SPARK_OK : SPARK_ERR_LAUNCH;
-  }
-  if (merged_backward(p)) {
-    const int rc = launch_bwd_merged<T, D, CAUSAL, DROP>(p, Q, K, V, O, LSE, dO, dQ, dK, dV, Dws);
-    if (rc != SPARK_OK) return rc;
-    return mark(1) && mark(2) ? SPARK_OK : SPARK_ERR_LAUNCH;
-  }
   {  // dQ: one workgroup per tile of 128 queries (8-wave workgroups measured 3 % slower here).
      // Also writes D = rowsum(dO o O) and LSE * log2(e) for the dK/dV kernel.
     using C = BwdQCfg<D, CAUSAL, DROP>;
     auto kernel = mha_bwd_dq_kernel<T, D, CAUSAL, DROP>;
+    if constexpr (FAR_ROWS) kernel = mha_bwd_dq_far_kernel<T, D, CAUSAL>;
     static std::atomic<uint64_t> ready{0};
     const int attr = ensure_smem(kernel, C::SMEM, ready);
     if (attr != SPARK_OK) return attr;
     const int nqt = (p.Nq + C::BM - 1) / C::BM;
     const int paired = pair_tiles(CAUSAL, BH, nqt, 2);
     hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * (paired ? causal_items<true>(nqt) : nqt))), dim3(256), C::SMEM, p.st,
-                       q, k, v, o, dout, LSE, Dws, LSE2ws, static_cast<T*>(dQ), p.mq, p.mk, p.mv, p.mo,
+                       q, k, v, o, dout, LSE, Dws, LSE2ws, dq, p.mq, p.mk, p.mv, p.mo,
                        p.mdo, p.mdq, p.H, p.Nq, p.Nk, p.d, nqt, paired, p.scale, p.scale * 1.4426950408889634f, dr);
-    if (!launch_ok("dQ kernel") || !mark(1)) return SPARK_ERR_LAUNCH;
+    if (!launch_ok("dQ kernel") || !mark(p, ev, 1)) return SPARK_ERR_LAUNCH;
   }
   {  // dK, dV: one workgroup per tile of 128 keys, software-pipelined
     using C = BwdKvPipeCfg<D>;
     auto kernel = mha_bwd_dkdv_pipe_kernel<T, D, CAUSAL, DROP>;
+    if constexpr (FAR_ROWS) kernel = mha_bwd_dkdv_pipe_far_kernel<T, D, CAUSAL>;
     static std::atomic<uint64_t> ready{0};
     const int attr = ensure_smem(kernel, C::SMEM, ready);
     if (attr != SPARK_OK) return attr;
     const int nkt = (p.Nk + C::BN - 1) / C::BN;
     const int paired = pair_tiles(CAUSAL, BH, nkt, dkdv_per_cu<D>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)(BH * (paired ? causal_items<true>(nkt) : nkt))), dim3(256), C::SMEM, p.st,
-                       q, k, v, dout, LSE2ws, Dws, static_cast<T*>(dK), static_cast<T*>(dV), p.mq, p.mk,
+                       q, k, v, dout, LSE2ws, Dws, dk, dv, p.mq, p.mk,
                        p.mv, p.mdo, p.mdk, p.mdv, p.H, p.Nq, p.Nk, p.d, nkt, paired, p.scale, dr);
-    if (!launch_ok("dK/dV kernel") || !mark(2)) return SPARK_ERR_LAUNCH;
+    if (!launch_ok("dK/dV kernel") || !mark(p, ev, 2)) return SPARK_ERR_LAUNCH;
   }
   return SPARK_OK;
+}
+
+template <typename T, int D, bool CAUSAL, bool DROP>
+int launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, const void* O,
+               const float* LSE, const void* dO, void* dQ, void* dK, void* dV, float* Dws,
+               void* const* ev) {
+  if (!mark(p, ev, 0)) return SPARK_ERR_LAUNCH;
+  if (split_backward(p)) {  // one kernel: both later marks follow it
+    const int rc = launch_bwd_split<T, lds_row<D>, CAUSAL, DROP>(p, Q, K, V, O, LSE, dO, dQ, dK, dV);
+    if (rc != SPARK_OK) return rc;
+    return mark(p, ev, 1) && mark(p, ev, 2) ? SPARK_OK : SPARK_ERR_LAUNCH;
+  }
+  if (merged_backward(p)) {
+    const int rc = launch_bwd_merged<T, D, CAUSAL, DROP>(p, Q, K, V, O, LSE, dO, dQ, dK, dV, Dws);
+    if (rc != SPARK_OK) return rc;
+    return mark(p, ev, 1) && mark(p, ev, 2) ? SPARK_OK : SPARK_ERR_LAUNCH;
+  }
+  auto sides = launch_bwd_sides<T, D, CAUSAL, DROP, false>;
+  if constexpr (DROP && D != 96) {
+    if (far_rows(p)) sides = launch_bwd_sides<T, D, CAUSAL, DROP, true>;
+  }
+  return sides(p, static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), static_cast<const T*>(O),
+               LSE, static_cast<const T*>(dO), static_cast<T*>(dQ), static_cast<T*>(dK), static_cast<T*>(dV), Dws, ev);
 }
 
 size_t workspace_bytes(int B, int H, int Nq) { return 2 * (size_t)B * H * Nq * sizeof(float); }

@@ -254,8 +254,8 @@ template <int D> struct WaveDma {
 
 // Write a wave's transposed accumulator (D x 32, lane = column) times `mul` as 32 rows of D
 // 16-bit values: through the wave's LDS slice `ob`, then 16-byte row stores for rows < N
-// and columns < dh (`row_stride` elements apart).  DROP: the rows are permuted among the lanes (column_row).
-template <typename T, int D, int OSTR, bool DROP = false>
+// and columns < dh (`row_stride` elements apart).  The rows lie in the lanes as column_row<M> says.
+template <typename T, int D, int OSTR, Lanes M = IN_ORDER>
 static __device__ __forceinline__ void store_transposed(const f32x16 (&acc)[D / 32], float mul,
                                                         SPARK_LDS char* ob, T* __restrict__ out,
                                                         int row0, int N, int lane, size_t row_stride, int dh) {
@@ -264,7 +264,7 @@ static __device__ __forceinline__ void store_transposed(const f32x16 (&acc)[D / 
   constexpr int RPP = 64 / CPR;
   // read anew: addresses formed from the caller's index would be held in registers across its loop over tiles
   asm volatile("" : "+v"(lane));
-  const int g = lane >> 5, c32 = column_row<DROP>(lane);
+  const int g = lane >> 5, c32 = column_row<M>(lane);
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
