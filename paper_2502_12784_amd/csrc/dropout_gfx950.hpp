@@ -26,6 +26,11 @@ struct Dropout {
   float keep_prob;      // (256 - thr) / 256
   float rescale;        // 256 / (256 - thr)
 };
+// The same without what a kernel can form from `thr`: an argument fewer to hold.
+struct DropoutLean {
+  uint32_t key0, key1, offset, thr;
+  float keep_prob, rescale;
+};
 
 // Philox4x32-10, one round at a time so that a kernel can place the rounds between its MFMAs.
 // The key schedule (key + round * Weyl constant) is uniform across the wave: scalar registers.

@@ -371,12 +371,13 @@ int launch_bwd_split(const Problem& p, const void* Q, const void* K, const void*
   static std::atomic<uint64_t> ready{0};
   const int attr = ensure_smem(kernel, C::SMEM, ready);
   if (attr != SPARK_OK) return attr;
+  const Dropout dr = make_dropout(p.thr, p.seed, p.offset);
   hipLaunchKernelGGL(kernel, dim3((unsigned)bwd_split_workgroups(p)), dim3(64 * C::NW), C::SMEM, p.st,
                      static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
                      static_cast<const T*>(O), static_cast<const T*>(dO), LSE, static_cast<T*>(dQ),
                      static_cast<T*>(dK), static_cast<T*>(dV), p.mq, p.mk, p.mv, p.mo, p.mdo, p.mdq, p.mdk, p.mdv,
                      p.H, p.Nq, p.Nk, p.d, (p.Nq + C::BM - 1) / C::BM, (p.Nk + C::BM - 1) / C::BM, p.scale,
-                     make_dropout(p.thr, p.seed, p.offset));
+                     DropoutLean{dr.key0, dr.key1, dr.offset, dr.thr, dr.keep_prob, dr.rescale});
   return launch_ok("backward kernel (split)") ? SPARK_OK : SPARK_ERR_LAUNCH;
 }
 

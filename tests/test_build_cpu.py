@@ -180,3 +180,22 @@ def test_kernels_of_rows_far_apart_wait_no_earlier(asm, name):
         assert rows, kernel
         for w in (w for i in rows for w in flow.behind(i, "tile", "mfma", "barrier") if isinstance(flow.events[w], tuple)):
             assert "tile" not in {flow.events[k] for k in flow.behind(w, "mfma", "barrier")}, kernel
+
+
+def test_split_backward_loops_load_no_argument(asm):
+    """A kernel argument loaded inside a loop over tiles is awaited there, in every round, with the wave's only chain of
+    work behind it: the arguments of the split backward fit the scalar registers it has."""
+    seen = 0
+    for m in re.finditer(r"\n(_ZN5spark20mha_bwd_split_kernelI\w+):", asm):
+        body = asm[m.end():]
+        body = body[:body.index("\n.Lfunc_end")]
+        parts = re.split(r"\n(\.LBB[0-9_]+):", body)
+        labels, blocks = ["entry"] + parts[1::2], [parts[0]] + parts[2::2]
+        loops = [(labels.index(t), i) for i, b in enumerate(blocks) for t in re.findall(r"s_c?branch\w* (\.LBB[0-9_]+)", b)
+                 if t in labels and labels.index(t) <= i]
+        inner = [l for l in loops if not any(o != l and l[0] <= o[0] and o[1] <= l[1] for o in loops)]
+        tiles = [b for a, z in inner for b in ["\n".join(blocks[a:z + 1])] if "v_mfma" in b]
+        assert len(tiles) >= 2, m.group(1)  # dQ and dK/dV
+        assert not any("s_load" in b or "scratch_" in b for b in tiles), m.group(1)
+        seen += 1
+    assert seen == 16
