@@ -87,7 +87,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
   using C = BwdKvPipeCfg<D>;
   constexpr int KS = D / 16, DT = D / 32;
 
-  // D = 64: few offset registers; with dropout the kernel needs 248 to 255 of its 256 and spilled with all of them
+  // D = 64: few offset registers; with dropout the kernel needs 247 to 254 of its 256 and spilled with all of them
   // (dK/dV, us, 256 causal heads x 512 44.1 -> 41.4; without dropout 0 ... 1 % less)
   using LaneOffsets = std::conditional_t<D == 64, SwzLaneLean<D>, SwzLane<D>>;
   SPARK_LDS char* const smem = lds_origin();
@@ -250,10 +250,11 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
         pk_ds[r8 >> 1] = pack2<T>(ds[r8 - 1], ds[r8]);
       }
     };
-    // With dropout at D = 64 there is one register too few for krow - 4 g across the loop: formed anew where a mask needs
-    // it.  Spilled, it was awaited inside the loop, together with the stage just requested (us, bf16, causal 256 heads x 512
-    // 39.4 -> 38.5, equal at 256 x 2048).
-    constexpr bool ANEW = DROP && D == 64;
+    // In fp16 with dropout at D = 64, rows far apart, there is one register too few for krow - 4 g across the loop: formed anew
+    // where a mask needs it.  Spilled, it is awaited inside the loop, together with the stage just requested (us, backward,
+    // 512 heads x 192 44.5 -> 42.3, 256 x 512 70.2 -> 68.4).  The other kernels hold it and are slower without it (bf16
+    // 64 x 2048 162.4 -> 164.4, 140 x 512 60.1 -> 60.5; fp16, rows in order, d = 48 140 x 512 55.0 -> 55.4).
+    constexpr bool ANEW = DROP && D == 64 && F::FINITE_DOT && M == FAR;
     auto ahead_of = [&](int q0s) {
       int l = lane;
       if (ANEW) asm volatile("" : "+v"(l));
