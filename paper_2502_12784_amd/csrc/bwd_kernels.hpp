@@ -75,7 +75,7 @@ static __device__ __forceinline__ float dropout_ds(uint32_t keep, float pe, floa
 }
 
 // The workgroup's part: key tile `item` of `head`, and its partner if the causal tiles are paired.
-template <typename T, int D, bool CAUSAL, bool DROP, Lanes M>
+template <typename T, int D, bool CAUSAL, bool DROP, Lanes M, bool COMPARE = false>
 static __device__ __forceinline__ void bwd_dkdv_pipe(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const T* __restrict__ dO, const float* __restrict__ LSE2, const float* __restrict__ Dws,
@@ -232,8 +232,13 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
       float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2, -l[r8 >> 2][r8 & 3]));
       if (mask) pe = ahead > 8 * (r / 4) + (r % 4) ? 0.f : pe;
       if (DROP) {
-        if ((r & 3) == 0) strip = keep_strip(kb[r >> 2], dr);  // in the slot of the first of four entries
-        const uint32_t keep = keep_mask(strip, r & 3);
+        uint32_t keep;
+        if (COMPARE) {
+          keep = keep_reg(kb, r, dr.thr) ? 0xFFFFFFFFu : 0u;
+        } else {
+          if ((r & 3) == 0) strip = keep_strip(kb[r >> 2], dr);  // in the slot of the first of four entries
+          keep = keep_mask(strip, r & 3);
+        }
         p[r8] = keep_float(keep, pe);
         asm volatile("" : "+v"(p[r8]));  // keeps the select in front of the packed conversion
         ds[r8] = dropout_ds<T>(keep, pe, p[r8], dp[r], d[r8 >> 2][r8 & 3]);
@@ -515,6 +520,9 @@ static __device__ __forceinline__ void bwd_dq(
   using F = Frag<T>;
   using v8 = typename F::v8;
   using C = BwdQCfg<D, CAUSAL, DROP>;
+  // The exchange of the generator's words behind one score product or two: far apart in one slot causal kernels at D > 64 lost 1 %, in
+  // order in two slots all of them 1 to 5 % (us, fp16, both sides, 4 heads x 4096, d = 112 146.5 -> 139.8 in one).
+  constexpr bool TWO_SLOTS = D == 64 || M == FAR;
   constexpr int KS = D / 16, DT = D / 32;
 
   // few offset registers in the causal kernels: with dropout at D = 128 all of them spill (dQ, us, 512 heads x 512 115.7 ->
@@ -704,12 +712,12 @@ static __device__ __forceinline__ void bwd_dq(
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt) {
             dp[mt] = F::mfma(fa[(KS + ks) % AHEAD][mt], dof[ks], dp[mt]);
-            if (DROP && ks == 0) {  // in two parts: in one slot, causal kernels at D > 64 lost 1 %
+            if (DROP && ks == 0) {
               keep[mt][0] = rng[mt].c0; keep[mt][1] = rng[mt].c1; keep[mt][2] = rng[mt].c2; keep[mt][3] = rng[mt].c3;
               exchange_bit0<M>(keep[mt], lane);
-              asm volatile("" : "+v"(keep[mt][0]), "+v"(keep[mt][1]), "+v"(keep[mt][2]), "+v"(keep[mt][3]));
+              if (TWO_SLOTS) asm volatile("" : "+v"(keep[mt][0]), "+v"(keep[mt][1]), "+v"(keep[mt][2]), "+v"(keep[mt][3]));
             }
-            if (DROP && ks == 2) {
+            if (DROP && ks == (TWO_SLOTS ? 2 : 0)) {
               exchange_bit1<M>(keep[mt], lane);
               asm volatile("" : "+v"(keep[mt][0]), "+v"(keep[mt][1]), "+v"(keep[mt][2]), "+v"(keep[mt][3]));
             }
@@ -852,13 +860,36 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void mha_bwd_merged_kernel(
   const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
   const int head = logical / (qitems + kitems);
   const int item = logical - head * (qitems + kitems);
+  // decisions of dropout by a compare and a select each instead of masks: us, fp16, causal, 6 heads x 4000, d = 80 147.5 ->
+  // 146.2, 24 x 1024 47.5 -> 47.0; bf16 equal
+  constexpr bool COMPARE = D == 96 && CAUSAL && Frag<T>::FINITE_DOT;
   if (item < kitems)  // the longer ones first
-    bwd_dkdv_pipe<T, D, CAUSAL, DROP, IN_ORDER>(Q, K, V, dO, LSE2ws, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq, Nk, dh, nkt,
-                                      paired, scale, dr, head, item);
+    bwd_dkdv_pipe<T, D, CAUSAL, DROP, IN_ORDER, COMPARE>(Q, K, V, dO, LSE2ws, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq,
+                                                         Nk, dh, nkt, paired, scale, dr, head, item);
   else
-    bwd_dq<T, D, CAUSAL, DROP, true, IN_ORDER>(Q, K, V, nullptr, dO, nullptr, Dws, LSE2ws, dQ, mq, mk, mv, mdo, mdo, mdq, H, Nq,
-                                     Nk, dh, nqt, paired, scale, scale * 1.4426950408889634f, dr, head,
-                                     item - kitems);
+    bwd_dq<T, D, CAUSAL, DROP, true, IN_ORDER>(Q, K, V, nullptr, dO, nullptr, Dws, LSE2ws, dQ, mq, mk, mv, mdo, mdo, mdq, H,
+                                               Nq, Nk, dh, nqt, paired, scale, scale * 1.4426950408889634f, dr, head,
+                                               item - kitems);
+}
+
+// With dropout, the rows far apart in the lanes (column_row); the rule is far_rows.
+template <typename T, int D, bool CAUSAL>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void mha_bwd_merged_far_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
+    float* __restrict__ Dws, float* __restrict__ LSE2ws, T* __restrict__ dQ, T* __restrict__ dK, T* __restrict__ dV,
+    TensorMap mq, TensorMap mk, TensorMap mv, TensorMap mdo, TensorMap mdq, TensorMap mdk, TensorMap mdv, int H,
+    int Nq, int Nk, int dh, int nqt, int nkt, int paired, float scale, Dropout dr) {
+  const int qitems = paired ? causal_items<CAUSAL>(nqt) : nqt, kitems = paired ? causal_items<CAUSAL>(nkt) : nkt;
+  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int head = logical / (qitems + kitems);
+  const int item = logical - head * (qitems + kitems);
+  if (item < kitems)  // the longer ones first
+    bwd_dkdv_pipe<T, D, CAUSAL, true, FAR>(Q, K, V, dO, LSE2ws, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq, Nk, dh,
+                                           nkt, paired, scale, dr, head, item);
+  else
+    bwd_dq<T, D, CAUSAL, true, true, FAR>(Q, K, V, nullptr, dO, nullptr, Dws, LSE2ws, dQ, mq, mk, mv, mdo, mdo, mdq, H,
+                                          Nq, Nk, dh, nqt, paired, scale, scale * 1.4426950408889634f, dr, head,
+                                          item - kitems);
 }
 
 }  // namespace spark

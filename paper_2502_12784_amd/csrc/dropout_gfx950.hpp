@@ -79,10 +79,11 @@ static __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, u
 //   IN_ORDER  0, 1                               16                       15.4 /  9.2 / 27 / 13.0 / 14.1 / 14.0 / 27
 //   NEAR      0, 4                               10                       15.5 / 14.5 / 27 / 14.3 / 14.1 / 15.1 / 27
 //   FAR       3, 4                                8                       28.8 / 27.9 / 27 / 27.5 / 27.3 / 27.2 / 27
-// FAR in the forward at 64 columns, which loads one operand's rows for a long loop, and in a backward of two grids as far_rows
-// decides there; NEAR in mha_fwd_split_kernel, whose eight waves load the same rows; IN_ORDER elsewhere.  (FAR in all of them,
-// us, fp16: forward 4 heads x 512, d = 96 9.0 -> 9.6, now 8.8; 100 x 384, d = 112 17.9 -> 18.2, now 17.2; backward
-// causal 140 x 512, d = 48 55.0 -> 57.2; d = 96 87.9 -> 92.3; 4 x 512, d = 48 8.2 -> 8.9.)
+// FAR in the forward at 64 columns and in its workgroups of eight waves, which load one operand's rows for a long loop, and in the
+// backward's 128-row tiles as far_rows decides; NEAR in mha_fwd_split_kernel, whose eight waves load the same rows (IN_ORDER where its
+// causal form has 128 columns: 4 heads x 512 10.8 -> 10.6 us); IN_ORDER elsewhere.  (FAR in all of them, us, fp16: forward 4 x 512,
+// d = 96 9.0 -> 9.6, now 8.8; 100 x 384, d = 112 17.9 -> 18.2, now 17.2; backward causal 140 x 512, d = 48 55.0 -> 57.2, d = 96
+// 87.9 -> 92.3; 4 x 512, d = 48 8.2 -> 8.9.  IN_ORDER with eight waves: causal 10 x 7168, d = 128 207.3 -> 210.9.)
 enum Lanes { IN_ORDER, NEAR, FAR };
 template <Lanes M> static __device__ __forceinline__ int column_row(int lane) {
   return M == NEAR  ? (lane & 14) << 1 | ((lane >> 3) & 2) | (lane & 1)

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void mha_
   // the lane index read anew in the epilogue, 17 ... 25 vector registers less and no spills: causal d = 64 128 x 1024
   // 31.8 -> 29.3 us, d = 80 36 x 1333 29.4 -> 27.1, d = 64 96 x 512 14.4 -> 13.2.)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  constexpr Lanes LANES = DROP && D == 64 ? FAR : IN_ORDER;
+  constexpr Lanes LANES = DROP && (D == 64 || NW == 8) ? FAR : IN_ORDER;
   const int g = lane >> 5, c32 = column_row<LANES>(lane);
   const uint32_t k_row_bytes = (uint32_t)mk.row * 2, v_row_bytes = (uint32_t)mv.row * 2;
   const uint32_t k_lane_src = dma_lane_src<D>(wave & 3, lane, k_row_bytes, dh);

@@ -61,7 +61,7 @@ __global__ __launch_bounds__(512, 1) void mha_fwd_split_kernel(
   SPARK_LDS char* const smem = lds_origin();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  constexpr Lanes LANES = DROP ? NEAR : IN_ORDER;
+  constexpr Lanes LANES = DROP && !(CAUSAL && D == 128) ? NEAR : IN_ORDER;
   const int g = lane >> 5, c32 = column_row<LANES>(lane);
   SPARK_LDS char* const kb = smem + wave * 2 * C::TILE;
   SPARK_LDS char* const vb = kb + C::TILE;

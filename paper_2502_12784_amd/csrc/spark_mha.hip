@@ -424,13 +424,40 @@ bool merged_backward(const Problem& p) {
 
 template <int D> constexpr int dkdv_per_cu = D == 64 ? 2 : 1;  // workgroups of the dK/dV and of the merged kernel on a CU
 
+// How the kernels of 128-row tiles spread their rows over the lanes under dropout (column_row): far apart the exchange of the
+// generator's words is cheaper, which is kept where no operand's rows load faster in order.  Neighbouring lanes' addresses agree
+// in bit 6, in order if rows are a multiple of 128 bytes apart, far apart already at a multiple of 32.  Backward, us, fp16 / bf16,
+// in order -> far:
+//   d = 64:   64 heads x 2048 299 / 291 -> 292 / 283      512 x 192 48.0 / 47.5 -> 48.4 / 47.7
+//             both sides in one grid: 8 x 2048 49.0 / 49.9 -> 48.3 / 48.9, causal 6 x 4000 96.0 / 99.1 -> 94.5 / 96.1
+//   d = 128:  64 x 2048 524 / 505 -> 513 / 493, causal 301 / 291 -> 297 / 287      140 x 512 120.2 / 117.9 -> 119.8 / 117.6
+//             but 512 x 192 94.1 / 93.0 -> 95.1 / 94.5, causal 140 x 512 109.1 / 107.9 -> 110.2 / 109.0: from 512 rows of the loop on
+//   rows of 96 and 224 bytes, causal 140 x 512: d = 48 55.0 / 56.3 -> 57.2 / 58.4, d = 112 100.0 / 100.5 -> 106.2 / 106.4
+//   odd multiples of 16 bytes, which agree less often: d = 56 causal 140 x 512 56.1 / 57.4 -> 57.2 / 57.8, 64 x 2048 290 / 282 -> 284 / 277: from
+//             1024 rows on
+// Not at 96 columns (d = 80, 64 x 2048 equal; causal 140 x 512 85.7 / 86.7 -> 90.3 / 91.5).
+bool far_rows(const Problem& p) {
+  const int loop = p.Nq < p.Nk ? p.Nq : p.Nk;
+  if (p.d > 64 && loop < (p.causal ? 1024 : 512)) return false;
+  for (const TensorMap* m : {&p.mq, &p.mk, &p.mv, &p.mo, &p.mdo}) {
+    const long long bytes = m->row * 2;
+    if (bytes % 128 != 0 && (bytes % 32 == 0 || loop < 1024)) return false;
+  }
+  return true;
+}
+
 template <typename T, int D, bool CAUSAL, bool DROP>
 int launch_bwd_merged(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const float* LSE,
                       const void* dO, void* dQ, void* dK, void* dV, float* Dws) {
   auto kernel = mha_bwd_merged_kernel<T, D, CAUSAL, DROP>;
+  static std::atomic<uint64_t> ready[2] = {};
+  bool far = false;
+  if constexpr (DROP && D != 96) {
+    far = far_rows(p);
+    if (far) kernel = mha_bwd_merged_far_kernel<T, D, CAUSAL>;
+  }
   constexpr int SMEM = BwdMergedCfg<D>::SMEM;
-  static std::atomic<uint64_t> ready{0};
-  const int attr = ensure_smem(kernel, SMEM, ready);
+  const int attr = ensure_smem(kernel, SMEM, ready[far]);
   if (attr != SPARK_OK) return attr;
   const int BH = p.B * p.H, rows = BH * p.Nq;
   const Dropout dr = make_dropout(p.thr, p.seed, p.offset);
@@ -453,21 +480,6 @@ int launch_bwd_merged(const Problem& p, const void* Q, const void* K, const void
 // Optional profiling marks between the kernels of a backward (spark_mha_bwd_marked).
 bool mark(const Problem& p, void* const* ev, int i) {
   return !ev || hipEventRecord(static_cast<hipEvent_t>(ev[i]), p.st) == hipSuccess;
-}
-
-// How a kernel per side spreads its rows over the lanes under dropout (column_row): far apart the exchange of the generator's
-// words is cheaper, which is kept where no operand's rows load faster in order.  Neighbouring lanes' addresses agree in bit 6, in
-// order if rows are a multiple of 128 bytes apart, far apart already at a multiple of 32.  Backward, us, fp16 / bf16, in order -> far:
-//   d = 64:   64 heads x 2048 299 / 291 -> 292 / 283      512 x 192 48.0 / 47.5 -> 48.4 / 47.7
-//   d = 128:  64 x 2048 524 / 505 -> 513 / 493, causal 301 / 291 -> 297 / 287      140 x 512 120.2 / 117.9 -> 119.8 / 117.6
-//             but 512 x 192 94.1 / 93.0 -> 95.1 / 94.5, causal 140 x 512 109.1 / 107.9 -> 110.2 / 109.0: from 512 rows of the loop on
-//   rows of 96 and 224 bytes, causal 140 x 512: d = 48 55.0 / 56.3 -> 57.2 / 58.4, d = 112 100.0 / 100.5 -> 106.2 / 106.4
-// Not at 96 columns (d = 80, 64 x 2048 equal; 140 x 512 causal 85.6 -> 90.1).
-bool far_rows(const Problem& p) {
-  if (p.d > 64 && (p.Nq < p.Nk ? p.Nq : p.Nk) < (p.causal ? 1024 : 512)) return false;
-  for (const TensorMap* m : {&p.mq, &p.mk, &p.mv, &p.mo, &p.mdo})
-    if ((m->row * 2) % 32 == 0 && (m->row * 2) % 128 != 0) return false;
-  return true;
 }
 
 // One kernel per side.

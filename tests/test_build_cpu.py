@@ -163,7 +163,7 @@ def test_host_binding_needs_no_compiler_but_hipccs(monkeypatch, tmp_path):
     assert seen[1][0] == "some-c++"
 
 
-@pytest.mark.parametrize("name", ["mha_bwd_dq_far_kernel", "mha_bwd_dkdv_pipe_far_kernel"])
+@pytest.mark.parametrize("name", ["mha_bwd_dq_far_kernel", "mha_bwd_dkdv_pipe_far_kernel", "mha_bwd_merged_far_kernel"])
 def test_kernels_of_rows_far_apart_wait_no_earlier(asm, name):
     """The two orders above in the dropout kernels whose rows are spread over the lanes: with the loop's wait at its
     barrier, and, without a mask, rows and first tile requested before anything is waited for."""
@@ -175,7 +175,7 @@ def test_kernels_of_rows_far_apart_wait_no_earlier(asm, name):
         for w in (w for i in loops for w in flow.behind(i, "barrier") if isinstance(flow.events[w], tuple)):
             assert "mfma" not in {flow.events[k] for k in flow.behind(w, "barrier")}, kernel
         rows = [i for i, e in enumerate(flow.events) if e == "row"]
-        if not re.search(r"Li64ELb0E" if "dkdv" in name else r"Li\d+ELb0E", kernel):
+        if not re.search(r"Li\d+ELb0E" if "_dq_" in name else r"Li64ELb0E", kernel):
             continue
         assert rows, kernel
         for w in (w for i in rows for w in flow.behind(i, "tile", "mfma", "barrier") if isinstance(flow.events[w], tuple)):

@@ -1,5 +1,5 @@
-"""The rows of a block may be spread over the lanes in two ways by the dropout kernels of a backward in two grids, by the
-strides of the operands' rows and the length of the loop (far_rows in csrc/spark_mha.hip).  Which lane holds a row does not
+"""The rows of a block may be spread over the lanes in two ways by the dropout kernels of the backward's 128-row tiles, by
+the strides of the operands' rows and the length of the loop (far_rows in csrc/spark_mha.hip).  Which lane holds a row does not
 enter its arithmetic: the same problem with rows further apart gives the same bits."""
 import math
 
@@ -11,14 +11,15 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["float16", "bfloat16"])
-@pytest.mark.parametrize("heads, Nq, Nk, d, causal", [
-    (160, 203, 203, 64, False), (160, 203, 203, 64, True), (160, 203, 140, 48, False), (160, 190, 190, 32, True),
-    (130, 140, 300, 40, False), (40, 530, 520, 128, False), (40, 1030, 1030, 128, True), (40, 1030, 1030, 112, True)])
-def test_row_strides_do_not_change_the_bits(heads, Nq, Nk, d, causal, dtype):
+@pytest.mark.parametrize("heads, Nq, Nk, d, causal, grids", [
+    (160, 203, 203, 64, False, 2), (160, 203, 203, 64, True, 2), (160, 203, 140, 48, False, 2), (160, 190, 190, 32, True, 2),
+    (130, 140, 300, 40, False, 2), (40, 530, 520, 128, False, 2), (40, 1030, 1030, 128, True, 2), (40, 1030, 1030, 112, True, 2),
+    (20, 530, 520, 64, False, 1), (50, 300, 300, 48, True, 1), (11, 700, 530, 128, False, 1), (20, 1030, 1030, 128, True, 1)])
+def test_row_strides_do_not_change_the_bits(heads, Nq, Nk, d, causal, grids, dtype):
     import torch
     from paper_2502_12784_amd import spark_mha_strided_bwd, spark_mha_strided_fwd
     dt = getattr(torch, dtype)
-    assert load_library().spark_mha_bwd_grids(1, heads, Nq, Nk, d, causal, 0.1, int(dtype == "bfloat16")) == 2
+    assert load_library().spark_mha_bwd_grids(1, heads, Nq, Nk, d, causal, 0.1, int(dtype == "bfloat16")) == grids
     print(f"\n[lanes] {heads} x {Nq} over {Nk}, d = {d}, {'causal' if causal else 'full'} {dtype}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(11)
     src = [torch.randn(1, heads, n, d, generator=g, device="cuda").to(dt) for n in (Nq, Nk, Nk, Nq)]
