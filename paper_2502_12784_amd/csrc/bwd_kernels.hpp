@@ -240,7 +240,7 @@ static __device__ __forceinline__ void bwd_dkdv_pipe(
           keep = keep_mask(strip, r & 3);
         }
         p[r8] = keep_float(keep, pe);
-        asm volatile("" : "+v"(p[r8]));  // keeps the select in front of the packed conversion
+        asm volatile("" : "+v"(p[r8]));  // keeps the mask in front of the packed conversion
         ds[r8] = dropout_ds<T>(keep, pe, p[r8], dp[r], d[r8 >> 2][r8 & 3]);
       } else {
         p[r8] = pe;

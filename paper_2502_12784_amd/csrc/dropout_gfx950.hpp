@@ -21,8 +21,8 @@ namespace spark {
 struct Dropout {
   uint32_t key0, key1;  // seed, low and high word
   uint32_t offset;      // counter word 3: distinguishes calls that share a seed
-  uint32_t thr;         // drop iff byte < thr (0..255)
-  uint32_t keep_add;    // 256 - thr in every byte: byte + (256 - thr) carries iff byte >= thr
+  uint32_t thr;         // drop iff byte < thr (1..255 in the kernels below; a rate of 0 runs the kernels without dropout)
+  uint32_t keep_add;    // 256 - thr in every byte, which holds none for 0: byte + (256 - thr) carries iff byte >= thr
   float keep_prob;      // (256 - thr) / 256
   float rescale;        // 256 / (256 - thr)
 };
@@ -130,7 +130,8 @@ template <Lanes M> static __device__ __forceinline__ void exchange_words(uint32_
 // byte brings the others there.  A compare and a select for each entry are eight instructions for four; in pairs it is six, by
 // strips seven, whose last four (v_and_b32 of a sign-extended byte) sit where the entries are used (us, forward, d = 64 256
 // heads x 2048 403 -> 386, causal d = 128 64 x 4096 352 -> 339; dK/dV, d = 64, the same 640 -> 629).  In the dQ kernel, whose
-// entries choose between two values, a compare and a select stay the shorter form.
+// entries choose between two values, a compare and a select stay the shorter form.  mha_fwd_split_kernel, too, compares and selects
+// each entry; masks have not been measured there.
 static __device__ __forceinline__ uint32_t keep_flags(uint32_t bytes, const Dropout& dr) {
   return __builtin_amdgcn_lerp(bytes, dr.keep_add, 0);
 }

@@ -118,7 +118,7 @@ Dropout make_dropout(int thr, unsigned long long seed, unsigned offset) {
   dr.key1 = (uint32_t)(seed >> 32);
   dr.offset = offset;
   dr.thr = (uint32_t)thr;
-  dr.keep_add = (uint32_t)(256 - thr) * 0x01010101u;
+  dr.keep_add = thr ? (uint32_t)(256 - thr) * 0x01010101u : 0;  // of use to kernels with dropout only
   dr.keep_prob = (float)(256 - thr) / 256.0f;
   dr.rescale = 256.0f / (float)(256 - thr);
   return dr;
@@ -582,7 +582,8 @@ int launch_bwd_atomic(const Problem& p, const void* Q, const void* K, const void
   return hipGetLastError() == hipSuccess ? SPARK_OK : SPARK_ERR_LAUNCH;
 }
 
-// Expand the (dtype, d, causal, dropout) runtime tuple into a template instantiation.
+// Expand the (dtype, d, causal, dropout) runtime tuple into a template instantiation.  A threshold of 0 must not reach the
+// kernels with dropout: what they add to a byte to decide it has no byte for it.
 #define SPARK_DISPATCH_CD(FN, T, D, ...)                                                    \
   do {                                                                                      \
     if (p.causal) return p.thr ? FN<T, D, true, true>(__VA_ARGS__)                          \

@@ -254,7 +254,8 @@ template <int D> struct WaveDma {
 
 // Write a wave's transposed accumulator (D x 32, lane = column) times `mul` as 32 rows of D
 // 16-bit values: through the wave's LDS slice `ob`, then 16-byte row stores for rows < N
-// and columns < dh (`row_stride` elements apart).  The rows lie in the lanes as column_row<M> says.
+// and columns < dh (`row_stride` elements apart).  The rows lie in the lanes as column_row<M> says; rows four
+// apart in neighbouring lanes (FAR) meet two to a bank in the slice, whose row stride spreads consecutive ones.
 template <typename T, int D, int OSTR, Lanes M = IN_ORDER>
 static __device__ __forceinline__ void store_transposed(const f32x16 (&acc)[D / 32], float mul,
                                                         SPARK_LDS char* ob, T* __restrict__ out,
