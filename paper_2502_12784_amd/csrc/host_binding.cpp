@@ -4,7 +4,8 @@
 //
 // Small problems are bound by the host: a training step of 2 heads x 128 tokens took 33 us a pass with its
 // marshalling in Python through ctypes (nine tensors checked and six allocated in the interpreter, arguments
-// converted one by one), here 18 us with the same three launches, 14 us with two (12 us of kernels).
+// converted one by one), here 18 us with the same three launches, 14.4 us with two and 13.8 us with the allocations
+// below (10.7 us of kernels).
 //
 // Nothing is refused or reported here.  Whatever is not an ordinary call (a wrong shape, type, device or
 // layout, a tensor subclass or transform wrapper, an active dispatch mode, a number that is not a plain
@@ -99,7 +100,8 @@ bool modes_active() {
 
 // Allocations of a call.  With nothing in the thread's dispatch state that wants to see them (a tracer, a transform, a
 // profiler) they go to the device's kernel directly: a step of 2 heads x 128 tokens makes six of them, and the way there
-// through the dispatcher, and through empty_like's choice of a layout, took 0.65 of its 14.2 us.
+// through the dispatcher, and through empty_like's choice of a layout, took 0.6 of its 14.4 us (both ways in alternating
+// blocks of one process, whose medians vary by 0.1 us; from process to process a pass varies by 1 us).
 class Allocator {
  public:
   explicit Allocator(const at::Tensor& like)

@@ -93,23 +93,39 @@ def test_unusual_calls_take_the_general_path():
         spark_mha_fwd(q.float(), q.float(), q.float(), 0.125, False)
 
 
-@pytest.mark.parametrize("profiled", [False, True])
-def test_allocated_outputs_have_the_layout_of_empty_like(profiled):
-    """Outputs that the call allocates by itself, with and without a profiler that watches allocations."""
+@pytest.mark.parametrize("watched", ["not", "profiler", "inference"])
+def test_allocated_outputs_are_those_of_empty_like(watched, monkeypatch):
+    """Outputs that the call allocates by itself: the layout of empty_like, and nobody who watches allocations misses one.
+    The dispatcher reports an allocation to a profiler, the device's allocation kernel by itself does not."""
     import contextlib
     import torch
-    from paper_2502_12784_amd import spark_mha_strided_bwd, spark_mha_strided_fwd
+    from paper_2502_12784_amd import binding, spark_mha_strided_bwd, spark_mha_strided_fwd
+    binding.load_library()
     dense = torch.randn(2, 3, 40, 64, device="cuda").half()
     views = [dense, dense.transpose(0, 1).contiguous().transpose(0, 1), dense.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3),
              dense[:, :1], dense[:1, :, :, :32], dense.as_strided((1, 3, 40, 64), (8, 2560, 64, 1)), dense[:, :, :1]]
-    watch = torch.profiler.profile if profiled else contextlib.nullcontext
-    with watch():
-        for q in views:
+    host, taken = binding._host, []
+
+    class Seen:
+        fwd = staticmethod(lambda *a: taken.append(host.fwd(*a)) or taken[-1])
+        bwd = staticmethod(lambda *a: taken.append(host.bwd(*a)) or taken[-1])
+
+    monkeypatch.setattr(binding, "_host", Seen)
+    for q in views:
+        grad = torch.empty_like(q).copy_(q)
+        watch = {"not": contextlib.nullcontext, "inference": torch.inference_mode,
+                 "profiler": lambda: torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU])}[watched]()
+        with watch:
             O, L = spark_mha_strided_fwd(q, q, q, 0.125)
-            out = (O,) + spark_mha_strided_bwd(q, q, q, O, L, torch.empty_like(q).copy_(q), 0.125)
-            for t in out:
-                assert t.stride() == torch.empty_like(q).stride() and t.device == q.device and not t.requires_grad
-            assert L.stride() == torch.empty(L.shape).stride() and L.dtype == torch.float32
+            out = (O,) + spark_mha_strided_bwd(q, q, q, O, L, grad, 0.125)
+        for t in out:
+            assert t.stride() == torch.empty_like(q).stride() and t.device == q.device and not t.requires_grad
+        assert L.stride() == torch.empty(L.shape).stride() and L.dtype == torch.float32
+        assert all(t.is_inference() == (watched == "inference") for t in out + (L,))
+        if watched == "profiler":  # O, LSE, dQ, dK, dV and the workspace
+            names = [e.name for e in watch.events()]
+            assert sum(n in ("aten::empty", "aten::empty_like", "aten::empty_strided") for n in names) >= 6
+    assert len(taken) == 2 * len(views) and all(t is not None for t in taken)
 
 
 @pytest.mark.filterwarnings("ignore:Named tensors")
