@@ -299,9 +299,11 @@ __global__ __launch_bounds__(64 * BwdSplitCfg<D>::NW, 1) void mha_bwd_split_kern
         if (DROP) {
           // fp16: a compare and a select, behind which dS and its conversion are one v_fma_mix (us, masks -> so: causal
           // 2 x 128, d = 128 10.5 -> 10.4; 4 x 1024 equal).  bf16: masks (compare and select: 4 x 1024, d = 64 14.5
-          // against 13.7, causal d = 128 26.4 against 25.5, but d = 128 without a mask 24.2 against 24.6).
+          // against 13.7, causal d = 128 26.4 against 25.5), but not at more than 64 columns without the causal mask (masks -> so: 2 x
+          // 1000, d = 128 24.5 -> 24.0, d = 96 23.4 -> 22.9; 4 x 200, d = 128 12.3 -> 12.1).
+          constexpr bool COMPARE = F::FINITE_DOT || (D > 64 && !CAUSAL);
           uint32_t kept;
-          if (F::FINITE_DOT) {
+          if (COMPARE) {
             kept = keep_reg(keep, r, dr.thr) ? 0xFFFFFFFFu : 0u;
           } else {
             if ((r & 3) == 0) keep[r >> 2] = keep_strip(keep[r >> 2], dr);
