@@ -850,6 +850,14 @@ template <int D> struct BwdMergedCfg {
   static_assert(SMEM >= BwdQCfg<D, false, false>::SMEM, "the dK/dV side needs more, whatever the other's tile");
 };
 
+// dK/dV's decisions of dropout by a compare and a select each in the causal merged kernels that gain by it (backward, us, masks ->
+// so): 96 columns, 6 heads x 4000, d = 80 fp16 147.5 -> 146.2, bf16 152.4 -> 150.7, 24 x 1024 47.5 -> 47.0, 49.9 -> 49.4; fp16 at
+// d = 64, 64 x 384 21.3 -> 21.2, 24 x 1024 36.7 -> 36.6 (bf16 36.8 -> 38.2); bf16 at d = 128, rows far apart, 7 x 2240 87.7 -> 86.0
+// (fp16 85.3 -> 86.3; in order, 60 x 400, 37.5 -> 38.0 in both types).  With one grid per side masks are as fast or faster
+// (bf16, 140 x 512, d = 96 89.6 -> 90.5, d = 64 61.2 -> 62.9; 64 x 2048, d = 128 291 -> 295).
+template <typename T, int D, bool CAUSAL, Lanes M>
+constexpr bool merged_compares = CAUSAL && (D == 96 || (D == 64 ? Frag<T>::FINITE_DOT : !Frag<T>::FINITE_DOT && M == FAR));
+
 template <typename T, int D, bool CAUSAL, bool DROP>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void mha_bwd_merged_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
@@ -860,9 +868,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void mha_bwd_merged_kernel(
   const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
   const int head = logical / (qitems + kitems);
   const int item = logical - head * (qitems + kitems);
-  // decisions of dropout by a compare and a select each instead of masks: us, fp16, causal, 6 heads x 4000, d = 80 147.5 ->
-  // 146.2, 24 x 1024 47.5 -> 47.0; bf16 equal
-  constexpr bool COMPARE = D == 96 && CAUSAL && Frag<T>::FINITE_DOT;
+  constexpr bool COMPARE = merged_compares<T, D, CAUSAL, IN_ORDER>;
   if (item < kitems)  // the longer ones first
     bwd_dkdv_pipe<T, D, CAUSAL, DROP, IN_ORDER, COMPARE>(Q, K, V, dO, LSE2ws, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq,
                                                          Nk, dh, nkt, paired, scale, dr, head, item);
@@ -884,8 +890,8 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void mha_bwd_merged_far_kerne
   const int head = logical / (qitems + kitems);
   const int item = logical - head * (qitems + kitems);
   if (item < kitems)  // the longer ones first
-    bwd_dkdv_pipe<T, D, CAUSAL, true, FAR>(Q, K, V, dO, LSE2ws, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq, Nk, dh,
-                                           nkt, paired, scale, dr, head, item);
+    bwd_dkdv_pipe<T, D, CAUSAL, true, FAR, merged_compares<T, D, CAUSAL, FAR>>(
+        Q, K, V, dO, LSE2ws, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq, Nk, dh, nkt, paired, scale, dr, head, item);
   else
     bwd_dq<T, D, CAUSAL, true, true, FAR>(Q, K, V, nullptr, dO, nullptr, Dws, LSE2ws, dQ, mq, mk, mv, mdo, mdo, mdq, H,
                                           Nq, Nk, dh, nqt, paired, scale, scale * 1.4426950408889634f, dr, head,
