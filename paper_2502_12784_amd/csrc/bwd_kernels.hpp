@@ -470,8 +470,11 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void mha_bwd_dkdv_pipe_kernel
   const int items = paired ? causal_items<CAUSAL>(nkt) : nkt;  // causal: key tiles (p, nkt-1-p)
   const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
   const int head = logical / items;
-  bwd_dkdv_pipe<T, D, CAUSAL, DROP, IN_ORDER>(Q, K, V, dO, LSE2, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq, Nk, dh,
-                                              nkt, paired, scale, dr, head, logical - head * items);
+  // decisions of dropout by a compare and a select each in fp16 at 128 columns, causal (backward, us, masks -> so: 140 x 512,
+  // d = 112 101.3 -> 100.5, d = 128 140 x 700 135.7 -> 134.8; without the causal mask, d = 112 115.7 -> 116.5)
+  constexpr bool COMPARE = D == 128 && CAUSAL && Frag<T>::FINITE_DOT;
+  bwd_dkdv_pipe<T, D, CAUSAL, DROP, IN_ORDER, COMPARE>(Q, K, V, dO, LSE2, Dws, dK, dV, mq, mk, mv, mdo, mdk, mdv, H, Nq,
+                                                       Nk, dh, nkt, paired, scale, dr, head, logical - head * items);
 }
 
 // With dropout, the rows far apart in the lanes (column_row); the rule is far_rows.
@@ -854,7 +857,7 @@ template <int D> struct BwdMergedCfg {
 // so): 96 columns, 6 heads x 4000, d = 80 fp16 147.5 -> 146.2, bf16 152.4 -> 150.7, 24 x 1024 47.5 -> 47.0, 49.9 -> 49.4; fp16 at
 // d = 64, 64 x 384 21.3 -> 21.2, 24 x 1024 36.7 -> 36.6 (bf16 36.8 -> 38.2); bf16 at d = 128, rows far apart, 7 x 2240 87.7 -> 86.0
 // (fp16 85.3 -> 86.3; in order, 60 x 400, 37.5 -> 38.0 in both types).  With one grid per side masks are as fast or faster
-// (bf16, 140 x 512, d = 96 89.6 -> 90.5, d = 64 61.2 -> 62.9; 64 x 2048, d = 128 291 -> 295).
+// at those (bf16, 140 x 512, d = 96 89.6 -> 90.5, d = 64 61.2 -> 62.9; 64 x 2048, d = 128 291 -> 295).
 template <typename T, int D, bool CAUSAL, Lanes M>
 constexpr bool merged_compares = CAUSAL && (D == 96 || (D == 64 ? Frag<T>::FINITE_DOT : !Frag<T>::FINITE_DOT && M == FAR));
 
