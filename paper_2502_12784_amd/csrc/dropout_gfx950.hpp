@@ -131,7 +131,7 @@ template <Lanes M> static __device__ __forceinline__ void exchange_words(uint32_
 // strips seven, whose last four (v_and_b32 of a sign-extended byte) sit where the entries are used (us, forward, d = 64 256
 // heads x 2048 403 -> 386, causal d = 128 64 x 4096 352 -> 339; dK/dV, d = 64, the same 640 -> 629).  In the dQ kernel, whose
 // entries choose between two values, a compare and a select stay the shorter form.  mha_fwd_split_kernel, too, compares and selects
-// each entry; masks have not been measured there.
+// each entry (masks have not been measured there), and so do the dK/dV kernels that were faster so (COMPARE in each).
 static __device__ __forceinline__ uint32_t keep_flags(uint32_t bytes, const Dropout& dr) {
   return __builtin_amdgcn_lerp(bytes, dr.keep_add, 0);
 }
